@@ -163,6 +163,33 @@ def test_river_construction_bit_exact(dtype):
                            zo.view(torch.int16 if dtype == torch.bfloat16 else torch.int32))
 
 
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16], ids=["fp32", "bf16"])
+@pytest.mark.parametrize("rows,cols,group", [(1, 16, 32), (3, 48, 32), (300, 208, 96), (5, 1040, 64), (3, 4112, 1024),
+                                             (2, 6176, 2048), (7, 496, 4096), (65, 14336, 128)])
+def test_river_construction_lane_groups(dtype, rows, cols, group):
+    """Edges of the lane-per-run split: groups that are no power of two of runs, groups longer than a
+    wavefront's 64 runs, one group per row, rows that share a workgroup, a ragged last group; aligned
+    pointers (16-byte loads) and pointers one element off."""
+    say(f"quantiser lane groups {rows}x{cols} group {group} {dtype}")
+    w = (torch.randn(rows, cols, generator=torch.Generator().manual_seed(rows + cols)) * 0.02).to(dtype)
+    want = ro.quantize_w4(w, group)
+    bits = lambda t: t.cpu().reshape(rows, -1).view(torch.uint8)      # noqa: E731
+    off = torch.empty(rows * cols + 1, dtype=dtype, device="cuda")[1:].view(rows, cols).copy_(w)
+    for src in (w.cuda(), off):
+        got = binding.river_quantize_w4(src, group)
+        torch.cuda.synchronize()
+        for a, b in zip(got, want):
+            assert torch.equal(bits(a), bits(b))
+    # values without an order (NaN), infinities and signed zeros: both load widths write the same bits
+    w[0, ::5] = float("nan")
+    w[-1, ::7] = float("inf")
+    w[rows // 2] = torch.where(torch.arange(cols) % 2 == 0, 0.0, -0.0).to(dtype)
+    off.copy_(w)
+    a, b = binding.river_quantize_w4(w.cuda(), group), binding.river_quantize_w4(off, group)
+    for x, y in zip(a, b):
+        assert torch.equal(bits(x), bits(y))
+
+
 # ------------------------------------------------------------- tiny configs
 
 @pytest.mark.parametrize("mode", MODES, ids=MODE_IDS)
