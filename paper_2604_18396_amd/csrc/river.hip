@@ -12,6 +12,7 @@
 #include <cstring>
 #include <mutex>
 #include <string>
+#include <utility>
 #include <vector>
 
 #include "river_device.h"
@@ -305,7 +306,7 @@ struct Layout {
   size_t bd_ssq;
   size_t bd_stream, bd_stream_bytes;     // batched contexts: the GEMM weights a second time, in stream order (bd::BdB)
   // activation buffers of the GEMM prefill (pf_rows rows each; 0 rows: that path is not offered)
-  size_t pf_tok, pf_h, pf_x16, pf_q16, pf_a16, pf_big;
+  size_t pf_tok, pf_h, pf_x16, pf_q16, pf_a16, pf_big, pf_big_bytes;
   int pf_rows;
   // batched contexts (max_batch > 1): per-sequence state, step buffers, records
   size_t bd_state, bd_hprev, bd_part_o, bd_part_ml, bd_tickets, bd_logits, bd_hist, bd_rec_token, bd_rec_exit,
@@ -541,7 +542,9 @@ static Layout make_layout(const river_config *c) {
     y.pf_x16 = take(rows * std::max((size_t)c->d_model, qd) * 2);
     y.pf_q16 = take(rows * qd * 2);
     y.pf_a16 = take(rows * c->d_ffn * 2);
-    y.pf_big = take(rows * std::max((size_t)2 * c->d_ffn, qd + 2 * kvd) * 4);
+    // fp32 planes of the QKV, O and down GEMMs: one of all rows, or several K slices of fewer
+    y.pf_big_bytes = std::max(rows, std::min((size_t)pf::kChunk, 16 * rows)) * std::max((size_t)c->d_model, qd + 2 * kvd) * 4;
+    y.pf_big = take(y.pf_big_bytes);
   }
   if (c->max_batch > 1) {
     const size_t B = c->max_batch, qd = (size_t)c->n_q_heads * c->head_dim;
@@ -893,10 +896,17 @@ static int create_impl(const river_config *cfg, const river_weights *w, const ri
       if ((e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, lb)) != hipSuccess)
         return fail("hipFuncSetAttribute(max dynamic LDS)", e);
     if (gemm_prefill_ok(cfg)) {
-      const void *pfg[] = {(const void *)pf::k_pf_gemm<false, false>, (const void *)pf::k_pf_gemm<false, true>,
-                           (const void *)pf::k_pf_gemm<true, false>, (const void *)pf::k_pf_gemm<true, true>};
-      for (const void *f : pfg)
-        if ((e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, pf::kGemmLdsBytes)) != hipSuccess)
+      const std::pair<const void *, int> pfg[] = {
+          {(const void *)pf::k_pf_gemm<pf::TileM, false, pf::PF_STORE>, pf::TileM::LDS_BYTES},
+          {(const void *)pf::k_pf_gemm<pf::TileM, false, pf::PF_SWIGLU>, pf::TileM::LDS_BYTES},
+          {(const void *)pf::k_pf_gemm<pf::TileM, true, pf::PF_STORE>, pf::TileM::LDS_BYTES},
+          {(const void *)pf::k_pf_gemm<pf::TileM, true, pf::PF_SWIGLU>, pf::TileM::LDS_BYTES},
+          {(const void *)pf::k_pf_gemm<pf::TileL, false, pf::PF_STORE>, pf::TileL::LDS_BYTES},
+          {(const void *)pf::k_pf_gemm<pf::TileL, false, pf::PF_SWIGLU>, pf::TileL::LDS_BYTES},
+          {(const void *)pf::k_pf_gemm<pf::TileL, true, pf::PF_STORE>, pf::TileL::LDS_BYTES},
+          {(const void *)pf::k_pf_gemm<pf::TileL, true, pf::PF_SWIGLU>, pf::TileL::LDS_BYTES}};
+      for (const auto &f : pfg)
+        if ((e = hipFuncSetAttribute(f.first, hipFuncAttributeMaxDynamicSharedMemorySize, f.second)) != hipSuccess)
           return fail("hipFuncSetAttribute(prefill GEMM LDS)", e);
     }
     if (cfg->max_batch > 1) {
@@ -1002,27 +1012,62 @@ static int check_device_error(river_ctx *x) {
     if ((x)->broken) return RIVER_EHIP;                \
   } while (0)
 
-// GEMM of the prefill: C[rows, N] (+)= A[rows, K] B^T over the stacked matrices ms[0..nm) of block l.
-template <bool W4, bool ADD>
-static void launch_gemm(river_ctx *x, int l, const int *ms, int nm, const _Float16 *A, int K, float *C, int rows) {
+// Tile and number of K slices of a prefill GEMM.  A workgroup's time is its K tiles times what one
+// takes: TileL (256 x 256, one workgroup per CU) 2.1 us, TileM (128 x 128) 0.8 us alone on its CU and
+// 1.45 us beside a second one; a K slice costs the write and the read of a plane of partial sums (4 MB
+// per us).  The rule takes the least of that over both tiles and up to 16 slices of at least four K
+// tiles.  (us measured: N 4096 K 14336: 77 rows TileM 140 / 28 with 1 / 8 slices, 512 rows TileL 291 /
+// 63 with 1 / 8, TileM 73 with 4; N 28672 K 4096: 512 rows TileM 156, TileL 118.)
+struct PfPlan { bool large; int split; };
+static PfPlan pf_plan(const river_ctx *x, int N, int K, int m, bool may_split) {
+  PfPlan best{false, 1};
+  double best_us = 1e30;
+  const int nk = K / pf::TK, cus = x->grid_persist;
+  for (int large = 0; large < 2; ++large) {
+    const int tm = large ? pf::TileL::TM : pf::TileM::TM, tn = large ? pf::TileL::TN : pf::TileM::TN;
+    const long long tiles = (long long)((N + tn - 1) / tn) * ((m + tm - 1) / tm);
+    for (int sp = 1; sp <= (may_split ? 16 : 1); ++sp) {
+      if (sp > 1 && (nk / sp < 4 || (size_t)sp * m * N * 4 > x->lay.pf_big_bytes)) break;
+      const double per_cu = (double)((tiles * sp + cus - 1) / cus), k_tiles = (double)((nk + sp - 1) / sp);
+      const double us = k_tiles * (large ? 2.1 * per_cu : 0.15 + 0.65 * per_cu) + (sp > 1 ? 2.0 * sp * m * N * 4 / 4e6 : 0.0);
+      if (us < best_us) { best_us = us; best = PfPlan{large != 0, sp}; }
+    }
+  }
+  return best;
+}
+
+// GEMM of the prefill over the stacked matrices ms[0..nm) of block l: fp32 planes of partial sums in
+// C (returns how many), or with EPI = PF_SWIGLU the fp16 activation of the down projection.
+template <class T, bool W4, int EPI>
+static void launch_gemm_t(river_ctx *x, const pf::GemmB &B, int N, const _Float16 *A, int K, void *C, int ldc, int m, int split) {
+  const int n_tiles = (N + T::TN - 1) / T::TN, m_tiles = (m + T::TM - 1) / T::TM;
+  const dim3 grid((n_tiles * split + 7) / 8 * 8 * m_tiles);      // (see the kernel's workgroup -> tile mapping)
+  pf::k_pf_gemm<T, W4, EPI><<<grid, dim3(T::NT), T::LDS_BYTES, x->stream>>>(A, K, B, N, K, x->cfg.river_group, C, ldc, m,
+                                                                           m_tiles, split);
+}
+template <int EPI>
+static int launch_gemm(river_ctx *x, int l, bool w4, const int *ms, int nm, const _Float16 *A, int K, void *C, int m) {
   pf::GemmB B{};
   int N = 0;
   for (int i = 0; i < nm; ++i) {
     long long r, c;
     matrix_shape(&x->cfg, ms[i], &r, &c);
-    B.w[i] = W4 ? (const void *)x->layers_h[l].qc[ms[i]] : x->layers_h[l].w[ms[i]];
+    B.w[i] = w4 ? (const void *)x->layers_h[l].qc[ms[i]] : x->layers_h[l].w[ms[i]];
     B.sz[i] = x->layers_h[l].qsz[ms[i]];
     B.rows[i] = (int)r;
     N += (int)r;
   }
   for (int i = nm; i < 3; ++i) { B.w[i] = B.w[0]; B.sz[i] = B.sz[0]; B.rows[i] = 0; }
-  const int n_tiles = (N + pf::TN - 1) / pf::TN, m_tiles = rows / pf::TM;
-  const dim3 grid((n_tiles + 7) / 8 * 8 * m_tiles);            // (see the kernel's workgroup -> tile mapping)
-  pf::k_pf_gemm<W4, ADD><<<grid, dim3(256), pf::kGemmLdsBytes, x->stream>>>(A, K, B, N, K, x->cfg.river_group, C, N,
-                                                                            m_tiles);
+  const PfPlan p = pf_plan(x, N, K, m, EPI == pf::PF_STORE);
+  const int ldc = EPI == pf::PF_SWIGLU ? B.rows[0] : N;
+  if (p.large && w4) launch_gemm_t<pf::TileL, true, EPI>(x, B, N, A, K, C, ldc, m, p.split);
+  else if (p.large) launch_gemm_t<pf::TileL, false, EPI>(x, B, N, A, K, C, ldc, m, p.split);
+  else if (w4) launch_gemm_t<pf::TileM, true, EPI>(x, B, N, A, K, C, ldc, m, p.split);
+  else launch_gemm_t<pf::TileM, false, EPI>(x, B, N, A, K, C, ldc, m, p.split);
+  return p.split;
 }
 
-// Prefill phase on the matrix cores: the prompt in chunks of up to pf_rows tokens, every block
+// Prefill phase on the matrix cores: the prompt in equal chunks of up to pf_rows tokens, every block
 // as MFMA GEMMs over the chunk (see river_prefill.h); blocks above ep run as river twins.
 static int prefill_gemm(river_ctx *x, int seq, const int32_t *tokens, int n, int ep) {
   const river_config &c = x->cfg;
@@ -1036,19 +1081,19 @@ static int prefill_gemm(river_ctx *x, int seq, const int32_t *tokens, int n, int
   _Float16 *a16 = (_Float16 *)(x->ws + y.pf_a16);
   char *kc = (char *)D.kcache + (size_t)seq * y.cache_bytes, *vc = (char *)D.vcache + (size_t)seq * y.cache_bytes;
   const int m_qkv[3] = {M_WQ, M_WK, M_WV}, m_o[1] = {M_WO}, m_gu[2] = {M_GATE, M_UP}, m_d[1] = {M_DOWN};
-  for (int c0 = 0; c0 < n; c0 += y.pf_rows) {
-    const int m = std::min(y.pf_rows, n - c0), rows = (m + 127) / 128 * 128;
-    const bool last = c0 + m == n;
+  const int chunks = (n + y.pf_rows - 1) / y.pf_rows, step = std::min(y.pf_rows, ((n + chunks - 1) / chunks + 255) / 256 * 256);
+  for (int c0 = 0; c0 < n; c0 += step) {
+    const int m = std::min(step, n - c0);
+    const int last = c0 + m == n ? m - 1 : -1;              // the row whose h(0..L) is kept
     HIP_TRY(x, hipMemcpyAsync(tok, tokens + c0, (size_t)m * 4, hipMemcpyHostToDevice, s));
-    pf::k_pf_embed<<<dim3(m), dim3(256), 0, s>>>(tok, D.tok_emb, d, h);
-    if (last) pf::k_pf_copy_row<<<dim3(4), dim3(256), 0, s>>>(h + (size_t)(m - 1) * d, D.hidden, d);
+    int parts = 0;                                           // partial sums waiting to be added into h
     for (int l = 0; l < L; ++l) {
       const bool river = l >= ep;
       const DevLayer &W = x->layers_h[l];
-      pf::k_pf_rmsnorm<<<dim3(m), dim3(256), 0, s>>>(h, W.attn_norm, d, c.rms_eps, x16);
-      if (river) launch_gemm<true, false>(x, l, m_qkv, 3, x16, d, big, rows);
-      else launch_gemm<false, false>(x, l, m_qkv, 3, x16, d, big, rows);
-      pf::k_pf_rope_store<<<dim3(m), dim3(256), 0, s>>>(big, D.rope, c.n_q_heads, c.n_kv_heads, c.head_dim, c0, l,
+      pf::k_pf_norm<<<dim3(m), dim3(256), 0, s>>>(h, l ? nullptr : tok, D.tok_emb, big, parts, m, W.attn_norm, d, c.rms_eps,
+                                                  x16, D.hidden + (size_t)l * d, last, 0);
+      parts = launch_gemm<pf::PF_STORE>(x, l, river, m_qkv, 3, x16, d, big, m);
+      pf::k_pf_rope_store<<<dim3(m), dim3(256), 0, s>>>(big, parts, m, D.rope, c.n_q_heads, c.n_kv_heads, c.head_dim, c0, l,
                                                         c.max_seq, kc, vc, D.kv_f16, q16);
       const dim3 ga(c.n_q_heads, (m + 127) / 128);
       if (c.head_dim == 128)
@@ -1057,17 +1102,16 @@ static int prefill_gemm(river_ctx *x, int seq, const int32_t *tokens, int n, int
       else
         pf::k_pf_attn<64><<<ga, dim3(256), 0, s>>>(q16, kc, vc, D.kv_f16, c.n_q_heads, c.n_kv_heads, l, c.max_seq,
                                                    c0, m, x16);
-      if (river) launch_gemm<true, true>(x, l, m_o, 1, x16, qd, h, rows);
-      else launch_gemm<false, true>(x, l, m_o, 1, x16, qd, h, rows);
-      pf::k_pf_rmsnorm<<<dim3(m), dim3(256), 0, s>>>(h, W.ffn_norm, d, c.rms_eps, x16);
-      if (river) launch_gemm<true, false>(x, l, m_gu, 2, x16, d, big, rows);
-      else launch_gemm<false, false>(x, l, m_gu, 2, x16, d, big, rows);
-      pf::k_pf_swiglu<<<dim3(m), dim3(256), 0, s>>>(big, ffn, a16);
-      if (river) launch_gemm<true, true>(x, l, m_d, 1, a16, ffn, h, rows);
-      else launch_gemm<false, true>(x, l, m_d, 1, a16, ffn, h, rows);
-      if (last)
-        pf::k_pf_copy_row<<<dim3(4), dim3(256), 0, s>>>(h + (size_t)(m - 1) * d, D.hidden + (size_t)(l + 1) * d, d);
+      parts = launch_gemm<pf::PF_STORE>(x, l, river, m_o, 1, x16, qd, big, m);
+      pf::k_pf_norm<<<dim3(m), dim3(256), 0, s>>>(h, nullptr, nullptr, big, parts, m, W.ffn_norm, d, c.rms_eps, x16, nullptr,
+                                                  -1, 0);
+      (void)launch_gemm<pf::PF_SWIGLU>(x, l, river, m_gu, 2, x16, d, a16, m);
+      parts = launch_gemm<pf::PF_STORE>(x, l, river, m_d, 1, a16, ffn, big, m);
     }
+    // h(L) of the last prompt position, the head's input
+    if (last >= 0)
+      pf::k_pf_norm<<<dim3(1), dim3(256), 0, s>>>(h, nullptr, nullptr, big, parts, m, nullptr, d, c.rms_eps, nullptr,
+                                                  D.hidden + (size_t)L * d, last, last);
     HIP_TRY(x, hipGetLastError());
   }
   // the original final norm + LM head + argmax on the last prompt position (the decode path's kernel)

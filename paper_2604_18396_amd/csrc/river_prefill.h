@@ -6,8 +6,8 @@
 // into chunks of up to kChunk tokens and each block is a sequence of MFMA GEMMs over the
 // chunk (fp16 operands, fp32 accumulation) with small element-wise kernels between them:
 //
-//   embed -> [ rmsnorm -> GEMM(Wq;Wk;Wv) -> rope + cache store -> causal attention
-//              -> GEMM(Wo) += h -> rmsnorm -> GEMM(Wg;Wu) -> swiglu -> GEMM(Wd) += h1 ] x L
+//   [ (embed | h += Wd's sums) + rmsnorm -> GEMM(Wq;Wk;Wv) -> rope + cache store -> causal attention
+//     -> GEMM(Wo) -> h += its sums, rmsnorm -> GEMM(Wg;Wu) with swiglu -> GEMM(Wd) ] x L
 //
 // Operand types: activations are rounded to half precision (fp16) when they enter a GEMM or
 // the attention; backbone weights (bf16) are converted to fp16 while a tile is staged in LDS
@@ -28,10 +28,9 @@ typedef _Float16 half4 __attribute__((ext_vector_type(4)));
 typedef _Float16 half2v __attribute__((ext_vector_type(2)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
-constexpr int kChunk = 1024;          // prompt tokens per pass (rows of the activation buffers)
-constexpr int TM = 128, TN = 128, TK = 64;
+constexpr int kChunk = 4096;          // most prompt tokens per pass (rows of the activation buffers)
+constexpr int TK = 64;
 constexpr int LDK = TK + 8;           // LDS row stride in halfs: 144 B, rows 4 banks apart
-constexpr int kGemmLdsBytes = 2 * (TM + TN) * LDK * 2;     // k_pf_gemm: two buffers each of the A and B tiles
 
 // v_mfma_f32_32x32x16_f16: D[32x32] += A[32x16] B[16x32].  Lane l supplies row l % 32 of A and
 // column l % 32 of B, eight K values each (those of lane group l / 32; which eight is the same
@@ -54,6 +53,21 @@ __device__ __forceinline__ half8 bf16x8_to_half8(const uint4 &w) {
   return h;
 }
 
+// Eight 4-bit codes of a row-major word (nibble i = column i) -> (code - zero) * scale as fp16, one
+// rounding of the fp32 product sum: a nibble placed in bits 6..9 of the mantissa of 16.0 is exactly
+// 16 + code, and the mixed-precision fma takes it from there: (16 + code) * s + c, c = -s (16 + zero).
+__device__ __forceinline__ half8 dequant8(uint32_t w, float s, float c) {
+  half8 h;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {                // nibbles k and k + 4
+    const uint32_t sh = k < 2 ? w << (6 - 4 * k) : w >> (4 * k - 6);
+    const half2v q = __builtin_bit_cast(half2v, (sh & 0x03c003c0u) | 0x4c004c00u);
+    h[k] = (_Float16)fmaf((float)q[0], s, c);
+    h[k + 4] = (_Float16)fmaf((float)q[1], s, c);
+  }
+  return h;
+}
+
 // A 16-bit KV cache holds bf16 values, or IEEE half values when the context keeps its cache in
 // FP16 (kv_f16): store one element / fetch eight as fp16 / fetch one as fp32.
 __device__ __forceinline__ void cache_store(void *cache, size_t i, float v, int kv_f16) {
@@ -72,13 +86,12 @@ __device__ __forceinline__ float cache_hi(uint32_t w, int kv_f16) {
 
 // ------------------------------------------------------------------ GEMM
 //
-// C[M, N] (+)= A[M, K] B^T, B = up to three matrices stacked along N (rows of W_q, W_k, W_v;
+// C[M, N] = op(A[M, K] B^T), B = up to three matrices stacked along N (rows of W_q, W_k, W_v;
 // of W_gate, W_up), each [rows, K] row-major: dense bf16, or 4-bit codes with one packed
-// (scale, zero) pair per (row, group of `group` columns).  One workgroup of four wavefronts
-// per 128 x 128 tile of C, each wavefront a 64 x 64 quarter (2 x 2 MFMA blocks); K in tiles of
-// 64 staged through LDS, the next tile's global loads in flight while the current one is
-// multiplied.  M must be a multiple of 128 (the activation buffers are; rows beyond the
-// prompt hold don't-care values); N is guarded; K % 64 == 0, group % 64 == 0.
+// (scale, zero) pair per (row, group of `group` columns).  K % 64 == 0, group % 64 == 0, rows of
+// every matrix % 64 == 0; M and N are guarded (rows of A beyond M - 1 read row M - 1).
+// op: store fp32, slice ks of K into its own [M, N] plane for the consumer to add up in order, or
+// SwiGLU of a gate and an up matrix stored as fp16 [M, ffn] (k_split = 1).
 struct GemmB {
   const void *w[3];
   const void *sz[3];
@@ -93,214 +106,371 @@ __device__ __forceinline__ void gemm_b_row(const GemmB &B, int n, int N, int &ma
   row = n;
 }
 
-template <bool W4, bool ADD>
-__global__ __launch_bounds__(256, 2) void k_pf_gemm(const _Float16 *__restrict__ A, int lda, GemmB B, int N, int K,
-                                                 int group, float *C, int ldc, int m_tiles) {
-  extern __shared__ __attribute__((aligned(16))) _Float16 pf_lds[];   // kGemmLdsBytes: two buffers each of A and B
-  _Float16 *const As = pf_lds, *const Bs = pf_lds + 2 * TM * LDK;
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  // Workgroup -> tile of C.  Consecutive workgroup ids go round the 8 XCDs; the workgroups of one
-  // XCD take all M tiles of a column of N tiles before the next column, so the workgroups resident
-  // on an XCD at a time cover all M tiles of a few N tiles: a B tile is fetched from HBM once (its
-  // XCD's L2 serves the other M tiles) and the A tiles stay in every L2.
-  // (one-dimensional grid of 8 * ceil(N tiles / 8) * m_tiles workgroups)
-  const int xcd = blockIdx.x & 7, j = blockIdx.x >> 3;
-  const int n_tile = (j / m_tiles) * 8 + xcd, m_tile = j % m_tiles;
-  if (n_tile * TN >= N) return;
-  const int m0 = m_tile * TM, n0 = n_tile * TN;
-  const int wm = wv >> 1, wn = wv & 1;
+// What bounds it: many rows -- the matrix cores (at the clock the power limit leaves: 68 % of the
+// cycles issue MFMAs at 4096 x 28672 x 4096, 1.05 PFLOP/s, where the 128 x 128 tile with one K tile in
+// flight reached 0.85); few rows -- the weight stream and, before the K slices, the chain of K tiles of
+// the few workgroups there are (512 x 4096 x 14336: 209 us without slices and one tile in flight, 63
+// now).  A 256 x 256 tile halves the LDS reads per MFMA of a 128 x 128 one.  B goes through registers
+// because it is converted on the way (bf16 -> fp16, codes -> fp16); one conversion serves all
+// wavefronts of the tile.
+//
+// Tile of C per workgroup (TM x TN), its WM x WN wavefronts, K tiles in flight in registers (PF) and
+// workgroups per CU (OCC, bounds the registers).
+template <int TM_, int TN_, int WM_, int WN_, int PF_, int OCC_> struct GemmTile {
+  static constexpr int TM = TM_, TN = TN_, WM = WM_, WN = WN_, PF = PF_, OCC = OCC_;
+  static constexpr int NT = WM * WN * 64;                      // threads
+  static constexpr int MW = TM / WM, NW = TN / WN;             // a wavefront's part of the tile
+  static constexpr int MB = MW / 32, NB = NW / 32;             // ... in MFMA blocks
+  static constexpr int GR = NT / 8;                            // rows a staging round of the workgroup covers
+  static constexpr int LDS_BYTES = 2 * (TM + TN) * LDK * 2;    // two buffers each of A and B
+  static_assert(TM == 4 * GR && TN == 4 * GR, "four staging rounds per K tile for A and for B");
+};
+typedef GemmTile<128, 128, 2, 2, 3, 2> TileM;
+typedef GemmTile<256, 256, 4, 2, 1, 1> TileL;
+enum { PF_STORE = 0, PF_SWIGLU = 1 };
 
-  // what this thread stages per K tile: four 16-byte segments of A; of B four 16-byte
-  // segments (dense) or one 16-byte run of 32 codes with its (scale, zero) pair (river)
-  const char *a_src[4];
-  int a_dst[4];
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int seg = tid + 256 * i, row = seg >> 3, ks = seg & 7;
-    a_src[i] = (const char *)(A + (size_t)(m0 + row) * lda + ks * 8);
-    a_dst[i] = row * LDK + ks * 8;
-  }
-  const char *b_src[W4 ? 1 : 4];
-  const char *b_sz = nullptr;
-  int b_dst[W4 ? 1 : 4];
-  if constexpr (W4) {
-    const int row = tid >> 1, hf = tid & 1;
-    int mat, r;
-    gemm_b_row(B, n0 + row, N, mat, r);
-    b_src[0] = (const char *)B.w[mat] + (size_t)r * (K >> 1) + hf * 16;
-    b_sz = (const char *)B.sz[mat] + (size_t)r * (K / group) * 4;
-    b_dst[0] = row * LDK + hf * 32;
+// Rows [GR * i, GR * (i + 1)) of B's tile -> matrix and its first row.  SwiGLU: the rows alternate
+// between gate and up every NW / 2 rows, so that a wavefront holds both factors of an output.
+template <class T, int EPI>
+__device__ __forceinline__ void gemm_b_group(const GemmB &B, int n_tile, int i, int N, int &mat, int &row) {
+  if constexpr (EPI == PF_SWIGLU) {
+    static_assert(T::GR == T::NW / 2, "a staging round is half of a wavefront's columns");
+    mat = i & 1;
+    row = min(n_tile * (T::TN / 2) + (i >> 1) * T::GR, B.rows[0] - T::GR);
   } else {
+    gemm_b_row(B, min(n_tile * T::TN + i * T::GR, N - T::GR), N, mat, row);
+  }
+}
+
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t gemm_rsrc(const void *p) {
+  return __builtin_amdgcn_make_buffer_rsrc((void *)p, 0, 0x7ffffff0, 0x00020000);
+}
+
+template <class T, bool W4, int EPI>
+__global__ __launch_bounds__(T::NT, T::OCC) void k_pf_gemm(const _Float16 *__restrict__ A, int lda, GemmB B, int N,
+                                                           int K, int group, void *C, int ldc, int M, int m_tiles,
+                                                           int k_split) {
+  extern __shared__ __attribute__((aligned(16))) _Float16 pf_lds[];
+  constexpr int TM = T::TM, TN = T::TN, PF = T::PF, GR = T::GR;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6), wm = wv / T::WN, wn = wv % T::WN;
+  // Workgroup -> (tile of C, slice of K).  Consecutive workgroup ids go round the 8 XCDs; the
+  // workgroups of one XCD take all M tiles of a (column of N tiles, slice of K) before the next, so
+  // that a B tile is fetched from HBM once (its XCD's L2 serves the other M tiles).
+  // (one-dimensional grid of 8 * ceil(N tiles * k_split / 8) * m_tiles workgroups)
+  const int n_tiles = (N + TN - 1) / TN;
+  const int col = ((blockIdx.x >> 3) / m_tiles) * 8 + (blockIdx.x & 7), m_tile = (blockIdx.x >> 3) % m_tiles;
+  if (col >= n_tiles * k_split) return;
+  const int n_tile = col / k_split, ks_i = col % k_split;
+  const int m0 = m_tile * TM;
+  const int nk_all = K / TK, kt0 = (int)((long long)nk_all * ks_i / k_split);
+  const int nk = (int)((long long)nk_all * (ks_i + 1) / k_split) - kt0;
+
+  // what this thread stages per K tile: four 16-byte segments of A; of B four 16-byte segments
+  // (dense) or one 16-byte run of 32 codes with its (scale, zero) pair (river)
+  const int srow = tid >> 3, sk = tid & 7;
+  unsigned a_off[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) a_off[i] = (unsigned)min(m0 + i * GR + srow, M - 1) * (unsigned)lda * 2u + sk * 16u;
+  const __amdgpu_buffer_rsrc_t a_rsrc = gemm_rsrc((const char *)A + (size_t)kt0 * TK * 2);
+  const int s_dst = srow * LDK + sk * 8;                       // + i * GR * LDK
+  __amdgpu_buffer_rsrc_t b_rsrc[W4 ? 1 : 4];
+  unsigned b_off = 0;
+  const char *b_src = nullptr, *b_sz = nullptr;                // (W4: a thread's row may be of any of the matrices)
+  int b_dst = 0;
+  if constexpr (W4) {
+    const int row_l = tid >> 1, hf = tid & 1;
+    int mat, row;
+    gemm_b_group<T, EPI>(B, n_tile, row_l / GR, N, mat, row);
+    row += row_l % GR;
+    b_src = (const char *)B.w[mat] + (size_t)row * (K >> 1) + hf * 16 + kt0 * (TK / 2);
+    b_sz = (const char *)B.sz[mat] + (size_t)row * (K / group) * 4;
+    b_dst = row_l * LDK + hf * 32;
+  } else {
+    b_off = (unsigned)srow * (unsigned)K * 2u + sk * 16u;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      const int seg = tid + 256 * i, row = seg >> 3, ks = seg & 7;
-      int mat, r;
-      gemm_b_row(B, n0 + row, N, mat, r);
-      b_src[i] = (const char *)B.w[mat] + ((size_t)r * K + ks * 8) * 2;
-      b_dst[i] = row * LDK + ks * 8;
+      int mat, row;
+      gemm_b_group<T, EPI>(B, n_tile, i, N, mat, row);
+      b_rsrc[i] = gemm_rsrc((const char *)B.w[mat] + ((size_t)row * K + kt0 * TK) * 2);
     }
   }
 
-  // a K tile on its way from global memory to LDS
-  u32x4 fa[4], fb[W4 ? 1 : 4];                  // (native vectors: as structs they are kept in scratch memory)
-  uint32_t fsz = 0;
-  const int nk = K / TK;
-  auto load = [&](int kt) {
-    const int k0 = kt * TK;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) fa[i] = *(const u32x4 *)(a_src[i] + (size_t)k0 * 2);
+  // K tiles on their way from global memory to LDS: a ring of PF register sets
+  u32x4 fa[PF][4], fb[PF][W4 ? 1 : 4];          // (native vectors: as structs they are kept in scratch memory)
+  uint32_t fsz[PF];
+  auto load_part = [&](int kt, int u, int i) {   // part i of tile kt into set u
+    fa[u][i] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(a_rsrc, a_off[i], kt * (TK * 2), 0));
     if constexpr (W4) {
-      fb[0] = *(const u32x4 *)(b_src[0] + (k0 >> 1));
-      fsz = *(const uint32_t *)(b_sz + (size_t)(k0 / group) * 4);
-    } else {
-#pragma unroll
-      for (int i = 0; i < 4; ++i) fb[i] = *(const u32x4 *)(b_src[i] + (size_t)k0 * 2);
-    }
-  };
-  auto stage = [&](int buf) {
-    _Float16 *const As = pf_lds + buf * TM * LDK, *const Bs = pf_lds + 2 * TM * LDK + buf * TN * LDK;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) *(u32x4 *)(As + a_dst[i]) = fa[i];
-    if constexpr (W4) {
-      // weight = (code - zero) * scale in fp32, then fp16; byte j of the run holds column 2j
-      // in its low nibble and column 2j + 1 in its high nibble
-      const float s = bf16_lo(fsz), z = bf16_hi(fsz);
-      const uint32_t wds[4] = {fb[0].x, fb[0].y, fb[0].z, fb[0].w};
-#pragma unroll
-      for (int w = 0; w < 4; ++w) {
-        half8 h;
-#pragma unroll
-        for (int b = 0; b < 4; ++b) {
-          const uint32_t byte = (wds[w] >> (8 * b)) & 0xffu;
-          h[2 * b] = (_Float16)(((float)(byte & 15u) - z) * s);
-          h[2 * b + 1] = (_Float16)(((float)(byte >> 4) - z) * s);
-        }
-        *(half8 *)(Bs + b_dst[0] + w * 8) = h;
+      if (i == 3) {                               // (all four parts of the set have been staged)
+        fb[u][0] = *RIVER_GLOBAL(u32x4, b_src + kt * (TK / 2));
+        fsz[u] = *RIVER_GLOBAL(uint32_t, b_sz + (size_t)((kt0 + kt) * TK / group) * 4);
       }
     } else {
-#pragma unroll
-      for (int i = 0; i < 4; ++i) *(half8 *)(Bs + b_dst[i]) = bf16x8_to_half8(make_uint4(fb[i].x, fb[i].y, fb[i].z, fb[i].w));
+      fb[u][i] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(b_rsrc[i], b_off, kt * (TK * 2), 0));
+    }
+  };
+  auto stage_part = [&](int u, int i, int buf) {  // part i of set u into LDS buffer buf
+    _Float16 *const As = pf_lds + buf * TM * LDK, *const Bs = pf_lds + 2 * TM * LDK + buf * TN * LDK;
+    *(u32x4 *)(As + s_dst + i * GR * LDK) = fa[u][i];
+    if constexpr (W4) {
+      const float s = bf16_lo(fsz[u]), c = -s * (16.0f + bf16_hi(fsz[u]));
+      const uint32_t w = i == 0 ? fb[u][0].x : i == 1 ? fb[u][0].y : i == 2 ? fb[u][0].z : fb[u][0].w;
+      *(half8 *)(Bs + b_dst + i * 8) = dequant8(w, s, c);
+    } else {
+      const u32x4 w = fb[u][i];
+      *(half8 *)(Bs + s_dst + i * GR * LDK) = bf16x8_to_half8(make_uint4(w.x, w.y, w.z, w.w));
     }
   };
 
-  f32x16 acc[2][2];
+  f32x16 acc[T::MB][T::NB];
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+  for (int i = 0; i < T::MB; ++i)
 #pragma unroll
-    for (int j = 0; j < 2; ++j)
+    for (int j = 0; j < T::NB; ++j)
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
 
   const int r32 = lane & 31, g8 = (lane >> 5) * 8;
-  // Tile kt is multiplied from LDS buffer kt % 2 while tile kt + 1 (fetched during the previous
-  // iteration) is written into the other buffer and tile kt + 2 is fetched: one workgroup barrier
-  // per K tile.
-  load(0);
-  stage(0);
-  if (nk > 1) load(1);
-  __syncthreads();
-  for (int kt = 0; kt < nk; ++kt) {
+  const int ra = (wm * T::MW + r32) * LDK + g8, rb = (wn * T::NW + r32) * LDK + g8;
+  // Tile kt is multiplied from LDS buffer kt % 2 while tile kt + 1 goes from its register set into the
+  // other buffer and tile kt + 1 + PF into that set.  The operands of MFMA step ks + 1 are read from
+  // LDS in front of the products of step ks; those of the next tile's first step in front of the last
+  // one's, behind the only workgroup barrier of the tile (by then every wavefront has read all of the
+  // tile and written its part of the next), which does not wait for the global loads in flight.
+  half8 xa[2][T::MB], xb[2][T::NB];
+  auto frags = [&](int buf, int ks, int f) {
+    const _Float16 *const Ac = pf_lds + buf * TM * LDK, *const Bc = pf_lds + 2 * TM * LDK + buf * TN * LDK;
+#pragma unroll
+    for (int i = 0; i < T::MB; ++i) xa[f][i] = *(const half8 *)(Ac + ra + i * 32 * LDK + ks * 16);
+#pragma unroll
+    for (int j = 0; j < T::NB; ++j) xb[f][j] = *(const half8 *)(Bc + rb + j * 32 * LDK + ks * 16);
+  };
+  auto body = [&](int kt, int u1, bool stage, bool load) {     // u1: the set of tile kt + 1
     const int cur = kt & 1;
-    if (kt + 1 < nk) stage(cur ^ 1);
-    if (kt + 2 < nk) load(kt + 2);
-    const _Float16 *const Ac = As + cur * TM * LDK, *const Bc = Bs + cur * TN * LDK;
 #pragma unroll
-    for (int ks = 0; ks < TK / 16; ++ks) {
-      half8 a[2], b[2];
+    for (int ks = 0; ks < 4; ++ks) {
+      if (ks == 3) lds_barrier();
+      if (ks < 3 || stage) frags(ks < 3 ? cur : cur ^ 1, (ks + 1) & 3, (ks + 1) & 1);
+      __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int i = 0; i < 2; ++i) a[i] = *(const half8 *)(Ac + (wm * 64 + i * 32 + r32) * LDK + ks * 16 + g8);
+      for (int i = 0; i < 4; ++i) {                            // parts 0, 1 | 2 | 3
+        if (ks != (i < 1 ? 0 : i - 1)) continue;
+        if (stage) stage_part(u1, i, cur ^ 1);
+        if (load) load_part(kt + 1 + PF, u1, i);
+      }
 #pragma unroll
-      for (int j = 0; j < 2; ++j) b[j] = *(const half8 *)(Bc + (wn * 64 + j * 32 + r32) * LDK + ks * 16 + g8);
+      for (int i = 0; i < T::MB; ++i)
 #pragma unroll
-      for (int i = 0; i < 2; ++i)
+        for (int j = 0; j < T::NB; ++j) acc[i][j] = mfma16(xa[ks & 1][i], xb[ks & 1][j], acc[i][j]);
+      // the step's conversions, LDS writes and loads go between its MFMAs, not in front of them
 #pragma unroll
-        for (int j = 0; j < 2; ++j) acc[i][j] = mfma16(a[i], b[j], acc[i][j]);
+      for (int q = 0; q < T::MB * T::NB; ++q) {
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);      // one MFMA
+        __builtin_amdgcn_sched_group_barrier(0x002, 4, 0);      // VALU
+        __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);      // LDS write
+        __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);      // global load
+      }
+      __builtin_amdgcn_sched_barrier(0);
     }
-    __syncthreads();
+  };
+#pragma unroll
+  for (int u = 0; u < PF; ++u)
+    if (u < nk) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) load_part(u, u, i);
+    }
+#pragma unroll
+  for (int i = 0; i < 4; ++i) stage_part(0, i, 0);
+  if (PF < nk) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) load_part(PF, 0, i);
+  }
+  lds_barrier();
+  frags(0, 0, 0);
+  int kt = 0;
+  for (; kt + 2 * PF < nk; kt += PF) {            // every load of the round exists
+#pragma unroll
+    for (int u = 0; u < PF; ++u) body(kt + u, (u + 1) % PF, true, true);
   }
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+  for (int u = 0; u < 2 * PF; ++u) {
+    if (kt + u >= nk) goto done;
+    body(kt + u, (u + 1) % PF, kt + u + 1 < nk, kt + u + 1 + PF < nk);
+  }
+done:
+  if constexpr (EPI == PF_SWIGLU) {
+    constexpr int HB = T::NB / 2;
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      const int col = n0 + wn * 64 + j * 32 + r32;
-      if (col < N) {
+    for (int i = 0; i < T::MB; ++i)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          float *p = C + (size_t)(m0 + wm * 64 + i * 32 + c_row(r, lane)) * ldc + col;
-          if constexpr (ADD) *p += acc[i][j][r];
-          else *p = acc[i][j][r];
+      for (int j = 0; j < HB; ++j) {
+        const int cc = n_tile * (TN / 2) + wn * (T::NW / 2) + j * 32 + r32;
+        if (cc < ldc) {
+#pragma unroll
+          for (int r = 0; r < 16; ++r) {
+            const int row = m0 + wm * T::MW + i * 32 + c_row(r, lane);
+            const float g = acc[i][j][r], v = acc[i][j + HB][r];
+            if (row < M) ((_Float16 *)C)[(size_t)row * ldc + cc] = (_Float16)(g / (1.0f + expf(-g)) * v);
+          }
         }
       }
-    }
+  } else {
+    float *const out = (float *)C + (size_t)ks_i * M * ldc;
+#pragma unroll
+    for (int i = 0; i < T::MB; ++i)
+#pragma unroll
+      for (int j = 0; j < T::NB; ++j) {
+        const int cc = n_tile * TN + wn * T::NW + j * 32 + r32;
+        if (cc < N) {
+#pragma unroll
+          for (int r = 0; r < 16; ++r) {
+            const int row = m0 + wm * T::MW + i * 32 + c_row(r, lane);
+            if (row < M) out[(size_t)row * ldc + cc] = acc[i][j][r];
+          }
+        }
+      }
+  }
 }
 
 // ------------------------------------------------------- element-wise kernels
+//
+// Bound by the stream of their operands; one workgroup of 256 per token, 16 bytes and more per lane
+// and load.  Partial sums of a K-sliced GEMM (planes of [m, columns], see k_pf_gemm) are added here,
+// in slice order, by the kernel that consumes the sum anyway.
 
-// h[t, :] = E[token[t], :] for the m tokens of the chunk; one workgroup per token
-__global__ void k_pf_embed(const int *__restrict__ tokens, const void *tok_emb, int d, float *h) {
-  const int t = blockIdx.x;
-  const size_t src = (size_t)tokens[t] * d;
-  for (int i = threadIdx.x; i < d; i += blockDim.x) h[(size_t)t * d + i] = Store<1>::ld(tok_emb, src + i);
+struct Run8 { float v[8]; };
+__device__ __forceinline__ Run8 ld_run8(const float *p) {
+  const float4 a = *(const float4 *)p, b = *(const float4 *)(p + 4);
+  return Run8{{a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w}};
+}
+__device__ __forceinline__ void st_run8(float *p, const Run8 &x) {
+  *(float4 *)p = make_float4(x.v[0], x.v[1], x.v[2], x.v[3]);
+  *(float4 *)(p + 4) = make_float4(x.v[4], x.v[5], x.v[6], x.v[7]);
+}
+__device__ __forceinline__ Run8 ld_run8_16(const void *p, size_t i) {       // eight bf16 values
+  float f[8];
+  const u32x4 w = *RIVER_GLOBAL(u32x4, (const char *)p + i * 2);
+  Store<1>::unpack(w, f);
+  return Run8{{f[0], f[1], f[2], f[3], f[4], f[5], f[6], f[7]}};
 }
 
-// x16[t, :] = fp16(h[t, :] * rsqrt(mean(h[t, :]^2) + eps) * gain); one workgroup (256) per token
-__global__ __launch_bounds__(256) void k_pf_rmsnorm(const float *__restrict__ h, const void *gain, int d, float eps,
-                                                    _Float16 *x16) {
+// The residual stream in front of a norm, and the norm: h[t, :] = E[token[t], :] (tokens given: block
+// 1's first norm) or h[t, :] += the n_part partial sums of the GEMM in front; x16[t, :] =
+// fp16(h[t, :] * rsqrt(mean(h[t, :]^2) + eps) * gain) (x16 null: no norm, the last block's sums only).
+// row_out: the row of the last prompt position (t == row_t) is also kept there, the debug view of
+// h(0..L) and the head's input.  d % 8 == 0, rows 16-byte aligned.  A row of up to 8192 columns is
+// read once and kept in registers between the reduction and the scaling.
+constexpr int kNormKeep = 4;
+__global__ __launch_bounds__(256) void k_pf_norm(float *__restrict__ h, const int *__restrict__ tokens,
+                                                 const void *tok_emb, const float *__restrict__ part, int n_part, int m,
+                                                 const void *gain, int d, float eps, _Float16 *x16, float *row_out,
+                                                 int row_t, int t0) {
   __shared__ float red[16];
-  const int t = blockIdx.x;
-  const float *row = h + (size_t)t * d;
+  const int t = t0 + blockIdx.x;
+  float *const row = h + (size_t)t * d;
+  float *const keep_row = t == row_t ? row_out : nullptr;
+  const size_t emb = tokens ? (size_t)tokens[t] * d : 0;
+  const bool emb_wide = ((uintptr_t)tok_emb & 15) == 0;        // (the embedding may have any alignment)
   float ss = 0.f;
-  for (int i = threadIdx.x; i < d; i += blockDim.x) ss += row[i] * row[i];
-  const float tot = block_sum(ss, red);
-  const float r = 1.0f / sqrtf(tot / (float)d + eps);
-  for (int i = threadIdx.x; i < d; i += blockDim.x)
-    x16[(size_t)t * d + i] = (_Float16)(row[i] * r * Store<1>::ld(gain, i));
+  auto take = [&](int k) {
+    Run8 x;
+    if (tokens && emb_wide) {
+      x = ld_run8_16(tok_emb, emb + k);
+    } else if (tokens) {
+      for (int e = 0; e < 8; ++e) x.v[e] = Store<1>::ld(tok_emb, emb + k + e);
+    } else {
+      x = ld_run8(row + k);
+      for (int j = 0; j < n_part; ++j) {
+        const Run8 q = ld_run8(part + ((size_t)j * m + t) * d + k);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) x.v[e] += q.v[e];
+      }
+    }
+    if (tokens || n_part) st_run8(row + k, x);
+    if (keep_row) st_run8(keep_row + k, x);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) ss = fmaf(x.v[e], x.v[e], ss);
+    return x;
+  };
+  Run8 keep[kNormKeep];
+#pragma unroll
+  for (int i = 0; i < kNormKeep; ++i) {
+    const int k = threadIdx.x * 8 + i * 2048;
+    if (k < d) keep[i] = take(k);
+  }
+  for (int k = threadIdx.x * 8 + kNormKeep * 2048; k < d; k += 2048) (void)take(k);
+  if (!x16) return;
+  const float r = 1.0f / sqrtf(block_sum(ss, red) / (float)d + eps);
+  auto put = [&](int k, const Run8 &x) {
+    const Run8 g = ld_run8_16(gain, k);
+    half8 o;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) o[e] = (_Float16)(x.v[e] * r * g.v[e]);
+    *(half8 *)(x16 + (size_t)t * d + k) = o;
+  };
+#pragma unroll
+  for (int i = 0; i < kNormKeep; ++i) {
+    const int k = threadIdx.x * 8 + i * 2048;
+    if (k < d) put(k, keep[i]);
+  }
+  for (int k = threadIdx.x * 8 + kNormKeep * 2048; k < d; k += 2048) put(k, ld_run8(row + k));   // (this thread's own)
 }
 
 // RoPE on q and k at position pos0 + t; q scaled by log2(e) / sqrt(hd) and stored as fp16 for
 // the attention kernel; k (rotated) and v rounded to the cache dtype and written to slot
-// (l, pos0 + t) of the shared cache.  qkv: fp32 [m, qd + 2 kvd] as the QKV GEMM left it.
-// One workgroup per token; thread i handles rotation pair (i, i + hd/2) of one head.
-__global__ void k_pf_rope_store(const float *__restrict__ qkv, const float2 *__restrict__ rope, int nq, int nkv,
-                                int hd, int pos0, int l, int max_seq, void *kcache, void *vcache, int kv_f16,
-                                _Float16 *q16) {
-  const int t = blockIdx.x, p = pos0 + t, half = hd >> 1;
+// (l, pos0 + t) of the shared cache.  qkv: n_part fp32 planes [m, qd + 2 kvd] of the QKV GEMM, added
+// in order.  One workgroup per token; a thread handles four rotation pairs (i, i + hd/2) of one head,
+// or four columns of v.
+__global__ __launch_bounds__(256) void k_pf_rope_store(const float *__restrict__ qkv, int n_part, int m,
+                                                       const float2 *__restrict__ rope, int nq, int nkv, int hd, int pos0,
+                                                       int l, int max_seq, void *kcache, void *vcache, int kv_f16,
+                                                       _Float16 *q16) {
+  const int t = blockIdx.x, p = pos0 + t, half = hd >> 1, per = half >> 2;
   const int qd = nq * hd, kvd = nkv * hd, ld = qd + 2 * kvd;
-  const float *row = qkv + (size_t)t * ld;
   const float qs = 1.4426950408889634f / sqrtf((float)hd);
-  for (int i = threadIdx.x; i < (nq + nkv) * half; i += blockDim.x) {
-    const int head = i / half, e = i % half;
-    const float2 cs = rope[(size_t)p * half + e];
-    const float *src = row + head * hd;            // q heads, then k heads: contiguous in qkv
-    const float a = src[e], b = src[e + half];
-    const float lo = a * cs.x - b * cs.y, hi = a * cs.y + b * cs.x;
-    if (head < nq) {
-      q16[(size_t)t * qd + head * hd + e] = (_Float16)(lo * qs);
-      q16[(size_t)t * qd + head * hd + e + half] = (_Float16)(hi * qs);
+  auto get = [&](int c) {
+    float4 a = *(const float4 *)(qkv + (size_t)t * ld + c);
+    for (int j = 1; j < n_part; ++j) {
+      const float4 b = *(const float4 *)(qkv + ((size_t)j * m + t) * ld + c);
+      a.x += b.x; a.y += b.y; a.z += b.z; a.w += b.w;
+    }
+    return a;
+  };
+  auto to_cache = [&](void *cache, size_t i, float x, float y, float z, float w) {
+    u32x2 v;
+    if (kv_f16) {
+      v.x = __builtin_bit_cast(uint32_t, half2v{(_Float16)x, (_Float16)y});
+      v.y = __builtin_bit_cast(uint32_t, half2v{(_Float16)z, (_Float16)w});
     } else {
-      const size_t o = ((size_t)l * max_seq + p) * kvd + (size_t)(head - nq) * hd;
-      cache_store(kcache, o + e, lo, kv_f16);
-      cache_store(kcache, o + e + half, hi, kv_f16);
+      v.x = (uint32_t)Store<1>::rne(x) | (uint32_t)Store<1>::rne(y) << 16;
+      v.y = (uint32_t)Store<1>::rne(z) | (uint32_t)Store<1>::rne(w) << 16;
+    }
+    *(u32x2 *)((char *)cache + i * 2) = v;
+  };
+  for (int i = threadIdx.x; i < (nq + nkv) * per; i += blockDim.x) {
+    const int head = i / per, e = (i % per) * 4;
+    const float4 c01 = *(const float4 *)(rope + (size_t)p * half + e), c23 = *(const float4 *)(rope + (size_t)p * half + e + 2);
+    const float4 a = get(head * hd + e), b = get(head * hd + e + half);     // q heads, then k heads: contiguous in qkv
+    const float lo[4] = {a.x * c01.x - b.x * c01.y, a.y * c01.z - b.y * c01.w, a.z * c23.x - b.z * c23.y, a.w * c23.z - b.w * c23.w};
+    const float hi[4] = {a.x * c01.y + b.x * c01.x, a.y * c01.w + b.y * c01.z, a.z * c23.y + b.z * c23.x, a.w * c23.w + b.w * c23.z};
+    if (head < nq) {
+      half4 ql, qh;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) { ql[j] = (_Float16)(lo[j] * qs); qh[j] = (_Float16)(hi[j] * qs); }
+      _Float16 *const q = q16 + (size_t)t * qd + head * hd + e;
+      *(half4 *)q = ql;
+      *(half4 *)(q + half) = qh;
+    } else {
+      const size_t o = ((size_t)l * max_seq + p) * kvd + (size_t)(head - nq) * hd + e;
+      to_cache(kcache, o, lo[0], lo[1], lo[2], lo[3]);
+      to_cache(kcache, o + half, hi[0], hi[1], hi[2], hi[3]);
     }
   }
-  for (int i = threadIdx.x; i < kvd; i += blockDim.x)
-    cache_store(vcache, ((size_t)l * max_seq + p) * kvd + i, row[qd + kvd + i], kv_f16);
-}
-
-// a16[t, i] = fp16(silu(G[t, i]) * U[t, i]); gu: fp32 [m, 2 ffn], gate columns first
-__global__ void k_pf_swiglu(const float *__restrict__ gu, int ffn, _Float16 *a16) {
-  const int t = blockIdx.x;
-  const float *row = gu + (size_t)t * 2 * ffn;
-  for (int i = threadIdx.x; i < ffn; i += blockDim.x) {
-    const float g = row[i], u = row[ffn + i];
-    a16[(size_t)t * ffn + i] = (_Float16)(g / (1.0f + expf(-g)) * u);
+  for (int i = threadIdx.x * 4; i < kvd; i += blockDim.x * 4) {
+    const float4 v = get(qd + kvd + i);
+    to_cache(vcache, ((size_t)l * max_seq + p) * kvd + i, v.x, v.y, v.z, v.w);
   }
-}
-
-// dst[0 .. d) = src[0 .. d)   (the last prompt position's hidden state, kept for the head and
-// for the debug view of h(0..L))
-__global__ void k_pf_copy_row(const float *__restrict__ src, float *dst, int d) {
-  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < d; i += gridDim.x * blockDim.x) dst[i] = src[i];
 }
 
 // ------------------------------------------------------------- attention
@@ -599,7 +769,6 @@ __global__ void k_bd_pack_pairs(GemmB S, int interleaved, int N, int K, int grou
 // again).  n_part > 0: the partial sums [n_part][32][d] of the K-sliced GEMM that adds into h are
 // added first, in order, and h is updated.
 constexpr int kRowKeep = 4;
-struct Run8 { float v[8]; };
 __device__ __forceinline__ Run8 load_run8(float *row, const float *part, int n_part, int t, int d, int k) {
   float4 a = *(const float4 *)(row + k), b = *(const float4 *)(row + k + 4);
   if (n_part > 0) {

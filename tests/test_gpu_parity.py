@@ -671,6 +671,31 @@ def test_gemm_prefill_in_chunks_equals_serial_prefill_closely():
         assert relerr(a, np.asarray(b, np.float64)) <= 5e-3
 
 
+@pytest.mark.parametrize("shape,n_prompt", [
+    ("long", 4300),          # two passes over the activation buffers, the second one shorter
+    ("wide", 2100),          # 256 x 256 tiles for QKV and gate/up (ragged last row tile), K slices for O and down
+    ("wide", 771),           # 256 x 256 tiles for gate/up only
+])
+def test_gemm_prefill_tiles_and_k_slices_equal_serial_prefill_closely(shape, n_prompt):
+    """The tile and K-slice choices of the prefill GEMM, backbone and river, against the per-position
+    prefill (tolerance of the half-precision operands, as above)."""
+    cfg = LONG if shape == "long" else configs.ModelConfig("wide-pf-bf16", 2, 256, 32, 8, 128, 7168, 1002, 500000.0, 1e-5,
+                                                           configs.DTYPE_BF16, 64, 1, 2.0)
+    cfg = cfg.with_(max_seq=n_prompt + 8)
+    say(f"GEMM prefill tiles {cfg.name} {n_prompt}")
+    dw = binding.upload_weights(inputs.make_weights(cfg, 97, gain_std=0.05))
+    dr = binding.quantize_river(cfg, dw)
+    prompt = inputs.make_prompt(cfg.vocab, n_prompt, 98)
+    outs = []
+    for min_tokens in (-1, 1):
+        g = binding.River(cfg, dw, dr, prefill_gemm_min_tokens=min_tokens)
+        g.prefill(prompt, 1)
+        outs.append((g.hidden(), g.logits(), g.kcache()[:, :n_prompt].copy(), g.vcache()[:, :n_prompt].copy()))
+        g.close()
+    for a, b in zip(outs[1], outs[0]):
+        assert relerr(a, np.asarray(b, np.float64)) <= 5e-3
+
+
 # ------------------------------------------------------------ backbone offloading
 
 @pytest.mark.parametrize("mode", MODES, ids=MODE_IDS)
