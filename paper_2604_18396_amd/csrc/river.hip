@@ -1013,11 +1013,13 @@ static int check_device_error(river_ctx *x) {
   } while (0)
 
 // Tile and number of K slices of a prefill GEMM.  A workgroup's time is its K tiles times what one
-// takes: TileL (256 x 256, one workgroup per CU) 2.1 us, TileM (128 x 128) 0.8 us alone on its CU and
-// 1.45 us beside a second one; a K slice costs the write and the read of a plane of partial sums (4 MB
-// per us).  The rule takes the least of that over both tiles and up to 16 slices of at least four K
-// tiles.  (us measured: N 4096 K 14336: 77 rows TileM 140 / 28 with 1 / 8 slices, 512 rows TileL 291 /
-// 63 with 1 / 8, TileM 73 with 4; N 28672 K 4096: 512 rows TileM 156, TileL 118.)
+// takes, which grows with the share of the chip that is at work (clock, caches): TileM (128 x 128)
+// 0.5 .. 0.67 us, and as much again for every further one of its CU; TileL (256 x 256, one workgroup per
+// CU) 1.4 .. 2.05 us.  A K slice costs the write and the read of a plane of partial sums (4 MB per us).
+// The rule takes the least of that over both tiles and up to 16 slices of at least four K tiles.
+// (us measured: N 4096 K 14336: 512 rows TileL 290 / 63 with 1 / 8 slices, TileM 116 / 73 with 1 / 4; N
+// 28672 K 4096: 512 rows TileM 148, TileL 115; N 3072 K 2048: 255 rows TileM 10 with 4 slices, TileL 15
+// with 16.)
 struct PfPlan { bool large; int split; };
 static PfPlan pf_plan(const river_ctx *x, int N, int K, int m, bool may_split) {
   PfPlan best{false, 1};
@@ -1025,11 +1027,13 @@ static PfPlan pf_plan(const river_ctx *x, int N, int K, int m, bool may_split) {
   const int nk = K / pf::TK, cus = x->grid_persist;
   for (int large = 0; large < 2; ++large) {
     const int tm = large ? pf::TileL::TM : pf::TileM::TM, tn = large ? pf::TileL::TN : pf::TileM::TN;
+    const double alone = large ? 1.4 : 0.5, full = large ? 2.05 : 0.67;
     const long long tiles = (long long)((N + tn - 1) / tn) * ((m + tm - 1) / tm);
     for (int sp = 1; sp <= (may_split ? 16 : 1); ++sp) {
       if (sp > 1 && (nk / sp < 4 || (size_t)sp * m * N * 4 > x->lay.pf_big_bytes)) break;
-      const double per_cu = (double)((tiles * sp + cus - 1) / cus), k_tiles = (double)((nk + sp - 1) / sp);
-      const double us = k_tiles * (large ? 2.1 * per_cu : 0.15 + 0.65 * per_cu) + (sp > 1 ? 2.0 * sp * m * N * 4 / 4e6 : 0.0);
+      const double load = (double)(tiles * sp) / cus, whole = std::floor(load), part = load - whole;
+      const double k_tile_us = whole * full + (part > 0.0 ? alone + (full - alone) * part : 0.0);
+      const double us = (nk + sp - 1) / sp * k_tile_us + (sp > 1 ? 2.0 * sp * m * N * 4 / 4e6 : 0.0);
       if (us < best_us) { best_us = us; best = PfPlan{large != 0, sp}; }
     }
   }
@@ -1086,31 +1090,31 @@ static int prefill_gemm(river_ctx *x, int seq, const int32_t *tokens, int n, int
     const int m = std::min(step, n - c0);
     const int last = c0 + m == n ? m - 1 : -1;              // the row whose h(0..L) is kept
     HIP_TRY(x, hipMemcpyAsync(tok, tokens + c0, (size_t)m * 4, hipMemcpyHostToDevice, s));
+    const dim3 rowwise(m <= 2 * x->grid_persist ? 512 : 256);
     int parts = 0;                                           // partial sums waiting to be added into h
     for (int l = 0; l < L; ++l) {
       const bool river = l >= ep;
       const DevLayer &W = x->layers_h[l];
-      pf::k_pf_norm<<<dim3(m), dim3(256), 0, s>>>(h, l ? nullptr : tok, D.tok_emb, big, parts, m, W.attn_norm, d, c.rms_eps,
+      pf::k_pf_norm<<<dim3(m), rowwise, 0, s>>>(h, l ? nullptr : tok, D.tok_emb, big, parts, m, W.attn_norm, d, c.rms_eps,
                                                   x16, D.hidden + (size_t)l * d, last, 0);
       parts = launch_gemm<pf::PF_STORE>(x, l, river, m_qkv, 3, x16, d, big, m);
-      pf::k_pf_rope_store<<<dim3(m), dim3(256), 0, s>>>(big, parts, m, D.rope, c.n_q_heads, c.n_kv_heads, c.head_dim, c0, l,
+      pf::k_pf_rope_store<<<dim3(m), rowwise, 0, s>>>(big, parts, m, D.rope, c.n_q_heads, c.n_kv_heads, c.head_dim, c0, l,
                                                         c.max_seq, kc, vc, D.kv_f16, q16);
-      const dim3 ga(c.n_q_heads, (m + 127) / 128);
-      if (c.head_dim == 128)
-        pf::k_pf_attn<128><<<ga, dim3(256), 0, s>>>(q16, kc, vc, D.kv_f16, c.n_q_heads, c.n_kv_heads, l, c.max_seq,
-                                                    c0, m, x16);
-      else
-        pf::k_pf_attn<64><<<ga, dim3(256), 0, s>>>(q16, kc, vc, D.kv_f16, c.n_q_heads, c.n_kv_heads, l, c.max_seq,
-                                                   c0, m, x16);
+      // attention: as many query heads of a kv head per workgroup (4, 2 or 1) as divide them
+      const int rep = c.n_q_heads / c.n_kv_heads, hg = rep % 4 == 0 ? 4 : rep % 2 == 0 ? 2 : 1, qt = 256 / hg;
+      auto attn = c.head_dim == 128 ? (hg == 4 ? pf::k_pf_attn<128, 4> : hg == 2 ? pf::k_pf_attn<128, 2> : pf::k_pf_attn<128, 1>)
+                                    : (hg == 4 ? pf::k_pf_attn<64, 4> : hg == 2 ? pf::k_pf_attn<64, 2> : pf::k_pf_attn<64, 1>);
+      attn<<<dim3(c.n_q_heads / hg, (m + qt - 1) / qt), dim3(512), 0, s>>>(q16, kc, vc, D.kv_f16, c.n_q_heads, c.n_kv_heads,
+                                                                            l, c.max_seq, c0, m, x16);
       parts = launch_gemm<pf::PF_STORE>(x, l, river, m_o, 1, x16, qd, big, m);
-      pf::k_pf_norm<<<dim3(m), dim3(256), 0, s>>>(h, nullptr, nullptr, big, parts, m, W.ffn_norm, d, c.rms_eps, x16, nullptr,
+      pf::k_pf_norm<<<dim3(m), rowwise, 0, s>>>(h, nullptr, nullptr, big, parts, m, W.ffn_norm, d, c.rms_eps, x16, nullptr,
                                                   -1, 0);
       (void)launch_gemm<pf::PF_SWIGLU>(x, l, river, m_gu, 2, x16, d, a16, m);
       parts = launch_gemm<pf::PF_STORE>(x, l, river, m_d, 1, a16, ffn, big, m);
     }
     // h(L) of the last prompt position, the head's input
     if (last >= 0)
-      pf::k_pf_norm<<<dim3(1), dim3(256), 0, s>>>(h, nullptr, nullptr, big, parts, m, nullptr, d, c.rms_eps, nullptr,
+      pf::k_pf_norm<<<dim3(1), dim3(512), 0, s>>>(h, nullptr, nullptr, big, parts, m, nullptr, d, c.rms_eps, nullptr,
                                                   D.hidden + (size_t)L * d, last, last);
     HIP_TRY(x, hipGetLastError());
   }

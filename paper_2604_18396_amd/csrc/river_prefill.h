@@ -122,23 +122,25 @@ template <int TM_, int TN_, int WM_, int WN_, int PF_, int OCC_> struct GemmTile
   static constexpr int MW = TM / WM, NW = TN / WN;             // a wavefront's part of the tile
   static constexpr int MB = MW / 32, NB = NW / 32;             // ... in MFMA blocks
   static constexpr int GR = NT / 8;                            // rows a staging round of the workgroup covers
+  static constexpr int RA = TM / GR, RB = TN / GR;             // staging rounds per K tile
   static constexpr int LDS_BYTES = 2 * (TM + TN) * LDK * 2;    // two buffers each of A and B
-  static_assert(TM == 4 * GR && TN == 4 * GR, "four staging rounds per K tile for A and for B");
+  static_assert(RA == RB && (RA == 2 || RA == 4) && RA * GR == TM && RB * GR == TN, "two or four staging rounds");
 };
-typedef GemmTile<128, 128, 2, 2, 3, 2> TileM;
+typedef GemmTile<128, 128, 4, 2, 2, 2> TileM;
 typedef GemmTile<256, 256, 4, 2, 1, 1> TileL;
 enum { PF_STORE = 0, PF_SWIGLU = 1 };
 
-// Rows [GR * i, GR * (i + 1)) of B's tile -> matrix and its first row.  SwiGLU: the rows alternate
-// between gate and up every NW / 2 rows, so that a wavefront holds both factors of an output.
+// Row r of B's tile (a multiple of 8: the matrices' row counts are multiples of 64, so eight rows
+// never straddle two of them) -> matrix and row.  SwiGLU: the rows alternate between gate and up
+// every NW / 2 rows, so that a wavefront holds both factors of an output.
 template <class T, int EPI>
-__device__ __forceinline__ void gemm_b_group(const GemmB &B, int n_tile, int i, int N, int &mat, int &row) {
+__device__ __forceinline__ void gemm_b_row8(const GemmB &B, int n_tile, int r, int N, int &mat, int &row) {
   if constexpr (EPI == PF_SWIGLU) {
-    static_assert(T::GR == T::NW / 2, "a staging round is half of a wavefront's columns");
-    mat = i & 1;
-    row = min(n_tile * (T::TN / 2) + (i >> 1) * T::GR, B.rows[0] - T::GR);
+    constexpr int G = T::NW / 2;
+    mat = (r / G) & 1;
+    row = min(n_tile * (T::TN / 2) + r / (2 * G) * G + r % G, B.rows[0] - 8);
   } else {
-    gemm_b_row(B, min(n_tile * T::TN + i * T::GR, N - T::GR), N, mat, row);
+    gemm_b_row(B, min(n_tile * T::TN + r, N - 8), N, mat, row);
   }
 }
 
@@ -166,44 +168,50 @@ __global__ __launch_bounds__(T::NT, T::OCC) void k_pf_gemm(const _Float16 *__res
   const int nk_all = K / TK, kt0 = (int)((long long)nk_all * ks_i / k_split);
   const int nk = (int)((long long)nk_all * (ks_i + 1) / k_split) - kt0;
 
-  // what this thread stages per K tile: four 16-byte segments of A; of B four 16-byte segments
-  // (dense) or one 16-byte run of 32 codes with its (scale, zero) pair (river)
+  // what this thread stages per K tile: a 16-byte segment of A per round; of B one per round (dense)
+  // or as many words of 8 codes, consecutive, with the (scale, zero) pair of their row (river)
+  constexpr int RA = T::RA, RB = T::RB;
   const int srow = tid >> 3, sk = tid & 7;
-  unsigned a_off[4];
+  unsigned a_off[RA];
 #pragma unroll
-  for (int i = 0; i < 4; ++i) a_off[i] = (unsigned)min(m0 + i * GR + srow, M - 1) * (unsigned)lda * 2u + sk * 16u;
+  for (int i = 0; i < RA; ++i) a_off[i] = (unsigned)min(m0 + i * GR + srow, M - 1) * (unsigned)lda * 2u + sk * 16u;
   const __amdgpu_buffer_rsrc_t a_rsrc = gemm_rsrc((const char *)A + (size_t)kt0 * TK * 2);
   const int s_dst = srow * LDK + sk * 8;                       // + i * GR * LDK
-  __amdgpu_buffer_rsrc_t b_rsrc[W4 ? 1 : 4];
+  __amdgpu_buffer_rsrc_t b_rsrc[W4 ? 1 : RB];
   unsigned b_off = 0;
   const char *b_src = nullptr, *b_sz = nullptr;                // (W4: a thread's row may be of any of the matrices)
   int b_dst = 0;
   if constexpr (W4) {
-    const int row_l = tid >> 1, hf = tid & 1;
+    const int row_l = tid / (8 / RB), q = tid % (8 / RB);
     int mat, row;
-    gemm_b_group<T, EPI>(B, n_tile, row_l / GR, N, mat, row);
-    row += row_l % GR;
-    b_src = (const char *)B.w[mat] + (size_t)row * (K >> 1) + hf * 16 + kt0 * (TK / 2);
+    gemm_b_row8<T, EPI>(B, n_tile, row_l & ~7, N, mat, row);
+    row += row_l & 7;
+    b_src = (const char *)B.w[mat] + (size_t)row * (K >> 1) + q * RB * 4 + kt0 * (TK / 2);
     b_sz = (const char *)B.sz[mat] + (size_t)row * (K / group) * 4;
-    b_dst = row_l * LDK + hf * 32;
+    b_dst = row_l * LDK + q * RB * 8;
   } else {
-    b_off = (unsigned)srow * (unsigned)K * 2u + sk * 16u;
+    b_off = (unsigned)(lane >> 3) * (unsigned)K * 2u + sk * 16u;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
+    for (int i = 0; i < RB; ++i) {                             // the eight rows of this wavefront
       int mat, row;
-      gemm_b_group<T, EPI>(B, n_tile, i, N, mat, row);
+      gemm_b_row8<T, EPI>(B, n_tile, i * GR + wv * 8, N, mat, row);
       b_rsrc[i] = gemm_rsrc((const char *)B.w[mat] + ((size_t)row * K + kt0 * TK) * 2);
     }
   }
 
   // K tiles on their way from global memory to LDS: a ring of PF register sets
-  u32x4 fa[PF][4], fb[PF][W4 ? 1 : 4];          // (native vectors: as structs they are kept in scratch memory)
+  u32x4 fa[PF][RA], fb[PF][W4 ? 1 : RB];        // (native vectors: as structs they are kept in scratch memory)
   uint32_t fsz[PF];
   auto load_part = [&](int kt, int u, int i) {   // part i of tile kt into set u
     fa[u][i] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(a_rsrc, a_off[i], kt * (TK * 2), 0));
     if constexpr (W4) {
-      if (i == 3) {                               // (all four parts of the set have been staged)
-        fb[u][0] = *RIVER_GLOBAL(u32x4, b_src + kt * (TK / 2));
+      if (i == RB - 1) {                          // (all parts of the set have been staged)
+        if constexpr (RB == 4) {
+          fb[u][0] = *RIVER_GLOBAL(u32x4, b_src + kt * (TK / 2));
+        } else {
+          const u32x2 v = *RIVER_GLOBAL(u32x2, b_src + kt * (TK / 2));
+          fb[u][0] = u32x4{v.x, v.y, 0u, 0u};
+        }
         fsz[u] = *RIVER_GLOBAL(uint32_t, b_sz + (size_t)((kt0 + kt) * TK / group) * 4);
       }
     } else {
@@ -254,8 +262,8 @@ __global__ __launch_bounds__(T::NT, T::OCC) void k_pf_gemm(const _Float16 *__res
       if (ks < 3 || stage) frags(ks < 3 ? cur : cur ^ 1, (ks + 1) & 3, (ks + 1) & 1);
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {                            // parts 0, 1 | 2 | 3
-        if (ks != (i < 1 ? 0 : i - 1)) continue;
+      for (int i = 0; i < RA; ++i) {                           // parts 0, 1 | 2 | 3, or 0 | 1
+        if (ks != (RA == 2 ? i : i < 1 ? 0 : i - 1)) continue;
         if (stage) stage_part(u1, i, cur ^ 1);
         if (load) load_part(kt + 1 + PF, u1, i);
       }
@@ -278,13 +286,13 @@ __global__ __launch_bounds__(T::NT, T::OCC) void k_pf_gemm(const _Float16 *__res
   for (int u = 0; u < PF; ++u)
     if (u < nk) {
 #pragma unroll
-      for (int i = 0; i < 4; ++i) load_part(u, u, i);
+      for (int i = 0; i < RA; ++i) load_part(u, u, i);
     }
 #pragma unroll
-  for (int i = 0; i < 4; ++i) stage_part(0, i, 0);
+  for (int i = 0; i < RA; ++i) stage_part(0, i, 0);
   if (PF < nk) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i) load_part(PF, 0, i);
+    for (int i = 0; i < RA; ++i) load_part(PF, 0, i);
   }
   lds_barrier();
   frags(0, 0, 0);
@@ -355,14 +363,25 @@ __device__ __forceinline__ Run8 ld_run8_16(const void *p, size_t i) {       // e
   return Run8{{f[0], f[1], f[2], f[3], f[4], f[5], f[6], f[7]}};
 }
 
+// f(element, exists) for every one of n planes, in order, four at a time so that their loads go out
+// together (an element beyond the last plane is plane 0's again, for f to leave out)
+template <class F>
+__device__ __forceinline__ void add_planes(const float *p, size_t stride, int n, F f) {
+  for (int j = 0; j < n; j += 4) {
+#pragma unroll
+    for (int u = 0; u < 4; ++u) f(p + (j + u < n ? (size_t)(j + u) * stride : 0), j + u < n);
+  }
+}
+
 // The residual stream in front of a norm, and the norm: h[t, :] = E[token[t], :] (tokens given: block
 // 1's first norm) or h[t, :] += the n_part partial sums of the GEMM in front; x16[t, :] =
 // fp16(h[t, :] * rsqrt(mean(h[t, :]^2) + eps) * gain) (x16 null: no norm, the last block's sums only).
 // row_out: the row of the last prompt position (t == row_t) is also kept there, the debug view of
 // h(0..L) and the head's input.  d % 8 == 0, rows 16-byte aligned.  A row of up to 8192 columns is
-// read once and kept in registers between the reduction and the scaling.
+// read once and kept in registers between the reduction and the scaling.  256 threads, or 512 for few
+// rows, which then leave CUs idle (the host chooses).
 constexpr int kNormKeep = 4;
-__global__ __launch_bounds__(256) void k_pf_norm(float *__restrict__ h, const int *__restrict__ tokens,
+__global__ __launch_bounds__(512) void k_pf_norm(float *__restrict__ h, const int *__restrict__ tokens,
                                                  const void *tok_emb, const float *__restrict__ part, int n_part, int m,
                                                  const void *gain, int d, float eps, _Float16 *x16, float *row_out,
                                                  int row_t, int t0) {
@@ -381,11 +400,11 @@ __global__ __launch_bounds__(256) void k_pf_norm(float *__restrict__ h, const in
       for (int e = 0; e < 8; ++e) x.v[e] = Store<1>::ld(tok_emb, emb + k + e);
     } else {
       x = ld_run8(row + k);
-      for (int j = 0; j < n_part; ++j) {
-        const Run8 q = ld_run8(part + ((size_t)j * m + t) * d + k);
+      add_planes(part + (size_t)t * d + k, (size_t)m * d, n_part, [&](const float *p, bool ok) {
+        const Run8 q = ld_run8(p);
 #pragma unroll
-        for (int e = 0; e < 8; ++e) x.v[e] += q.v[e];
-      }
+        for (int e = 0; e < 8; ++e) x.v[e] += ok ? q.v[e] : 0.f;
+      });
     }
     if (tokens || n_part) st_run8(row + k, x);
     if (keep_row) st_run8(keep_row + k, x);
@@ -396,10 +415,10 @@ __global__ __launch_bounds__(256) void k_pf_norm(float *__restrict__ h, const in
   Run8 keep[kNormKeep];
 #pragma unroll
   for (int i = 0; i < kNormKeep; ++i) {
-    const int k = threadIdx.x * 8 + i * 2048;
+    const int k = threadIdx.x * 8 + i * (int)blockDim.x * 8;
     if (k < d) keep[i] = take(k);
   }
-  for (int k = threadIdx.x * 8 + kNormKeep * 2048; k < d; k += 2048) (void)take(k);
+  for (int k = threadIdx.x * 8 + kNormKeep * (int)blockDim.x * 8; k < d; k += (int)blockDim.x * 8) (void)take(k);
   if (!x16) return;
   const float r = 1.0f / sqrtf(block_sum(ss, red) / (float)d + eps);
   auto put = [&](int k, const Run8 &x) {
@@ -411,10 +430,10 @@ __global__ __launch_bounds__(256) void k_pf_norm(float *__restrict__ h, const in
   };
 #pragma unroll
   for (int i = 0; i < kNormKeep; ++i) {
-    const int k = threadIdx.x * 8 + i * 2048;
+    const int k = threadIdx.x * 8 + i * (int)blockDim.x * 8;
     if (k < d) put(k, keep[i]);
   }
-  for (int k = threadIdx.x * 8 + kNormKeep * 2048; k < d; k += 2048) put(k, ld_run8(row + k));   // (this thread's own)
+  for (int k = threadIdx.x * 8 + kNormKeep * (int)blockDim.x * 8; k < d; k += (int)blockDim.x * 8) put(k, ld_run8(row + k));   // (this thread's own)
 }
 
 // RoPE on q and k at position pos0 + t; q scaled by log2(e) / sqrt(hd) and stored as fp16 for
@@ -422,7 +441,7 @@ __global__ __launch_bounds__(256) void k_pf_norm(float *__restrict__ h, const in
 // (l, pos0 + t) of the shared cache.  qkv: n_part fp32 planes [m, qd + 2 kvd] of the QKV GEMM, added
 // in order.  One workgroup per token; a thread handles four rotation pairs (i, i + hd/2) of one head,
 // or four columns of v.
-__global__ __launch_bounds__(256) void k_pf_rope_store(const float *__restrict__ qkv, int n_part, int m,
+__global__ __launch_bounds__(512) void k_pf_rope_store(const float *__restrict__ qkv, int n_part, int m,
                                                        const float2 *__restrict__ rope, int nq, int nkv, int hd, int pos0,
                                                        int l, int max_seq, void *kcache, void *vcache, int kv_f16,
                                                        _Float16 *q16) {
@@ -430,11 +449,11 @@ __global__ __launch_bounds__(256) void k_pf_rope_store(const float *__restrict__
   const int qd = nq * hd, kvd = nkv * hd, ld = qd + 2 * kvd;
   const float qs = 1.4426950408889634f / sqrtf((float)hd);
   auto get = [&](int c) {
-    float4 a = *(const float4 *)(qkv + (size_t)t * ld + c);
-    for (int j = 1; j < n_part; ++j) {
-      const float4 b = *(const float4 *)(qkv + ((size_t)j * m + t) * ld + c);
-      a.x += b.x; a.y += b.y; a.z += b.z; a.w += b.w;
-    }
+    float4 a = make_float4(0.f, 0.f, 0.f, 0.f);
+    add_planes(qkv + (size_t)t * ld + c, (size_t)m * ld, n_part, [&](const float *p, bool ok) {
+      const float4 b = *(const float4 *)p;
+      a.x += ok ? b.x : 0.f; a.y += ok ? b.y : 0.f; a.z += ok ? b.z : 0.f; a.w += ok ? b.w : 0.f;
+    });
     return a;
   };
   auto to_cache = [&](void *cache, size_t i, float x, float y, float z, float w) {
@@ -476,27 +495,36 @@ __global__ __launch_bounds__(256) void k_pf_rope_store(const float *__restrict__
 // ------------------------------------------------------------- attention
 //
 // Causal attention of the chunk's queries (positions pos0 .. pos0 + m - 1) over cache
-// positions 0 .. their own.  One workgroup of four wavefronts per (query head, 128 queries),
-// 32 queries per wavefront.  Keys in tiles of 64 through LDS.  Transposed products, so that
-// the softmax over keys runs along a lane's registers and the probabilities feed the second
-// product from the registers they are in:
+// positions 0 .. their own.  One workgroup of eight wavefronts per (kv head, HG of its query heads,
+// QT = 256 / HG queries), 32 queries of one head per wavefront: the heads that share K and V share
+// their staging, which for a bf16 cache is a conversion (HG = 4: half as much of it per product as
+// with one head and 128 queries).  Keys in tiles of 64 through two LDS buffers: the next tile's rows
+// are fetched while a tile is multiplied and written to the other buffer behind it, one barrier per
+// tile.  Transposed products, so that the softmax over keys runs along a lane's registers and the
+// probabilities feed the second product from the registers they are in:
 //   S^T[key, q] = K[key, :] . Q[q, :]        A = K tile rows (LDS), B = Q (registers, whole loop)
 //   O^T[d, q]  += V^T[d, key] P^T[key, q]    A = V tile stored transposed (LDS), B = P^T (registers)
 // In S^T's register layout lane l holds, for query l % 32, keys (r/4)*8 + (l/32)*4 + r%4: the
 // eight keys of registers 0..7 (8..15) are the K slots of that lane group in the first
-// (second) MFMA of a 32-key block, and V^T is read from LDS with the same assignment.
-// The scores carry log2(e)/sqrt(hd) (folded into q16): base-2 online softmax.
-template <int HD>
-__global__ __launch_bounds__(256, 2) void k_pf_attn(const _Float16 *__restrict__ q16, const void *kcache,
-                                                 const void *vcache, int kv_f16, int nq, int nkv, int l, int max_seq,
-                                                 int pos0, int m, _Float16 *o16) {
+// (second) MFMA of a 32-key block; V^T keeps the keys of a lane group next to each other (the middle
+// two quadruples of every 16 keys swapped), so that its operand is one 16-byte read.
+// The scores carry log2(e)/sqrt(hd) (folded into q16): base-2 online softmax.  Bound by the matrix
+// cores and, per tile about as long, the vector units (32 exponentials per lane beside the 32 MFMAs).
+// Key 0 is visible to every query, so the running maximum is a real score after the first tile.
+template <int HD, int HG>
+__global__ __launch_bounds__(512, 1) void k_pf_attn(const _Float16 *__restrict__ q16, const void *kcache,
+                                                    const void *vcache, int kv_f16, int nq, int nkv, int l, int max_seq,
+                                                    int pos0, int m, _Float16 *o16) {
   constexpr int LDH = HD + 8;                 // K tile row stride (halfs)
   constexpr int LDV = 64 + 8;                 // V^T tile row stride (halfs)
-  __shared__ __attribute__((aligned(16))) _Float16 Ks[64 * LDH];
-  __shared__ __attribute__((aligned(16))) _Float16 Vt[HD * LDV];
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  const int h = blockIdx.x, kvh = h / (nq / nkv);
-  const int q0 = blockIdx.y * 128 + wv * 32;               // first query (chunk-relative) of this wavefront
+  constexpr int QT = 256 / HG, NK = HD / 64;  // queries per workgroup; 16-byte K segments per thread
+  __shared__ __attribute__((aligned(16))) _Float16 Ks[2][64 * LDH];
+  __shared__ __attribute__((aligned(16))) _Float16 Vt[2][HD * LDV];
+  const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  // (the kv head changes fastest: with eight of them every XCD's L2 sees the K and V of one)
+  const int kvh = blockIdx.x % nkv, h = kvh * (nq / nkv) + (blockIdx.x / nkv) * HG + wv % HG;
+  const int qt = (int)(gridDim.y - 1 - blockIdx.y) * QT;    // the longest rows first
+  const int q0 = qt + (wv / HG) * 32;                       // first query (chunk-relative) of this wavefront
   const int r32 = lane & 31, g = lane >> 5;
   const int qd = nq * HD, kvd = nkv * HD;
   const int tq = min(q0 + r32, m - 1);                      // this lane's query row (clamped: rows >= m are don't-care)
@@ -514,95 +542,116 @@ __global__ __launch_bounds__(256, 2) void k_pf_attn(const _Float16 *__restrict__
   for (int b = 0; b < HD / 32; ++b)
 #pragma unroll
     for (int r = 0; r < 16; ++r) oacc[b][r] = 0.f;
-  float mrun = -1.0e30f, lrun = 0.f;
+  float mrun = -1.0e30f, lrun = 0.f;                        // lrun: this lane group's keys only
 
-  const int last_pos = min(pos0 + (int)blockIdx.y * 128 + 127, pos0 + m - 1);   // last key any query here attends
+  const int last_pos = min(pos0 + qt + QT - 1, pos0 + m - 1);   // last key any query here attends
   const size_t cbase = (size_t)l * max_seq * kvd + (size_t)kvh * HD;
-  for (int kt = 0; kt <= last_pos; kt += 64) {
-    __syncthreads();                                        // previous tile consumed
-    // stage the K tile [64 keys][HD] (16-byte runs along d, consecutive lanes along d) and the V
-    // tile transposed [HD][64 keys] (consecutive lanes along the keys, so that the 2-byte
-    // transposed stores of a wavefront fall into one row)
-    for (int seg = tid; seg < 64 * (HD / 8); seg += 256) {
-      const int key = seg / (HD / 8), ds = seg % (HD / 8);
-      const int p = min(kt + key, last_pos);
-      const uint4 kw = *(const uint4 *)((const char *)kcache + (cbase + (size_t)p * kvd + ds * 8) * 2);
-      *(half8 *)(Ks + key * LDH + ds * 8) = cache_half8(kw, kv_f16);
+  // A key tile on its way: K rows as 16-byte segments along d; of V two neighbouring keys' segments
+  // per thread, which leave as eight 4-byte writes into the transposed tile.
+  const int v_key = 2 * (tid & 31), v_ds = tid >> 5;
+  const bool v_mine = v_ds < HD / 8;                        // (uniform per wavefront)
+  const int v_dst = v_ds * 8 * LDV + (v_key & ~15) + (((v_key >> 2) & 1) << 3) + (((v_key >> 3) & 1) << 2) + (v_key & 3);
+  u32x4 fk[NK], fv[2];
+  auto fetch = [&](int kt) {
+#pragma unroll
+    for (int i = 0; i < NK; ++i) {
+      const int seg = tid + 512 * i, key = seg / (HD / 8), ds = seg % (HD / 8);
+      fk[i] = *RIVER_GLOBAL(u32x4, (const char *)kcache + (cbase + (size_t)min(kt + key, last_pos) * kvd + ds * 8) * 2);
     }
-    for (int seg = tid; seg < 64 * (HD / 8); seg += 256) {
-      const int key = seg & 63, ds = seg >> 6;
-      const int p = min(kt + key, last_pos);
-      const uint4 vw = *(const uint4 *)((const char *)vcache + (cbase + (size_t)p * kvd + ds * 8) * 2);
-      const half8 vh = cache_half8(vw, kv_f16);
+    if (v_mine) {
 #pragma unroll
-      for (int e = 0; e < 8; ++e) Vt[(ds * 8 + e) * LDV + key] = vh[e];
+      for (int j = 0; j < 2; ++j)
+        fv[j] = *RIVER_GLOBAL(u32x4, (const char *)vcache + (cbase + (size_t)min(kt + v_key + j, last_pos) * kvd + v_ds * 8) * 2);
     }
-    __syncthreads();
-    // wavefronts whose queries all lie before this tile have nothing to add (uniform per wavefront)
-    if (kt > pos0 + q0 + 31) continue;
-
-    // S^T for the two 32-key blocks of the tile
-    f32x16 s[2];
+  };
+  auto stage = [&](int buf) {
 #pragma unroll
-    for (int kb = 0; kb < 2; ++kb) {
-#pragma unroll
-      for (int r = 0; r < 16; ++r) s[kb][r] = 0.f;
-#pragma unroll
-      for (int ks = 0; ks < HD / 16; ++ks) {
-        const half8 ka = *(const half8 *)(Ks + (kb * 32 + r32) * LDH + ks * 16 + g * 8);
-        s[kb] = mfma16(ka, qb[ks], s[kb]);
-      }
+    for (int i = 0; i < NK; ++i) {
+      const int seg = tid + 512 * i, key = seg / (HD / 8), ds = seg % (HD / 8);
+      const u32x4 w = fk[i];
+      *(half8 *)(Ks[buf] + key * LDH + ds * 8) = cache_half8(make_uint4(w.x, w.y, w.z, w.w), kv_f16);
     }
-    // mask keys beyond the query's position, running maximum over the lane's 32 keys and the
-    // other lane group's 32
-    float mx = mrun;
+    if (v_mine) {
+      const u32x4 w0 = fv[0], w1 = fv[1];
+      const half8 a = cache_half8(make_uint4(w0.x, w0.y, w0.z, w0.w), kv_f16), b = cache_half8(make_uint4(w1.x, w1.y, w1.z, w1.w), kv_f16);
 #pragma unroll
-    for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int key = kt + kb * 32 + c_row(r, lane);
-        if (key > my_pos) s[kb][r] = -1.0e30f;
-        mx = fmaxf(mx, s[kb][r]);
-      }
-    mx = fmaxf(mx, __shfl_xor(mx, 32));
-    const float corr = __builtin_amdgcn_exp2f(mrun - mx);
-    mrun = mx;
-    float psum = 0.f;
-    half8 pb[2][2];                                          // [key block][MFMA of the block]: B operands
-#pragma unroll
-    for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const float p = s[kb][r] > -0.5e30f ? __builtin_amdgcn_exp2f(s[kb][r] - mx) : 0.f;
-        const _Float16 ph = (_Float16)p;
-        psum += (float)ph;                                   // the sum of what is actually multiplied
-        pb[kb][r >> 3][r & 7] = ph;
-      }
-    psum += __shfl_xor(psum, 32);
-    lrun = lrun * corr + psum;
-#pragma unroll
-    for (int b = 0; b < HD / 32; ++b)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) oacc[b][r] *= corr;
-    // O^T += V^T P^T: per 32-key block two MFMAs; K slots of lane group g in MFMA j are keys
-    // kb*32 + j*16 + {g*4 .. g*4+3, 8 + g*4 .. 8 + g*4+3} (registers 8j .. 8j+7 of S^T)
-#pragma unroll
-    for (int b = 0; b < HD / 32; ++b)
+      for (int e = 0; e < 8; ++e) *(half2v *)(Vt[buf] + v_dst + e * LDV) = half2v{a[e], b[e]};
+    }
+  };
+  fetch(0);
+  stage(0);
+  lds_barrier();
+  int buf = 0;
+  for (int kt = 0; kt <= last_pos; kt += 64, buf ^= 1) {
+    const bool more = kt + 64 <= last_pos;
+    if (more) fetch(kt + 64);
+    // wavefronts without queries, and those whose queries all lie before this tile, have nothing to add
+    if (q0 < m && kt <= pos0 + q0 + 31) {
+      // S^T for the two 32-key blocks of the tile
+      f32x16 s[2];
 #pragma unroll
       for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
-        for (int j = 0; j < 2; ++j) {
-          const _Float16 *vp = Vt + (b * 32 + r32) * LDV + kb * 32 + j * 16 + g * 4;
-          const half4 v0 = *(const half4 *)vp, v1 = *(const half4 *)(vp + 8);
-          half8 va;
-          va[0] = v0[0]; va[1] = v0[1]; va[2] = v0[2]; va[3] = v0[3];
-          va[4] = v1[0]; va[5] = v1[1]; va[6] = v1[2]; va[7] = v1[3];
-          oacc[b] = mfma16(va, pb[kb][j], oacc[b]);
+        for (int r = 0; r < 16; ++r) s[kb][r] = 0.f;
+#pragma unroll
+      for (int ks = 0; ks < HD / 16; ++ks)
+#pragma unroll
+        for (int kb = 0; kb < 2; ++kb) {
+          const half8 ka = *(const half8 *)(Ks[buf] + (kb * 32 + r32) * LDH + ks * 16 + g * 8);
+          s[kb] = mfma16(ka, qb[ks], s[kb]);
         }
+      if (kt + 63 > pos0 + q0) {                             // the tile reaches beyond the first query: mask
+#pragma unroll
+        for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+          for (int r = 0; r < 16; ++r)
+            if (kt + kb * 32 + c_row(r, lane) > my_pos) s[kb][r] = -1.0e30f;
+      }
+      // running maximum over the lane's 32 keys and the other lane group's 32
+      float mx = s[0][0];
+#pragma unroll
+      for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) mx = fmaxf(mx, s[kb][r]);
+      mx = fmaxf(mx, __shfl_xor(mx, 32));
+      if (__any(mx > mrun)) {                                // (lanes whose maximum stays multiply by one)
+        mx = fmaxf(mx, mrun);
+        const float corr = __builtin_amdgcn_exp2f(mrun - mx);
+        mrun = mx;
+        lrun *= corr;
+#pragma unroll
+        for (int b = 0; b < HD / 32; ++b)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) oacc[b][r] *= corr;
+      }
+      half8 pb[2][2];                                        // [key block][MFMA of the block]: B operands
+#pragma unroll
+      for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+        for (int r = 0; r < 16; r += 2) {
+          const half2v p = {(_Float16)__builtin_amdgcn_exp2f(s[kb][r] - mrun), (_Float16)__builtin_amdgcn_exp2f(s[kb][r + 1] - mrun)};
+          pb[kb][r >> 3][r & 7] = p[0];
+          pb[kb][r >> 3][(r & 7) + 1] = p[1];
+          // the sum of what is actually multiplied, in fp32
+          lrun = __builtin_amdgcn_fdot2(p, half2v{(_Float16)1.f, (_Float16)1.f}, lrun, false);
+        }
+      // O^T += V^T P^T: per 32-key block two MFMAs
+#pragma unroll
+      for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+          for (int b = 0; b < HD / 32; ++b) {
+            const half8 va = *(const half8 *)(Vt[buf] + (b * 32 + r32) * LDV + kb * 32 + j * 16 + g * 8);
+            oacc[b] = mfma16(va, pb[kb][j], oacc[b]);
+          }
+    }
+    if (more) stage(buf ^ 1);
+    lds_barrier();
   }
   // O^T[d, q] / l -> o16[q, h*HD + d]; registers 4i .. 4i+3 are four consecutive d
   if (q0 + r32 < m) {
-    const float inv = 1.0f / lrun;
+    const float inv = 1.0f / (lrun + __shfl_xor(lrun, 32));
 #pragma unroll
     for (int b = 0; b < HD / 32; ++b)
 #pragma unroll
