@@ -376,13 +376,14 @@ __device__ __forceinline__ void add_planes(const float *p, size_t stride, int n,
 // The residual stream in front of a norm, and the norm: h[t, :] = E[token[t], :] (tokens given: block
 // 1's first norm) or h[t, :] += the n_part partial sums of the GEMM in front; x16[t, :] =
 // fp16(h[t, :] * rsqrt(mean(h[t, :]^2) + eps) * gain) (x16 null: no norm, the last block's sums only).
+// One workgroup per row, rows t0 .. t0 + gridDim.x - 1, which the planes hold from their row 0 on.
 // row_out: the row of the last prompt position (t == row_t) is also kept there, the debug view of
 // h(0..L) and the head's input.  d % 8 == 0, rows 16-byte aligned.  A row of up to 8192 columns is
 // read once and kept in registers between the reduction and the scaling.  256 threads, or 512 for few
 // rows, which then leave CUs idle (the host chooses).
 constexpr int kNormKeep = 4;
 __global__ __launch_bounds__(512) void k_pf_norm(float *__restrict__ h, const int *__restrict__ tokens,
-                                                 const void *tok_emb, const float *__restrict__ part, int n_part, int m,
+                                                 const void *tok_emb, const float *__restrict__ part, int n_part,
                                                  const void *gain, int d, float eps, _Float16 *x16, float *row_out,
                                                  int row_t, int t0) {
   __shared__ float red[16];
@@ -400,7 +401,7 @@ __global__ __launch_bounds__(512) void k_pf_norm(float *__restrict__ h, const in
       for (int e = 0; e < 8; ++e) x.v[e] = Store<1>::ld(tok_emb, emb + k + e);
     } else {
       x = ld_run8(row + k);
-      add_planes(part + (size_t)t * d + k, (size_t)m * d, n_part, [&](const float *p, bool ok) {
+      add_planes(part + (size_t)blockIdx.x * d + k, (size_t)gridDim.x * d, n_part, [&](const float *p, bool ok) {
         const Run8 q = ld_run8(p);
 #pragma unroll
         for (int e = 0; e < 8; ++e) x.v[e] += ok ? q.v[e] : 0.f;
@@ -514,7 +515,7 @@ __global__ __launch_bounds__(512) void k_pf_rope_store(const float *__restrict__
 template <int HD, int HG>
 __global__ __launch_bounds__(512, 1) void k_pf_attn(const _Float16 *__restrict__ q16, const void *kcache,
                                                     const void *vcache, int kv_f16, int nq, int nkv, int l, int max_seq,
-                                                    int pos0, int m, _Float16 *o16) {
+                                                    int pos0, int m, int qt0, _Float16 *o16) {
   constexpr int LDH = HD + 8;                 // K tile row stride (halfs)
   constexpr int LDV = 64 + 8;                 // V^T tile row stride (halfs)
   constexpr int QT = 256 / HG, NK = HD / 64;  // queries per workgroup; 16-byte K segments per thread
@@ -523,7 +524,7 @@ __global__ __launch_bounds__(512, 1) void k_pf_attn(const _Float16 *__restrict__
   const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   // (the kv head changes fastest: with eight of them every XCD's L2 sees the K and V of one)
   const int kvh = blockIdx.x % nkv, h = kvh * (nq / nkv) + (blockIdx.x / nkv) * HG + wv % HG;
-  const int qt = (int)(gridDim.y - 1 - blockIdx.y) * QT;    // the longest rows first
+  const int qt = qt0 + (int)(gridDim.y - 1 - blockIdx.y) * QT;   // the longest rows first; qt0: the first query at work
   const int q0 = qt + (wv / HG) * 32;                       // first query (chunk-relative) of this wavefront
   const int r32 = lane & 31, g = lane >> 5;
   const int qd = nq * HD, kvd = nkv * HD;
