@@ -300,7 +300,7 @@ __global__ void k_fill_bytes(uint4 *p, size_t n16, uint32_t word) {
 
 struct Layout {
   size_t kcache, vcache, rope, hidden, qbuf, obuf, kvcur, h1, abuf, logits, part_o, part_ml, cos_part,
-      amax_val, amax_idx, state, rec_token, rec_exit, rec_sims, layers, dev, trace, qsz, total;
+      amax_val, amax_idx, state, rec, layers, dev, trace, qsz, total;
   size_t cache_bytes, qsz_bytes;
   size_t bd_partial;                     // [kBdKSplit][32][d_model] partial sums of the K-sliced GEMMs
   size_t bd_ssq;
@@ -309,8 +309,7 @@ struct Layout {
   size_t pf_tok, pf_h, pf_x16, pf_q16, pf_a16, pf_big, pf_big_bytes;
   int pf_rows;
   // batched contexts (max_batch > 1): per-sequence state, step buffers, records
-  size_t bd_state, bd_hprev, bd_part_o, bd_part_ml, bd_tickets, bd_logits, bd_hist, bd_rec_token, bd_rec_exit,
-      bd_rec_sims;
+  size_t bd_state, bd_hprev, bd_part_o, bd_part_ml, bd_tickets, bd_logits, bd_hist, bd_rec;
 };
 
 
@@ -403,6 +402,7 @@ struct river_ctx {
   std::vector<DevLayer> layers_h;   // host copy of the per-block pointer table (GEMM prefill launches)
   std::vector<bd::BdB> bd_dense_h, bd_twin_h;   // [L][4] stream-order weights of the QKV / O / gate-up / down GEMMs
   bd::BdB bd_head;                  // (batched contexts; a twin that was not given: null)
+  std::vector<int32_t> rec_h;       // host copy of a step's record
   std::vector<int> pos_b;           // batched contexts: positions in the cache, per sequence
   long long steps_b = 0;            // batched decode steps recorded so far
   int last_n = 0;                   // sequences of the last batched step
@@ -521,9 +521,7 @@ static Layout make_layout(const river_config *c) {
   y.amax_val = take((size_t)kMaxGrid * 4);
   y.amax_idx = take((size_t)kMaxGrid * 4);
   y.state = take(sizeof(DevState));
-  y.rec_token = take((size_t)kRecords * 4);
-  y.rec_exit = take((size_t)kRecords * 4);
-  y.rec_sims = take((size_t)kRecords * c->n_layers * 4);
+  y.rec = take((size_t)kRecords * (kRecHead + c->n_layers) * 4);
   y.layers = take((size_t)c->n_layers * sizeof(DevLayer));
   y.dev = take(sizeof(Dev));
   y.trace = take(((size_t)5 * c->n_layers * 2 * kMaxGrid + 64) * 8);
@@ -555,9 +553,7 @@ static Layout make_layout(const river_config *c) {
     y.bd_tickets = take((size_t)bd::kRows * c->n_q_heads * 4);
     y.bd_logits = take(B * c->vocab * 4);
     y.bd_hist = take((size_t)(c->n_layers + 1) * B * c->d_model * 4);
-    y.bd_rec_token = take((size_t)bd::kRecordsB * B * 4);
-    y.bd_rec_exit = take((size_t)bd::kRecordsB * B * 4);
-    y.bd_rec_sims = take((size_t)bd::kRecordsB * B * c->n_layers * 4);
+    y.bd_rec = take((size_t)bd::kRecordsB * B * (2 + c->n_layers) * 4);         // a step's row: tokens, exits, similarities
     y.bd_partial = take((size_t)bd::kBdKSplit * bd::kRows * c->d_model * 4);
     y.bd_ssq = take((size_t)kMaxGrid * bd::kRows * 4);                          // sums of squares per GEMM workgroup and row
     y.bd_stream_bytes = bd_stream_bytes_of(c);
@@ -762,8 +758,7 @@ static int create_impl(const river_config *cfg, const river_weights *w, const ri
     D.bar = (unsigned long long *)bp;
     D.bar_vector_poll = 0;
   }
-  D.rec_token = (int *)(act + lay.rec_token); D.rec_exit = (int *)(act + lay.rec_exit);
-  D.rec_sims = (float *)(act + lay.rec_sims);
+  D.rec = (int *)(act + lay.rec);
   D.trace = (unsigned long long *)(act + lay.trace);
   x->lds_bytes = ((size_t)D.xcap + lds_half_floats(D.xcap) + 64) * sizeof(float);
 
@@ -992,18 +987,18 @@ static int enqueue(river_ctx *x, int token, int forced_e, int want_head, int rec
   return rc;
 }
 
+static int device_wait_gave_up(river_ctx *x) {
+  x->err = "a device-wide barrier wait exceeded spin_limit; results of the step are invalid";
+  x->broken = true;
+  return RIVER_EHIP;
+}
 // After a synchronising call: did a bounded device wait give up?
 static int check_device_error(river_ctx *x) {
   int err = 0;
   HIP_TRY(x, hipMemcpyAsync(&err, (char *)x->dev.bar + kBarErrorByte, sizeof(int),
                             hipMemcpyDeviceToHost, x->stream));
   HIP_TRY(x, hipStreamSynchronize(x->stream));
-  if (err) {
-    x->err = "a device-wide barrier wait exceeded spin_limit; results of the step are invalid";
-    x->broken = true;
-    return RIVER_EHIP;
-  }
-  return RIVER_OK;
+  return err ? device_wait_gave_up(x) : RIVER_OK;
 }
 
 #define CHECK_CTX(x)                                   \
@@ -1132,7 +1127,7 @@ static int prefill_gemm(river_ctx *x, int seq, const int32_t *tokens, int n, int
   A.pos = n - 1; A.token = -1; A.forced_e = ep; A.want_head = 1; A.rec_slot = -1; A.n_splits = 1; A.bar_base = 0;
   k_head<1><<<dim3(x->grid_gemv), dim3(x->block), x->lds_bytes, s>>>(x->dev_d, A);
   if (c.max_batch > 1)
-    bd::k_bd_after_prefill<<<dim3(1), dim3(64), 0, s>>>(x->st_b, seq, &D.st->cur_token, n);
+    bd::k_bd_after_prefill<<<dim3(1), dim3(64), 0, s>>>(x->st_b, seq, &D.st->cur_token);
   HIP_TRY(x, hipGetLastError());
   if (c.max_batch > 1) x->pos_b[seq] = n;
   else x->pos = n;
@@ -1219,13 +1214,15 @@ extern "C" int river_decode_step(river_ctx *x, const int32_t *in_token, const in
   x->steps += 1;
   x->have_token = true;
   if (!out_token) return RIVER_OK;
-  HIP_TRY(x, hipMemcpyAsync(out_token, x->dev.rec_token + slot, 4, hipMemcpyDeviceToHost, x->stream));
-  if (out_exit_layer)
-    HIP_TRY(x, hipMemcpyAsync(out_exit_layer, x->dev.rec_exit + slot, 4, hipMemcpyDeviceToHost, x->stream));
-  if (out_sims)
-    HIP_TRY(x, hipMemcpyAsync(out_sims, x->dev.rec_sims + (size_t)slot * L, (size_t)L * 4,
-                              hipMemcpyDeviceToHost, x->stream));
-  return check_device_error(x);
+  // the step's record in one copy, the device's error flag with it
+  const size_t row = (size_t)kRecHead + L;
+  x->rec_h.resize(row);
+  HIP_TRY(x, hipMemcpyAsync(x->rec_h.data(), x->dev.rec + slot * row, row * 4, hipMemcpyDeviceToHost, x->stream));
+  HIP_TRY(x, hipStreamSynchronize(x->stream));
+  *out_token = x->rec_h[0];
+  if (out_exit_layer) *out_exit_layer = x->rec_h[1] & ~kRecErrorBit;
+  if (out_sims) std::memcpy(out_sims, x->rec_h.data() + kRecHead, (size_t)L * 4);
+  return x->rec_h[1] & kRecErrorBit ? device_wait_gave_up(x) : RIVER_OK;
 }
 
 // GEMM g (QKV, O, gate/up, down) of block l of a batched decode step, or the LM head (Bq null,
@@ -1284,8 +1281,12 @@ extern "C" int river_decode_batch(river_ctx *x, int32_t n_seq, const int32_t *in
     return RIVER_EINVAL;
   }
   const int L = c.n_layers, n = n_seq;
-  std::vector<int32_t> fe(n, -1);
+  bd::StepIn in{};
+  int *const fe = in.forced;
   for (int b = 0; b < n; ++b) {
+    in.pos[b] = x->pos_b[b];
+    in.token[b] = in_tokens ? in_tokens[b] : -1;
+    fe[b] = -1;
     if (x->pos_b[b] < 1) { x->err = "decode before prefill of every sequence"; return RIVER_ESTATE; }
     if (x->pos_b[b] >= c.max_seq) { x->err = "KV cache full"; return RIVER_ENOSPC; }
     if (in_tokens && (in_tokens[b] < 0 || in_tokens[b] >= c.vocab)) { x->err = "token id out of range"; return RIVER_EINVAL; }
@@ -1313,15 +1314,14 @@ extern "C" int river_decode_batch(river_ctx *x, int32_t n_seq, const int32_t *in
   _Float16 *a16 = (_Float16 *)(x->ws + y.pf_a16);
   const int slot = (int)(x->steps_b % bd::kRecordsB);
   const size_t B = c.max_batch;
-  int *rec_token = (int *)(x->ws + y.bd_rec_token) + (size_t)slot * B;
-  int *rec_exit = (int *)(x->ws + y.bd_rec_exit) + (size_t)slot * B;
-  float *rec_sims = (float *)(x->ws + y.bd_rec_sims) + (size_t)slot * B * L;
+  int *const rec_token = (int *)(x->ws + y.bd_rec) + (size_t)slot * B * (2 + L), *const rec_exit = rec_token + B;
+  float *const rec_sims = (float *)(rec_exit + B);
   const bd::SeqState st = x->st_b;
   float *s_of = (float *)(st.forced + B);                    // [max_batch] similarities of the current block
-  HIP_TRY(x, hipMemcpyAsync(st.forced, fe.data(), (size_t)n * 4, hipMemcpyHostToDevice, s));
-  if (in_tokens) HIP_TRY(x, hipMemcpyAsync(st.token, in_tokens, (size_t)n * 4, hipMemcpyHostToDevice, s));
-  bd::k_bd_fill_nan<<<dim3((n * L + 255) / 256), dim3(256), 0, s>>>(rec_sims, n * L);
-  bd::k_bd_embed<<<dim3(n), dim3(256), 0, s>>>(st, D.tok_emb, d, c.vocab, L, h, hprev, hist);
+  // the sequences' state, h(0), and the norm in front of block 1's QKV GEMM (the other norms: the
+  // previous block's last kernel)
+  bd::k_bd_begin<<<dim3(n), dim3(256), 0, s>>>(in, st, D.tok_emb, d, c.vocab, L, h, hprev, hist, rec_sims,
+                                               x->layers_h[0].attn_norm, c.rms_eps, x16);
   const size_t seq_stride = y.cache_bytes / 2;               // elements (bf16)
   // attention: one workgroup per (sequence, kv head, group of query heads, split of the positions);
   // splits so that every CU has two workgroups (measured best) of at least 128 positions
@@ -1335,8 +1335,6 @@ extern "C" int river_decode_batch(river_ctx *x, int32_t n_seq, const int32_t *in
   const int qkv_ld = qd + 2 * c.n_kv_heads * c.head_dim;
   for (int l = 0; l < L; ++l) {
     const DevLayer &W = x->layers_h[l];
-    // the norm in front of the QKV GEMM: block 1's here, the others' by the previous block's last kernel
-    if (l == 0) bd::k_bd_rmsnorm<<<dim3(n), dim3(256), 0, s>>>(h, W.attn_norm, d, c.rms_eps, x16, nullptr, 0);
     launch_bd_gemm(x, l, 0, x16, big, qkv_ld, bd::EPI_STORE, n);
     {
       const dim3 ga((n * c.n_kv_heads * n_splits + 7) / 8 * 8 * hgs);
@@ -1376,10 +1374,12 @@ extern "C" int river_decode_batch(river_ctx *x, int32_t n_seq, const int32_t *in
   x->steps_b += 1;
   x->last_n = n;
   if (!out_tokens) return RIVER_OK;
-  HIP_TRY(x, hipMemcpyAsync(out_tokens, rec_token, (size_t)n * 4, hipMemcpyDeviceToHost, s));
-  if (out_exit_layers) HIP_TRY(x, hipMemcpyAsync(out_exit_layers, rec_exit, (size_t)n * 4, hipMemcpyDeviceToHost, s));
-  if (out_sims) HIP_TRY(x, hipMemcpyAsync(out_sims, rec_sims, (size_t)n * L * 4, hipMemcpyDeviceToHost, s));
+  x->rec_h.resize(B * (2 + L));
+  HIP_TRY(x, hipMemcpyAsync(x->rec_h.data(), rec_token, (out_sims ? B * 2 + (size_t)n * L : B + n) * 4, hipMemcpyDeviceToHost, s));
   HIP_TRY(x, hipStreamSynchronize(s));
+  std::memcpy(out_tokens, x->rec_h.data(), (size_t)n * 4);
+  if (out_exit_layers) std::memcpy(out_exit_layers, x->rec_h.data() + B, (size_t)n * 4);
+  if (out_sims) std::memcpy(out_sims, x->rec_h.data() + 2 * B, (size_t)n * L * 4);
   return RIVER_OK;
 }
 
@@ -1391,15 +1391,18 @@ extern "C" int river_read_batch_records(river_ctx *x, int32_t n_steps, int32_t n
     x->err = "bad batch record request";
     return RIVER_EINVAL;
   }
-  const size_t B = x->cfg.max_batch;
+  const size_t B = x->cfg.max_batch, row = B * (2 + (size_t)x->cfg.n_layers);
+  std::vector<int32_t> rows(2 * B * (size_t)n_steps);         // tokens and exits of a step are neighbours
   for (int i = 0; i < n_steps; ++i) {
     const size_t slot = (size_t)((x->steps_b - n_steps + i) % bd::kRecordsB);
-    HIP_TRY(x, hipMemcpyAsync(tokens + (size_t)i * n_seq, (int *)(x->ws + x->lay.bd_rec_token) + slot * B,
-                              (size_t)n_seq * 4, hipMemcpyDeviceToHost, x->stream));
-    HIP_TRY(x, hipMemcpyAsync(exit_layers + (size_t)i * n_seq, (int *)(x->ws + x->lay.bd_rec_exit) + slot * B,
-                              (size_t)n_seq * 4, hipMemcpyDeviceToHost, x->stream));
+    HIP_TRY(x, hipMemcpyAsync(rows.data() + 2 * B * i, (int *)(x->ws + x->lay.bd_rec) + slot * row, 2 * B * 4,
+                              hipMemcpyDeviceToHost, x->stream));
   }
   HIP_TRY(x, hipStreamSynchronize(x->stream));
+  for (int i = 0; i < n_steps; ++i) {
+    std::memcpy(tokens + (size_t)i * n_seq, rows.data() + 2 * B * i, (size_t)n_seq * 4);
+    std::memcpy(exit_layers + (size_t)i * n_seq, rows.data() + 2 * B * i + B, (size_t)n_seq * 4);
+  }
   return RIVER_OK;
 }
 
@@ -1410,18 +1413,20 @@ extern "C" int river_read_records(river_ctx *x, int32_t n, int32_t *tokens, int3
     x->err = "bad record count";
     return RIVER_EINVAL;
   }
-  const int L = x->cfg.n_layers;
   int rc = check_device_error(x);
   if (rc) return rc;
-  for (int i = 0; i < n; ++i) {
-    const int slot = (int)((x->steps - n + i) % kRecords);
-    HIP_TRY(x, hipMemcpyAsync(tokens + i, x->dev.rec_token + slot, 4, hipMemcpyDeviceToHost, x->stream));
-    HIP_TRY(x, hipMemcpyAsync(exit_layers + i, x->dev.rec_exit + slot, 4, hipMemcpyDeviceToHost, x->stream));
-    if (sims)
-      HIP_TRY(x, hipMemcpyAsync(sims + (size_t)i * L, x->dev.rec_sims + (size_t)slot * L, (size_t)L * 4,
-                                hipMemcpyDeviceToHost, x->stream));
-  }
+  // the ring's rows in at most two copies
+  const size_t row = (size_t)kRecHead + x->cfg.n_layers;
+  std::vector<int32_t> rows(row * (size_t)n);
+  const int first = n ? (int)((x->steps - n) % kRecords) : 0, n0 = std::min(n, kRecords - first);
+  if (n0 > 0) HIP_TRY(x, hipMemcpyAsync(rows.data(), x->dev.rec + first * row, n0 * row * 4, hipMemcpyDeviceToHost, x->stream));
+  if (n > n0) HIP_TRY(x, hipMemcpyAsync(rows.data() + n0 * row, x->dev.rec, (n - n0) * row * 4, hipMemcpyDeviceToHost, x->stream));
   HIP_TRY(x, hipStreamSynchronize(x->stream));
+  for (int i = 0; i < n; ++i) {
+    tokens[i] = rows[i * row];
+    exit_layers[i] = rows[i * row + 1] & ~kRecErrorBit;
+    if (sims) std::memcpy(sims + (size_t)i * x->cfg.n_layers, rows.data() + i * row + kRecHead, (size_t)x->cfg.n_layers * 4);
+  }
   return RIVER_OK;
 }
 
@@ -1432,9 +1437,7 @@ extern "C" int river_rewind(river_ctx *x, int32_t seq, int32_t new_len) {
       x->err = "bad rewind length";
       return RIVER_EINVAL;
     }
-    x->pos_b[seq] = new_len;
-    HIP_TRY(x, hipMemcpyAsync(x->st_b.pos + seq, &x->pos_b[seq], 4, hipMemcpyHostToDevice, x->stream));
-    HIP_TRY(x, hipStreamSynchronize(x->stream));
+    x->pos_b[seq] = new_len;                                  // (the next step is told)
     return RIVER_OK;
   }
   if (seq != 0 || new_len < 0 || new_len > x->pos) { x->err = "bad rewind length"; return RIVER_EINVAL; }

@@ -32,6 +32,8 @@ constexpr int kNL = 8;             // 16-byte loads per lane per step
 constexpr int kMaxGrid = 512;      // upper bound on workgroups per launch (partial-result arrays)
 constexpr int kMaxSplits = 8;     // split-K factor of decode attention
 constexpr int kRecords = 4096;     // ring of per-step records
+constexpr int kRecHead = 2;        // words of a record in front of the similarities
+constexpr int kRecErrorBit = 1 << 30;
 
 enum { M_WQ = 0, M_WK, M_WV, M_WO, M_GATE, M_UP, M_DOWN };
 
@@ -71,8 +73,8 @@ struct Dev {
   int *amax_idx;                  // [kMaxGrid]
   DevState *st;
   unsigned long long *bar;        // barrier block (see barrier_arrive): 8 counters 128 B apart, error flag at byte 1024
-  int *rec_token, *rec_exit;      // [kRecords]
-  float *rec_sims;                // [kRecords][L]
+  int *rec;                       // [kRecords][kRecHead + L] one row per step: token, exit position (with
+                                  // kRecErrorBit if a bounded device wait has given up), similarities
   unsigned long long *trace;      // [5L][2][grid] barrier arrive / release times (RIVER_TRACE builds)
 };
 
@@ -93,6 +95,10 @@ struct StepArgs {
 #define RIVER_CONSTANT(T, p) ((const __attribute__((address_space(4))) T *)(p))
 typedef const __attribute__((address_space(4))) Dev &DevRef;
 typedef const __attribute__((address_space(4))) DevLayer &LayerRef;
+// the similarities of this step's record
+__device__ __forceinline__ float *rec_sims(DevRef D, const StepArgs &A) {
+  return (float *)(D.rec + (size_t)A.rec_slot * (kRecHead + D.L) + kRecHead);
+}
 __device__ __forceinline__ LayerRef layer_of(DevRef D, int l) { return *RIVER_CONSTANT(DevLayer, D.layers + l); }
 
 // Exit state of the current token, identical in every workgroup (each derives it from the
@@ -1111,7 +1117,7 @@ __device__ __forceinline__ void exit_test(DevRef D, const StepArgs &A, int l1, C
   }
   const float s = similarity_from_partials(D, lds_red(D, lds));
   if (blockIdx.x == 0 && threadIdx.x == 0 && A.rec_slot >= 0)
-    pub(D.rec_sims + (size_t)A.rec_slot * D.L + (l1 - 1), s);
+    pub(rec_sims(D, A) + (l1 - 1), s);
   if (may && s > D.tau) {
     ctl.river = true;
     ctl.exit_pos = l1;
@@ -1126,7 +1132,7 @@ __device__ __forceinline__ void record_similarity(DevRef D, const StepArgs &A, i
   if (ctl.river && ctl.exit_pos < l1) return;          // block l1 ran as a river block: no similarity
   const float s = similarity_from_partials(D, lds_red(D, lds));
   // device-coherent stores: the record row is written by workgroups of different XCDs
-  if (threadIdx.x == 0) pub(D.rec_sims + (size_t)A.rec_slot * D.L + (l1 - 1), s);
+  if (threadIdx.x == 0) pub(rec_sims(D, A) + (l1 - 1), s);
 }
 
 // Which format will block l1 + 1 run in, as far as can be known before block l1's
@@ -1704,7 +1710,7 @@ __device__ __forceinline__ void phase_head(DevRef D, const StepArgs &A, const Ct
   float *red = lds_red(D, lds);
   if (!ctl.river && A.rec_slot >= 0) {      // similarity of the last backbone block: recorded, never tested
     const float s = similarity_from_partials(D, red);
-    if (blockIdx.x == 0 && threadIdx.x == 0) pub(D.rec_sims + (size_t)A.rec_slot * D.L + (D.L - 1), s);
+    if (blockIdx.x == 0 && threadIdx.x == 0) pub(rec_sims(D, A) + (D.L - 1), s);
   }
   stage_norm<DT>(D.hidden + (size_t)D.L * D.d, D.final_norm, D.d, D.eps, run_log2<DT>(false, D.d), lds, red, late);
   const int lane = pre.lane;
@@ -1736,8 +1742,10 @@ __device__ __forceinline__ void phase_head(DevRef D, const StepArgs &A, const Ct
     if (threadIdx.x == 0) {
       D.st->cur_token = bi;
       if (A.rec_slot >= 0) {
-        D.rec_token[A.rec_slot] = bi;
-        D.rec_exit[A.rec_slot] = ctl.exit_pos;
+        int *const row = D.rec + (size_t)A.rec_slot * (kRecHead + D.L);
+        const int err = __hip_atomic_load(bar_error(D.bar), __ATOMIC_RELAXED, RIVER_AG);
+        row[0] = bi;
+        row[1] = ctl.exit_pos | (err ? kRecErrorBit : 0);
       }
     }
   }
@@ -1755,7 +1763,7 @@ __device__ __forceinline__ Ctl ctl_init(DevRef D, const StepArgs &A) {
 __device__ __forceinline__ void record_init(DevRef D, const StepArgs &A) {
   if (blockIdx.x == 0 && A.rec_slot >= 0)
     for (int i = threadIdx.x; i < D.L; i += blockDim.x)
-      pub(D.rec_sims + (size_t)A.rec_slot * D.L + i, __uint_as_float(0x7fc00000u));
+      pub(rec_sims(D, A) + i, __uint_as_float(0x7fc00000u));
 }
 
 }  // namespace river

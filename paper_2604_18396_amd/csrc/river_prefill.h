@@ -202,6 +202,9 @@ __global__ __launch_bounds__(T::NT, T::OCC) void k_pf_gemm(const _Float16 *__res
   // K tiles on their way from global memory to LDS: a ring of PF register sets
   u32x4 fa[PF][RA], fb[PF][W4 ? 1 : RB];        // (native vectors: as structs they are kept in scratch memory)
   uint32_t fsz[PF];
+  // (tiles are loaded one after the other: the group of the next one by counting, no division per tile)
+  const int tiles_per_group = group / TK;
+  int g_at = W4 ? kt0 / tiles_per_group : 0, g_left = W4 ? tiles_per_group - kt0 % tiles_per_group : 0;
   auto load_part = [&](int kt, int u, int i) {   // part i of tile kt into set u
     fa[u][i] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(a_rsrc, a_off[i], kt * (TK * 2), 0));
     if constexpr (W4) {
@@ -212,7 +215,8 @@ __global__ __launch_bounds__(T::NT, T::OCC) void k_pf_gemm(const _Float16 *__res
           const u32x2 v = *RIVER_GLOBAL(u32x2, b_src + kt * (TK / 2));
           fb[u][0] = u32x4{v.x, v.y, 0u, 0u};
         }
-        fsz[u] = *RIVER_GLOBAL(uint32_t, b_sz + (size_t)((kt0 + kt) * TK / group) * 4);
+        fsz[u] = *RIVER_GLOBAL(uint32_t, b_sz + (size_t)g_at * 4);
+        if (--g_left == 0) { g_left = tiles_per_group; ++g_at; }
       }
     } else {
       fb[u][i] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(b_rsrc[i], b_off, kt * (TK * 2), 0));
@@ -689,7 +693,7 @@ constexpr int kRows = 32;             // most sequences per step (rows of the ac
 constexpr int kRecordsB = 1024;       // ring of per-step records of a batched context
 
 struct SeqState {                     // device-side state of the sequences, [max_batch] each
-  int *pos;                           // positions in the cache = position the next token is written to
+  int *pos;                           // position the token of the current step is written to
   int *token;                         // token to consume next (produced by the last step / prefill)
   int *river;                         // 1: the sequence has left the backbone in the current step
   int *exit_pos;                      // exit position of the current step
@@ -840,37 +844,60 @@ __device__ __forceinline__ void norm_store_run8(const Run8 &x, float r, const vo
   frag_store8(xf, t, k, o);
 }
 
-// xf[t, :] = fp16(h[t, :] * rsqrt(mean(h[t, :]^2) + eps) * gain) in fragment order; d % 8 == 0
-__global__ __launch_bounds__(256) void k_bd_rmsnorm(float *__restrict__ h, const void *gain, int d, float eps,
-                                                    _Float16 *xf, const float *__restrict__ part, int n_part) {
+// What a step is told about its sequences, by value: nothing to copy to the device in front of it.
+struct StepIn {
+  int pos[kRows];             // position the token is written to (the host's count)
+  int token[kRows];           // token to consume, or < 0: the one the last step / prefill left
+  int forced[kRows];          // forced exit position (< 0: Eq. 1 decides)
+};
+
+// Start of a step, one workgroup per sequence: its state (forced exit position 0 puts it into the
+// river from the first block on), h[b, :] = E[token[b], :] (also h_prev and the debug view of h(0)),
+// sims[b, :] = NaN (blocks that run as river twins keep it), and block 1's attention norm:
+// xf[b, :] = fp16(h[b, :] * rsqrt(mean(h[b, :]^2) + eps) * gain) in fragment order; d % 8 == 0.
+__global__ __launch_bounds__(256) void k_bd_begin(StepIn in, SeqState st, const void *tok_emb, int d, int vocab, int L,
+                                                  float *h, float *h_prev, float *hist, float *sims, const void *gain,
+                                                  float eps, _Float16 *xf) {
   __shared__ float red[16];
-  const int t = blockIdx.x;
-  float *row = h + (size_t)t * d;
-  Run8 keep[kRowKeep];
+  const int b = blockIdx.x;
+  const int given = in.token[b], tok = min(max(given >= 0 ? given : st.token[b], 0), vocab - 1);
+  const bool wide = ((uintptr_t)tok_emb & 15) == 0;            // (the embedding may have any alignment)
   float ss = 0.f;
-#pragma unroll
-  for (int i = 0; i < kRowKeep; ++i) {
-    const int k = threadIdx.x * 8 + i * 2048;
-    if (k < d) {
-      keep[i] = load_run8(row, part, n_part, t, d, k);
-#pragma unroll
-      for (int j = 0; j < 8; ++j) ss = fmaf(keep[i].v[j], keep[i].v[j], ss);
-    }
-  }
-  for (int k = threadIdx.x * 8 + kRowKeep * 2048; k < d; k += 2048) {
-    const Run8 x = load_run8(row, part, n_part, t, d, k);
+  auto take = [&](int k) {
+    const size_t i = (size_t)tok * d + k, o = (size_t)b * d + k;
+    Run8 x;
+    if (wide) x = ld_run8_16(tok_emb, i);
+    else for (int j = 0; j < 8; ++j) x.v[j] = Store<1>::ld(tok_emb, i + j);
+    st_run8(h + o, x);
+    st_run8(h_prev + o, x);
+    st_run8(hist + o, x);
 #pragma unroll
     for (int j = 0; j < 8; ++j) ss = fmaf(x.v[j], x.v[j], ss);
-  }
-  const float tot = block_sum(ss, red);
-  const float r = 1.0f / sqrtf(tot / (float)d + eps);
+    return x;
+  };
+  Run8 keep[kRowKeep];
 #pragma unroll
   for (int i = 0; i < kRowKeep; ++i) {
     const int k = threadIdx.x * 8 + i * 2048;
-    if (k < d) norm_store_run8(keep[i], r, gain, xf, d, t, k);
+    if (k < d) keep[i] = take(k);
   }
-  for (int k = threadIdx.x * 8 + kRowKeep * 2048; k < d; k += 2048)    // updated by this thread itself above
-    norm_store_run8(load_run8(row, nullptr, 0, t, d, k), r, gain, xf, d, t, k);
+  for (int k = threadIdx.x * 8 + kRowKeep * 2048; k < d; k += 2048) (void)take(k);
+  for (int i = threadIdx.x; i < L; i += 256) sims[(size_t)b * L + i] = __uint_as_float(0x7fc00000u);
+  if (threadIdx.x == 0) {
+    const bool r0 = in.forced[b] == 0;
+    st.pos[b] = in.pos[b];
+    st.forced[b] = in.forced[b];
+    st.river[b] = r0 ? 1 : 0;
+    st.exit_pos[b] = r0 ? 0 : L;
+  }
+  const float r = 1.0f / sqrtf(block_sum(ss, red) / (float)d + eps);
+#pragma unroll
+  for (int i = 0; i < kRowKeep; ++i) {
+    const int k = threadIdx.x * 8 + i * 2048;
+    if (k < d) norm_store_run8(keep[i], r, gain, xf, d, b, k);
+  }
+  for (int k = threadIdx.x * 8 + kRowKeep * 2048; k < d; k += 2048)    // stored by this thread itself above
+    norm_store_run8(ld_run8(h + (size_t)b * d + k), r, gain, xf, d, b, k);
 }
 
 // C[rows, N] (op)= A[rows, K] B^T for the rows r < n_rows with river[r] == want (want < 0: all
@@ -1173,30 +1200,6 @@ __global__ __launch_bounds__(512) void k_bd_gemm(const _Float16 *__restrict__ Af
   if (twin && (!dense || second))
     bd_gemm_pass<true, MB, RBW>(Af, Bq, N, K, C, ldc, epi, river, 1, n_rows,
                                 rows_per_wg, k_split, dense ? ND : 0, dense ? kBdWaves - ND : kBdWaves, red, nrm, rsc);
-}
-
-// h[b, :] = E[token[b], :] (also h_prev and the debug view of h(0)); start-of-step state of
-// sequence b (forced exit position 0 puts it into the river from the first block on)
-__global__ void k_bd_embed(SeqState st, const void *tok_emb, int d, int vocab, int L, float *h, float *h_prev,
-                           float *hist) {
-  const int b = blockIdx.x;
-  const int tok = min(max(st.token[b], 0), vocab - 1);
-  for (int i = threadIdx.x; i < d; i += blockDim.x) {
-    const float v = Store<1>::ld(tok_emb, (size_t)tok * d + i);
-    h[(size_t)b * d + i] = v;
-    h_prev[(size_t)b * d + i] = v;
-    hist[(size_t)b * d + i] = v;
-  }
-  if (threadIdx.x == 0) {
-    const bool r0 = st.forced[b] == 0;
-    st.river[b] = r0 ? 1 : 0;
-    st.exit_pos[b] = r0 ? 0 : L;
-  }
-}
-
-__global__ void k_bd_copy(const float *__restrict__ src, float *dst, size_t n) {
-  for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x)
-    dst[i] = src[i];
 }
 
 // Single-query attention of a batched step with RoPE and the KV write in front of it.  One
@@ -1527,8 +1530,7 @@ __global__ void k_bd_decide(int n, int l1, int L, int min_exit, float tau, int r
   }
 }
 
-// Greedy token of every sequence (lowest index on ties), its record, and the step's end: the
-// sequence advances by one position.  kBdArgmaxChunks workgroups per sequence scan a chunk of the
+// Greedy token of every sequence (lowest index on ties) and its record.  kBdArgmaxChunks workgroups per sequence scan a chunk of the
 // row each and publish (value, index); the last one to arrive takes the best of them in chunk
 // order (part: [n][chunks][2], tickets: [n], zero between launches).
 constexpr int kBdArgmaxChunks = 16;
@@ -1568,20 +1570,14 @@ __global__ __launch_bounds__(256) void k_bd_argmax(const float *__restrict__ log
       argmax_take(best, besti, sub(pj), __float_as_int(sub(pj + 1)));
     }
     st.token[b] = besti;
-    st.pos[b] += 1;
-    if (rec_token) { rec_token[b] = besti; rec_exit[b] = st.exit_pos[b]; }
+    rec_token[b] = besti;
+    rec_exit[b] = st.exit_pos[b];
   }
 }
 
-// sims[b][l] = NaN for every block (blocks that run as river twins keep it)
-__global__ void k_bd_fill_nan(float *p, int n) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) p[i] = __uint_as_float(0x7fc00000u);
-}
-
-// after a prefill of sequence `seq`: its next token and length
-__global__ void k_bd_after_prefill(SeqState st, int seq, const int *cur_token, int len) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) { st.token[seq] = *cur_token; st.pos[seq] = len; }
+// after a prefill of sequence `seq`: its next token
+__global__ void k_bd_after_prefill(SeqState st, int seq, const int *cur_token) {
+  if (threadIdx.x == 0 && blockIdx.x == 0) st.token[seq] = *cur_token;
 }
 
 }  // namespace bd
