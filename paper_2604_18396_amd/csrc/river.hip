@@ -687,7 +687,14 @@ static int create_impl(const river_config *cfg, const river_weights *w, const ri
   const int cus = prop.multiProcessorCount;
   // one workgroup per CU, a multiple of 8 (the device-wide barrier counts in 8 groups)
   x->grid_persist = std::max(8, std::min(cus, kMaxGrid) / 8 * 8);
-  x->grid_gemv = x->grid_persist;
+  // One launch per phase: no more workgroups than the widest phase has tasks for (a task is one or two
+  // rows per wavefront; attention: a query head and split), a multiple of 8.  Small models only: the
+  // tiny fp32 shape runs 88 workgroups instead of 256.
+  {
+    const int qkv = (cfg->n_q_heads + 2 * cfg->n_kv_heads) * cfg->head_dim, splits = std::min(kMaxSplits, (cfg->max_seq + 255) / 256);
+    const int tasks = std::max({qkv, cfg->d_model, cfg->d_ffn, (cfg->vocab + 1) / 2, kWaves * cfg->n_q_heads * splits});
+    x->grid_gemv = std::min(x->grid_persist, (tasks + 8 * kWaves - 1) / (8 * kWaves) * 8);
+  }
 
   // Where the step-transient part of the layout [hidden, qsz) lives: in the workspace, or in
   // the device's static scratch followed by the barrier block (`act + lay.X` addresses member
@@ -1226,10 +1233,10 @@ extern "C" int river_decode_step(river_ctx *x, const int32_t *in_token, const in
 }
 
 // GEMM g (QKV, O, gate/up, down) of block l of a batched decode step, or the LM head (Bq null,
-// by_flag 0): bf16 matrices for the rows in the backbone, 4-bit twins for the others (see
+// sides = kSideDense): bf16 matrices for the rows in the backbone, 4-bit twins for the others (see
 // bd::k_bd_gemm).  The rows of B are dealt out to one workgroup per CU, eight at a time.
 static int launch_bd_gemm_b(river_ctx *x, const bd::BdB &Bd, const bd::BdB &Bq, int N, const _Float16 *Af, int K,
-                            void *C, int ldc, int epi, int by_flag, int n, bd::BdNorm nrm = bd::BdNorm{},
+                            void *C, int ldc, int epi, int sides, int n, bd::BdNorm nrm = bd::BdNorm{},
                             int *grid_out = nullptr) {
   // A matrix with at most 16 rows per CU (the down projection; the output projection, which also
   // prepares the next norm, stays whole) would have every workgroup
@@ -1249,7 +1256,7 @@ static int launch_bd_gemm_b(river_ctx *x, const bd::BdB &Bd, const bd::BdB &Bq, 
   if (k_split > 1) { C = x->ws + x->lay.bd_partial; epi = bd::EPI_STORE; }
 #define RIVER_BD_LAUNCH(MB, RBW)                                                                               \
   bd::k_bd_gemm<MB, RBW><<<grid, blk, bd::bd_gemm_lds_bytes(RBW, MB), s>>>(Af, Bd, Bq, N, K, C, ldc, epi, rv, \
-                                                                          by_flag, n, rows_per_wg, k_split, nrm)
+                                                                          sides, n, rows_per_wg, k_split, nrm)
   if (n <= 16) {
     if (blocks <= 1) RIVER_BD_LAUNCH(1, 1);
     else if (blocks <= 2) RIVER_BD_LAUNCH(1, 2);
@@ -1263,11 +1270,11 @@ static int launch_bd_gemm_b(river_ctx *x, const bd::BdB &Bd, const bd::BdB &Bq, 
 #undef RIVER_BD_LAUNCH
   return k_split > 1 ? k_split : 0;          // partial sums the consumer has to add
 }
-static int launch_bd_gemm(river_ctx *x, int l, int g, const _Float16 *Af, void *C, int ldc, int epi, int n,
+static int launch_bd_gemm(river_ctx *x, int l, int g, int sides, const _Float16 *Af, void *C, int ldc, int epi, int n,
                           bd::BdNorm nrm = bd::BdNorm{}, int *grid_out = nullptr) {
   const BdGemmShape sh = bd_gemm_shape(&x->cfg, g);
   return launch_bd_gemm_b(x, x->bd_dense_h[(size_t)l * 4 + g], x->bd_twin_h[(size_t)l * 4 + g], sh.N, Af, sh.K, C, ldc,
-                          epi, 1, n, nrm, grid_out);
+                          epi, sides, n, nrm, grid_out);
 }
 
 extern "C" int river_decode_batch(river_ctx *x, int32_t n_seq, const int32_t *in_tokens, const int32_t *forced_exit,
@@ -1335,7 +1342,17 @@ extern "C" int river_decode_batch(river_ctx *x, int32_t n_seq, const int32_t *in
   const int qkv_ld = qd + 2 * c.n_kv_heads * c.head_dim;
   for (int l = 0; l < L; ++l) {
     const DevLayer &W = x->layers_h[l];
-    launch_bd_gemm(x, l, 0, x16, big, qkv_ld, bd::EPI_STORE, n);
+    // Which weight sets have rows in this block, where it does not depend on the step's similarities:
+    // forced exits, thresholds that never fire, blocks in front of the first exit test (else 0).  The
+    // GEMMs then start their weight stream without looking at the rows' flags first (1.4 us each).
+    int sides = 0;
+    for (int b = 0; b < n && sides >= 0; ++b) {
+      if (fe[b] >= 0) sides |= l >= fe[b] ? bd::kSideTwin : bd::kSideDense;
+      else if (c.tau >= 1.0f || l < std::max(c.min_exit_layer, 1)) sides |= bd::kSideDense;
+      else sides = -1;
+    }
+    sides = std::max(sides, 0);
+    launch_bd_gemm(x, l, 0, sides, x16, big, qkv_ld, bd::EPI_STORE, n);
     {
       const dim3 ga((n * c.n_kv_heads * n_splits + 7) / 8 * 8 * hgs);
       auto attn = c.head_dim == 128
@@ -1351,10 +1368,10 @@ extern "C" int river_decode_batch(river_ctx *x, int32_t n_seq, const int32_t *in
     // second (see bd::BdNorm).
     float *ssq = (float *)(x->ws + y.bd_ssq);
     int o_grid = 0;
-    launch_bd_gemm(x, l, 1, o16, h, d, bd::EPI_ADD_NORM, n, bd::BdNorm{W.ffn_norm, x16, ssq, nullptr, 0, 0, 0.f}, &o_grid);
+    launch_bd_gemm(x, l, 1, sides, o16, h, d, bd::EPI_ADD_NORM, n, bd::BdNorm{W.ffn_norm, x16, ssq, nullptr, 0, 0, 0.f}, &o_grid);
     // gate and up rows interleaved, SwiGLU in the epilogue: the down projection's input as fp16
-    launch_bd_gemm(x, l, 2, x16, a16, ffn, bd::EPI_SWIGLU, n, bd::BdNorm{nullptr, nullptr, nullptr, ssq, o_grid, d, c.rms_eps});
-    const int pd = launch_bd_gemm(x, l, 3, a16, h, d, bd::EPI_ADD, n);
+    launch_bd_gemm(x, l, 2, sides, x16, a16, ffn, bd::EPI_SWIGLU, n, bd::BdNorm{nullptr, nullptr, nullptr, ssq, o_grid, d, c.rms_eps});
+    const int pd = launch_bd_gemm(x, l, 3, sides, a16, h, d, bd::EPI_ADD, n);
     // similarity, the sequences' own exit decisions, and the norm in front of the next GEMM
     const bool may_exit = l + 1 >= c.min_exit_layer && l + 1 < L;
     const bool batch_rule = c.batch_exit_rule == 1;
@@ -1366,7 +1383,7 @@ extern "C" int river_decode_batch(river_ctx *x, int32_t n_seq, const int32_t *in
       bd::k_bd_decide<<<dim3(1), dim3(64), 0, s>>>(n, l + 1, L, c.min_exit_layer, c.tau, c.batch_exit_rule, st, s_of);
   }
   // the original LM head (its input is already normalised), greedy token per sequence
-  launch_bd_gemm_b(x, x->bd_head, x->bd_head, c.vocab, x16, d, logits, c.vocab, bd::EPI_STORE, 0, n);
+  launch_bd_gemm_b(x, x->bd_head, x->bd_head, c.vocab, x16, d, logits, c.vocab, bd::EPI_STORE, bd::kSideDense, n);
   // (the attention kernels are done with their partial-result area and tickets)
   bd::k_bd_argmax<<<dim3(n * bd::kBdArgmaxChunks), dim3(256), 0, s>>>(logits, c.vocab, st, rec_token, rec_exit, part_ml, tickets);
   HIP_TRY(x, hipGetLastError());

@@ -960,7 +960,7 @@ __host__ __device__ inline size_t bd_gemm_lds_bytes(int rbw, int mb) { return (s
 template <bool W4, int MB, int RBW>
 __device__ __forceinline__ void bd_gemm_pass(const _Float16 *__restrict__ Af, const BdB &B, int N,
                                              int K, void *C, int ldc, int epi,
-                                             const int *__restrict__ river, int want, int n_rows, int rows_per_wg,
+                                             const int (&flag)[MB + 1], int want, int n_rows, int rows_per_wg,
                                              int k_split, int w0, int nw,
                                              float *red /* [kBdWaves][RBW][MB][256] */, const BdNorm &nrm,
                                              const BdRowScale &rsc) {
@@ -1114,7 +1114,10 @@ __device__ __forceinline__ void bd_gemm_pass(const _Float16 *__restrict__ Af, co
     constexpr int TILE_F = RBW * MB * 256;
     for (int e = tid; e < TILE_F; e += nw * 64) {
       const int rb = e / (MB * 256), i = (e / 256) % MB, row = i * 16 + ((e & 255) >> 4), n = p0 + rb * 16 + (e & 15);
-      if (row >= n_rows || n >= wg_r1 || !(want < 0 || river[row] == want)) continue;
+      int f = flag[0];                                        // (rows i * 16 + (tid % 256) / 16: see k_bd_gemm)
+#pragma unroll
+      for (int i2 = 1; i2 < MB; ++i2) f = i2 == i ? flag[i2] : f;
+      if (row >= n_rows || n >= wg_r1 || !(want < 0 || f == want)) continue;
       const float rs_row = rscale ? rscale[row] : 1.0f;
       auto total = [&](int idx) {
         float v = red[idx];
@@ -1151,7 +1154,7 @@ __device__ __forceinline__ void bd_gemm_pass(const _Float16 *__restrict__ Af, co
       if ((tid & 15) == 0) red[(tid >> 8) * kRows + i * 16 + ((tid & 255) >> 4)] = sr;
     }
     __syncthreads();
-    if (tid < MB * 16 && tid < n_rows && (want < 0 || river[tid] == want)) {
+    if (tid < MB * 16 && tid < n_rows && (want < 0 || flag[MB] == want)) {
       float v = red[tid];
       if (nw * 64 > 256) v += red[kRows + tid];
       nrm.ssq_out[(size_t)blockIdx.x * kRows + tid] = v;
@@ -1159,23 +1162,41 @@ __device__ __forceinline__ void bd_gemm_pass(const _Float16 *__restrict__ Af, co
   }
 }
 
-// One launch per GEMM of a step: the bf16 matrices for the rows still in the backbone, then the
-// 4-bit twins for the rows that have left it (by_flag; otherwise the bf16 matrices for all
-// rows, as the LM head needs).  A side without rows is not read.  Af: the activations in fragment
+// One launch per GEMM of a step: the bf16 matrices for the rows still in the backbone, the 4-bit
+// twins for the rows that have left it (sides: which of the two have rows, 0 if only the device
+// knows; kSideDense alone: the bf16 matrices for all rows, as the LM head needs).  A side without rows is not read.  Af: the activations in fragment
 // order (see frag_index).  k_split > 1: narrow matrices (16 rows per CU would leave every
 // workgroup reading all of A for one row block) are dealt out as k_split K slices of four times
 // the rows; C is then the partial-sum buffer [k_split][32][ldc].
+enum { kSideDense = 1, kSideTwin = 2 };
 template <int MB, int RBW>
 __global__ __launch_bounds__(512) void k_bd_gemm(const _Float16 *__restrict__ Af, BdB Bd, BdB Bq,
                                                  int N, int K, void *C, int ldc, int epi,
-                                                 const int *__restrict__ river, int by_flag, int n_rows,
+                                                 const int *__restrict__ river, int sides, int n_rows,
                                                  int rows_per_wg, int k_split, BdNorm nrm) {
   extern __shared__ float red[];
-  __shared__ int any[2];
   __shared__ float rscale[kRows];
-  if (threadIdx.x < 2) any[threadIdx.x] = 0;
-  __syncthreads();
-  if ((int)threadIdx.x < n_rows) any[by_flag && river[threadIdx.x] != 0] = 1;
+  // Which sides have rows: told by the host where it is known before the step, else every wavefront
+  // looks at the rows' flags for itself (no workgroup barrier in front of the first weight load).
+  // Only when both have does a row's flag matter beyond that; this thread's are fetched here, their
+  // latency is the K loop's: rows i * 16 + (tid % 256) / 16 of the epilogue and row tid of the sums
+  // of squares, tid counted from the first wavefront of its side.
+  if (sides == 0) {
+    const int l64 = threadIdx.x & 63, f = l64 < n_rows ? river[l64] : -1;
+    sides = (__any(f == 0) ? kSideDense : 0) | (__any(f > 0) ? kSideTwin : 0);
+  }
+  sides = __builtin_amdgcn_readfirstlane(sides);
+  const bool dense = sides & kSideDense, twin = sides & kSideTwin;
+  int flag[MB + 1] = {};
+  if (dense && twin) {
+    const int tid = threadIdx.x & (kBdWaves / 2 * 64 - 1);
+#pragma unroll
+    for (int i = 0; i < MB; ++i) {
+      const int row = i * 16 + ((tid & 255) >> 4);
+      flag[i] = row < n_rows ? river[row] : -1;
+    }
+    flag[MB] = tid < n_rows ? river[tid] : -1;
+  }
   // consumer of a fused norm: the producer's partial sums of squares of row threadIdx.x / 16 are
   // fetched here (16 lanes per row, up to kSsqLoads each) and added up, in a fixed order, where the
   // first product tile is complete (BdRowScale::finish) -- their latency is the K loop's
@@ -1188,17 +1209,15 @@ __global__ __launch_bounds__(512) void k_bd_gemm(const _Float16 *__restrict__ Af
       rsc.part[u] = row < n_rows && j < nrm.ssq_wgs ? nrm.ssq_in[(size_t)j * kRows + row] : 0.f;
     }
   }
-  __syncthreads();
-  const bool dense = any[0] != 0, twin = any[1] != 0;
   // Both sides: four wavefronts each, side by side -- the 4-bit side's dequantisation runs in the
   // shadow of the bf16 side's memory waits, and there is one ramp-up and one tail instead of two.
   constexpr int ND = kBdWaves / 2;                              // wavefronts of the bf16 side when both run (3 .. 4 measured best)
   const bool second = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)) >= ND;   // (a scalar branch)
   if (dense && (!twin || !second))
-    bd_gemm_pass<false, MB, RBW>(Af, Bd, N, K, C, ldc, epi, river, by_flag ? 0 : -1, n_rows,
+    bd_gemm_pass<false, MB, RBW>(Af, Bd, N, K, C, ldc, epi, flag, twin ? 0 : -1, n_rows,
                                  rows_per_wg, k_split, 0, twin ? ND : kBdWaves, red, nrm, rsc);
   if (twin && (!dense || second))
-    bd_gemm_pass<true, MB, RBW>(Af, Bq, N, K, C, ldc, epi, river, 1, n_rows,
+    bd_gemm_pass<true, MB, RBW>(Af, Bq, N, K, C, ldc, epi, flag, dense ? 1 : -1, n_rows,
                                 rows_per_wg, k_split, dense ? ND : 0, dense ? kBdWaves - ND : kBdWaves, red, nrm, rsc);
 }
 
