@@ -903,6 +903,10 @@ static int create_impl(const river_config *cfg, const river_weights *w, const ri
           {(const void *)pf::k_pf_gemm<pf::TileM, false, pf::PF_SWIGLU>, pf::TileM::LDS_BYTES},
           {(const void *)pf::k_pf_gemm<pf::TileM, true, pf::PF_STORE>, pf::TileM::LDS_BYTES},
           {(const void *)pf::k_pf_gemm<pf::TileM, true, pf::PF_SWIGLU>, pf::TileM::LDS_BYTES},
+          {(const void *)pf::k_pf_gemm<pf::TileN, false, pf::PF_STORE>, pf::TileN::LDS_BYTES},
+          {(const void *)pf::k_pf_gemm<pf::TileN, false, pf::PF_SWIGLU>, pf::TileN::LDS_BYTES},
+          {(const void *)pf::k_pf_gemm<pf::TileN, true, pf::PF_STORE>, pf::TileN::LDS_BYTES},
+          {(const void *)pf::k_pf_gemm<pf::TileN, true, pf::PF_SWIGLU>, pf::TileN::LDS_BYTES},
           {(const void *)pf::k_pf_gemm<pf::TileL, false, pf::PF_STORE>, pf::TileL::LDS_BYTES},
           {(const void *)pf::k_pf_gemm<pf::TileL, false, pf::PF_SWIGLU>, pf::TileL::LDS_BYTES},
           {(const void *)pf::k_pf_gemm<pf::TileL, true, pf::PF_STORE>, pf::TileL::LDS_BYTES},
@@ -1016,27 +1020,30 @@ static int check_device_error(river_ctx *x) {
 
 // Tile and number of K slices of a prefill GEMM.  A workgroup's time is its K tiles times what one
 // takes, which grows with the share of the chip that is at work (clock, caches): TileM (128 x 128)
-// 0.5 .. 0.67 us, and as much again for every further one of its CU; TileL (256 x 256, one workgroup per
-// CU) 1.4 .. 2.05 us.  A K slice costs the write and the read of a plane of partial sums (4 MB per us).
-// The rule takes the least of that over both tiles and up to 16 slices of at least four K tiles.
-// (us measured: N 4096 K 14336: 512 rows TileL 290 / 63 with 1 / 8 slices, TileM 116 / 73 with 1 / 4; N
-// 28672 K 4096: 512 rows TileM 148, TileL 115; N 3072 K 2048: 255 rows TileM 10 with 4 slices, TileL 15
-// with 16.)
-struct PfPlan { bool large; int split; };
+// 0.5 .. 0.67 us, and as much again for every further one of its CU; TileN (256 x 128) 0.85 .. 1.15 and
+// TileL (256 x 256) 1.4 .. 2.05 us, one workgroup per CU.  A K slice costs the write and the read of a
+// plane of partial sums (4 MB per us).  The rule takes the least of that over the tiles and up to 16
+// slices of at least four K tiles.  (us measured, best K slices of TileM / TileN / TileL: N 3072 K 2048,
+// 255 rows 10 / - / 15; N 6144 K 4096, 512 rows 40 / 36 / 36; N 4096 K 14336, 512 rows 75 / 64 / 64, one
+// slice 116 / 205 / 290; N 28672 K 4096, 512 rows 148 / 131 / 115, 4096 rows 1236 / 1119 / 900.)
+struct PfTile { int tm, tn; double alone, full; };
+constexpr PfTile kPfTiles[3] = {{pf::TileM::TM, pf::TileM::TN, 0.5, 0.67},
+                                {pf::TileN::TM, pf::TileN::TN, 0.85, 1.15},
+                                {pf::TileL::TM, pf::TileL::TN, 1.4, 2.05}};
+struct PfPlan { int tile, split; };
 static PfPlan pf_plan(const river_ctx *x, int N, int K, int m, bool may_split) {
-  PfPlan best{false, 1};
+  PfPlan best{0, 1};
   double best_us = 1e30;
   const int nk = K / pf::TK, cus = x->grid_persist;
-  for (int large = 0; large < 2; ++large) {
-    const int tm = large ? pf::TileL::TM : pf::TileM::TM, tn = large ? pf::TileL::TN : pf::TileM::TN;
-    const double alone = large ? 1.4 : 0.5, full = large ? 2.05 : 0.67;
-    const long long tiles = (long long)((N + tn - 1) / tn) * ((m + tm - 1) / tm);
+  for (int i = 0; i < 3; ++i) {
+    const PfTile &t = kPfTiles[i];
+    const long long tiles = (long long)((N + t.tn - 1) / t.tn) * ((m + t.tm - 1) / t.tm);
     for (int sp = 1; sp <= (may_split ? 16 : 1); ++sp) {
       if (sp > 1 && (nk / sp < 4 || (size_t)sp * m * N * 4 > x->lay.pf_big_bytes)) break;
       const double load = (double)(tiles * sp) / cus, whole = std::floor(load), part = load - whole;
-      const double k_tile_us = whole * full + (part > 0.0 ? alone + (full - alone) * part : 0.0);
+      const double k_tile_us = whole * t.full + (part > 0.0 ? t.alone + (t.full - t.alone) * part : 0.0);
       const double us = (nk + sp - 1) / sp * k_tile_us + (sp > 1 ? 2.0 * sp * m * N * 4 / 4e6 : 0.0);
-      if (us < best_us) { best_us = us; best = PfPlan{large != 0, sp}; }
+      if (us < best_us) { best_us = us; best = PfPlan{i, sp}; }
     }
   }
   return best;
@@ -1066,10 +1073,14 @@ static int launch_gemm(river_ctx *x, int l, bool w4, const int *ms, int nm, cons
   for (int i = nm; i < 3; ++i) { B.w[i] = B.w[0]; B.sz[i] = B.sz[0]; B.rows[i] = 0; }
   const PfPlan p = pf_plan(x, N, K, m, EPI == pf::PF_STORE);
   const int ldc = EPI == pf::PF_SWIGLU ? B.rows[0] : N;
-  if (p.large && w4) launch_gemm_t<pf::TileL, true, EPI>(x, B, N, A, K, C, ldc, m, p.split);
-  else if (p.large) launch_gemm_t<pf::TileL, false, EPI>(x, B, N, A, K, C, ldc, m, p.split);
-  else if (w4) launch_gemm_t<pf::TileM, true, EPI>(x, B, N, A, K, C, ldc, m, p.split);
-  else launch_gemm_t<pf::TileM, false, EPI>(x, B, N, A, K, C, ldc, m, p.split);
+  auto launch = [&](auto tile) {
+    typedef decltype(tile) T;
+    if (w4) launch_gemm_t<T, true, EPI>(x, B, N, A, K, C, ldc, m, p.split);
+    else launch_gemm_t<T, false, EPI>(x, B, N, A, K, C, ldc, m, p.split);
+  };
+  if (p.tile == 0) launch(pf::TileM{});
+  else if (p.tile == 1) launch(pf::TileN{});
+  else launch(pf::TileL{});
   return p.split;
 }
 

@@ -124,9 +124,11 @@ template <int TM_, int TN_, int WM_, int WN_, int PF_, int OCC_> struct GemmTile
   static constexpr int GR = NT / 8;                            // rows a staging round of the workgroup covers
   static constexpr int RA = TM / GR, RB = TN / GR;             // staging rounds per K tile
   static constexpr int LDS_BYTES = 2 * (TM + TN) * LDK * 2;    // two buffers each of A and B
-  static_assert(RA == RB && (RA == 2 || RA == 4) && RA * GR == TM && RB * GR == TN, "two or four staging rounds");
+  static_assert((RA == 2 || RA == 4) && (RB == 2 || RB == 4) && RA >= RB && RA * GR == TM && RB * GR == TN,
+                "two or four staging rounds");
 };
 typedef GemmTile<128, 128, 4, 2, 2, 2> TileM;
+typedef GemmTile<256, 128, 4, 2, 2, 1> TileN;
 typedef GemmTile<256, 256, 4, 2, 1, 1> TileL;
 enum { PF_STORE = 0, PF_SWIGLU = 1 };
 
@@ -208,7 +210,7 @@ __global__ __launch_bounds__(T::NT, T::OCC) void k_pf_gemm(const _Float16 *__res
   auto load_part = [&](int kt, int u, int i) {   // part i of tile kt into set u
     fa[u][i] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(a_rsrc, a_off[i], kt * (TK * 2), 0));
     if constexpr (W4) {
-      if (i == RB - 1) {                          // (all parts of the set have been staged)
+      if (i == RA - 1) {                          // (all parts of the set have been staged)
         if constexpr (RB == 4) {
           fb[u][0] = *RIVER_GLOBAL(u32x4, b_src + kt * (TK / 2));
         } else {
@@ -218,19 +220,21 @@ __global__ __launch_bounds__(T::NT, T::OCC) void k_pf_gemm(const _Float16 *__res
         fsz[u] = *RIVER_GLOBAL(uint32_t, b_sz + (size_t)g_at * 4);
         if (--g_left == 0) { g_left = tiles_per_group; ++g_at; }
       }
-    } else {
-      fb[u][i] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(b_rsrc[i], b_off, kt * (TK * 2), 0));
+    } else if (i < RB) {
+      constexpr int n = RB - 1;
+      fb[u][i & n] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(b_rsrc[i & n], b_off, kt * (TK * 2), 0));
     }
   };
   auto stage_part = [&](int u, int i, int buf) {  // part i of set u into LDS buffer buf
     _Float16 *const As = pf_lds + buf * TM * LDK, *const Bs = pf_lds + 2 * TM * LDK + buf * TN * LDK;
     *(u32x4 *)(As + s_dst + i * GR * LDK) = fa[u][i];
+    if (i >= RB) return;
     if constexpr (W4) {
       const float s = bf16_lo(fsz[u]), c = -s * (16.0f + bf16_hi(fsz[u]));
       const uint32_t w = i == 0 ? fb[u][0].x : i == 1 ? fb[u][0].y : i == 2 ? fb[u][0].z : fb[u][0].w;
       *(half8 *)(Bs + b_dst + i * 8) = dequant8(w, s, c);
     } else {
-      const u32x4 w = fb[u][i];
+      const u32x4 w = fb[u][i & (RB - 1)];
       *(half8 *)(Bs + s_dst + i * GR * LDK) = bf16x8_to_half8(make_uint4(w.x, w.y, w.z, w.w));
     }
   };
