@@ -215,7 +215,7 @@ __global__ void k_pack_sz(const void *scale, const void *zero, void *out, long l
 // wavefront; longer groups take several rounds, and lanes beyond the group's last run repeat its
 // first one, which changes neither extreme).  slots = groups per row << lg_log2 lanes serve a row.
 // WIDE: w is 16-byte and codes 8-byte aligned (every row then is too: cols % 16 == 0); otherwise the
-// same runs go element by element.  14336 x 4096 bf16, group 64: 1529 us as one lane per group with
+// same runs go element by element.  14336 x 4096 bf16, group 64: 1531 us as one lane per group with
 // scalar loads, 42 us now (3.7 TB/s; a large copy reaches 4.7).
 template <int DT, bool WIDE>
 __device__ __forceinline__ void quant_load16(const void *w, size_t i, float (&v)[16]) {

@@ -5,6 +5,7 @@ import sys
 
 import numpy as np
 import pytest
+import torch
 
 import helpers
 from oracle import batch_oracle as bo
@@ -347,3 +348,23 @@ def test_batch_river_quantised_elsewhere():
         B.toks = [r[0] for r in res]
     B.compare_caches()
     B.close()
+
+
+def test_embedding_without_16_byte_alignment():
+    """The embedding is the one table whose alignment create does not ask for: its rows are then read
+    element by element, with the same results bit for bit (prefill, batched steps)."""
+    cfg = MIDB.with_(max_seq=64)
+    dw = binding.upload_weights(inputs.make_weights(cfg, 61))
+    dr = binding.quantize_river(cfg, dw)
+    e = dw["tok_emb"]
+    off = torch.empty(e.numel() + 1, dtype=e.dtype, device=e.device)[1:].view(e.shape).copy_(e)
+    assert off.data_ptr() % 16 != 0
+    outs = []
+    for emb in (e, off):
+        g = binding.River(cfg, {**dw, "tok_emb": emb}, dr, max_batch=3)
+        toks = [g.prefill(inputs.make_prompt(cfg.vocab, 33 + b, 62 + b), seq=b) for b in range(3)]
+        t, x, s = g.decode_batch(3, None, [3, 1, 2])
+        outs.append((toks, t, x, s, g.batch_hidden(), g.batch_logits(), g.kcache(), g.vcache()))
+        g.close()
+    for a, b in zip(*outs):
+        np.testing.assert_array_equal(np.asarray(a), np.asarray(b))

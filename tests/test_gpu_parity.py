@@ -674,14 +674,15 @@ def test_gemm_prefill_in_chunks_equals_serial_prefill_closely():
 @pytest.mark.parametrize("shape,n_prompt", [
     ("long", 4300),          # two passes over the activation buffers, the second one shorter
     ("wide", 2100),          # 256 x 256 tiles for QKV and gate/up (ragged last row tile), K slices for O and down
-    ("wide", 771),           # 256 x 256 tiles for gate/up only
+    ("wide", 771),           # 256 x 128 tiles for QKV, 256 x 256 for gate/up
+    ("wider", 255),          # 256 x 128 tiles for gate/up
 ])
 def test_gemm_prefill_tiles_and_k_slices_equal_serial_prefill_closely(shape, n_prompt):
     """The tile and K-slice choices of the prefill GEMM, backbone and river, against the per-position
     prefill (tolerance of the half-precision operands, as above)."""
     cfg = LONG if shape == "long" else configs.ModelConfig("wide-pf-bf16", 2, 256, 32, 8, 128, 7168, 1002, 500000.0, 1e-5,
                                                            configs.DTYPE_BF16, 64, 1, 2.0)
-    cfg = cfg.with_(max_seq=n_prompt + 8)
+    cfg = cfg.with_(max_seq=n_prompt + 8, d_ffn=14336 if shape == "wider" else cfg.d_ffn)
     say(f"GEMM prefill tiles {cfg.name} {n_prompt}")
     dw = binding.upload_weights(inputs.make_weights(cfg, 97, gain_std=0.05))
     dr = binding.quantize_river(cfg, dw)
