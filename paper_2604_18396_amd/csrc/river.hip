@@ -532,8 +532,11 @@ static Layout make_layout(const river_config *c) {
   y.qsz = take(y.qsz_bytes);
   y.pf_rows = 0;
   if (gemm_prefill_ok(c)) {
-    const size_t rows = align_up((size_t)std::min(c->max_seq, pf::kChunk), 128);
     const size_t qd = (size_t)c->n_q_heads * c->head_dim;
+    // (the GEMMs address their fp16 input with 31-bit offsets: fewer rows for matrices wider than 262000)
+    const size_t widest = std::max({(size_t)c->d_model, (size_t)c->d_ffn, qd}) * 2;
+    const size_t most = std::max((size_t)128, std::min((size_t)pf::kChunk, (size_t)0x7fff0000 / widest / 128 * 128));
+    const size_t rows = std::min(align_up((size_t)c->max_seq, 128), most);
     y.pf_rows = (int)rows;
     y.pf_tok = take(rows * 4);
     y.pf_h = take(rows * c->d_model * 4);
