@@ -1389,7 +1389,7 @@ extern "C" int river_decode_batch(river_ctx *x, int32_t n_seq, const int32_t *in
     // similarity, the sequences' own exit decisions, and the norm in front of the next GEMM
     const bool may_exit = l + 1 >= c.min_exit_layer && l + 1 < L;
     const bool batch_rule = c.batch_exit_rule == 1;
-    bd::k_bd_block_end<<<dim3(n), dim3(256), 0, s>>>(hprev, h, d, l + 1, L, st, s_of, rec_sims,
+    bd::k_bd_block_end<<<dim3(n), dim3(512), 0, s>>>(hprev, h, d, l + 1, L, st, s_of, rec_sims,
                                                      hist + (size_t)(l + 1) * B * d, may_exit && !batch_rule, c.tau,
                                                      l + 1 < L ? x->layers_h[l + 1].attn_norm : D.final_norm,
                                                      c.rms_eps, x16, partial, pd);

@@ -821,21 +821,20 @@ __global__ void k_bd_pack_pairs(GemmB S, int interleaved, int N, int K, int grou
   out[i] = v;
 }
 
-// The row-wise kernels of a batched step (one workgroup of 256 per sequence row) read their row
-// once: thread t owns columns 8 t + 2048 i .. + 7 and keeps up to kRowKeep such runs in registers
-// between the reduction and the second use (rows longer than 2048 kRowKeep columns are read
-// again).  n_part > 0: the partial sums [n_part][32][d] of the K-sliced GEMM that adds into h are
+// The row-wise kernels of a batched step (one workgroup per sequence row: 256 threads at its start,
+// 512 at a block's end, where a thread's loads are a chain of latencies) read their row once: thread t
+// of T owns columns 8 t + 8 T i .. + 7 and keeps up to kRowKeep such runs in registers between the
+// reduction and the second use (longer rows are read again).  n_part > 0: the partial sums [n_part][32][d] of the K-sliced GEMM that adds into h are
 // added first, in order, and h is updated.
 constexpr int kRowKeep = 4;
 __device__ __forceinline__ Run8 load_run8(float *row, const float *part, int n_part, int t, int d, int k) {
   float4 a = *(const float4 *)(row + k), b = *(const float4 *)(row + k + 4);
   if (n_part > 0) {
-    for (int j = 0; j < n_part; ++j) {
-      const float *p = part + ((size_t)j * kRows + t) * d + k;
+    add_planes(part + (size_t)t * d + k, (size_t)kRows * d, n_part, [&](const float *p, bool ok) {
       const float4 pa = *(const float4 *)p, pb = *(const float4 *)(p + 4);
-      a.x += pa.x; a.y += pa.y; a.z += pa.z; a.w += pa.w;
-      b.x += pb.x; b.y += pb.y; b.z += pb.z; b.w += pb.w;
-    }
+      a.x += ok ? pa.x : 0.f; a.y += ok ? pa.y : 0.f; a.z += ok ? pa.z : 0.f; a.w += ok ? pa.w : 0.f;
+      b.x += ok ? pb.x : 0.f; b.y += ok ? pb.y : 0.f; b.z += ok ? pb.z : 0.f; b.w += ok ? pb.w : 0.f;
+    });
     *(float4 *)(row + k) = a;
     *(float4 *)(row + k + 4) = b;
   }
@@ -1482,7 +1481,7 @@ __global__ __launch_bounds__(256) void k_bd_attn(const float *__restrict__ qkv, 
 // caller passes decide = 0 outside that range and when Eq. 1's batch rule decides); then the
 // RMSNorm in front of the next GEMM (the next block's attention norm, or the final norm) into
 // xf in fragment order -- its sum of squares is the similarity's <h, h>.
-__global__ __launch_bounds__(256) void k_bd_block_end(float *h_prev, float *__restrict__ h, int d, int l1, int L,
+__global__ __launch_bounds__(512) void k_bd_block_end(float *h_prev, float *__restrict__ h, int d, int l1, int L,
                                                       SeqState st, float *s_of, float *sims /* [n][L] of this step */,
                                                       float *hist /* [n][d] */, int decide, float tau,
                                                       const void *next_gain, float eps, _Float16 *xf,
@@ -1509,10 +1508,10 @@ __global__ __launch_bounds__(256) void k_bd_block_end(float *h_prev, float *__re
   Run8 keep[kRowKeep];
 #pragma unroll
   for (int i = 0; i < kRowKeep; ++i) {
-    const int k = threadIdx.x * 8 + i * 2048;
+    const int k = threadIdx.x * 8 + i * (int)blockDim.x * 8;
     if (k < d) keep[i] = take(k);
   }
-  for (int k = threadIdx.x * 8 + kRowKeep * 2048; k < d; k += 2048) (void)take(k);
+  for (int k = threadIdx.x * 8 + kRowKeep * (int)blockDim.x * 8; k < d; k += (int)blockDim.x * 8) (void)take(k);
   block_sum_k<3>(p3, red);
   if (live && threadIdx.x == 0) {
     float s = 0.f;
@@ -1527,10 +1526,10 @@ __global__ __launch_bounds__(256) void k_bd_block_end(float *h_prev, float *__re
   const float r = 1.0f / sqrtf(p3[2] / (float)d + eps);
 #pragma unroll
   for (int i = 0; i < kRowKeep; ++i) {
-    const int k = threadIdx.x * 8 + i * 2048;
+    const int k = threadIdx.x * 8 + i * (int)blockDim.x * 8;
     if (k < d) norm_store_run8(keep[i], r, next_gain, xf, d, b, k);
   }
-  for (int k = threadIdx.x * 8 + kRowKeep * 2048; k < d; k += 2048)    // updated by this thread itself above
+  for (int k = threadIdx.x * 8 + kRowKeep * (int)blockDim.x * 8; k < d; k += (int)blockDim.x * 8)    // updated by this thread itself above
     norm_store_run8(load_run8(row, nullptr, 0, b, d, k), r, next_gain, xf, d, b, k);
 }
 
