@@ -88,8 +88,8 @@ __device__ __forceinline__ float cache_hi(uint32_t w, int kv_f16) {
 //
 // C[M, N] = op(A[M, K] B^T), B = up to three matrices stacked along N (rows of W_q, W_k, W_v;
 // of W_gate, W_up), each [rows, K] row-major: dense bf16, or 4-bit codes with one packed
-// (scale, zero) pair per (row, group of `group` columns).  K % 64 == 0, group % 64 == 0, rows of
-// every matrix % 64 == 0; M and N are guarded (rows of A beyond M - 1 read row M - 1).
+// (scale, zero) pair per (row, group of `group` columns; ceil(K / group) pairs a row).  K % 64 == 0,
+// group % 64 == 0, rows of every matrix % 64 == 0; M and N are guarded (rows of A beyond M - 1 read row M - 1).
 // op: store fp32, slice ks of K into its own [M, N] plane for the consumer to add up in order, or
 // SwiGLU of a gate and an up matrix stored as fp16 [M, ffn] (k_split = 1).
 struct GemmB {
@@ -189,7 +189,7 @@ __global__ __launch_bounds__(T::NT, T::OCC) void k_pf_gemm(const _Float16 *__res
     gemm_b_row8<T, EPI>(B, n_tile, row_l & ~7, N, mat, row);
     row += row_l & 7;
     b_src = (const char *)B.w[mat] + (size_t)row * (K >> 1) + q * RB * 4 + kt0 * (TK / 2);
-    b_sz = (const char *)B.sz[mat] + (size_t)row * (K / group) * 4;
+    b_sz = (const char *)B.sz[mat] + (size_t)row * ((K + group - 1) / group) * 4;   // (the last group may be shorter)
     b_dst = row_l * LDK + q * RB * 8;
   } else {
     b_off = (unsigned)(lane >> 3) * (unsigned)K * 2u + sk * 16u;

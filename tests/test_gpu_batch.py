@@ -95,13 +95,19 @@ class Batch:
             o.close()
 
 
-@pytest.mark.parametrize("cfg", [MIDB, HD64B], ids=lambda c: c.name)
+# contraction lengths that the quantisation group does not divide (a shorter last group per row)
+RAGGEDB = configs.ModelConfig("ragged-group-batch-bf16", 3, 320, 5, 1, 64, 704, 1002, 10000.0, 1e-5,
+                              configs.DTYPE_BF16, 160, 1, 2.0, river_group=128)
+
+
+@pytest.mark.parametrize("cfg", [MIDB, HD64B, RAGGEDB], ids=lambda c: c.name)
 def test_batch_per_sequence_exits_ragged(cfg):
     """Five sequences at different positions; per step every sequence gets its own forced exit
-    position (all depths incl. 0 where allowed and L), so most blocks run both weight sets."""
+    position (all depths incl. 0 where allowed and L), so most blocks run both weight sets.  The
+    shape with a ragged last group is prefilled at a unified depth, through river blocks too."""
     say(f"batched decode, forced ragged exits, {cfg.name}")
     L, Ls = cfg.n_layers, cfg.min_exit_layer
-    B = Batch(cfg, 5, [7, 33, 64, 130, 20], 201)
+    B = Batch(cfg, 5, [7, 33, 64, 130, 20], 201, prefill_depth=1 if cfg is RAGGEDB else None)
     rng = np.random.default_rng(5)
     for step in range(6):
         forced = [int(rng.integers(Ls, L + 1)) for _ in range(5)]

@@ -626,7 +626,13 @@ GEMM_SHAPES = [MID,
                configs.ModelConfig("pf-hd64-bf16", 2, 512, 16, 4, 64, 1024, 1002, 10000.0, 1e-5,
                                    configs.DTYPE_BF16, 400, 0, 2.0),
                configs.ModelConfig("pf-g128-bf16", 2, 256, 4, 4, 128, 640, 300, 500000.0, 1e-5,
-                                   configs.DTYPE_BF16, 400, 0, 2.0, river_group=128)]
+                                   configs.DTYPE_BF16, 400, 0, 2.0, river_group=128),
+               # every contraction length an odd multiple of 64: the last group of a row is half as long
+               # as the others, or (512) longer than a whole row of all matrices but W_down
+               configs.ModelConfig("pf-g128-ragged-bf16", 2, 320, 5, 1, 64, 704, 300, 500000.0, 1e-5,
+                                   configs.DTYPE_BF16, 400, 0, 2.0, river_group=128),
+               configs.ModelConfig("pf-g512-ragged-bf16", 2, 320, 5, 1, 64, 704, 300, 500000.0, 1e-5,
+                                   configs.DTYPE_BF16, 400, 0, 2.0, river_group=512)]
 
 
 @pytest.mark.parametrize("n_prompt", [1, 33, 130, 300])
