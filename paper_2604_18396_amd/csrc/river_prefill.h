@@ -53,17 +53,17 @@ __device__ __forceinline__ half8 bf16x8_to_half8(const uint4 &w) {
   return h;
 }
 
-// Eight 4-bit codes of a row-major word (nibble i = column i) -> (code - zero) * scale as fp16, one
-// rounding of the fp32 product sum: a nibble placed in bits 6..9 of the mantissa of 16.0 is exactly
-// 16 + code, and the mixed-precision fma takes it from there: (16 + code) * s + c, c = -s (16 + zero).
-__device__ __forceinline__ half8 dequant8(uint32_t w, float s, float c) {
+// Eight 4-bit codes of a row-major word (nibble i = column i) -> fp16 of (code - zero) * scale, taken in
+// fp32 as the decode kernels and the oracle take it.  A nibble in bits 6..9 of an fp16 word is the
+// subnormal number code * 2^-18, which the mixed-precision fma reads exactly.
+__device__ __forceinline__ half8 dequant8(uint32_t w, float s, float zero) {
   half8 h;
 #pragma unroll
   for (int k = 0; k < 4; ++k) {                // nibbles k and k + 4
     const uint32_t sh = k < 2 ? w << (6 - 4 * k) : w >> (4 * k - 6);
-    const half2v q = __builtin_bit_cast(half2v, (sh & 0x03c003c0u) | 0x4c004c00u);
-    h[k] = (_Float16)fmaf((float)q[0], s, c);
-    h[k + 4] = (_Float16)fmaf((float)q[1], s, c);
+    const half2v q = __builtin_bit_cast(half2v, sh & 0x03c003c0u);
+    h[k] = (_Float16)(fmaf((float)q[0], 0x1p18f, -zero) * s);
+    h[k + 4] = (_Float16)(fmaf((float)q[1], 0x1p18f, -zero) * s);
   }
   return h;
 }
@@ -230,9 +230,8 @@ __global__ __launch_bounds__(T::NT, T::OCC) void k_pf_gemm(const _Float16 *__res
     *(u32x4 *)(As + s_dst + i * GR * LDK) = fa[u][i];
     if (i >= RB) return;
     if constexpr (W4) {
-      const float s = bf16_lo(fsz[u]), c = -s * (16.0f + bf16_hi(fsz[u]));
       const uint32_t w = i == 0 ? fb[u][0].x : i == 1 ? fb[u][0].y : i == 2 ? fb[u][0].z : fb[u][0].w;
-      *(half8 *)(Bs + b_dst + i * 8) = dequant8(w, s, c);
+      *(half8 *)(Bs + b_dst + i * 8) = dequant8(w, bf16_lo(fsz[u]), bf16_hi(fsz[u]));
     } else {
       const u32x4 w = fb[u][i & (RB - 1)];
       *(half8 *)(Bs + s_dst + i * GR * LDK) = bf16x8_to_half8(make_uint4(w.x, w.y, w.z, w.w));

@@ -657,6 +657,24 @@ def test_gemm_prefill_matches_oracle(cfg0, n_prompt):
         pair.close()
 
 
+def test_gemm_prefill_river_groups_of_one_small_value():
+    """Groups whose weights are all the same: scale 1, zero point minus the weight, code 0.  The zero
+    point (1e-5 .. 2e-5) must survive the way to fp16: half a unit of 16.0 in fp32 is 5 % of it."""
+    cfg = GEMM_SHAPES[0].with_(min_exit_layer=0, max_seq=80)
+    w = inputs.make_weights(cfg, 99, gain_std=0.05)
+    gen = torch.Generator().manual_seed(100)
+    for name in ("wk", "wv"):
+        rows, cols = w["layers"][0][name].shape
+        v = 1e-5 * (1 + torch.rand(rows, cols // cfg.river_group, generator=gen))
+        v *= torch.where(torch.rand(v.shape, generator=gen) < 0.5, -1.0, 1.0)
+        w["layers"][0][name] = v.to(torch.bfloat16).repeat_interleave(cfg.river_group, 1)
+    say("GEMM prefill, constant groups")
+    pair = Pair(cfg, w, None, prefill_gemm_min_tokens=1)
+    pair.prefill(inputs.make_prompt(cfg.vocab, 70, 101), 0)
+    pair.compare_cache(70)
+    pair.close()
+
+
 def test_gemm_prefill_in_chunks_equals_serial_prefill_closely():
     """A prompt longer than one chunk (1024 rows): positions of later chunks attend to the
     cache the earlier chunks wrote.  Compared with the per-position prefill of the same
