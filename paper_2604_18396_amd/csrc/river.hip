@@ -238,7 +238,7 @@ __global__ __launch_bounds__(256) void k_quantize_w4(const void *w, long long ro
                                                      int lg_log2, uint8_t *codes, void *scale, void *zero) {
   // workgroup -> its first lane's (row, slot): a uniform division; the lane's own is a 32-bit one
   const unsigned slots = (unsigned)gpr << lg_log2;
-  const unsigned long long first = (unsigned long long)blockIdx.x * 256u;
+  const unsigned long long first = ((unsigned long long)blockIdx.y * gridDim.x + blockIdx.x) * 256u;
   const unsigned in_row = (unsigned)(first % slots) + threadIdx.x;
   const long long r = (long long)(first / slots) + in_row / slots;
   if (r >= rows) return;                               // (whole groups of lanes: 256 and slots are multiples of one)
@@ -590,9 +590,11 @@ extern "C" int river_quantize_w4(const void *w, int64_t rows, int64_t cols, int3
   const long long gpr = (cols + group - 1) / group;
   int lg = 0;                                              // log2 of the lanes per group
   while (lg < 6 && (16 << lg) < std::min<long long>(group, cols)) ++lg;
-  const long long slots = gpr << lg;                       // lanes per row: at most cols / 8
+  const long long slots = gpr << lg;                       // lanes per row
   if (rows > (0x7fffffffLL << 8) / slots) return RIVER_EINVAL;
-  const dim3 grid((unsigned)((rows * slots + 255) / 256)), blk(256);
+  // two grid dimensions: one holds fewer than 2^32 threads (a larger launch is cut off without an error)
+  const long long wgs = (rows * slots + 255) / 256, most = 1 << 23;
+  const dim3 grid((unsigned)std::min(wgs, most), (unsigned)((wgs + most - 1) / most)), blk(256);
   const bool wide = ((uintptr_t)w) % 16 == 0 && ((uintptr_t)codes) % 8 == 0;
   hipStream_t st = (hipStream_t)hip_stream;
   auto k = dtype == RIVER_BF16 ? (wide ? k_quantize_w4<1, true> : k_quantize_w4<1, false>)

@@ -190,6 +190,22 @@ def test_river_construction_lane_groups(dtype, rows, cols, group):
         assert torch.equal(bits(x), bits(y))
 
 
+def test_river_construction_beyond_2_32_lanes():
+    """35 runs per row in two groups of 64 lanes: from 38 GB of weights on more than 2^32 lanes, which one
+    grid dimension does not hold.  The rows repeat, so must the codes, scales and zero points."""
+    block, group, n = 1024, 544, 2 ** 15 + 1
+    if torch.cuda.mem_get_info()[0] < 80 << 30:
+        pytest.skip("needs 80 GB of free device memory")
+    say("quantiser, 2^32 lanes")
+    w = (torch.randn(block, group + 16, generator=torch.Generator().manual_seed(7)) * 0.02).to(torch.bfloat16).cuda()
+    want = binding.river_quantize_w4(w, group)
+    got = binding.river_quantize_w4(w.repeat(n, 1), group)
+    for a, b in zip(got, want):
+        assert bool((a.view(n, block, -1) == b.view(1, block, -1)).all())
+    del got, a
+    torch.cuda.empty_cache()
+
+
 # ------------------------------------------------------------- tiny configs
 
 @pytest.mark.parametrize("mode", MODES, ids=MODE_IDS)
