@@ -557,15 +557,21 @@ __device__ __forceinline__ int half_sums_offset(int n) { return ((n + 2047) >> 1
 // Store eight consecutive values v[0..7] (columns c .. c+7, c % 8 == 0) of the half layout
 // and add their rounded sum into the run sum; the four threads that hold one lane's run
 // are neighbours (c / 8 consecutive), so the run sum is a quad reduction.
+// The sum is taken of the stored words themselves, which the compiler must not see through: given
+// (float)(_Float16)v it rounds v a second time, in another instruction (a product straight to fp16
+// where the stored value went through fp32), and where the two differ in the last bit, 1024 times that
+// bit is left over in the result (see dot8h): one element in 10^4, rows off by 1e-2 to 4e-2 at 256 columns.
 __device__ __forceinline__ void half_store8(float *xh, int n, int c, const float (&v)[8]) {
   const int g = c >> 11, lane = (c >> 5) & 63, w = (c >> 3) & 3;
-  uint4 o;
-  o.x = pack_half2(v[0], v[4]); o.y = pack_half2(v[1], v[5]);
-  o.z = pack_half2(v[2], v[6]); o.w = pack_half2(v[3], v[7]);
-  *(uint4 *)((uint32_t *)xh + g * 1024 + w * 256 + lane * 4) = o;
+  uint32_t o[4];
   float sr = 0.f;
 #pragma unroll
-  for (int k = 0; k < 8; ++k) sr += (float)(_Float16)v[k];
+  for (int k = 0; k < 4; ++k) {
+    o[k] = pack_half2(v[k], v[k + 4]);
+    asm("" : "+v"(o[k]));
+    sr = __builtin_amdgcn_fdot2(__builtin_bit_cast(half2_t, o[k]), half2_t{(_Float16)1.f, (_Float16)1.f}, sr, false);
+  }
+  *(uint4 *)((uint32_t *)xh + g * 1024 + w * 256 + lane * 4) = make_uint4(o[0], o[1], o[2], o[3]);
   sr = dpp_add<0xB1>(sr);       // quad_perm [1,0,3,2]
   sr = dpp_add<0x4E>(sr);       // quad_perm [2,3,0,1]
   if (w == 0) xh[half_sums_offset(n) + g * 64 + lane] = sr;

@@ -636,6 +636,25 @@ def test_barrier_slot_pool_reuse_and_exhaustion():
     g.close()
 
 
+@pytest.mark.parametrize("mode", MODES, ids=MODE_IDS)
+def test_river_steps_subtract_the_sum_of_the_inputs_they_multiply(mode):
+    """The 4-bit phases of a bf16 model multiply 1024 + code by the input rounded to fp16 and take
+    1024 + zero times the sum of the inputs off again: one input that enters the sum rounded the other
+    way is an error of a whole code step.  Keys and values of 1000 positions, every row by itself: at
+    most 2^-9 of it is the cache's rounding to bf16, 2^-11 the inputs' rounding, as much again in block
+    2 what block 1 passed on of that; a wrong sum is 5e-3 to 4e-2."""
+    cfg = configs.ModelConfig("river-sums-bf16", 2, 256, 4, 4, 64, 256, 1002, 10000.0, 1e-5, configs.DTYPE_BF16, 1000, 0, 2.0)
+    say(f"river input sums, mode {mode}")
+    pair = Pair(cfg, inputs.make_weights(cfg, 103, gain_std=0.1), mode, prefill_gemm_min_tokens=-1)
+    pair.prefill(inputs.make_prompt(cfg.vocab, 1000, 104), 0)
+    for got, want in ((pair.g.kcache(), pair.o.kcache()), (pair.g.vcache(), pair.o.vcache())):
+        got, want = (np.asarray(a, np.float64).reshape(2, 1000, -1) for a in (got, want))
+        err = np.linalg.norm(got - want, axis=-1) / np.linalg.norm(want, axis=-1)
+        say("largest row error per block " + " ".join(f"{e:.1e}" for e in err.max(-1)))
+        assert err.max() <= 2.0 ** -8, [int(i) for i in np.argwhere(err > 2.0 ** -8)[:, 1]]
+    pair.close()
+
+
 # ------------------------------------------------------- prefill on the matrix cores
 
 GEMM_SHAPES = [MID,
