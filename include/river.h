@@ -128,6 +128,10 @@ int river_quantize_w4(const void *w, int64_t rows, int64_t cols, int32_t group, 
 
 /* Bytes of DEVICE workspace river_create needs for this configuration (KV cache,
  * RoPE table, activations, partial results, step records); 0 if cfg is invalid.
+ * A RIVER_BF16 context with d_model, d_ffn and river_group multiples of 64 also holds the
+ * activations and partial sums of one prefill pass of min(max_seq, 4096) prompt positions
+ * (unless prefill_gemm_min_tokens < 0): at the 8B shape 164 MB for max_seq 1024, 352 MB from
+ * 4096 on.
  * A batched context (max_batch > 1) also keeps, in the workspace, a second copy of
  * every block matrix (bf16 and 4-bit) and of the LM head in the order its GEMM
  * streams them, written by river_create: about the size of the model again. */

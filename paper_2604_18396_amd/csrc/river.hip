@@ -1026,11 +1026,13 @@ static int check_device_error(river_ctx *x) {
 // Tile and number of K slices of a prefill GEMM.  A workgroup's time is its K tiles times what one
 // takes, which grows with the share of the chip that is at work (clock, caches): TileM (128 x 128)
 // 0.5 .. 0.67 us, and as much again for every further one of its CU; TileN (256 x 128) 0.85 .. 1.15 and
-// TileL (256 x 256) 1.4 .. 2.05 us, one workgroup per CU.  A K slice costs the write and the read of a
-// plane of partial sums (4 MB per us).  The rule takes the least of that over the tiles and up to 16
-// slices of at least four K tiles.  (us measured, best K slices of TileM / TileN / TileL: N 3072 K 2048,
-// 255 rows 10 / - / 15; N 6144 K 4096, 512 rows 40 / 36 / 36; N 4096 K 14336, 512 rows 75 / 64 / 64, one
-// slice 116 / 205 / 290; N 28672 K 4096, 512 rows 148 / 131 / 115, 4096 rows 1236 / 1119 / 900.)
+// TileL (256 x 256) 1.4 .. 2.05 us, one workgroup per CU.  K slices cost the write and the read of their
+// planes of partial sums (4 MB per us); the one plane of an unsliced matrix is not counted, so slices have
+// to win by more than a plane.  The rule takes the least of that over the tiles and up to 16 slices of at
+// least four K tiles.  (us measured, the kernel by itself, its planes not yet read, best K slices of
+// TileM / TileN / TileL: N 3072 K 2048, 255 rows 10 / 12 / 15; N 6144 K 4096, 512 rows 40 / 36 / 36, and 41
+// for TileM unsliced, which the rule takes: 44 in a prefill; N 4096 K 14336, 512 rows 75 / 64 / 64, one
+// slice 132 / 187 / 272; N 28672 K 4096, 512 rows 147 / 132 / 114, 4096 rows 1199 / 1144 / 903.)
 struct PfTile { int tm, tn; double alone, full; };
 constexpr PfTile kPfTiles[3] = {{pf::TileM::TM, pf::TileM::TN, 0.5, 0.67},
                                 {pf::TileN::TM, pf::TileN::TN, 0.85, 1.15},
