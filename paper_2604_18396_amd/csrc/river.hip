@@ -45,15 +45,15 @@ __global__ __launch_bounds__(kBlock) void k_qkv(const Dev *Dp, StepArgs A, int l
     record_init(D, A);
   } else {
     ctl = load_ctl(D, l - 1);
-    exit_test(D, A, l, ctl, lds);
   }
+  Pre<DT> pre;
+  const bool guess = l == 0 ? ctl.river : guess_river_after(A, ctl, l);
+  prefetch_phase<DT>(D, l, PH_QKV, guess, pre);
+  phase_qkv<DT>(D, A, l, guess, ctl, lds, pre);
   if (blockIdx.x == 0 && threadIdx.x == 0) {
     D.st->slot_river[l & 1] = ctl.river;
     D.st->slot_exit[l & 1] = ctl.exit_pos;
   }
-  Pre<DT> pre;
-  prefetch_phase<DT>(D, l, PH_QKV, ctl.river, pre);
-  phase_qkv<DT>(D, A, l, ctl.river, lds, pre, [] {});
 }
 // F16: the 16-bit KV cache of a bf16 model holds IEEE half values (a kernel of its own per
 // cache type, so that no kernel carries both conversions)
@@ -70,7 +70,7 @@ __global__ __launch_bounds__(kBlock) void k_oproj(const Dev *Dp, StepArgs A, int
   const Ctl ctl = load_ctl(D, l);
   Pre<DT> pre;
   prefetch_phase<DT>(D, l, PH_O, ctl.river, pre);
-  phase_oproj<DT>(D, A, l, ctl.river, lds, pre, [] {});
+  phase_oproj<DT>(D, A, l, ctl.river, lds, pre);
 }
 template <int DT>
 __global__ __launch_bounds__(kBlock) void k_gateup(const Dev *Dp, StepArgs A, int l) {
@@ -79,7 +79,7 @@ __global__ __launch_bounds__(kBlock) void k_gateup(const Dev *Dp, StepArgs A, in
   const Ctl ctl = load_ctl(D, l);
   Pre<DT> pre;
   prefetch_phase<DT>(D, l, PH_GU, ctl.river, pre);
-  phase_gateup<DT>(D, A, l, ctl.river, lds, pre, [] {});
+  phase_gateup<DT>(D, A, l, ctl.river, lds, pre);
 }
 template <int DT>
 __global__ __launch_bounds__(kBlock) void k_down(const Dev *Dp, StepArgs A, int l) {
@@ -88,7 +88,7 @@ __global__ __launch_bounds__(kBlock) void k_down(const Dev *Dp, StepArgs A, int 
   const Ctl ctl = load_ctl(D, l);
   Pre<DT> pre;
   prefetch_phase<DT>(D, l, PH_DOWN, ctl.river, pre);
-  phase_down<DT>(D, A, l, ctl.river, lds, pre, [] {});
+  phase_down<DT>(D, A, l, ctl.river, lds, pre);
 }
 template <int DT>
 __global__ __launch_bounds__(kBlock) void k_head(const Dev *Dp, StepArgs A) {
@@ -97,7 +97,7 @@ __global__ __launch_bounds__(kBlock) void k_head(const Dev *Dp, StepArgs A) {
   const Ctl ctl = load_ctl(D, D.L - 1);
   Pre<DT> pre;
   prefetch_head<DT>(D, pre);
-  phase_head<DT>(D, A, ctl, lds, pre, [] {});
+  phase_head<DT>(D, A, ctl, lds, pre);
 }
 
 #ifdef RIVER_TRACE
@@ -131,16 +131,9 @@ __device__ RIVER_PSTEP_INLINE int pstep_qkv(const Dev *Dp, StepArgs A, int l, in
   // block l (1-based) has just run: what will block l + 1 run as, as far as known now
   const bool guess = (l == 0) ? ctl.river : guess_river_after(A, ctl, l);
   if (l > 0) { barrier_arrive(D.bar, k); TRACE_ARRIVE(); }
-  prefetch_phase<DT>(D, l, PH_QKV, guess, pre, l > 0 ? 0 : 2);
-  bool late_part = false;                 // the late part of the prefetch is still to be issued
-  if (l > 0) {
-    barrier_wait(D.bar, k, D.spin_limit, D.bar_vector_poll); TRACE_RELEASE();
-    exit_test(D, A, l, ctl, lds);
-    if (ctl.river != guess) prefetch_phase<DT>(D, l, PH_QKV, ctl.river, pre);   // wrong guess: everything again
-    else late_part = true;
-  }
-  const bool rv = ctl.river;
-  phase_qkv<DT>(D, A, l, rv, lds, pre, [&] { if (late_part) prefetch_phase<DT>(D, l, PH_QKV, rv, pre, 1); });
+  prefetch_phase<DT>(D, l, PH_QKV, guess, pre);
+  if (l > 0) { barrier_wait(D.bar, k, D.spin_limit, D.bar_vector_poll); TRACE_RELEASE(); }
+  phase_qkv<DT>(D, A, l, guess, ctl, lds, pre);
   return pack_ctl(ctl);
 }
 template <int DT, bool F16>
@@ -156,13 +149,11 @@ __device__ RIVER_PSTEP_INLINE void pstep_gemv(const Dev *Dp, StepArgs A, int l, 
   DevRef D = *RIVER_CONSTANT(Dev, Dp);
   Pre<DT> pre;
   barrier_arrive(D.bar, k); TRACE_ARRIVE();
-  prefetch_phase<DT>(D, l, PH, river, pre, 0);
+  prefetch_phase<DT>(D, l, PH, river, pre);
   barrier_wait(D.bar, k, D.spin_limit, D.bar_vector_poll); TRACE_RELEASE();
-  // the late part of the prefetch goes out behind the first loads of the phase's input vector
-  auto late = [&] { prefetch_phase<DT>(D, l, PH, river, pre, 1); };
-  if (PH == PH_O) phase_oproj<DT>(D, A, l, river, lds, pre, late);
-  else if (PH == PH_GU) phase_gateup<DT>(D, A, l, river, lds, pre, late);
-  else phase_down<DT>(D, A, l, river, lds, pre, late);
+  if (PH == PH_O) phase_oproj<DT>(D, A, l, river, lds, pre);
+  else if (PH == PH_GU) phase_gateup<DT>(D, A, l, river, lds, pre);
+  else phase_down<DT>(D, A, l, river, lds, pre);
 }
 template <int DT>
 __device__ RIVER_PSTEP_INLINE void pstep_head(const Dev *Dp, StepArgs A, int ctl_packed, unsigned long long k,
@@ -171,9 +162,9 @@ __device__ RIVER_PSTEP_INLINE void pstep_head(const Dev *Dp, StepArgs A, int ctl
   const Ctl ctl = unpack_ctl(ctl_packed);
   Pre<DT> pre;
   barrier_arrive(D.bar, k); TRACE_ARRIVE();
-  prefetch_head<DT>(D, pre, 0);
+  prefetch_head<DT>(D, pre);
   barrier_wait(D.bar, k, D.spin_limit, D.bar_vector_poll); TRACE_RELEASE();
-  phase_head<DT>(D, A, ctl, lds, pre, [&] { prefetch_head<DT>(D, pre, 1); });
+  phase_head<DT>(D, A, ctl, lds, pre);
 }
 
 // The number of barriers (5 L - 1, one more with the head) is the same for every workgroup

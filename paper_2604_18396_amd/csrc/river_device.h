@@ -263,14 +263,14 @@ __device__ __forceinline__ float block_sum(float v, float *red) {
   return t;
 }
 
-// K sums at once (one pair of workgroup barriers), each in the order block_sum uses.
-// red: LDS scratch of at least 8 K floats.
-template <int K>
+// K sums at once, each in the order block_sum uses.  red: LDS scratch of at least 8 K floats.
+// FREE: nobody has used red since the last workgroup barrier, so one barrier does.
+template <int K, bool FREE = false>
 __device__ __forceinline__ void block_sum_k(float (&v)[K], float *red) {
 #pragma unroll
   for (int k = 0; k < K; ++k) v[k] = wave_sum(v[k]);
   const int w = threadIdx.x >> 6, nw = blockDim.x >> 6;
-  lds_barrier();
+  if constexpr (!FREE) lds_barrier();
   if ((threadIdx.x & 63) == 0) {
 #pragma unroll
     for (int k = 0; k < K; ++k) red[w * K + k] = v[k];
@@ -433,54 +433,8 @@ __device__ __forceinline__ int x_slot(int c, int lp) {
   return ((c >> (6 + lp)) << (6 + lp)) + (((c & (P - 1)) >> 2) << 8) + (((c >> lp) & 63) << 2) + (c & 3);
 }
 
-// xl = h * rsqrt(mean(h^2) + eps) * gain   (fused RMSNorm prologue), stored for runs of
-// 2^lp; h published by other workgroups, n % 4 == 0.
-// `mid` is called once, after the first global loads of the vector have been issued and before
-// their data is used: loads issued there (a late part of the weight prefetch) are in flight
-// while the vector arrives, and cannot delay it (a wavefront's loads return in order).
-#define RIVER_PIN_ORDER() __builtin_amdgcn_sched_barrier(0)
-template <int DT, class Mid>
-__device__ __forceinline__ void stage_norm(const float *h, const void *gain, int n, float eps, int lp,
-                                           float *xl, float *red, Mid mid) {
-  float ss = 0.f;
-  const int stride = blockDim.x * 4;
-  bool first = true;
-  for (int i0 = threadIdx.x * 4; i0 < n || first; i0 += 4 * stride) {
-    float4 v[4];
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      const int i = i0 + k * stride;
-      v[k] = i < n ? sub4(h, i) : make_float4(0.f, 0.f, 0.f, 0.f);
-    }
-    if (first) {
-      RIVER_PIN_ORDER();
-      mid();
-      RIVER_PIN_ORDER();
-      first = false;
-    }
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      const int i = i0 + k * stride;
-      if (i < n) {
-        *(float4 *)(xl + x_slot(i, lp)) = v[k];
-        ss += (v[k].x * v[k].x + v[k].y * v[k].y) + (v[k].z * v[k].z + v[k].w * v[k].w);
-      }
-    }
-  }
-  const float tot = block_sum(ss, red);
-  const float r = 1.0f / sqrtf(tot / (float)n + eps);
-  for (int i = threadIdx.x * 4; i < n; i += blockDim.x * 4) {
-    float4 v = *(float4 *)(xl + x_slot(i, lp));
-    v.x = v.x * r * Store<DT>::ld(gain, i);
-    v.y = v.y * r * Store<DT>::ld(gain, i + 1);
-    v.z = v.z * r * Store<DT>::ld(gain, i + 2);
-    v.w = v.w * r * Store<DT>::ld(gain, i + 3);
-    *(float4 *)(xl + x_slot(i, lp)) = v;
-  }
-  lds_barrier();
-}
-
-// Same, the source being row `tok` of the embedding table (block 1 of a token); also
+// xl = h * rsqrt(mean(h^2) + eps) * gain stored for runs of 2^lp, h being row `tok` of the embedding
+// table (block 1 of a token); also
 // publishes h(0) (each workgroup a slice) for the residual adds and the similarity.
 // lp < 0: the half layout, written to xh (see half_store8; defined further down).
 __device__ __forceinline__ void half_store8(float *xh, int n, int c, const float (&v)[8]);
@@ -512,30 +466,33 @@ __device__ __forceinline__ void stage_norm_embed(DevRef D, int tok, const void *
   lds_barrier();
 }
 
-template <class Mid>
-__device__ __forceinline__ void stage_copy(const float *src, int n, int lp, float *xl, Mid mid) {
-  lds_barrier();
-  const int stride = blockDim.x * 4;
-  bool first = true;
-  for (int i0 = threadIdx.x * 4; i0 < n || first; i0 += 4 * stride) {
-    float4 v[4];
+// A vector other workgroups have published is fetched in runs of eight columns per thread, all of
+// them issued before the first is used: these phases wait for the round trip, not for the bytes
+// (14336 columns in two trips instead of one: +0.6 us per block).  Longer vectors take several trips.
+constexpr int kCopyRuns = 4;         // runs per thread and trip: 16384 columns
+template <class Put>
+__device__ __forceinline__ void fetch_runs(const float *src, int n, Put put) {
+  for (int base = 0; base < n; base += kCopyRuns * kBlock * 8) {
+    float4 a[kCopyRuns][2];
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      const int i = i0 + k * stride;
-      v[k] = i < n ? sub4(src, i) : make_float4(0.f, 0.f, 0.f, 0.f);
-    }
-    if (first) {
-      RIVER_PIN_ORDER();
-      mid();
-      RIVER_PIN_ORDER();
-      first = false;
+    for (int k = 0; k < kCopyRuns; ++k) {
+      const int i = base + (k * kBlock + (int)threadIdx.x) * 8;
+      a[k][0] = i < n ? sub4(src, i) : make_float4(0.f, 0.f, 0.f, 0.f);
+      a[k][1] = i < n ? sub4(src, i + 4) : make_float4(0.f, 0.f, 0.f, 0.f);
     }
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      const int i = i0 + k * stride;
-      if (i < n) *(float4 *)(xl + x_slot(i, lp)) = v[k];
+    for (int k = 0; k < kCopyRuns; ++k) {
+      const int i = base + (k * kBlock + (int)threadIdx.x) * 8;
+      if (i < n) put(i, a[k][0], a[k][1]);
     }
   }
+}
+__device__ __forceinline__ void stage_copy(const float *src, int n, int lp, float *xl) {
+  lds_barrier();
+  fetch_runs(src, n, [&](int i, const float4 &a, const float4 &b) {
+    *(float4 *)(xl + x_slot(i, lp)) = a;
+    *(float4 *)(xl + x_slot(i + 4, lp)) = b;
+  });
   lds_barrier();
 }
 
@@ -577,77 +534,98 @@ __device__ __forceinline__ void half_store8(float *xh, int n, int c, const float
   if (w == 0) xh[half_sums_offset(n) + g * 64 + lane] = sr;
 }
 
-// xh = half layout of h * rsqrt(mean(h^2) + eps) * gain; n % 32 == 0.  `xl` (n floats)
-// holds h between the two passes.
-template <int DT, class Mid>
-__device__ __forceinline__ void stage_norm_half(const float *h, const void *gain, int n, float eps,
-                                                float *xl, float *xh, float *red, Mid mid) {
-  float ss = 0.f;
-  const int stride = blockDim.x * 4;
-  bool first = true;
-  for (int i0 = threadIdx.x * 4; i0 < n || first; i0 += 4 * stride) {
-    float4 v[4];
+// Fused RMSNorm prologue of a phase: x = h * rsqrt(mean(h^2) + eps) * gain, h published by other
+// workgroups, n % 8 == 0.  A thread fetches runs of eight columns of h and of the gains together and
+// keeps them in registers between the sum and the scaling, so a phase waits for one round trip and one
+// reduction (gains fetched behind the reduction were a second trip with the memory idle: 0.5 us
+// and more, twice per block).  Vectors of more than kNormRuns * 4096 columns are fetched twice.
+constexpr int kNormRuns = 2;
+template <int DT> struct NormIn {
+  float4 v[kNormRuns][2];
+  float g[kNormRuns][8];
+  __device__ __forceinline__ void load(const float *h, const void *gain, int base, int n) {
+    const bool wide = ((uintptr_t)gain & 15) == 0;             // (the final norm's gains may have any alignment)
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      const int i = i0 + k * stride;
-      v[k] = i < n ? sub4(h, i) : make_float4(0.f, 0.f, 0.f, 0.f);
-    }
-    if (first) {
-      RIVER_PIN_ORDER();
-      mid();
-      RIVER_PIN_ORDER();
-      first = false;
-    }
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      const int i = i0 + k * stride;
+    for (int k = 0; k < kNormRuns; ++k) {
+      const int i = base + (k * kBlock + (int)threadIdx.x) * 8;
       if (i < n) {
-        *(float4 *)(xl + i) = v[k];
-        ss += (v[k].x * v[k].x + v[k].y * v[k].y) + (v[k].z * v[k].z + v[k].w * v[k].w);
+        v[k][0] = sub4(h, i);
+        v[k][1] = sub4(h, i + 4);
+        if (wide) {
+          constexpr int EPL = Store<DT>::EPL;
+#pragma unroll
+          for (int e = 0; e < 8; e += EPL) {
+            float f[EPL];
+            const u32x4 w = *RIVER_GLOBAL(u32x4, (const char *)gain + (size_t)(i + e) * sizeof(typename Store<DT>::T));
+            Store<DT>::unpack(w, f);
+#pragma unroll
+            for (int q = 0; q < EPL; ++q) g[k][e + q] = f[q];
+          }
+        } else {
+#pragma unroll
+          for (int e = 0; e < 8; ++e) g[k][e] = Store<DT>::ld(gain, i + e);
+        }
       }
     }
   }
-  const float tot = block_sum(ss, red);
-  const float r = 1.0f / sqrtf(tot / (float)n + eps);
-  // whole quads of threads run the loop together (n % 32 == 0), as the run sums need
-  for (int i = threadIdx.x * 8; i < n; i += blockDim.x * 8) {
-    const float4 a = *(float4 *)(xl + i), b = *(float4 *)(xl + i + 4);
-    float v[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
+  // this thread's sum of squares of h
+  __device__ __forceinline__ float fetch(const float *h, const void *gain, int n) {
+    float ss = 0.f;
+    for (int base = 0; base < n; base += kNormRuns * kBlock * 8) {
+      load(h, gain, base, n);
 #pragma unroll
-    for (int k = 0; k < 8; ++k) v[k] = v[k] * r * Store<DT>::ld(gain, i + k);
-    half_store8(xh, n, i, v);
+      for (int k = 0; k < kNormRuns; ++k)
+        if (base + (k * kBlock + (int)threadIdx.x) * 8 < n) {
+          float q2[2];
+#pragma unroll
+          for (int q = 0; q < 2; ++q)
+            q2[q] = (v[k][q].x * v[k][q].x + v[k][q].y * v[k][q].y) + (v[k][q].z * v[k][q].z + v[k][q].w * v[k][q].w);
+          ss += q2[0] + q2[1];
+        }
+    }
+    return ss;
   }
+  // x into LDS: for runs of 2^lp in xl, or (lp < 0, n % 32 == 0: whole quads of threads take part, as the
+  // run sums need) in the half layout in xh
+  __device__ __forceinline__ void put(const float *h, const void *gain, int n, float r, int lp, float *xl, float *xh) {
+    const bool one_trip = n <= kNormRuns * kBlock * 8;
+    for (int base = 0; base < n; base += kNormRuns * kBlock * 8) {
+      if (!one_trip) load(h, gain, base, n);
+#pragma unroll
+      for (int k = 0; k < kNormRuns; ++k) {
+        const int i = base + (k * kBlock + (int)threadIdx.x) * 8;
+        if (i < n) {
+          float x[8] = {v[k][0].x, v[k][0].y, v[k][0].z, v[k][0].w, v[k][1].x, v[k][1].y, v[k][1].z, v[k][1].w};
+#pragma unroll
+          for (int e = 0; e < 8; ++e) x[e] = x[e] * r * g[k][e];
+          if (lp < 0) {
+            half_store8(xh, n, i, x);
+          } else {
+            *(float4 *)(xl + x_slot(i, lp)) = make_float4(x[0], x[1], x[2], x[3]);
+            *(float4 *)(xl + x_slot(i + 4, lp)) = make_float4(x[4], x[5], x[6], x[7]);
+          }
+        }
+      }
+    }
+  }
+};
+// (red: not used since the last workgroup barrier)
+template <int DT>
+__device__ __forceinline__ void stage_norm(const float *h, const void *gain, int n, float eps, int lp, float *xl,
+                                           float *xh, float *red) {
+  NormIn<DT> in;
+  float ss[1] = {in.fetch(h, gain, n)};
+  block_sum_k<1, true>(ss, red);
+  in.put(h, gain, n, 1.0f / sqrtf(ss[0] / (float)n + eps), lp, xl, xh);
   lds_barrier();
 }
 
-template <class Mid>
-__device__ __forceinline__ void stage_copy_half(const float *src, int n, float *xh, Mid mid) {
+__device__ __forceinline__ void stage_copy_half(const float *src, int n, float *xh) {
   lds_barrier();
-  const int stride = blockDim.x * 8;
-  bool first = true;
-  for (int i0 = threadIdx.x * 8; i0 < n || first; i0 += 2 * stride) {
-    float4 a[2], b[2];
-#pragma unroll
-    for (int k = 0; k < 2; ++k) {
-      const int i = i0 + k * stride;
-      a[k] = i < n ? sub4(src, i) : make_float4(0.f, 0.f, 0.f, 0.f);
-      b[k] = i < n ? sub4(src, i + 4) : make_float4(0.f, 0.f, 0.f, 0.f);
-    }
-    if (first) {
-      RIVER_PIN_ORDER();
-      mid();
-      RIVER_PIN_ORDER();
-      first = false;
-    }
-#pragma unroll
-    for (int k = 0; k < 2; ++k) {
-      const int i = i0 + k * stride;
-      if (i < n) {                                   // whole quads of threads: n % 32 == 0
-        const float v[8] = {a[k].x, a[k].y, a[k].z, a[k].w, b[k].x, b[k].y, b[k].z, b[k].w};
-        half_store8(xh, n, i, v);
-      }
-    }
-  }
+  fetch_runs(src, n, [&](int i, const float4 &a, const float4 &b) {   // whole quads of threads: n % 32 == 0
+    const float v[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
+    half_store8(xh, n, i, v);
+  });
   lds_barrier();
 }
 
@@ -827,9 +805,7 @@ template <int DT, int R, int U, int CPL> struct W4 {
 // An element occupies one "slot": a whole register set, or half of one for formats whose
 // step needs at most kNL / 2 loads (F::SUB == 2) -- then twice as many elements are in
 // flight for the same registers.  While one slot is consumed the others are in flight.
-// The slots of the first sets are issued before the barrier in front of the phase, the
-// last set's once the barrier has been passed (a larger burst in flight delays the barrier
-// itself), so that its latency is covered by the staging of the input vector.
+// The first elements are issued before the barrier in front of the phase.
 // `lane` is the lane id passed through an empty asm: with all phases of all blocks inlined
 // into one kernel the compiler would otherwise derive every lane-offset variant once at
 // kernel entry and keep (spill) them all; this way they are re-derived per phase.
@@ -838,10 +814,7 @@ __device__ __forceinline__ int fresh_lane() {
   asm volatile("" : "+v"(t));
   return t;
 }
-#ifndef RIVER_SETS
-#define RIVER_SETS 2
-#endif
-constexpr int kSets = RIVER_SETS;  // register sets of the streaming pipeline (a third one only delayed the phases)
+constexpr int kSets = 2;           // register sets of the streaming pipeline (a third one only delayed the phases)
 template <int DT> struct Pre {
   Regs<DT> set[kSets];
   float rh[2], r1[2];      // residual inputs of this wavefront's first two tasks (O, down phases)
@@ -862,19 +835,11 @@ __device__ __forceinline__ void issue_seq(int j, int slot, int n_tasks, int cols
     F::issue(pre.set[slot / F::SUB], (slot % F::SUB) * (kNL / F::SUB), rw, cols, group, j % NS, pre.lane);
   }
 }
-// The first elements into their slots.  part 0: the slots to fill before the barrier in
-// front of the phase; part 1: the rest, issued once the barrier has been passed; part 2: all.
-#ifndef RIVER_EARLY_SETS
-#define RIVER_EARLY_SETS 2
-#endif
+// The first elements into their slots.
 template <class F, int DT, int R, class RowsOf>
-__device__ __forceinline__ void issue_first(int part, int n_tasks, int cols, int group, Pre<DT> &pre,
-                                            RowsOf rows_of) {
-  constexpr int NSLOT = kSets * F::SUB;
-  constexpr int EARLY = RIVER_EARLY_SETS * F::SUB;
+__device__ __forceinline__ void issue_first(int n_tasks, int cols, int group, Pre<DT> &pre, RowsOf rows_of) {
 #pragma unroll
-  for (int q = 0; q < NSLOT; ++q)
-    if (part == 2 || (part == 0) == (q < EARLY)) issue_seq<F, DT, R>(q, q, n_tasks, cols, group, pre, rows_of);
+  for (int q = 0; q < kSets * F::SUB; ++q) issue_seq<F, DT, R>(q, q, n_tasks, cols, group, pre, rows_of);
 }
 
 // Runs all tasks of this wavefront of one GEMV phase.  The slots must already hold the first
@@ -1008,7 +973,7 @@ __device__ __forceinline__ void with_format(DevRef D, bool river, Fn f) {
 // Issue the first elements of this wavefront's sequence of phase PH of block l (dense or
 // river), one per slot.
 template <int DT, int PH>
-__device__ __forceinline__ void prefetch_phase_t(DevRef D, int l, bool river, Pre<DT> &g, int part) {
+__device__ __forceinline__ void prefetch_phase_t(DevRef D, int l, bool river, Pre<DT> &g) {
   LayerRef Lw = layer_of(D, l);
   with_format<DT, PH>(D, river, [&](auto ftag, auto rv, auto rr) {
     typedef typename decltype(ftag)::type F;
@@ -1016,11 +981,11 @@ __device__ __forceinline__ void prefetch_phase_t(DevRef D, int l, bool river, Pr
     constexpr int R = decltype(rr)::value;
     auto rows_of = [&](int t, Rows<R> &rw) { phase_rows<DT, PH, RV, R>(D, Lw, t, rw); };
     const int n = (phase_nrows(D, PH) + R - 1) / R, cols = phase_cols(D, PH);
-    issue_first<F, DT, R>(part, n, cols, D.group, g, rows_of);
+    issue_first<F, DT, R>(n, cols, D.group, g, rows_of);
     // The residual inputs of the phases that add to the hidden state (h for O and down, h1
     // for down) were published at least one barrier ago: fetch them for the first two tasks
     // now, so that the epilogue does not wait for them.
-    if ((PH == PH_O || PH == PH_DOWN) && part != 1) {
+    if (PH == PH_O || PH == PH_DOWN) {
       const float *hin = D.hidden + (size_t)l * D.d;
 #pragma unroll
       for (int j = 0; j < 2; ++j) {
@@ -1033,12 +998,12 @@ __device__ __forceinline__ void prefetch_phase_t(DevRef D, int l, bool river, Pr
   });
 }
 template <int DT>
-__device__ __forceinline__ void prefetch_phase(DevRef D, int l, int ph, bool river, Pre<DT> &g, int part = 2) {
+__device__ __forceinline__ void prefetch_phase(DevRef D, int l, int ph, bool river, Pre<DT> &g) {
   switch (ph) {
-    case PH_QKV: prefetch_phase_t<DT, PH_QKV>(D, l, river, g, part); break;
-    case PH_O: prefetch_phase_t<DT, PH_O>(D, l, river, g, part); break;
-    case PH_GU: prefetch_phase_t<DT, PH_GU>(D, l, river, g, part); break;
-    default: prefetch_phase_t<DT, PH_DOWN>(D, l, river, g, part); break;
+    case PH_QKV: prefetch_phase_t<DT, PH_QKV>(D, l, river, g); break;
+    case PH_O: prefetch_phase_t<DT, PH_O>(D, l, river, g); break;
+    case PH_GU: prefetch_phase_t<DT, PH_GU>(D, l, river, g); break;
+    default: prefetch_phase_t<DT, PH_DOWN>(D, l, river, g); break;
   }
 }
 
@@ -1090,55 +1055,71 @@ __device__ __forceinline__ float pick(const float (&acc)[R], int lane) {
 
 // ------------------------------------------------------------------ phases
 
-// Eq. 1 for block l1 = l (1-based) from the sums the down-projection phase of that block
-// published; every workgroup computes the same value in the same order.  Returns s.
-__device__ __forceinline__ float similarity_from_partials(DevRef D, float *red) {
-  float pab = 0.f, paa = 0.f, pbb = 0.f;
-  for (int i = threadIdx.x; i < (int)gridDim.x; i += blockDim.x) {
-    const float4 v = sub4(D.cos_part, i * 4);
-    pab += v.x; paa += v.y; pbb += v.z;
+// Eq. 1's similarity from the three sums <h,h2>, <h,h>, <h2,h2>
+__device__ __forceinline__ float similarity_of(float ab, float aa, float bb) {
+  if (!(aa > 0.f && bb > 0.f)) return 0.f;
+  return fminf(1.0f, fmaxf(-1.0f, ab / (sqrtf(aa) * sqrtf(bb))));
+}
+// This thread's share of the sums the down-projection phase published, one workgroup's each
+// (gridDim.x <= kMaxGrid <= kBlock)
+static_assert(kMaxGrid <= kBlock, "one partial sum per thread");
+__device__ __forceinline__ float4 similarity_part(DevRef D, int i) {
+  return i < (int)gridDim.x ? sub4(D.cos_part, i * 4) : make_float4(0.f, 0.f, 0.f, 0.f);
+}
+
+// The norm in front of a phase together with the similarity of the block behind it (want_s): one
+// round trip and one reduction for both, instead of one after the other.  Returns s; the vector
+// is in registers, for in.put.  Every workgroup computes the same values in the same order.
+template <int DT>
+__device__ __forceinline__ float norm_and_similarity(DevRef D, bool want_s, const float *h, const void *gain,
+                                                     NormIn<DT> &in, float &r, float *red) {
+  const float4 p = want_s ? similarity_part(D, threadIdx.x) : make_float4(0.f, 0.f, 0.f, 0.f);
+  const float ss = in.fetch(h, gain, D.d);
+  float s = 0.f, tot;
+  if (want_s) {
+    float p4[4] = {p.x, p.y, p.z, ss};
+    block_sum_k<4, true>(p4, red);
+    s = similarity_of(p4[0], p4[1], p4[2]);
+    tot = p4[3];
+  } else {
+    float p1[1] = {ss};
+    block_sum_k<1, true>(p1, red);
+    tot = p1[0];
   }
-  float p3[3] = {pab, paa, pbb};
-  block_sum_k<3>(p3, red);
-  pab = p3[0]; paa = p3[1]; pbb = p3[2];
-  float s = 0.f;
-  if (paa > 0.f && pbb > 0.f) {
-    s = pab / (sqrtf(paa) * sqrtf(pbb));
-    s = fminf(1.0f, fmaxf(-1.0f, s));
-  }
+  r = 1.0f / sqrtf(tot / (float)D.d + D.eps);
   return s;
 }
 
 // Exit test after backbone block l1 (1-based), Eq. 1: first hit at or above L_s, never at
-// L, strict '>'; a forced exit position overrides the threshold.  With a forced position the
-// decision needs no similarity, so the reduction is kept off the path of every workgroup:
-// the similarity is then computed for the record only, by one workgroup that has nothing to
-// do in the attention phase (record_similarity).
-__device__ __forceinline__ void exit_test(DevRef D, const StepArgs &A, int l1, Ctl &ctl, float *lds) {
+// L, strict '>'; a forced exit position overrides the threshold and needs no similarity, which is
+// then computed for the record only, off the path of every workgroup (record_similarity).
+__device__ __forceinline__ bool exit_by_similarity(const StepArgs &A, const Ctl &ctl) { return !ctl.river && A.forced_e < 0; }
+__device__ __forceinline__ void exit_test(DevRef D, const StepArgs &A, int l1, float s, Ctl &ctl) {
   if (ctl.river) return;
   const bool may = l1 >= D.min_exit && l1 < D.L;
-  if (A.forced_e >= 0) {
-    if (may && A.forced_e == l1) { ctl.river = true; ctl.exit_pos = l1; }
-    return;
-  }
-  const float s = similarity_from_partials(D, lds_red(D, lds));
-  if (blockIdx.x == 0 && threadIdx.x == 0 && A.rec_slot >= 0)
-    pub(rec_sims(D, A) + (l1 - 1), s);
-  if (may && s > D.tau) {
+  if (A.forced_e < 0 && blockIdx.x == 0 && threadIdx.x == 0 && A.rec_slot >= 0) pub(rec_sims(D, A) + (l1 - 1), s);
+  if (may && (A.forced_e >= 0 ? A.forced_e == l1 : s > D.tau)) {
     ctl.river = true;
     ctl.exit_pos = l1;
   }
 }
 // The similarity of backbone block l1 for the record of a forced-exit step (see exit_test).
 // ctl is the exit state AFTER the test that followed block l1.  Called by every workgroup in
-// the attention phase of the next block; the last workgroup does the work (the per-workgroup
-// sums it reads stay valid until the next down-projection).
-__device__ __forceinline__ void record_similarity(DevRef D, const StepArgs &A, int l1, const Ctl &ctl, float *lds) {
-  if (l1 < 1 || A.forced_e < 0 || A.rec_slot < 0 || blockIdx.x != gridDim.x - 1) return;
+// the attention phase of the next block, in front of the wait for the barrier: the sums are two barriers
+// old and stay valid until the next down-projection.  One wavefront of the last workgroup does the
+// work, in the order of block_sum_k, while the others wait; behind the attention (the same workgroup, with
+// an item of its own at long contexts) it was on the path of the whole chip.
+__device__ __forceinline__ void record_similarity(DevRef D, const StepArgs &A, int l1, const Ctl &ctl, int lane) {
+  if (l1 < 1 || A.forced_e < 0 || A.rec_slot < 0 || blockIdx.x != gridDim.x - 1 || wave_in_wg() != kWaves - 1) return;
   if (ctl.river && ctl.exit_pos < l1) return;          // block l1 ran as a river block: no similarity
-  const float s = similarity_from_partials(D, lds_red(D, lds));
+  float4 p[kWaves];
+#pragma unroll
+  for (int w = 0; w < kWaves; ++w) p[w] = similarity_part(D, w * 64 + lane);
+  float ab = 0.f, aa = 0.f, bb = 0.f;
+#pragma unroll
+  for (int w = 0; w < kWaves; ++w) { ab += wave_sum(p[w].x); aa += wave_sum(p[w].y); bb += wave_sum(p[w].z); }
   // device-coherent stores: the record row is written by workgroups of different XCDs
-  if (threadIdx.x == 0) pub(rec_sims(D, A) + (l1 - 1), s);
+  if (lane == 0) pub(rec_sims(D, A) + (l1 - 1), similarity_of(ab, aa, bb));
 }
 
 // Which format will block l1 + 1 run in, as far as can be known before block l1's
@@ -1151,23 +1132,27 @@ __device__ __forceinline__ bool guess_river_after(const StepArgs &A, const Ctl &
 // RoPE, the rounding of k, v to the cache dtype and the write of slot (l, pos) happen in the
 // attention phase (a2 there), which frees the row-to-wavefront assignment here: single rows,
 // three per wavefront at the 8B shape.
-template <int DT, class Late>
-__device__ __forceinline__ void phase_qkv(DevRef D, const StepArgs &A, int l, bool river, float *lds, Pre<DT> &pre,
-                                          Late late) {
+// `guess` is the format whose first elements pre holds; the exit test of the block before is taken
+// here (ctl), and where it turns out otherwise they are fetched again in the right one.
+template <int DT>
+__device__ __forceinline__ void phase_qkv(DevRef D, const StepArgs &A, int l, bool guess, Ctl &ctl, float *lds, Pre<DT> &pre) {
   RIVER_MARK(D, 16);
   LayerRef Lw = layer_of(D, l);
   if (l == 0) {
     int tok = A.token >= 0 ? A.token : D.st->cur_token;
     tok = min(max(tok, 0), D.vocab - 1);       // a NaN-poisoned argmax must not index out of range
-    late();
-    stage_norm_embed<DT>(D, tok, Lw.attn_norm, run_log2<DT>(river, D.d), lds, lds_half(D, lds), lds_red(D, lds));
-  } else if (run_log2<DT>(river, D.d) < 0) {
-    stage_norm_half<DT>(D.hidden + (size_t)l * D.d, Lw.attn_norm, D.d, D.eps, lds, lds_half(D, lds), lds_red(D, lds),
-                        late);
+    stage_norm_embed<DT>(D, tok, Lw.attn_norm, run_log2<DT>(ctl.river, D.d), lds, lds_half(D, lds), lds_red(D, lds));
   } else {
-    stage_norm<DT>(D.hidden + (size_t)l * D.d, Lw.attn_norm, D.d, D.eps, run_log2<DT>(river, D.d), lds,
-                   lds_red(D, lds), late);
+    const float *h = D.hidden + (size_t)l * D.d;
+    NormIn<DT> in;
+    float r;
+    const float s = norm_and_similarity<DT>(D, exit_by_similarity(A, ctl), h, Lw.attn_norm, in, r, lds_red(D, lds));
+    exit_test(D, A, l, s, ctl);
+    if (ctl.river != guess) prefetch_phase<DT>(D, l, PH_QKV, ctl.river, pre);
+    in.put(h, Lw.attn_norm, D.d, r, run_log2<DT>(ctl.river, D.d), lds, lds_half(D, lds));
+    lds_barrier();
   }
+  const bool river = ctl.river;
   RIVER_MARK(D, 17);
   const int qd = D.nq * D.hd, nrows = qd + 2 * D.nkv * D.hd;
   const int lane = pre.lane;
@@ -1397,15 +1382,13 @@ __device__ __forceinline__ void combine_splits8(DevRef D, int S, int h, int e8, 
 // Stage the attention output for the output projection: a copy of the finished vector
 // (one split), or the merge of the split partials, done by every workgroup for itself --
 // that costs the consumers some more loads but no extra hand-over between workgroups.
-template <class Mid>
-__device__ __forceinline__ void stage_attn_out(DevRef D, const StepArgs &A, int lp, float *xl, float *xh, Mid mid) {
+__device__ __forceinline__ void stage_attn_out(DevRef D, const StepArgs &A, int lp, float *xl, float *xh) {
   const int S = A.n_splits, n = D.nq * D.hd;
   if (S == 1) {
-    if (lp < 0) stage_copy_half(D.obuf, n, xh, mid);
-    else stage_copy(D.obuf, n, lp, xl, mid);
+    if (lp < 0) stage_copy_half(D.obuf, n, xh);
+    else stage_copy(D.obuf, n, lp, xl);
     return;
   }
-  mid();
   lds_barrier();
   for (int i = threadIdx.x * 8; i < n; i += blockDim.x * 8) {
     float v[8];
@@ -1593,22 +1576,20 @@ __device__ __forceinline__ void phase_attn(DevRef D, const StepArgs &A, int l, c
     constexpr int EL = decltype(el)::value;
     AttnPre<DT, EL> c;
     arrive();
+    record_similarity(D, A, l, ctl, lane);
     attn_prefetch<DT, EL>(D, A, l, blockIdx.x, lane, c);
     wait();
     attn_items<DT, EL, F16>(D, A, l, lds, lane, c);
   };
   if (D.hd == 128) run(IC<8>()); else run(IC<4>());
-  lds_barrier();                                   // the merge area of the last item is read
-  record_similarity(D, A, l, ctl, lds);
 }
 
 // a4: h1 = h + W_o o
-template <int DT, class Late>
-__device__ __forceinline__ void phase_oproj(DevRef D, const StepArgs &A, int l, bool river, float *lds, Pre<DT> &pre,
-                                            Late late) {
+template <int DT>
+__device__ __forceinline__ void phase_oproj(DevRef D, const StepArgs &A, int l, bool river, float *lds, Pre<DT> &pre) {
   RIVER_MARK(D, 20);
   const int lp = run_log2<DT>(river, D.nq * D.hd);
-  stage_attn_out(D, A, lp, lds, lds_half(D, lds), late);
+  stage_attn_out(D, A, lp, lds, lds_half(D, lds));
   RIVER_MARK(D, 21);
   const float *hin = D.hidden + (size_t)l * D.d;
   const int lane = pre.lane;
@@ -1627,14 +1608,11 @@ __device__ __forceinline__ void phase_oproj(DevRef D, const StepArgs &A, int l, 
 }
 
 // a5: y = RMSNorm(h1) * g2; a = silu(W_g y) * (W_u y); rows come as (gate i, up i) pairs
-template <int DT, class Late>
-__device__ __forceinline__ void phase_gateup(DevRef D, const StepArgs &A, int l, bool river, float *lds, Pre<DT> &pre,
-                                             Late late) {
+template <int DT>
+__device__ __forceinline__ void phase_gateup(DevRef D, const StepArgs &A, int l, bool river, float *lds, Pre<DT> &pre) {
   RIVER_MARK(D, 24);
   const int lp = run_log2<DT>(river, D.d);
-  if (lp < 0)
-    stage_norm_half<DT>(D.h1, layer_of(D, l).ffn_norm, D.d, D.eps, lds, lds_half(D, lds), lds_red(D, lds), late);
-  else stage_norm<DT>(D.h1, layer_of(D, l).ffn_norm, D.d, D.eps, lp, lds, lds_red(D, lds), late);
+  stage_norm<DT>(D.h1, layer_of(D, l).ffn_norm, D.d, D.eps, lp, lds, lds_half(D, lds), lds_red(D, lds));
   RIVER_MARK(D, 25);
   const int lane = pre.lane;
   auto epi = [&](int n0, auto &acc) {
@@ -1654,13 +1632,12 @@ __device__ __forceinline__ void phase_gateup(DevRef D, const StepArgs &A, int l,
 // Eq. 1's similarity <h,h2>, <h,h>, <h2,h2> reduced over this workgroup's rows.  The
 // reduction over workgroups and the exit decision are taken by every workgroup at the
 // start of the next block (exit_test), so no workgroup waits for another here.
-template <int DT, class Late>
-__device__ __forceinline__ void phase_down(DevRef D, const StepArgs &A, int l, bool river, float *lds, Pre<DT> &pre,
-                                           Late late) {
+template <int DT>
+__device__ __forceinline__ void phase_down(DevRef D, const StepArgs &A, int l, bool river, float *lds, Pre<DT> &pre) {
   RIVER_MARK(D, 28);
   const int lp = run_log2<DT>(river, D.ffn);
-  if (lp < 0) stage_copy_half(D.abuf, D.ffn, lds_half(D, lds), late);
-  else stage_copy(D.abuf, D.ffn, lp, lds, late);
+  if (lp < 0) stage_copy_half(D.abuf, D.ffn, lds_half(D, lds));
+  else stage_copy(D.abuf, D.ffn, lp, lds);
   RIVER_MARK(D, 29);
   const float *hin = D.hidden + (size_t)l * D.d;
   float *hout = D.hidden + (size_t)(l + 1) * D.d;
@@ -1705,20 +1682,22 @@ __device__ __forceinline__ void head_rows(DevRef D, int t, Rows<kRD> &rw) {
   }
 }
 template <int DT>
-__device__ __forceinline__ void prefetch_head(DevRef D, Pre<DT> &g, int part = 2) {
+__device__ __forceinline__ void prefetch_head(DevRef D, Pre<DT> &g) {
   auto rows_of = [&](int t, Rows<kRD> &rw) { head_rows<DT>(D, t, rw); };
   const int n = (D.vocab + kRD - 1) / kRD;
-  issue_first<Dense<DT, kRD, kUD>, DT, kRD>(part, n, D.d, D.group, g, rows_of);
+  issue_first<Dense<DT, kRD, kUD>, DT, kRD>(n, D.d, D.group, g, rows_of);
 }
-template <int DT, class Late>
-__device__ __forceinline__ void phase_head(DevRef D, const StepArgs &A, const Ctl &ctl, float *lds, Pre<DT> &pre,
-                                           Late late) {
+template <int DT>
+__device__ __forceinline__ void phase_head(DevRef D, const StepArgs &A, const Ctl &ctl, float *lds, Pre<DT> &pre) {
   float *red = lds_red(D, lds);
-  if (!ctl.river && A.rec_slot >= 0) {      // similarity of the last backbone block: recorded, never tested
-    const float s = similarity_from_partials(D, red);
-    if (blockIdx.x == 0 && threadIdx.x == 0) pub(rec_sims(D, A) + (D.L - 1), s);
-  }
-  stage_norm<DT>(D.hidden + (size_t)D.L * D.d, D.final_norm, D.d, D.eps, run_log2<DT>(false, D.d), lds, red, late);
+  const float *h = D.hidden + (size_t)D.L * D.d;
+  const bool rec_s = !ctl.river && A.rec_slot >= 0;       // similarity of the last backbone block: recorded, never tested
+  NormIn<DT> in;
+  float r;
+  const float s = norm_and_similarity<DT>(D, rec_s, h, D.final_norm, in, r, red);
+  if (rec_s && blockIdx.x == 0 && threadIdx.x == 0) pub(rec_sims(D, A) + (D.L - 1), s);
+  in.put(h, D.final_norm, D.d, r, run_log2<DT>(false, D.d), lds, lds_half(D, lds));
+  lds_barrier();
   const int lane = pre.lane;
   float best = -INFINITY;
   int besti = 0x7fffffff;
