@@ -318,7 +318,7 @@ unsigned long long g_bar_used[kBarDevices];
 // block, for callers that must not allocate.  Each device holds its own copy of the array;
 // host code uses the per-device address from hipGetSymbolAddress, never the array's name.
 constexpr size_t kStaticScratchBytes = (size_t)8 << 20;
-static __device__ __align__(256) unsigned char g_static_scratch[kStaticScratchBytes];
+static __device__ __align__(256) unsigned char g_static_scratch[kStaticScratchBytes + kBarBytes];
 namespace {
 char *g_static_ptr[kBarDevices];          // device address of g_static_scratch, per device
 bool g_static_live[kBarDevices];          // a live context uses the device's scratch
@@ -698,7 +698,7 @@ static int create_impl(const river_config *cfg, const river_weights *w, const ri
   char *act = x->ws;
   char *static_bar = nullptr;
   if (use_static) {
-    const size_t need = (lay.qsz - lay.hidden) + kBarBytes;
+    const size_t need = lay.qsz - lay.hidden;
     if (need > kStaticScratchBytes) {
       g_create_err = "configuration needs " + std::to_string(need) + " bytes of scratch; the static scratch of "
                      "river_create_static holds " + std::to_string(kStaticScratchBytes) + " (use river_create)";

@@ -72,7 +72,7 @@ struct Dev {
   float *amax_val;                // [kMaxGrid]
   int *amax_idx;                  // [kMaxGrid]
   DevState *st;
-  unsigned long long *bar;        // barrier block (see barrier_arrive): 8 counters 128 B apart, error flag at byte 1024
+  unsigned long long *bar;        // barrier block (see barrier_arrive): 16 counters 256 B apart, error flag at byte 16
   int *rec;                       // [kRecords][kRecHead + L] one row per step: token, exit position (with
                                   // kRecErrorBit if a bounded device wait has given up), similarities
   unsigned long long *trace;      // [5L][2][grid] barrier arrive / release times (RIVER_TRACE builds)
@@ -313,27 +313,32 @@ __device__ __forceinline__ void block_argmax(float &v, int &i, float *red) {
 // Device-wide barrier number k (1-based, counted over the life of the context) of the
 // persistent kernel, in two halves so that work which does not depend on other
 // workgroups (the next phase's weight prefetch) can be issued between arriving and
-// waiting.  Workgroup i adds one to counter i % 8 (eight counters on separate cache lines
-// keep the contention on one address low) and does not wait for the result; a waiting
-// workgroup reads all eight with independent loads and is released when they add up to
-// k * gridDim.x.  Counters are monotone, so nothing is ever reset and a sum of values read
-// at slightly different times can only under-count.  The hand-over is thus one atomic that
+// waiting.  Workgroup i adds one to counter i % 16 and does not wait for the result; a waiting
+// workgroup reads all counters with independent loads and is released when they add up to
+// k * gridDim.x.  Counters are monotone modulo 2^32 and read as a
+// difference, so nothing is ever reset and a sum of values read at slightly different times can only under-count.  The hand-over is thus one atomic that
 // nobody waits on plus one round of loads; a hierarchy of counters with a published
 // generation needs two dependent atomics with their results and a store before anybody can
-// see the release.  Only relaxed agent-scope operations are used: published values are
+// see the release.  Atomics on one 64-byte line are performed one after the other, about 12 ns each
+// (also on different words of it), so every counter has lines of its own: per barrier 256 workgroups on
+// 1, 2, 4, 8 lines cost 2.8, 1.2, 0.6, 0.2 us more than on 16; 32 lines make the poll longer than they save.
+// Only relaxed agent-scope operations are used: published values are
 // already device-coherent and publish_barrier() makes every wave wait for its own stores
 // before the arrival.
 // The wait is bounded: after spin_limit polls, or once another workgroup has flagged an
 // error, the workgroup flags the error and goes on, so every wave reaches the end of the
 // kernel whatever happens.
-constexpr int kBarErrorByte = 1024;      // offset of the error flag in the barrier block
-constexpr int kBarBytes = 2048;
+constexpr int kBarCounters = 16, kBarStride = 256;      // bytes between counters
+constexpr int kBarErrorByte = 16;        // offset of the error flag in the barrier block
+constexpr int kBarBytes = kBarCounters * kBarStride;
 __device__ __forceinline__ int *bar_error(unsigned long long *bar) { return (int *)((char *)bar + kBarErrorByte); }
+
+__device__ __forceinline__ unsigned *bar_counter(unsigned long long *bar, int i) { return (unsigned *)((char *)bar + i * kBarStride); }
 
 __device__ __forceinline__ void barrier_arrive(unsigned long long *bar, unsigned long long k) {
   publish_barrier();
   if (threadIdx.x == 0)
-    (void)__hip_atomic_fetch_add(&bar[(blockIdx.x & 7) * 16], 1ull, __ATOMIC_RELAXED, RIVER_AG);
+    (void)__hip_atomic_fetch_add(bar_counter(bar, blockIdx.x % kBarCounters), 1u, __ATOMIC_RELAXED, RIVER_AG);
 }
 // The barrier block lives in uncached device memory and is polled with scalar loads: vector
 // loads of a wavefront return in order, so a vector poll would wait for the weight prefetch
@@ -342,33 +347,46 @@ __device__ __forceinline__ void barrier_arrive(unsigned long long *bar, unsigned
 // scalar cache; uncached memory keeps the counters out of the (per-XCD, mutually
 // non-coherent) L2s.  The first wavefront polls; the others wait at the workgroup barrier.
 __device__ __forceinline__ bool barrier_poll(const unsigned long long *bar, unsigned long long target, int &err) {
-  unsigned long long c0, c1, c2, c3, c4, c5, c6, c7;
+  static_assert(kBarCounters == 16 && kBarStride == 256 && kBarErrorByte == 16, "the offsets below");
+  unsigned c[16], sum = 0;
   asm volatile(
-      "s_load_dwordx2 %0, %9, 0x0 glc\n\t"
-      "s_load_dwordx2 %1, %9, 0x80 glc\n\t"
-      "s_load_dwordx2 %2, %9, 0x100 glc\n\t"
-      "s_load_dwordx2 %3, %9, 0x180 glc\n\t"
-      "s_load_dwordx2 %4, %9, 0x200 glc\n\t"
-      "s_load_dwordx2 %5, %9, 0x280 glc\n\t"
-      "s_load_dwordx2 %6, %9, 0x300 glc\n\t"
-      "s_load_dwordx2 %7, %9, 0x380 glc\n\t"
-      "s_load_dword %8, %9, 0x400 glc\n\t"
+      "s_load_dword %0, %17, 0x0 glc\n\t"
+      "s_load_dword %1, %17, 0x100 glc\n\t"
+      "s_load_dword %2, %17, 0x200 glc\n\t"
+      "s_load_dword %3, %17, 0x300 glc\n\t"
+      "s_load_dword %4, %17, 0x400 glc\n\t"
+      "s_load_dword %5, %17, 0x500 glc\n\t"
+      "s_load_dword %6, %17, 0x600 glc\n\t"
+      "s_load_dword %7, %17, 0x700 glc\n\t"
+      "s_load_dword %8, %17, 0x800 glc\n\t"
+      "s_load_dword %9, %17, 0x900 glc\n\t"
+      "s_load_dword %10, %17, 0xa00 glc\n\t"
+      "s_load_dword %11, %17, 0xb00 glc\n\t"
+      "s_load_dword %12, %17, 0xc00 glc\n\t"
+      "s_load_dword %13, %17, 0xd00 glc\n\t"
+      "s_load_dword %14, %17, 0xe00 glc\n\t"
+      "s_load_dword %15, %17, 0xf00 glc\n\t"
+      "s_load_dword %16, %17, 0x10 glc\n\t"
       "s_waitcnt lgkmcnt(0)"
-      : "=&s"(c0), "=&s"(c1), "=&s"(c2), "=&s"(c3), "=&s"(c4), "=&s"(c5), "=&s"(c6), "=&s"(c7), "=&s"(err)
+      : "=&s"(c[0]), "=&s"(c[1]), "=&s"(c[2]), "=&s"(c[3]), "=&s"(c[4]), "=&s"(c[5]),
+        "=&s"(c[6]), "=&s"(c[7]), "=&s"(c[8]), "=&s"(c[9]), "=&s"(c[10]), "=&s"(c[11]),
+        "=&s"(c[12]), "=&s"(c[13]), "=&s"(c[14]), "=&s"(c[15]), "=&s"(err)
       : "s"(bar)
       : "memory");
-  return ((c0 + c1) + (c2 + c3)) + ((c4 + c5) + (c6 + c7)) >= target;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) sum += c[i];
+  return (int)(sum - (unsigned)target) >= 0;
 }
 // The same poll for a barrier block in ordinary device memory (contexts whose barrier block
 // lives in the library's static scratch): scalar loads could be served from a stale L2 line
 // there, so the counters are read with device-coherent vector loads.  These return behind the
 // weight prefetch the polling wavefront has issued, which costs a few percent of a token.
 __device__ __forceinline__ bool barrier_poll_vector(const unsigned long long *bar, unsigned long long target, int &err) {
-  unsigned long long c = 0;
+  unsigned c = 0;
 #pragma unroll
-  for (int i = 0; i < 8; ++i) c += __hip_atomic_load(bar + i * 16, __ATOMIC_RELAXED, RIVER_AG);
+  for (int i = 0; i < kBarCounters; ++i) c += __hip_atomic_load(bar_counter((unsigned long long *)bar, i), __ATOMIC_RELAXED, RIVER_AG);
   err = __hip_atomic_load(bar_error((unsigned long long *)bar), __ATOMIC_RELAXED, RIVER_AG);
-  return c >= target;
+  return (int)(c - (unsigned)target) >= 0;
 }
 __device__ __forceinline__ void barrier_wait(unsigned long long *bar, unsigned long long k, int spin_limit,
                                              int vector_poll = 0) {
@@ -382,7 +400,7 @@ __device__ __forceinline__ void barrier_wait(unsigned long long *bar, unsigned l
         if ((threadIdx.x & 63) == 0) __hip_atomic_store(bar_error(bar), 1, __ATOMIC_RELAXED, RIVER_AG);
         break;
       }
-      __builtin_amdgcn_s_sleep(2);
+      __builtin_amdgcn_s_sleep(1);
     }
   }
   lds_barrier();
