@@ -35,7 +35,7 @@ __device__ __forceinline__ Ctl load_ctl(DevRef D, int l) {
   return c;
 }
 
-template <int DT>
+template <int DT, bool N>
 __global__ __launch_bounds__(kBlock) void k_qkv(const Dev *Dp, StepArgs A, int l) {
   extern __shared__ float lds[];
   DevRef D = *RIVER_CONSTANT(Dev, Dp);
@@ -46,7 +46,7 @@ __global__ __launch_bounds__(kBlock) void k_qkv(const Dev *Dp, StepArgs A, int l
   } else {
     ctl = load_ctl(D, l - 1);
   }
-  Pre<DT> pre;
+  Pre<DT, N> pre;
   const bool guess = l == 0 ? ctl.river : guess_river_after(A, ctl, l);
   prefetch_phase<DT>(D, l, PH_QKV, guess, pre);
   phase_qkv<DT>(D, A, l, guess, ctl, lds, pre);
@@ -63,39 +63,40 @@ __global__ __launch_bounds__(kBlock) void k_attn(const Dev *Dp, StepArgs A, int 
   DevRef D = *RIVER_CONSTANT(Dev, Dp);
   phase_attn<DT, F16>(D, A, l, load_ctl(D, l), lds, [] {}, [] {});
 }
-template <int DT>
+template <int DT, bool N>
 __global__ __launch_bounds__(kBlock) void k_oproj(const Dev *Dp, StepArgs A, int l) {
   extern __shared__ float lds[];
   DevRef D = *RIVER_CONSTANT(Dev, Dp);
   const Ctl ctl = load_ctl(D, l);
-  Pre<DT> pre;
+  Pre<DT, N> pre;
   prefetch_phase<DT>(D, l, PH_O, ctl.river, pre);
   phase_oproj<DT>(D, A, l, ctl.river, lds, pre);
 }
-template <int DT>
+template <int DT, bool N>
 __global__ __launch_bounds__(kBlock) void k_gateup(const Dev *Dp, StepArgs A, int l) {
   extern __shared__ float lds[];
   DevRef D = *RIVER_CONSTANT(Dev, Dp);
   const Ctl ctl = load_ctl(D, l);
-  Pre<DT> pre;
+  Pre<DT, N> pre;
   prefetch_phase<DT>(D, l, PH_GU, ctl.river, pre);
   phase_gateup<DT>(D, A, l, ctl.river, lds, pre);
 }
-template <int DT>
+template <int DT, bool N>
 __global__ __launch_bounds__(kBlock) void k_down(const Dev *Dp, StepArgs A, int l) {
   extern __shared__ float lds[];
   DevRef D = *RIVER_CONSTANT(Dev, Dp);
   const Ctl ctl = load_ctl(D, l);
-  Pre<DT> pre;
+  Pre<DT, N> pre;
   prefetch_phase<DT>(D, l, PH_DOWN, ctl.river, pre);
   phase_down<DT>(D, A, l, ctl.river, lds, pre);
 }
 template <int DT>
 __global__ __launch_bounds__(kBlock) void k_head(const Dev *Dp, StepArgs A) {
+  constexpr bool N = false;
   extern __shared__ float lds[];
   DevRef D = *RIVER_CONSTANT(Dev, Dp);
   const Ctl ctl = load_ctl(D, D.L - 1);
-  Pre<DT> pre;
+  Pre<DT, N> pre;
   prefetch_head<DT>(D, pre);
   phase_head<DT>(D, A, ctl, lds, pre);
 }
@@ -122,12 +123,12 @@ __global__ __launch_bounds__(kBlock) void k_head(const Dev *Dp, StepArgs A) {
 __device__ __forceinline__ int pack_ctl(const Ctl &c) { return (c.exit_pos << 1) | (c.river ? 1 : 0); }
 __device__ __forceinline__ Ctl unpack_ctl(int v) { Ctl c; c.river = v & 1; c.exit_pos = v >> 1; return c; }
 
-template <int DT>
+template <int DT, bool N>
 __device__ RIVER_PSTEP_INLINE int pstep_qkv(const Dev *Dp, StepArgs A, int l, int ctl_packed,
                                       unsigned long long k, float *lds) {
   DevRef D = *RIVER_CONSTANT(Dev, Dp);
   Ctl ctl = unpack_ctl(ctl_packed);
-  Pre<DT> pre;
+  Pre<DT, N> pre;
   // block l (1-based) has just run: what will block l + 1 run as, as far as known now
   const bool guess = (l == 0) ? ctl.river : guess_river_after(A, ctl, l);
   if (l > 0) { barrier_arrive(D.bar, k); TRACE_ARRIVE(); }
@@ -143,11 +144,11 @@ __device__ RIVER_PSTEP_INLINE void pstep_attn(const Dev *Dp, StepArgs A, int l, 
   phase_attn<DT, F16>(D, A, l, unpack_ctl(ctl_packed), lds, [&] { barrier_arrive(D.bar, k); TRACE_ARRIVE(); },
                  [&] { barrier_wait(D.bar, k, D.spin_limit, D.bar_vector_poll); TRACE_RELEASE(); });
 }
-template <int DT, int PH>
+template <int DT, int PH, bool N>
 __device__ RIVER_PSTEP_INLINE void pstep_gemv(const Dev *Dp, StepArgs A, int l, bool river, unsigned long long k,
                                         float *lds) {
   DevRef D = *RIVER_CONSTANT(Dev, Dp);
-  Pre<DT> pre;
+  Pre<DT, N> pre;
   barrier_arrive(D.bar, k); TRACE_ARRIVE();
   prefetch_phase<DT>(D, l, PH, river, pre);
   barrier_wait(D.bar, k, D.spin_limit, D.bar_vector_poll); TRACE_RELEASE();
@@ -155,12 +156,12 @@ __device__ RIVER_PSTEP_INLINE void pstep_gemv(const Dev *Dp, StepArgs A, int l, 
   else if (PH == PH_GU) phase_gateup<DT>(D, A, l, river, lds, pre);
   else phase_down<DT>(D, A, l, river, lds, pre);
 }
-template <int DT>
+template <int DT, bool N>
 __device__ RIVER_PSTEP_INLINE void pstep_head(const Dev *Dp, StepArgs A, int ctl_packed, unsigned long long k,
                                         float *lds) {
   DevRef D = *RIVER_CONSTANT(Dev, Dp);
   const Ctl ctl = unpack_ctl(ctl_packed);
-  Pre<DT> pre;
+  Pre<DT, N> pre;
   barrier_arrive(D.bar, k); TRACE_ARRIVE();
   prefetch_head<DT>(D, pre);
   barrier_wait(D.bar, k, D.spin_limit, D.bar_vector_poll); TRACE_RELEASE();
@@ -169,7 +170,7 @@ __device__ RIVER_PSTEP_INLINE void pstep_head(const Dev *Dp, StepArgs A, int ctl
 
 // The number of barriers (5 L - 1, one more with the head) is the same for every workgroup
 // whatever the exit state.
-template <int DT, bool F16>
+template <int DT, bool F16, bool N>
 __global__ __launch_bounds__(kBlock) void k_step_persistent(const Dev *Dp, StepArgs A) {
   extern __shared__ float lds[];
   DevRef D = *RIVER_CONSTANT(Dev, Dp);
@@ -178,14 +179,14 @@ __global__ __launch_bounds__(kBlock) void k_step_persistent(const Dev *Dp, StepA
   record_init(D, A);
   int ctl = pack_ctl(ctl_init(D, A));
   for (int l = 0; l < L; ++l) {
-    ctl = pstep_qkv<DT>(Dp, A, l, ctl, l ? ++k : 0, lds);
+    ctl = pstep_qkv<DT, N>(Dp, A, l, ctl, l ? ++k : 0, lds);
     const bool river = ctl & 1;
     pstep_attn<DT, F16>(Dp, A, l, ctl, ++k, lds);
-    pstep_gemv<DT, PH_O>(Dp, A, l, river, ++k, lds);
-    pstep_gemv<DT, PH_GU>(Dp, A, l, river, ++k, lds);
-    pstep_gemv<DT, PH_DOWN>(Dp, A, l, river, ++k, lds);
+    pstep_gemv<DT, PH_O, N>(Dp, A, l, river, ++k, lds);
+    pstep_gemv<DT, PH_GU, N>(Dp, A, l, river, ++k, lds);
+    pstep_gemv<DT, PH_DOWN, N>(Dp, A, l, river, ++k, lds);
   }
-  if (A.want_head) pstep_head<DT>(Dp, A, ctl, ++k, lds);
+  if (A.want_head) pstep_head<DT, N>(Dp, A, ctl, ++k, lds);
 }
 
 // Interleaves the river's scale and zero arrays into one (scale, zero) pair per group,
@@ -884,12 +885,14 @@ static int create_impl(const river_config *cfg, const river_weights *w, const ri
   {
     const int lb = (int)x->lds_bytes;
     const void *fns[] = {
-        (const void *)k_qkv<0>, (const void *)k_qkv<1>, (const void *)k_attn<0, false>,
-        (const void *)k_attn<1, false>, (const void *)k_attn<1, true>,
-        (const void *)k_oproj<0>, (const void *)k_oproj<1>, (const void *)k_gateup<0>,
-        (const void *)k_gateup<1>, (const void *)k_down<0>, (const void *)k_down<1>,
-        (const void *)k_head<0>, (const void *)k_head<1>, (const void *)k_step_persistent<1, false>,
-        (const void *)k_step_persistent<1, true>};
+        (const void *)k_qkv<0, false>, (const void *)k_qkv<0, true>, (const void *)k_qkv<1, false>, (const void *)k_qkv<1, true>,
+        (const void *)k_attn<0, false>, (const void *)k_attn<1, false>, (const void *)k_attn<1, true>,
+        (const void *)k_oproj<0, false>, (const void *)k_oproj<0, true>, (const void *)k_oproj<1, false>, (const void *)k_oproj<1, true>,
+        (const void *)k_gateup<0, false>, (const void *)k_gateup<0, true>, (const void *)k_gateup<1, false>, (const void *)k_gateup<1, true>,
+        (const void *)k_down<0, false>, (const void *)k_down<0, true>, (const void *)k_down<1, false>, (const void *)k_down<1, true>,
+        (const void *)k_head<0>, (const void *)k_head<1>,
+        (const void *)k_step_persistent<1, false, false>, (const void *)k_step_persistent<1, true, false>,
+        (const void *)k_step_persistent<1, false, true>, (const void *)k_step_persistent<1, true, true>};
     for (const void *f : fns)
       if ((e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, lb)) != hipSuccess)
         return fail("hipFuncSetAttribute(max dynamic LDS)", e);
@@ -936,8 +939,8 @@ extern "C" int river_create_static(const river_config *cfg, const river_weights 
   return create_impl(cfg, w, q, workspace, workspace_bytes, hip_stream, out, true);
 }
 
-// Enqueue one token (prompt position or decode step).
-template <int DT>
+// Enqueue one token (prompt position or decode step).  N: the phases' shapes for narrow models.
+template <int DT, bool N>
 static int launch_step(river_ctx *x, const StepArgs &A0) {
   StepArgs A = A0;
   const Dev &D = x->dev;
@@ -949,8 +952,8 @@ static int launch_step(river_ctx *x, const StepArgs &A0) {
     // bf16 only (river_create refuses the combination with fp32)
     if constexpr (DT == 1) {
       A.bar_base = x->bar_total;
-      if (D.kv_f16) k_step_persistent<DT, true><<<dim3(x->grid_persist), blk, lds, s>>>(Dp, A);
-      else k_step_persistent<DT, false><<<dim3(x->grid_persist), blk, lds, s>>>(Dp, A);
+      if (D.kv_f16) k_step_persistent<DT, true, N><<<dim3(x->grid_persist), blk, lds, s>>>(Dp, A);
+      else k_step_persistent<DT, false, N><<<dim3(x->grid_persist), blk, lds, s>>>(Dp, A);
       x->bar_total += 5ull * D.L - 1 + (A.want_head ? 1 : 0);
     } else {
       x->err = "RIVER_EXEC_PERSISTENT is available for RIVER_BF16 only";
@@ -959,12 +962,12 @@ static int launch_step(river_ctx *x, const StepArgs &A0) {
   } else {
     const dim3 gg(x->grid_gemv);
     for (int l = 0; l < D.L; ++l) {
-      k_qkv<DT><<<gg, blk, lds, s>>>(Dp, A, l);
+      k_qkv<DT, N><<<gg, blk, lds, s>>>(Dp, A, l);
       if (DT == 1 && D.kv_f16) k_attn<DT, DT == 1><<<gg, blk, lds, s>>>(Dp, A, l);
       else k_attn<DT, false><<<gg, blk, lds, s>>>(Dp, A, l);
-      k_oproj<DT><<<gg, blk, lds, s>>>(Dp, A, l);
-      k_gateup<DT><<<gg, blk, lds, s>>>(Dp, A, l);
-      k_down<DT><<<gg, blk, lds, s>>>(Dp, A, l);
+      k_oproj<DT, N><<<gg, blk, lds, s>>>(Dp, A, l);
+      k_gateup<DT, N><<<gg, blk, lds, s>>>(Dp, A, l);
+      k_down<DT, N><<<gg, blk, lds, s>>>(Dp, A, l);
     }
     if (A.want_head) k_head<DT><<<gg, blk, lds, s>>>(Dp, A);
   }
@@ -989,7 +992,11 @@ static int enqueue(river_ctx *x, int token, int forced_e, int want_head, int rec
   if (S > 4) S = std::max(4, (T + 2 * kAttnPosPerSplit - 1) / (2 * kAttnPosPerSplit));
   A.n_splits = std::max(1, std::min(max_splits, S));
   A.bar_base = 0;
-  const int rc = x->cfg.dtype == RIVER_BF16 ? launch_step<1>(x, A) : launch_step<0>(x, A);
+  // rows of at most four 1 KiB granules (see Shape)
+  const bool bf16 = x->cfg.dtype == RIVER_BF16;
+  const bool narrow = std::max(x->cfg.d_model, x->cfg.n_q_heads * x->cfg.head_dim) * (bf16 ? 2 : 4) <= 4096;
+  const int rc = bf16 ? (narrow ? launch_step<1, true>(x, A) : launch_step<1, false>(x, A))
+                      : (narrow ? launch_step<0, true>(x, A) : launch_step<0, false>(x, A));
   if (rc == RIVER_OK) x->pos += 1;
   return rc;
 }

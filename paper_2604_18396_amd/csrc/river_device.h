@@ -434,7 +434,13 @@ __device__ __forceinline__ int *lds_flag(DevRef D, float *lds) { return (int *)(
 // wave-uniform by construction; readfirstlane tells the compiler, so that task indices and
 // row pointers live in scalar registers
 __device__ __forceinline__ int wave_in_wg() { return __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)); }
-__device__ __forceinline__ int wave_id() { return blockIdx.x * (blockDim.x >> 6) + wave_in_wg(); }
+// Tasks of a phase are dealt out over the wavefronts, consecutive ones to consecutive workgroups (spread:
+// a phase with fewer tasks than wavefronts then occupies every CU) or to the wavefronts of one (4-bit rows,
+// where neighbours share lines of (scale, zero) pairs).  1B shape, 256 tokens of context, spread / not:
+// backbone 631 / 659 us per token, river 504 / 488.
+__device__ __forceinline__ int wave_id(bool spread) {
+  return spread ? wave_in_wg() * (int)gridDim.x + (int)blockIdx.x : (int)blockIdx.x * (int)(blockDim.x >> 6) + wave_in_wg();
+}
 __device__ __forceinline__ int wave_count() { return gridDim.x * (blockDim.x >> 6); }
 
 // -------------------------------------------------------------- staging x
@@ -667,6 +673,7 @@ template <int R> struct Rows {
 // Dense format: a step covers R rows x U column granules of 64 lanes x 16 bytes (R*U <= kNL).
 template <int DT, int R, int U> struct Dense {
   static_assert(R * U <= kNL, "a step holds at most kNL lane loads");
+  static constexpr bool SPREAD = true;
   static constexpr int EPL = Store<DT>::EPL;
   static constexpr int SUB = (R * U * 2 <= kNL) ? 2 : 1;      // steps that fit one register set
   static __device__ __forceinline__ int steps(int cols) {
@@ -718,6 +725,7 @@ template <int DT, int R, int U> struct Dense {
 // scale * (sum code*x - zero * sum x).  group % CPL == 0, so a lane load never straddles
 // a group.
 template <int DT, int R, int U, int CPL> struct W4 {
+  static constexpr bool SPREAD = false;
   static_assert(R * U <= kNL, "a step holds at most kNL lane loads");
   static constexpr int SUB = (R * U * 2 <= kNL) ? 2 : 1;      // steps that fit one register set
   static __device__ __forceinline__ int steps(int cols) {
@@ -833,7 +841,7 @@ __device__ __forceinline__ int fresh_lane() {
   return t;
 }
 constexpr int kSets = 2;           // register sets of the streaming pipeline (a third one only delayed the phases)
-template <int DT> struct Pre {
+template <int DT, bool N> struct Pre {       // N: the phases' shapes for narrow models (see Shape)
   Regs<DT> set[kSets];
   float rh[2], r1[2];      // residual inputs of this wavefront's first two tasks (O, down phases)
   int lane;
@@ -842,11 +850,11 @@ template <int DT> struct Pre {
 
 // Issue element j of this wavefront's sequence into slot j % (kSets * F::SUB) (nothing if
 // the sequence is shorter).
-template <class F, int DT, int R, class RowsOf>
-__device__ __forceinline__ void issue_seq(int j, int slot, int n_tasks, int cols, int group, Pre<DT> &pre,
+template <class F, int DT, int R, bool N, class RowsOf>
+__device__ __forceinline__ void issue_seq(int j, int slot, int n_tasks, int cols, int group, Pre<DT, N> &pre,
                                           RowsOf rows_of) {
   const int NS = F::steps(cols);
-  const int t = wave_id() + (j / NS) * wave_count();
+  const int t = wave_id(F::SPREAD) + (j / NS) * wave_count();
   if (t < n_tasks) {
     Rows<R> rw;
     rows_of(t, rw);
@@ -854,8 +862,8 @@ __device__ __forceinline__ void issue_seq(int j, int slot, int n_tasks, int cols
   }
 }
 // The first elements into their slots.
-template <class F, int DT, int R, class RowsOf>
-__device__ __forceinline__ void issue_first(int n_tasks, int cols, int group, Pre<DT> &pre, RowsOf rows_of) {
+template <class F, int DT, int R, bool N, class RowsOf>
+__device__ __forceinline__ void issue_first(int n_tasks, int cols, int group, Pre<DT, N> &pre, RowsOf rows_of) {
 #pragma unroll
   for (int q = 0; q < kSets * F::SUB; ++q) issue_seq<F, DT, R>(q, q, n_tasks, cols, group, pre, rows_of);
 }
@@ -864,11 +872,11 @@ __device__ __forceinline__ void issue_first(int n_tasks, int cols, int group, Pr
 // elements of the sequence (issue_first, called by the caller, possibly before the
 // preceding barrier).  rows_of(task, Rows&) gives the rows of a task; epi(task, acc)
 // receives the R finished dot products (identical in all lanes).
-template <class F, int DT, int R, class RowsOf, class Epi>
+template <class F, int DT, int R, bool N, class RowsOf, class Epi>
 __device__ __forceinline__ void stream_tasks(int n_tasks, int cols, int group, const float *xl,
-                                             Pre<DT> &pre, RowsOf rows_of, Epi epi) {
+                                             Pre<DT, N> &pre, RowsOf rows_of, Epi epi) {
   constexpr int NSLOT = kSets * F::SUB;
-  const int nw = wave_count(), w = wave_id();
+  const int nw = wave_count(), w = wave_id(F::SPREAD);
   if (w >= n_tasks) return;
   const int NS = F::steps(cols);
   const int J = ((n_tasks - w + nw - 1) / nw) * NS;      // length of this wavefront's sequence
@@ -909,15 +917,26 @@ enum { PH_QKV = 0, PH_O, PH_GU, PH_DOWN };
 // and format so that (for the 8B shape) the tasks divide evenly over the 2048 wavefronts
 // and a step fills the load slots:   dense  QKV 1x8  O 1x8  GU 2x4  DOWN 2x4
 //                                    river  QKV 3x2  O 2x2  GU 2x2  DOWN 1x7
-template <int PH, bool RIVER> struct Shape;
-template <> struct Shape<PH_QKV, false> { static constexpr int R = 1, U = 8; };
-template <> struct Shape<PH_O, false> { static constexpr int R = 1, U = 8; };
-template <> struct Shape<PH_GU, false> { static constexpr int R = 2, U = 4; };
-template <> struct Shape<PH_DOWN, false> { static constexpr int R = 2, U = 4; };
-template <> struct Shape<PH_QKV, true> { static constexpr int R = 3, U = 2; };
-template <> struct Shape<PH_O, true> { static constexpr int R = 2, U = 2; };
-template <> struct Shape<PH_GU, true> { static constexpr int R = 2, U = 2; };
-template <> struct Shape<PH_DOWN, true> { static constexpr int R = 1, U = 7; };
+// NARROW: models whose rows of d_model and n_q * head_dim columns fill at most half a step (4 KiB; one
+// granule of codes): shorter steps, and single rows where d_model rows would leave half the wavefronts
+// without a task.  1B shape, 256 tokens of context: backbone 631 -> 620, river 477 -> 456 us per token.
+template <int PH, bool RIVER, bool NARROW> struct Shape;
+template <> struct Shape<PH_QKV, false, false> { static constexpr int R = 1, U = 8; };
+template <> struct Shape<PH_O, false, false> { static constexpr int R = 1, U = 8; };
+template <> struct Shape<PH_GU, false, false> { static constexpr int R = 2, U = 4; };
+template <> struct Shape<PH_DOWN, false, false> { static constexpr int R = 2, U = 4; };
+template <> struct Shape<PH_QKV, true, false> { static constexpr int R = 3, U = 2; };
+template <> struct Shape<PH_O, true, false> { static constexpr int R = 2, U = 2; };
+template <> struct Shape<PH_GU, true, false> { static constexpr int R = 2, U = 2; };
+template <> struct Shape<PH_DOWN, true, false> { static constexpr int R = 1, U = 7; };
+template <> struct Shape<PH_QKV, false, true> { static constexpr int R = 1, U = 4; };
+template <> struct Shape<PH_O, false, true> { static constexpr int R = 1, U = 4; };
+template <> struct Shape<PH_GU, false, true> { static constexpr int R = 2, U = 4; };
+template <> struct Shape<PH_DOWN, false, true> { static constexpr int R = 1, U = 8; };
+template <> struct Shape<PH_QKV, true, true> { static constexpr int R = 2, U = 1; };
+template <> struct Shape<PH_O, true, true> { static constexpr int R = 1, U = 1; };
+template <> struct Shape<PH_GU, true, true> { static constexpr int R = 4, U = 1; };
+template <> struct Shape<PH_DOWN, true, true> { static constexpr int R = 1, U = 4; };
 
 // Layout of the staged vector for the format a phase runs in: log2 of the columns a lane
 // owns per lane load (x_slot), or -1 for the half layout (4-bit phases of a bf16 model
@@ -977,23 +996,23 @@ __device__ __forceinline__ void phase_rows(DevRef D, LayerRef Lw, int t, Rows<R>
 
 // f(Format type tag) is called with the streaming format of (PH, river, column count).
 template <class F> struct Tag { typedef F type; };
-template <int DT, int PH, class Fn>
+template <int DT, int PH, bool N, class Fn>
 __device__ __forceinline__ void with_format(DevRef D, bool river, Fn f) {
   if (!river) {
-    f(Tag<Dense<DT, Shape<PH, false>::R, Shape<PH, false>::U>>(), IC<false>(), IC<Shape<PH, false>::R>());
+    f(Tag<Dense<DT, Shape<PH, false, N>::R, Shape<PH, false, N>::U>>(), IC<false>(), IC<Shape<PH, false, N>::R>());
   } else if ((phase_cols(D, PH) & 31) == 0) {
-    f(Tag<W4<DT, Shape<PH, true>::R, Shape<PH, true>::U, 32>>(), IC<true>(), IC<Shape<PH, true>::R>());
+    f(Tag<W4<DT, Shape<PH, true, N>::R, Shape<PH, true, N>::U, 32>>(), IC<true>(), IC<Shape<PH, true, N>::R>());
   } else {
-    f(Tag<W4<DT, Shape<PH, true>::R, Shape<PH, true>::U, 16>>(), IC<true>(), IC<Shape<PH, true>::R>());
+    f(Tag<W4<DT, Shape<PH, true, N>::R, Shape<PH, true, N>::U, 16>>(), IC<true>(), IC<Shape<PH, true, N>::R>());
   }
 }
 
 // Issue the first elements of this wavefront's sequence of phase PH of block l (dense or
 // river), one per slot.
-template <int DT, int PH>
-__device__ __forceinline__ void prefetch_phase_t(DevRef D, int l, bool river, Pre<DT> &g) {
+template <int DT, int PH, bool N>
+__device__ __forceinline__ void prefetch_phase_t(DevRef D, int l, bool river, Pre<DT, N> &g) {
   LayerRef Lw = layer_of(D, l);
-  with_format<DT, PH>(D, river, [&](auto ftag, auto rv, auto rr) {
+  with_format<DT, PH, N>(D, river, [&](auto ftag, auto rv, auto rr) {
     typedef typename decltype(ftag)::type F;
     constexpr bool RV = decltype(rv)::value;
     constexpr int R = decltype(rr)::value;
@@ -1007,7 +1026,7 @@ __device__ __forceinline__ void prefetch_phase_t(DevRef D, int l, bool river, Pr
       const float *hin = D.hidden + (size_t)l * D.d;
 #pragma unroll
       for (int j = 0; j < 2; ++j) {
-        const int row = (wave_id() + j * wave_count()) * R + g.lane;
+        const int row = (wave_id(F::SPREAD) + j * wave_count()) * R + g.lane;
         const bool ok = g.lane < R && row < D.d;
         g.rh[j] = ok ? sub(hin + row) : 0.f;
         if (PH == PH_DOWN) g.r1[j] = ok ? sub(D.h1 + row) : 0.f;
@@ -1015,8 +1034,8 @@ __device__ __forceinline__ void prefetch_phase_t(DevRef D, int l, bool river, Pr
     }
   });
 }
-template <int DT>
-__device__ __forceinline__ void prefetch_phase(DevRef D, int l, int ph, bool river, Pre<DT> &g) {
+template <int DT, bool N>
+__device__ __forceinline__ void prefetch_phase(DevRef D, int l, int ph, bool river, Pre<DT, N> &g) {
   switch (ph) {
     case PH_QKV: prefetch_phase_t<DT, PH_QKV>(D, l, river, g); break;
     case PH_O: prefetch_phase_t<DT, PH_O>(D, l, river, g); break;
@@ -1028,11 +1047,11 @@ __device__ __forceinline__ void prefetch_phase(DevRef D, int l, int ph, bool riv
 // Run phase PH of block l over the staged vector.  epi(n0, acc) is called once per task with
 // its first linear row n0 and the R finished dot products (lane-uniform); rows >= the row
 // count of the phase (a ragged last task) must be ignored by it.
-template <int DT, int PH, class Epi>
+template <int DT, int PH, bool N, class Epi>
 __device__ __forceinline__ void run_phase(DevRef D, int l, bool river, const float *xl,
-                                          Pre<DT> &pre, Epi epi) {
+                                          Pre<DT, N> &pre, Epi epi) {
   LayerRef Lw = layer_of(D, l);
-  with_format<DT, PH>(D, river, [&](auto ftag, auto rv, auto rr) {
+  with_format<DT, PH, N>(D, river, [&](auto ftag, auto rv, auto rr) {
     typedef typename decltype(ftag)::type F;
     constexpr bool RV = decltype(rv)::value;
     constexpr int R = decltype(rr)::value;
@@ -1152,8 +1171,8 @@ __device__ __forceinline__ bool guess_river_after(const StepArgs &A, const Ctl &
 // three per wavefront at the 8B shape.
 // `guess` is the format whose first elements pre holds; the exit test of the block before is taken
 // here (ctl), and where it turns out otherwise they are fetched again in the right one.
-template <int DT>
-__device__ __forceinline__ void phase_qkv(DevRef D, const StepArgs &A, int l, bool guess, Ctl &ctl, float *lds, Pre<DT> &pre) {
+template <int DT, bool N>
+__device__ __forceinline__ void phase_qkv(DevRef D, const StepArgs &A, int l, bool guess, Ctl &ctl, float *lds, Pre<DT, N> &pre) {
   RIVER_MARK(D, 16);
   LayerRef Lw = layer_of(D, l);
   if (l == 0) {
@@ -1603,8 +1622,8 @@ __device__ __forceinline__ void phase_attn(DevRef D, const StepArgs &A, int l, c
 }
 
 // a4: h1 = h + W_o o
-template <int DT>
-__device__ __forceinline__ void phase_oproj(DevRef D, const StepArgs &A, int l, bool river, float *lds, Pre<DT> &pre) {
+template <int DT, bool N>
+__device__ __forceinline__ void phase_oproj(DevRef D, const StepArgs &A, int l, bool river, float *lds, Pre<DT, N> &pre) {
   RIVER_MARK(D, 20);
   const int lp = run_log2<DT>(river, D.nq * D.hd);
   stage_attn_out(D, A, lp, lds, lds_half(D, lds));
@@ -1626,8 +1645,8 @@ __device__ __forceinline__ void phase_oproj(DevRef D, const StepArgs &A, int l, 
 }
 
 // a5: y = RMSNorm(h1) * g2; a = silu(W_g y) * (W_u y); rows come as (gate i, up i) pairs
-template <int DT>
-__device__ __forceinline__ void phase_gateup(DevRef D, const StepArgs &A, int l, bool river, float *lds, Pre<DT> &pre) {
+template <int DT, bool N>
+__device__ __forceinline__ void phase_gateup(DevRef D, const StepArgs &A, int l, bool river, float *lds, Pre<DT, N> &pre) {
   RIVER_MARK(D, 24);
   const int lp = run_log2<DT>(river, D.d);
   stage_norm<DT>(D.h1, layer_of(D, l).ffn_norm, D.d, D.eps, lp, lds, lds_half(D, lds), lds_red(D, lds));
@@ -1650,8 +1669,8 @@ __device__ __forceinline__ void phase_gateup(DevRef D, const StepArgs &A, int l,
 // Eq. 1's similarity <h,h2>, <h,h>, <h2,h2> reduced over this workgroup's rows.  The
 // reduction over workgroups and the exit decision are taken by every workgroup at the
 // start of the next block (exit_test), so no workgroup waits for another here.
-template <int DT>
-__device__ __forceinline__ void phase_down(DevRef D, const StepArgs &A, int l, bool river, float *lds, Pre<DT> &pre) {
+template <int DT, bool N>
+__device__ __forceinline__ void phase_down(DevRef D, const StepArgs &A, int l, bool river, float *lds, Pre<DT, N> &pre) {
   RIVER_MARK(D, 28);
   const int lp = run_log2<DT>(river, D.ffn);
   if (lp < 0) stage_copy_half(D.abuf, D.ffn, lds_half(D, lds));
@@ -1699,14 +1718,14 @@ __device__ __forceinline__ void head_rows(DevRef D, int t, Rows<kRD> &rw) {
     rw.sz[r] = nullptr;
   }
 }
-template <int DT>
-__device__ __forceinline__ void prefetch_head(DevRef D, Pre<DT> &g) {
+template <int DT, bool N>
+__device__ __forceinline__ void prefetch_head(DevRef D, Pre<DT, N> &g) {
   auto rows_of = [&](int t, Rows<kRD> &rw) { head_rows<DT>(D, t, rw); };
   const int n = (D.vocab + kRD - 1) / kRD;
   issue_first<Dense<DT, kRD, kUD>, DT, kRD>(n, D.d, D.group, g, rows_of);
 }
-template <int DT>
-__device__ __forceinline__ void phase_head(DevRef D, const StepArgs &A, const Ctl &ctl, float *lds, Pre<DT> &pre) {
+template <int DT, bool N>
+__device__ __forceinline__ void phase_head(DevRef D, const StepArgs &A, const Ctl &ctl, float *lds, Pre<DT, N> &pre) {
   float *red = lds_red(D, lds);
   const float *h = D.hidden + (size_t)D.L * D.d;
   const bool rec_s = !ctl.river && A.rec_slot >= 0;       // similarity of the last backbone block: recorded, never tested
