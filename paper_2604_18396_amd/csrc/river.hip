@@ -282,6 +282,12 @@ __global__ __launch_bounds__(256) void k_quantize_w4(const void *w, long long ro
   }
 }
 
+// A new sequence: the token state and the barrier's counters and error flag start at zero.  One workgroup of 64.
+__global__ void k_reset(DevState *st, unsigned long long *bar) {
+  if (threadIdx.x == 0) { *st = DevState{}; *bar_error(bar) = 0; }
+  if (threadIdx.x < kBarCounters) *bar_counter(bar, threadIdx.x) = 0;
+}
+
 __global__ void k_fill_bytes(uint4 *p, size_t n16, uint32_t word) {
   for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n16;
        i += (size_t)gridDim.x * blockDim.x)
@@ -365,6 +371,27 @@ static void bar_release(int dev, int slot) {
   if (slot >= 0) g_bar_used[dev] &= ~(1ull << slot);
 }
 
+// Pinned host memory of a context, beside its barrier slot (64 slots, allocated with the first context of
+// a device and kept): the last kernel of a synchronous call writes the record there, so that the call
+// waits for the stream and nothing else, and the first kernel of a short prefill reads its tokens there.
+// (A pageable copy and the wait for it take 19 us, a kernel's store and the wait 11.)  A record that does
+// not fit, and contexts without a barrier slot, use copies.
+constexpr int kHostRec = 4096, kHostTok = 512;
+struct HostSlot { int32_t rec[kHostRec], tok[kHostTok]; };
+namespace { HostSlot *g_host_pool[kBarDevices]; }
+static HostSlot *host_slot(int dev, int slot) {             // null: no pinned memory to be had
+  std::lock_guard<std::mutex> lk(g_bar_mu);
+  if (!g_host_pool[dev]) {
+    void *p = nullptr;
+    if (hipHostMalloc(&p, sizeof(HostSlot) * kBarSlots, hipHostMallocCoherent) != hipSuccess) {
+      (void)hipGetLastError();
+      return nullptr;
+    }
+    g_host_pool[dev] = (HostSlot *)p;
+  }
+  return g_host_pool[dev] + slot;
+}
+
 struct river_ctx {
   river_config cfg;
   Dev dev;              // host copy of the descriptor
@@ -379,6 +406,7 @@ struct river_ctx {
   unsigned long long bar_total;
   int bar_slot = -1;    // slot of the process-wide barrier pool
   int bar_device = 0;
+  HostSlot *host = nullptr;   // pinned memory of this context (null: copies)
   bool is_static = false; // activations and barrier block live in the device's static scratch
   ~river_ctx() {
     bar_release(bar_device, bar_slot);
@@ -596,8 +624,8 @@ extern "C" int river_quantize_w4(const void *w, int64_t rows, int64_t cols, int3
 }
 
 static int reset_state(river_ctx *x) {
-  HIP_TRY(x, hipMemsetAsync(x->ws + x->lay.state, 0, sizeof(DevState), x->stream));
-  HIP_TRY(x, hipMemsetAsync(x->dev.bar, 0, kBarBytes, x->stream));
+  k_reset<<<dim3(1), dim3(64), 0, x->stream>>>(x->dev.st, x->dev.bar);
+  HIP_TRY(x, hipGetLastError());
   x->bar_total = 0;
   return RIVER_OK;
 }
@@ -761,6 +789,8 @@ static int create_impl(const river_config *cfg, const river_weights *w, const ri
     if (rc != RIVER_OK) { g_create_err = why2; delete x; return rc; }
     D.bar = (unsigned long long *)bp;
     D.bar_vector_poll = 0;
+    const size_t words = cfg->max_batch > 1 ? (size_t)cfg->max_batch * (2 + L) : (size_t)kRecHead + L;
+    if (words <= kHostRec) x->host = host_slot(dev_id, x->bar_slot);
   }
   D.rec = (int *)(act + lay.rec);
   D.trace = (unsigned long long *)(act + lay.trace);
@@ -975,13 +1005,14 @@ static int launch_step(river_ctx *x, const StepArgs &A0) {
   return RIVER_OK;
 }
 
-static int enqueue(river_ctx *x, int token, int forced_e, int want_head, int rec_slot) {
+static int enqueue(river_ctx *x, int token, int forced_e, int want_head, int rec_slot, bool to_host) {
   StepArgs A{};
   A.pos = x->pos;
   A.token = token;
   A.forced_e = forced_e;
   A.want_head = want_head;
   A.rec_slot = rec_slot;
+  A.host_row = to_host && x->host ? x->host->rec : nullptr;
   const int T = x->pos + 1;
   // one workgroup per (query head, split); splits as far as there are workgroups for them
   const int max_splits = std::max(1, std::min(kMaxSplits, x->grid_persist / x->cfg.n_q_heads));
@@ -1006,7 +1037,7 @@ static int device_wait_gave_up(river_ctx *x) {
   x->broken = true;
   return RIVER_EHIP;
 }
-// After a synchronising call: did a bounded device wait give up?
+// Waits for the stream: did a bounded device wait give up?
 static int check_device_error(river_ctx *x) {
   int err = 0;
   HIP_TRY(x, hipMemcpyAsync(&err, (char *)x->dev.bar + kBarErrorByte, sizeof(int),
@@ -1107,13 +1138,19 @@ static int prefill_gemm(river_ctx *x, int seq, const int32_t *tokens, int n, int
   for (int c0 = 0; c0 < n; c0 += step) {
     const int m = std::min(step, n - c0);
     const int last = c0 + m == n ? m - 1 : -1;              // the row whose h(0..L) is kept
-    HIP_TRY(x, hipMemcpyAsync(tok, tokens + c0, (size_t)m * 4, hipMemcpyHostToDevice, s));
+    const int *tok_src = tok;
+    if (x->host && n <= kHostTok) {      // (the call waits for the stream: the slot is free)
+      std::memcpy(x->host->tok, tokens, (size_t)n * 4);
+      tok_src = x->host->tok;
+    } else {
+      HIP_TRY(x, hipMemcpyAsync(tok, tokens + c0, (size_t)m * 4, hipMemcpyHostToDevice, s));
+    }
     const dim3 rowwise(m <= 2 * x->grid_persist ? 512 : 256);
     int parts = 0;                                           // partial sums waiting to be added into h
     for (int l = 0; l < L; ++l) {
       const bool river = l >= ep;
       const DevLayer &W = x->layers_h[l];
-      pf::k_pf_norm<<<dim3(m), rowwise, 0, s>>>(h, l ? nullptr : tok, D.tok_emb, big, parts, W.attn_norm, d, c.rms_eps, x16,
+      pf::k_pf_norm<<<dim3(m), rowwise, 0, s>>>(h, l ? nullptr : tok_src, D.tok_emb, big, parts, W.attn_norm, d, c.rms_eps, x16,
                                                 D.hidden + (size_t)l * d, last, 0);
       parts = launch_gemm<pf::PF_STORE>(x, l, river, m_qkv, 3, x16, d, big, m);
       pf::k_pf_rope_store<<<dim3(m), rowwise, 0, s>>>(big, parts, m, D.rope, c.n_q_heads, c.n_kv_heads, c.head_dim, c0, l,
@@ -1148,6 +1185,7 @@ static int prefill_gemm(river_ctx *x, int seq, const int32_t *tokens, int n, int
   // the original final norm + LM head + argmax on the last prompt position (the decode path's kernel)
   StepArgs A{};
   A.pos = n - 1; A.token = -1; A.forced_e = ep; A.want_head = 1; A.rec_slot = -1; A.n_splits = 1; A.bar_base = 0;
+  A.host_row = x->host ? x->host->rec : nullptr;
   k_head<1><<<dim3(x->grid_gemv), dim3(x->block), x->lds_bytes, s>>>(x->dev_d, A);
   if (c.max_batch > 1)
     bd::k_bd_after_prefill<<<dim3(1), dim3(64), 0, s>>>(x->st_b, seq, &D.st->cur_token);
@@ -1188,13 +1226,20 @@ extern "C" int river_prefill(river_ctx *x, int32_t seq, const int32_t *tokens, i
     // short prompts, fp32 models and shapes the GEMM path does not take: the decode kernels,
     // one prompt position after the other
     for (int i = 0; i < n_tokens; ++i) {
-      rc = enqueue(x, tokens[i], ep, i == n_tokens - 1, -1);
+      rc = enqueue(x, tokens[i], ep, i == n_tokens - 1, -1, i == n_tokens - 1);
       if (rc) return rc;
     }
   }
   if (out_logits)
     HIP_TRY(x, hipMemcpyAsync(out_logits, x->dev.logits, (size_t)x->cfg.vocab * 4, hipMemcpyDeviceToDevice,
                               x->stream));
+  if (x->host) {
+    HIP_TRY(x, hipStreamSynchronize(x->stream));
+    if (x->host->rec[1] & kRecErrorBit) return device_wait_gave_up(x);
+    x->have_token = true;
+    if (out_token) *out_token = x->host->rec[0];
+    return RIVER_OK;
+  }
   rc = check_device_error(x);
   if (rc) return rc;
   x->have_token = true;
@@ -1232,20 +1277,26 @@ extern "C" int river_decode_step(river_ctx *x, const int32_t *in_token, const in
     return RIVER_EINVAL;
   }
   const int slot = (int)(x->steps % kRecords);
-  int rc = enqueue(x, tok, fe, 1, slot);
+  int rc = enqueue(x, tok, fe, 1, slot, out_token != nullptr);
   if (rc) return rc;
   x->steps += 1;
   x->have_token = true;
   if (!out_token) return RIVER_OK;
-  // the step's record in one copy, the device's error flag with it
+  // the step's record, the device's error flag with it: written to the host by the step, or in one copy
   const size_t row = (size_t)kRecHead + L;
-  x->rec_h.resize(row);
-  HIP_TRY(x, hipMemcpyAsync(x->rec_h.data(), x->dev.rec + slot * row, row * 4, hipMemcpyDeviceToHost, x->stream));
+  const int32_t *rec;
+  if (x->host) {
+    rec = x->host->rec;
+  } else {
+    x->rec_h.resize(row);
+    HIP_TRY(x, hipMemcpyAsync(x->rec_h.data(), x->dev.rec + slot * row, row * 4, hipMemcpyDeviceToHost, x->stream));
+    rec = x->rec_h.data();
+  }
   HIP_TRY(x, hipStreamSynchronize(x->stream));
-  *out_token = x->rec_h[0];
-  if (out_exit_layer) *out_exit_layer = x->rec_h[1] & ~kRecErrorBit;
-  if (out_sims) std::memcpy(out_sims, x->rec_h.data() + kRecHead, (size_t)L * 4);
-  return x->rec_h[1] & kRecErrorBit ? device_wait_gave_up(x) : RIVER_OK;
+  *out_token = rec[0];
+  if (out_exit_layer) *out_exit_layer = rec[1] & ~kRecErrorBit;
+  if (out_sims) std::memcpy(out_sims, rec + kRecHead, (size_t)L * 4);
+  return rec[1] & kRecErrorBit ? device_wait_gave_up(x) : RIVER_OK;
 }
 
 // GEMM g (QKV, O, gate/up, down) of block l of a batched decode step, or the LM head (Bq null,
@@ -1401,18 +1452,25 @@ extern "C" int river_decode_batch(river_ctx *x, int32_t n_seq, const int32_t *in
   // the original LM head (its input is already normalised), greedy token per sequence
   launch_bd_gemm_b(x, x->bd_head, x->bd_head, c.vocab, x16, d, logits, c.vocab, bd::EPI_STORE, bd::kSideDense, n);
   // (the attention kernels are done with their partial-result area and tickets)
-  bd::k_bd_argmax<<<dim3(n * bd::kBdArgmaxChunks), dim3(256), 0, s>>>(logits, c.vocab, st, rec_token, rec_exit, part_ml, tickets);
+  bd::k_bd_argmax<<<dim3(n * bd::kBdArgmaxChunks), dim3(256), 0, s>>>(logits, c.vocab, st, rec_token, rec_exit, part_ml, tickets,
+                                                                               out_tokens && x->host ? x->host->rec : nullptr, (int)B, rec_sims, L);
   HIP_TRY(x, hipGetLastError());
   for (int b = 0; b < n; ++b) x->pos_b[b] += 1;
   x->steps_b += 1;
   x->last_n = n;
   if (!out_tokens) return RIVER_OK;
-  x->rec_h.resize(B * (2 + L));
-  HIP_TRY(x, hipMemcpyAsync(x->rec_h.data(), rec_token, (out_sims ? B * 2 + (size_t)n * L : B + n) * 4, hipMemcpyDeviceToHost, s));
+  const int32_t *rec;
+  if (x->host) {
+    rec = x->host->rec;
+  } else {
+    x->rec_h.resize(B * (2 + L));
+    HIP_TRY(x, hipMemcpyAsync(x->rec_h.data(), rec_token, (out_sims ? B * 2 + (size_t)n * L : B + n) * 4, hipMemcpyDeviceToHost, s));
+    rec = x->rec_h.data();
+  }
   HIP_TRY(x, hipStreamSynchronize(s));
-  std::memcpy(out_tokens, x->rec_h.data(), (size_t)n * 4);
-  if (out_exit_layers) std::memcpy(out_exit_layers, x->rec_h.data() + B, (size_t)n * 4);
-  if (out_sims) std::memcpy(out_sims, x->rec_h.data() + 2 * B, (size_t)n * L * 4);
+  std::memcpy(out_tokens, rec, (size_t)n * 4);
+  if (out_exit_layers) std::memcpy(out_exit_layers, rec + B, (size_t)n * 4);
+  if (out_sims) std::memcpy(out_sims, rec + 2 * B, (size_t)n * L * 4);
   return RIVER_OK;
 }
 

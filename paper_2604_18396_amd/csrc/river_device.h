@@ -85,6 +85,7 @@ struct StepArgs {
   int want_head;      // 0: skip final norm + LM head (prompt positions but the last)
   int rec_slot;       // record ring slot of this step (< 0: no record)
   int n_splits;       // split-K factor for this step's attention
+  int *host_row;      // pinned host memory that also receives the record's row (null: nobody waits for it)
   unsigned long long bar_base;   // device-wide barriers completed before this launch
 };
 
@@ -194,6 +195,10 @@ __device__ __forceinline__ u32x4 ld_stream8(const void *p) {
 
 // ------------------------------------- activations shared between workgroups
 
+// A word of the pinned host row a synchronous call reads its results from.
+__device__ __forceinline__ void host_store(int *p, int v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
 // Values produced in this launch and read by other workgroups are published with
 // agent-scope atomic stores (written through to the device coherence point) and read
 // with agent-scope loads (sc1), so they never rely on a cache-wide flush.
@@ -1763,13 +1768,17 @@ __device__ __forceinline__ void phase_head(DevRef D, const StepArgs &A, const Ct
     block_argmax(b, bi, red);
     if (threadIdx.x == 0) {
       D.st->cur_token = bi;
+      const int err = __hip_atomic_load(bar_error(D.bar), __ATOMIC_RELAXED, RIVER_AG);
+      const int exit_word = ctl.exit_pos | (err ? kRecErrorBit : 0);
       if (A.rec_slot >= 0) {
         int *const row = D.rec + (size_t)A.rec_slot * (kRecHead + D.L);
-        const int err = __hip_atomic_load(bar_error(D.bar), __ATOMIC_RELAXED, RIVER_AG);
         row[0] = bi;
-        row[1] = ctl.exit_pos | (err ? kRecErrorBit : 0);
+        row[1] = exit_word;
       }
+      if (A.host_row) { host_store(A.host_row, bi); host_store(A.host_row + 1, exit_word); }
     }
+    if (A.host_row && A.rec_slot >= 0)
+      for (int i = threadIdx.x; i < D.L; i += blockDim.x) host_store(A.host_row + kRecHead + i, __float_as_int(sub(rec_sims(D, A) + i)));
   }
 }
 

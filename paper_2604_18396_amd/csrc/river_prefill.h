@@ -1555,8 +1555,10 @@ __global__ void k_bd_decide(int n, int l1, int L, int min_exit, float tau, int r
 // row each and publish (value, index); the last one to arrive takes the best of them in chunk
 // order (part: [n][chunks][2], tickets: [n], zero between launches).
 constexpr int kBdArgmaxChunks = 16;
+// host_row (pinned; null: nobody waits): [max_batch] tokens, [max_batch] exits, [n][L] similarities
 __global__ __launch_bounds__(256) void k_bd_argmax(const float *__restrict__ logits, int vocab, SeqState st,
-                                                   int *rec_token, int *rec_exit, float *part, unsigned int *tickets) {
+                                                   int *rec_token, int *rec_exit, float *part, unsigned int *tickets,
+                                                   int *host_row, int max_batch, const float *sims, int L) {
   __shared__ float red[64];
   __shared__ int flag;
   const int b = blockIdx.x / kBdArgmaxChunks, c = blockIdx.x % kBdArgmaxChunks;
@@ -1593,7 +1595,11 @@ __global__ __launch_bounds__(256) void k_bd_argmax(const float *__restrict__ log
     st.token[b] = besti;
     rec_token[b] = besti;
     rec_exit[b] = st.exit_pos[b];
+    if (host_row) { host_store(host_row + b, besti); host_store(host_row + max_batch + b, st.exit_pos[b]); }
   }
+  if (host_row)
+    for (int i = threadIdx.x; i < L; i += blockDim.x)
+      host_store(host_row + 2 * max_batch + b * L + i, __float_as_int(sims[(size_t)b * L + i]));
 }
 
 // after a prefill of sequence `seq`: its next token
