@@ -35,7 +35,7 @@ __device__ __forceinline__ Ctl load_ctl(DevRef D, int l) {
   return c;
 }
 
-template <int DT, bool N>
+template <int DT, int V>
 __global__ __launch_bounds__(kBlock) void k_qkv(const Dev *Dp, StepArgs A, int l) {
   extern __shared__ float lds[];
   DevRef D = *RIVER_CONSTANT(Dev, Dp);
@@ -46,7 +46,7 @@ __global__ __launch_bounds__(kBlock) void k_qkv(const Dev *Dp, StepArgs A, int l
   } else {
     ctl = load_ctl(D, l - 1);
   }
-  Pre<DT, N> pre;
+  Pre<DT, V> pre;
   const bool guess = l == 0 ? ctl.river : guess_river_after(A, ctl, l);
   prefetch_phase<DT>(D, l, PH_QKV, guess, pre);
   phase_qkv<DT>(D, A, l, guess, ctl, lds, pre);
@@ -61,42 +61,42 @@ template <int DT, bool F16>
 __global__ __launch_bounds__(kBlock) void k_attn(const Dev *Dp, StepArgs A, int l) {
   extern __shared__ float lds[];
   DevRef D = *RIVER_CONSTANT(Dev, Dp);
-  phase_attn<DT, F16>(D, A, l, load_ctl(D, l), lds, [] {}, [] {});
+  phase_attn<DT, F16, 0>(D, A, l, load_ctl(D, l), lds, [] {}, [] {});
 }
-template <int DT, bool N>
+template <int DT, int V>
 __global__ __launch_bounds__(kBlock) void k_oproj(const Dev *Dp, StepArgs A, int l) {
   extern __shared__ float lds[];
   DevRef D = *RIVER_CONSTANT(Dev, Dp);
   const Ctl ctl = load_ctl(D, l);
-  Pre<DT, N> pre;
+  Pre<DT, V> pre;
   prefetch_phase<DT>(D, l, PH_O, ctl.river, pre);
   phase_oproj<DT>(D, A, l, ctl.river, lds, pre);
 }
-template <int DT, bool N>
+template <int DT, int V>
 __global__ __launch_bounds__(kBlock) void k_gateup(const Dev *Dp, StepArgs A, int l) {
   extern __shared__ float lds[];
   DevRef D = *RIVER_CONSTANT(Dev, Dp);
   const Ctl ctl = load_ctl(D, l);
-  Pre<DT, N> pre;
+  Pre<DT, V> pre;
   prefetch_phase<DT>(D, l, PH_GU, ctl.river, pre);
   phase_gateup<DT>(D, A, l, ctl.river, lds, pre);
 }
-template <int DT, bool N>
+template <int DT, int V>
 __global__ __launch_bounds__(kBlock) void k_down(const Dev *Dp, StepArgs A, int l) {
   extern __shared__ float lds[];
   DevRef D = *RIVER_CONSTANT(Dev, Dp);
   const Ctl ctl = load_ctl(D, l);
-  Pre<DT, N> pre;
+  Pre<DT, V> pre;
   prefetch_phase<DT>(D, l, PH_DOWN, ctl.river, pre);
   phase_down<DT>(D, A, l, ctl.river, lds, pre);
 }
 template <int DT>
 __global__ __launch_bounds__(kBlock) void k_head(const Dev *Dp, StepArgs A) {
-  constexpr bool N = false;
+  constexpr int V = 0;
   extern __shared__ float lds[];
   DevRef D = *RIVER_CONSTANT(Dev, Dp);
   const Ctl ctl = load_ctl(D, D.L - 1);
-  Pre<DT, N> pre;
+  Pre<DT, V> pre;
   prefetch_head<DT>(D, pre);
   phase_head<DT>(D, A, ctl, lds, pre);
 }
@@ -123,12 +123,12 @@ __global__ __launch_bounds__(kBlock) void k_head(const Dev *Dp, StepArgs A) {
 __device__ __forceinline__ int pack_ctl(const Ctl &c) { return (c.exit_pos << 1) | (c.river ? 1 : 0); }
 __device__ __forceinline__ Ctl unpack_ctl(int v) { Ctl c; c.river = v & 1; c.exit_pos = v >> 1; return c; }
 
-template <int DT, bool N>
+template <int DT, int V>
 __device__ RIVER_PSTEP_INLINE int pstep_qkv(const Dev *Dp, StepArgs A, int l, int ctl_packed,
                                       unsigned long long k, float *lds) {
   DevRef D = *RIVER_CONSTANT(Dev, Dp);
   Ctl ctl = unpack_ctl(ctl_packed);
-  Pre<DT, N> pre;
+  Pre<DT, V> pre;
   // block l (1-based) has just run: what will block l + 1 run as, as far as known now
   const bool guess = (l == 0) ? ctl.river : guess_river_after(A, ctl, l);
   if (l > 0) { barrier_arrive(D.bar, k); TRACE_ARRIVE(); }
@@ -137,18 +137,18 @@ __device__ RIVER_PSTEP_INLINE int pstep_qkv(const Dev *Dp, StepArgs A, int l, in
   phase_qkv<DT>(D, A, l, guess, ctl, lds, pre);
   return pack_ctl(ctl);
 }
-template <int DT, bool F16>
+template <int DT, bool F16, int HD>
 __device__ RIVER_PSTEP_INLINE void pstep_attn(const Dev *Dp, StepArgs A, int l, int ctl_packed, unsigned long long k,
                                         float *lds) {
   DevRef D = *RIVER_CONSTANT(Dev, Dp);
-  phase_attn<DT, F16>(D, A, l, unpack_ctl(ctl_packed), lds, [&] { barrier_arrive(D.bar, k); TRACE_ARRIVE(); },
+  phase_attn<DT, F16, HD>(D, A, l, unpack_ctl(ctl_packed), lds, [&] { barrier_arrive(D.bar, k); TRACE_ARRIVE(); },
                  [&] { barrier_wait(D.bar, k, D.spin_limit, D.bar_vector_poll); TRACE_RELEASE(); });
 }
-template <int DT, int PH, bool N>
+template <int DT, int PH, int V>
 __device__ RIVER_PSTEP_INLINE void pstep_gemv(const Dev *Dp, StepArgs A, int l, bool river, unsigned long long k,
                                         float *lds) {
   DevRef D = *RIVER_CONSTANT(Dev, Dp);
-  Pre<DT, N> pre;
+  Pre<DT, V> pre;
   barrier_arrive(D.bar, k); TRACE_ARRIVE();
   prefetch_phase<DT>(D, l, PH, river, pre);
   barrier_wait(D.bar, k, D.spin_limit, D.bar_vector_poll); TRACE_RELEASE();
@@ -156,12 +156,12 @@ __device__ RIVER_PSTEP_INLINE void pstep_gemv(const Dev *Dp, StepArgs A, int l, 
   else if (PH == PH_GU) phase_gateup<DT>(D, A, l, river, lds, pre);
   else phase_down<DT>(D, A, l, river, lds, pre);
 }
-template <int DT, bool N>
+template <int DT, int V>
 __device__ RIVER_PSTEP_INLINE void pstep_head(const Dev *Dp, StepArgs A, int ctl_packed, unsigned long long k,
                                         float *lds) {
   DevRef D = *RIVER_CONSTANT(Dev, Dp);
   const Ctl ctl = unpack_ctl(ctl_packed);
-  Pre<DT, N> pre;
+  Pre<DT, V> pre;
   barrier_arrive(D.bar, k); TRACE_ARRIVE();
   prefetch_head<DT>(D, pre);
   barrier_wait(D.bar, k, D.spin_limit, D.bar_vector_poll); TRACE_RELEASE();
@@ -170,7 +170,7 @@ __device__ RIVER_PSTEP_INLINE void pstep_head(const Dev *Dp, StepArgs A, int ctl
 
 // The number of barriers (5 L - 1, one more with the head) is the same for every workgroup
 // whatever the exit state.
-template <int DT, bool F16, bool N>
+template <int DT, bool F16, int V, int HD>
 __global__ __launch_bounds__(kBlock) void k_step_persistent(const Dev *Dp, StepArgs A) {
   extern __shared__ float lds[];
   DevRef D = *RIVER_CONSTANT(Dev, Dp);
@@ -179,14 +179,14 @@ __global__ __launch_bounds__(kBlock) void k_step_persistent(const Dev *Dp, StepA
   record_init(D, A);
   int ctl = pack_ctl(ctl_init(D, A));
   for (int l = 0; l < L; ++l) {
-    ctl = pstep_qkv<DT, N>(Dp, A, l, ctl, l ? ++k : 0, lds);
+    ctl = pstep_qkv<DT, V>(Dp, A, l, ctl, l ? ++k : 0, lds);
     const bool river = ctl & 1;
-    pstep_attn<DT, F16>(Dp, A, l, ctl, ++k, lds);
-    pstep_gemv<DT, PH_O, N>(Dp, A, l, river, ++k, lds);
-    pstep_gemv<DT, PH_GU, N>(Dp, A, l, river, ++k, lds);
-    pstep_gemv<DT, PH_DOWN, N>(Dp, A, l, river, ++k, lds);
+    pstep_attn<DT, F16, HD>(Dp, A, l, ctl, ++k, lds);
+    pstep_gemv<DT, PH_O, V>(Dp, A, l, river, ++k, lds);
+    pstep_gemv<DT, PH_GU, V>(Dp, A, l, river, ++k, lds);
+    pstep_gemv<DT, PH_DOWN, V>(Dp, A, l, river, ++k, lds);
   }
-  if (A.want_head) pstep_head<DT, N>(Dp, A, ctl, ++k, lds);
+  if (A.want_head) pstep_head<DT, V>(Dp, A, ctl, ++k, lds);
 }
 
 // Interleaves the river's scale and zero arrays into one (scale, zero) pair per group,
@@ -430,6 +430,25 @@ struct river_ctx {
 };
 
 static thread_local std::string g_create_err;
+
+// rows of d_model and n_q * head_dim columns of at most four 1 KiB granules (see Shape)
+static bool narrow_model(const river_config &c) {
+  return std::max(c.d_model, c.n_q_heads * c.head_dim) * (c.dtype == RIVER_BF16 ? 2 : 4) <= 4096;
+}
+// The one-launch step kernel of a configuration (bf16), by cache type, head size and variant (see Pre)
+typedef void (*StepKernel)(const Dev *, StepArgs);
+template <bool F16, int HD>
+static StepKernel step_kernel_of(const river_config &c) {
+  const bool cols32 = c.d_model % 32 == 0 && c.d_ffn % 32 == 0 && c.n_q_heads * c.head_dim % 32 == 0;
+  if (!cols32) return k_step_persistent<1, F16, 0, HD>;
+  return narrow_model(c) ? k_step_persistent<1, F16, V_NARROW | V_COLS32, HD> : k_step_persistent<1, F16, V_COLS32, HD>;
+}
+static StepKernel step_kernel(const river_ctx *x) {
+  const river_config &c = x->cfg;
+  const bool f16 = c.kv_dtype == RIVER_KV_F16;
+  return c.head_dim == 128 ? (f16 ? step_kernel_of<true, 128>(c) : step_kernel_of<false, 128>(c))
+                           : (f16 ? step_kernel_of<true, 64>(c) : step_kernel_of<false, 64>(c));
+}
 
 static size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
@@ -915,14 +934,12 @@ static int create_impl(const river_config *cfg, const river_weights *w, const ri
   {
     const int lb = (int)x->lds_bytes;
     const void *fns[] = {
-        (const void *)k_qkv<0, false>, (const void *)k_qkv<0, true>, (const void *)k_qkv<1, false>, (const void *)k_qkv<1, true>,
+        (const void *)k_qkv<0, 0>, (const void *)k_qkv<0, V_NARROW>, (const void *)k_qkv<1, 0>,
         (const void *)k_attn<0, false>, (const void *)k_attn<1, false>, (const void *)k_attn<1, true>,
-        (const void *)k_oproj<0, false>, (const void *)k_oproj<0, true>, (const void *)k_oproj<1, false>, (const void *)k_oproj<1, true>,
-        (const void *)k_gateup<0, false>, (const void *)k_gateup<0, true>, (const void *)k_gateup<1, false>, (const void *)k_gateup<1, true>,
-        (const void *)k_down<0, false>, (const void *)k_down<0, true>, (const void *)k_down<1, false>, (const void *)k_down<1, true>,
-        (const void *)k_head<0>, (const void *)k_head<1>,
-        (const void *)k_step_persistent<1, false, false>, (const void *)k_step_persistent<1, true, false>,
-        (const void *)k_step_persistent<1, false, true>, (const void *)k_step_persistent<1, true, true>};
+        (const void *)k_oproj<0, 0>, (const void *)k_oproj<0, V_NARROW>, (const void *)k_oproj<1, 0>,
+        (const void *)k_gateup<0, 0>, (const void *)k_gateup<0, V_NARROW>, (const void *)k_gateup<1, 0>,
+        (const void *)k_down<0, 0>, (const void *)k_down<0, V_NARROW>, (const void *)k_down<1, 0>,
+        (const void *)k_head<0>, (const void *)k_head<1>, (const void *)step_kernel(x)};
     for (const void *f : fns)
       if ((e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, lb)) != hipSuccess)
         return fail("hipFuncSetAttribute(max dynamic LDS)", e);
@@ -969,8 +986,8 @@ extern "C" int river_create_static(const river_config *cfg, const river_weights 
   return create_impl(cfg, w, q, workspace, workspace_bytes, hip_stream, out, true);
 }
 
-// Enqueue one token (prompt position or decode step).  N: the phases' shapes for narrow models.
-template <int DT, bool N>
+// Enqueue one token (prompt position or decode step).  V: see Pre.
+template <int DT, int V>
 static int launch_step(river_ctx *x, const StepArgs &A0) {
   StepArgs A = A0;
   const Dev &D = x->dev;
@@ -982,8 +999,7 @@ static int launch_step(river_ctx *x, const StepArgs &A0) {
     // bf16 only (river_create refuses the combination with fp32)
     if constexpr (DT == 1) {
       A.bar_base = x->bar_total;
-      if (D.kv_f16) k_step_persistent<DT, true, N><<<dim3(x->grid_persist), blk, lds, s>>>(Dp, A);
-      else k_step_persistent<DT, false, N><<<dim3(x->grid_persist), blk, lds, s>>>(Dp, A);
+      step_kernel(x)<<<dim3(x->grid_persist), blk, lds, s>>>(Dp, A);
       x->bar_total += 5ull * D.L - 1 + (A.want_head ? 1 : 0);
     } else {
       x->err = "RIVER_EXEC_PERSISTENT is available for RIVER_BF16 only";
@@ -992,12 +1008,12 @@ static int launch_step(river_ctx *x, const StepArgs &A0) {
   } else {
     const dim3 gg(x->grid_gemv);
     for (int l = 0; l < D.L; ++l) {
-      k_qkv<DT, N><<<gg, blk, lds, s>>>(Dp, A, l);
+      k_qkv<DT, V><<<gg, blk, lds, s>>>(Dp, A, l);
       if (DT == 1 && D.kv_f16) k_attn<DT, DT == 1><<<gg, blk, lds, s>>>(Dp, A, l);
       else k_attn<DT, false><<<gg, blk, lds, s>>>(Dp, A, l);
-      k_oproj<DT, N><<<gg, blk, lds, s>>>(Dp, A, l);
-      k_gateup<DT, N><<<gg, blk, lds, s>>>(Dp, A, l);
-      k_down<DT, N><<<gg, blk, lds, s>>>(Dp, A, l);
+      k_oproj<DT, V><<<gg, blk, lds, s>>>(Dp, A, l);
+      k_gateup<DT, V><<<gg, blk, lds, s>>>(Dp, A, l);
+      k_down<DT, V><<<gg, blk, lds, s>>>(Dp, A, l);
     }
     if (A.want_head) k_head<DT><<<gg, blk, lds, s>>>(Dp, A);
   }
@@ -1023,11 +1039,10 @@ static int enqueue(river_ctx *x, int token, int forced_e, int want_head, int rec
   if (S > 4) S = std::max(4, (T + 2 * kAttnPosPerSplit - 1) / (2 * kAttnPosPerSplit));
   A.n_splits = std::max(1, std::min(max_splits, S));
   A.bar_base = 0;
-  // rows of at most four 1 KiB granules (see Shape)
-  const bool bf16 = x->cfg.dtype == RIVER_BF16;
-  const bool narrow = std::max(x->cfg.d_model, x->cfg.n_q_heads * x->cfg.head_dim) * (bf16 ? 2 : 4) <= 4096;
-  const int rc = bf16 ? (narrow ? launch_step<1, true>(x, A) : launch_step<1, false>(x, A))
-                      : (narrow ? launch_step<0, true>(x, A) : launch_step<0, false>(x, A));
+  const bool bf16 = x->cfg.dtype == RIVER_BF16, narrow = !bf16 && narrow_model(x->cfg);
+  // (bf16: the one-launch kernel, see step_kernel; its launch-per-phase mode is for debugging)
+  const int rc = bf16 ? launch_step<1, 0>(x, A)
+                      : (narrow ? launch_step<0, V_NARROW>(x, A) : launch_step<0, 0>(x, A));
   if (rc == RIVER_OK) x->pos += 1;
   return rc;
 }

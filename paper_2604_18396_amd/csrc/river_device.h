@@ -572,15 +572,16 @@ constexpr int kNormRuns = 2;
 template <int DT> struct NormIn {
   float4 v[kNormRuns][2];
   float g[kNormRuns][8];
+  // ANY: gains of any alignment (the final norm's; the blocks' are 16-byte aligned)
+  template <bool ANY>
   __device__ __forceinline__ void load(const float *h, const void *gain, int base, int n) {
-    const bool wide = ((uintptr_t)gain & 15) == 0;             // (the final norm's gains may have any alignment)
 #pragma unroll
     for (int k = 0; k < kNormRuns; ++k) {
       const int i = base + (k * kBlock + (int)threadIdx.x) * 8;
       if (i < n) {
         v[k][0] = sub4(h, i);
         v[k][1] = sub4(h, i + 4);
-        if (wide) {
+        if constexpr (!ANY) {
           constexpr int EPL = Store<DT>::EPL;
 #pragma unroll
           for (int e = 0; e < 8; e += EPL) {
@@ -598,10 +599,11 @@ template <int DT> struct NormIn {
     }
   }
   // this thread's sum of squares of h
+  template <bool ANY = false>
   __device__ __forceinline__ float fetch(const float *h, const void *gain, int n) {
     float ss = 0.f;
     for (int base = 0; base < n; base += kNormRuns * kBlock * 8) {
-      load(h, gain, base, n);
+      load<ANY>(h, gain, base, n);
 #pragma unroll
       for (int k = 0; k < kNormRuns; ++k)
         if (base + (k * kBlock + (int)threadIdx.x) * 8 < n) {
@@ -616,10 +618,11 @@ template <int DT> struct NormIn {
   }
   // x into LDS: for runs of 2^lp in xl, or (lp < 0, n % 32 == 0: whole quads of threads take part, as the
   // run sums need) in the half layout in xh
+  template <bool ANY = false>
   __device__ __forceinline__ void put(const float *h, const void *gain, int n, float r, int lp, float *xl, float *xh) {
     const bool one_trip = n <= kNormRuns * kBlock * 8;
     for (int base = 0; base < n; base += kNormRuns * kBlock * 8) {
-      if (!one_trip) load(h, gain, base, n);
+      if (!one_trip) load<ANY>(h, gain, base, n);
 #pragma unroll
       for (int k = 0; k < kNormRuns; ++k) {
         const int i = base + (k * kBlock + (int)threadIdx.x) * 8;
@@ -846,7 +849,13 @@ __device__ __forceinline__ int fresh_lane() {
   return t;
 }
 constexpr int kSets = 2;           // register sets of the streaming pipeline (a third one only delayed the phases)
-template <int DT, bool N> struct Pre {       // N: the phases' shapes for narrow models (see Shape)
+// V: what a kernel is built for, bit 0 the phases' shapes for narrow models (see Shape), bit 1 column
+// counts that are all multiples of 32 (no other 4-bit format).  The one-launch step kernel is built per
+// variant and head size: with all of them in one it is 210 KB of code instead of 135, of which a token touches 118 KB
+// in place of 84 (instruction cache misses).  1B shape, 256 tokens of context: backbone 620 -> 606, river 455 -> 445
+// us per token; 8B shape, 768: 704 -> 708, 440 -> 432.
+enum { V_NARROW = 1, V_COLS32 = 2 };
+template <int DT, int V> struct Pre {
   Regs<DT> set[kSets];
   float rh[2], r1[2];      // residual inputs of this wavefront's first two tasks (O, down phases)
   int lane;
@@ -855,8 +864,8 @@ template <int DT, bool N> struct Pre {       // N: the phases' shapes for narrow
 
 // Issue element j of this wavefront's sequence into slot j % (kSets * F::SUB) (nothing if
 // the sequence is shorter).
-template <class F, int DT, int R, bool N, class RowsOf>
-__device__ __forceinline__ void issue_seq(int j, int slot, int n_tasks, int cols, int group, Pre<DT, N> &pre,
+template <class F, int DT, int R, int V, class RowsOf>
+__device__ __forceinline__ void issue_seq(int j, int slot, int n_tasks, int cols, int group, Pre<DT, V> &pre,
                                           RowsOf rows_of) {
   const int NS = F::steps(cols);
   const int t = wave_id(F::SPREAD) + (j / NS) * wave_count();
@@ -867,8 +876,8 @@ __device__ __forceinline__ void issue_seq(int j, int slot, int n_tasks, int cols
   }
 }
 // The first elements into their slots.
-template <class F, int DT, int R, bool N, class RowsOf>
-__device__ __forceinline__ void issue_first(int n_tasks, int cols, int group, Pre<DT, N> &pre, RowsOf rows_of) {
+template <class F, int DT, int R, int V, class RowsOf>
+__device__ __forceinline__ void issue_first(int n_tasks, int cols, int group, Pre<DT, V> &pre, RowsOf rows_of) {
 #pragma unroll
   for (int q = 0; q < kSets * F::SUB; ++q) issue_seq<F, DT, R>(q, q, n_tasks, cols, group, pre, rows_of);
 }
@@ -877,9 +886,9 @@ __device__ __forceinline__ void issue_first(int n_tasks, int cols, int group, Pr
 // elements of the sequence (issue_first, called by the caller, possibly before the
 // preceding barrier).  rows_of(task, Rows&) gives the rows of a task; epi(task, acc)
 // receives the R finished dot products (identical in all lanes).
-template <class F, int DT, int R, bool N, class RowsOf, class Epi>
+template <class F, int DT, int R, int V, class RowsOf, class Epi>
 __device__ __forceinline__ void stream_tasks(int n_tasks, int cols, int group, const float *xl,
-                                             Pre<DT, N> &pre, RowsOf rows_of, Epi epi) {
+                                             Pre<DT, V> &pre, RowsOf rows_of, Epi epi) {
   constexpr int NSLOT = kSets * F::SUB;
   const int nw = wave_count(), w = wave_id(F::SPREAD);
   if (w >= n_tasks) return;
@@ -946,10 +955,10 @@ template <> struct Shape<PH_DOWN, true, true> { static constexpr int R = 1, U = 
 // Layout of the staged vector for the format a phase runs in: log2 of the columns a lane
 // owns per lane load (x_slot), or -1 for the half layout (4-bit phases of a bf16 model
 // whose column count is a multiple of 32).
-template <int DT>
+template <int DT, int V>
 __device__ __forceinline__ int run_log2(bool river, int cols) {
   if (!river) return Store<DT>::EPL == 8 ? 3 : 2;
-  if ((cols & 31) != 0) return 4;
+  if (!(V & V_COLS32) && (cols & 31) != 0) return 4;
   return DT == 1 ? -1 : 5;
 }
 // where the streaming engine finds the staged vector of that layout
@@ -1001,23 +1010,23 @@ __device__ __forceinline__ void phase_rows(DevRef D, LayerRef Lw, int t, Rows<R>
 
 // f(Format type tag) is called with the streaming format of (PH, river, column count).
 template <class F> struct Tag { typedef F type; };
-template <int DT, int PH, bool N, class Fn>
+template <int DT, int PH, int V, class Fn>
 __device__ __forceinline__ void with_format(DevRef D, bool river, Fn f) {
   if (!river) {
-    f(Tag<Dense<DT, Shape<PH, false, N>::R, Shape<PH, false, N>::U>>(), IC<false>(), IC<Shape<PH, false, N>::R>());
-  } else if ((phase_cols(D, PH) & 31) == 0) {
-    f(Tag<W4<DT, Shape<PH, true, N>::R, Shape<PH, true, N>::U, 32>>(), IC<true>(), IC<Shape<PH, true, N>::R>());
-  } else {
-    f(Tag<W4<DT, Shape<PH, true, N>::R, Shape<PH, true, N>::U, 16>>(), IC<true>(), IC<Shape<PH, true, N>::R>());
+    f(Tag<Dense<DT, Shape<PH, false, (V & V_NARROW) != 0>::R, Shape<PH, false, (V & V_NARROW) != 0>::U>>(), IC<false>(), IC<Shape<PH, false, (V & V_NARROW) != 0>::R>());
+  } else if ((V & V_COLS32) || (phase_cols(D, PH) & 31) == 0) {
+    f(Tag<W4<DT, Shape<PH, true, (V & V_NARROW) != 0>::R, Shape<PH, true, (V & V_NARROW) != 0>::U, 32>>(), IC<true>(), IC<Shape<PH, true, (V & V_NARROW) != 0>::R>());
+  } else if constexpr (!(V & V_COLS32)) {
+    f(Tag<W4<DT, Shape<PH, true, (V & V_NARROW) != 0>::R, Shape<PH, true, (V & V_NARROW) != 0>::U, 16>>(), IC<true>(), IC<Shape<PH, true, (V & V_NARROW) != 0>::R>());
   }
 }
 
 // Issue the first elements of this wavefront's sequence of phase PH of block l (dense or
 // river), one per slot.
-template <int DT, int PH, bool N>
-__device__ __forceinline__ void prefetch_phase_t(DevRef D, int l, bool river, Pre<DT, N> &g) {
+template <int DT, int PH, int V>
+__device__ __forceinline__ void prefetch_phase_t(DevRef D, int l, bool river, Pre<DT, V> &g) {
   LayerRef Lw = layer_of(D, l);
-  with_format<DT, PH, N>(D, river, [&](auto ftag, auto rv, auto rr) {
+  with_format<DT, PH, V>(D, river, [&](auto ftag, auto rv, auto rr) {
     typedef typename decltype(ftag)::type F;
     constexpr bool RV = decltype(rv)::value;
     constexpr int R = decltype(rr)::value;
@@ -1039,8 +1048,8 @@ __device__ __forceinline__ void prefetch_phase_t(DevRef D, int l, bool river, Pr
     }
   });
 }
-template <int DT, bool N>
-__device__ __forceinline__ void prefetch_phase(DevRef D, int l, int ph, bool river, Pre<DT, N> &g) {
+template <int DT, int V>
+__device__ __forceinline__ void prefetch_phase(DevRef D, int l, int ph, bool river, Pre<DT, V> &g) {
   switch (ph) {
     case PH_QKV: prefetch_phase_t<DT, PH_QKV>(D, l, river, g); break;
     case PH_O: prefetch_phase_t<DT, PH_O>(D, l, river, g); break;
@@ -1052,11 +1061,11 @@ __device__ __forceinline__ void prefetch_phase(DevRef D, int l, int ph, bool riv
 // Run phase PH of block l over the staged vector.  epi(n0, acc) is called once per task with
 // its first linear row n0 and the R finished dot products (lane-uniform); rows >= the row
 // count of the phase (a ragged last task) must be ignored by it.
-template <int DT, int PH, bool N, class Epi>
+template <int DT, int PH, int V, class Epi>
 __device__ __forceinline__ void run_phase(DevRef D, int l, bool river, const float *xl,
-                                          Pre<DT, N> &pre, Epi epi) {
+                                          Pre<DT, V> &pre, Epi epi) {
   LayerRef Lw = layer_of(D, l);
-  with_format<DT, PH, N>(D, river, [&](auto ftag, auto rv, auto rr) {
+  with_format<DT, PH, V>(D, river, [&](auto ftag, auto rv, auto rr) {
     typedef typename decltype(ftag)::type F;
     constexpr bool RV = decltype(rv)::value;
     constexpr int R = decltype(rr)::value;
@@ -1112,11 +1121,11 @@ __device__ __forceinline__ float4 similarity_part(DevRef D, int i) {
 // The norm in front of a phase together with the similarity of the block behind it (want_s): one
 // round trip and one reduction for both, instead of one after the other.  Returns s; the vector
 // is in registers, for in.put.  Every workgroup computes the same values in the same order.
-template <int DT>
+template <int DT, bool ANY = false>
 __device__ __forceinline__ float norm_and_similarity(DevRef D, bool want_s, const float *h, const void *gain,
                                                      NormIn<DT> &in, float &r, float *red) {
   const float4 p = want_s ? similarity_part(D, threadIdx.x) : make_float4(0.f, 0.f, 0.f, 0.f);
-  const float ss = in.fetch(h, gain, D.d);
+  const float ss = in.template fetch<ANY>(h, gain, D.d);
   float s = 0.f, tot;
   if (want_s) {
     float p4[4] = {p.x, p.y, p.z, ss};
@@ -1176,14 +1185,14 @@ __device__ __forceinline__ bool guess_river_after(const StepArgs &A, const Ctl &
 // three per wavefront at the 8B shape.
 // `guess` is the format whose first elements pre holds; the exit test of the block before is taken
 // here (ctl), and where it turns out otherwise they are fetched again in the right one.
-template <int DT, bool N>
-__device__ __forceinline__ void phase_qkv(DevRef D, const StepArgs &A, int l, bool guess, Ctl &ctl, float *lds, Pre<DT, N> &pre) {
+template <int DT, int V>
+__device__ __forceinline__ void phase_qkv(DevRef D, const StepArgs &A, int l, bool guess, Ctl &ctl, float *lds, Pre<DT, V> &pre) {
   RIVER_MARK(D, 16);
   LayerRef Lw = layer_of(D, l);
   if (l == 0) {
     int tok = A.token >= 0 ? A.token : D.st->cur_token;
     tok = min(max(tok, 0), D.vocab - 1);       // a NaN-poisoned argmax must not index out of range
-    stage_norm_embed<DT>(D, tok, Lw.attn_norm, run_log2<DT>(ctl.river, D.d), lds, lds_half(D, lds), lds_red(D, lds));
+    stage_norm_embed<DT>(D, tok, Lw.attn_norm, run_log2<DT, V>(ctl.river, D.d), lds, lds_half(D, lds), lds_red(D, lds));
   } else {
     const float *h = D.hidden + (size_t)l * D.d;
     NormIn<DT> in;
@@ -1191,7 +1200,7 @@ __device__ __forceinline__ void phase_qkv(DevRef D, const StepArgs &A, int l, bo
     const float s = norm_and_similarity<DT>(D, exit_by_similarity(A, ctl), h, Lw.attn_norm, in, r, lds_red(D, lds));
     exit_test(D, A, l, s, ctl);
     if (ctl.river != guess) prefetch_phase<DT>(D, l, PH_QKV, ctl.river, pre);
-    in.put(h, Lw.attn_norm, D.d, r, run_log2<DT>(ctl.river, D.d), lds, lds_half(D, lds));
+    in.put(h, Lw.attn_norm, D.d, r, run_log2<DT, V>(ctl.river, D.d), lds, lds_half(D, lds));
     lds_barrier();
   }
   const bool river = ctl.river;
@@ -1207,7 +1216,7 @@ __device__ __forceinline__ void phase_qkv(DevRef D, const StepArgs &A, int l, bo
       else pub(D.kvcur + (n - qd), v);          // [k (kvd); v (kvd)]
     }
   };
-  run_phase<DT, PH_QKV>(D, l, river, x_area(D, lds, run_log2<DT>(river, D.d)), pre, epi);
+  run_phase<DT, PH_QKV>(D, l, river, x_area(D, lds, run_log2<DT, V>(river, D.d)), pre, epi);
   RIVER_MARK(D, 18);
 }
 
@@ -1610,7 +1619,7 @@ __device__ __forceinline__ void attn_items(DevRef D, const StepArgs &A, int l, f
 // phase mode arrive and wait do nothing): what can be fetched ahead is issued between
 // arriving and waiting.  Register arrays are sized by the elements per lane (head_dim 64
 // or 128).
-template <int DT, bool F16, class Arrive, class Wait>
+template <int DT, bool F16, int HD, class Arrive, class Wait>   // HD: 64, 128 or 0 (either)
 __device__ __forceinline__ void phase_attn(DevRef D, const StepArgs &A, int l, const Ctl &ctl, float *lds,
                                            Arrive arrive, Wait wait) {
   const int lane = fresh_lane();
@@ -1623,14 +1632,18 @@ __device__ __forceinline__ void phase_attn(DevRef D, const StepArgs &A, int l, c
     wait();
     attn_items<DT, EL, F16>(D, A, l, lds, lane, c);
   };
-  if (D.hd == 128) run(IC<8>()); else run(IC<4>());
+  if constexpr (HD == 0) {
+    if (D.hd == 128) run(IC<8>()); else run(IC<4>());
+  } else {
+    run(IC<HD / 16>());
+  }
 }
 
 // a4: h1 = h + W_o o
-template <int DT, bool N>
-__device__ __forceinline__ void phase_oproj(DevRef D, const StepArgs &A, int l, bool river, float *lds, Pre<DT, N> &pre) {
+template <int DT, int V>
+__device__ __forceinline__ void phase_oproj(DevRef D, const StepArgs &A, int l, bool river, float *lds, Pre<DT, V> &pre) {
   RIVER_MARK(D, 20);
-  const int lp = run_log2<DT>(river, D.nq * D.hd);
+  const int lp = run_log2<DT, V>(river, D.nq * D.hd);
   stage_attn_out(D, A, lp, lds, lds_half(D, lds));
   RIVER_MARK(D, 21);
   const float *hin = D.hidden + (size_t)l * D.d;
@@ -1650,10 +1663,10 @@ __device__ __forceinline__ void phase_oproj(DevRef D, const StepArgs &A, int l, 
 }
 
 // a5: y = RMSNorm(h1) * g2; a = silu(W_g y) * (W_u y); rows come as (gate i, up i) pairs
-template <int DT, bool N>
-__device__ __forceinline__ void phase_gateup(DevRef D, const StepArgs &A, int l, bool river, float *lds, Pre<DT, N> &pre) {
+template <int DT, int V>
+__device__ __forceinline__ void phase_gateup(DevRef D, const StepArgs &A, int l, bool river, float *lds, Pre<DT, V> &pre) {
   RIVER_MARK(D, 24);
-  const int lp = run_log2<DT>(river, D.d);
+  const int lp = run_log2<DT, V>(river, D.d);
   stage_norm<DT>(D.h1, layer_of(D, l).ffn_norm, D.d, D.eps, lp, lds, lds_half(D, lds), lds_red(D, lds));
   RIVER_MARK(D, 25);
   const int lane = pre.lane;
@@ -1674,10 +1687,10 @@ __device__ __forceinline__ void phase_gateup(DevRef D, const StepArgs &A, int l,
 // Eq. 1's similarity <h,h2>, <h,h>, <h2,h2> reduced over this workgroup's rows.  The
 // reduction over workgroups and the exit decision are taken by every workgroup at the
 // start of the next block (exit_test), so no workgroup waits for another here.
-template <int DT, bool N>
-__device__ __forceinline__ void phase_down(DevRef D, const StepArgs &A, int l, bool river, float *lds, Pre<DT, N> &pre) {
+template <int DT, int V>
+__device__ __forceinline__ void phase_down(DevRef D, const StepArgs &A, int l, bool river, float *lds, Pre<DT, V> &pre) {
   RIVER_MARK(D, 28);
-  const int lp = run_log2<DT>(river, D.ffn);
+  const int lp = run_log2<DT, V>(river, D.ffn);
   if (lp < 0) stage_copy_half(D.abuf, D.ffn, lds_half(D, lds));
   else stage_copy(D.abuf, D.ffn, lp, lds);
   RIVER_MARK(D, 29);
@@ -1723,22 +1736,22 @@ __device__ __forceinline__ void head_rows(DevRef D, int t, Rows<kRD> &rw) {
     rw.sz[r] = nullptr;
   }
 }
-template <int DT, bool N>
-__device__ __forceinline__ void prefetch_head(DevRef D, Pre<DT, N> &g) {
+template <int DT, int V>
+__device__ __forceinline__ void prefetch_head(DevRef D, Pre<DT, V> &g) {
   auto rows_of = [&](int t, Rows<kRD> &rw) { head_rows<DT>(D, t, rw); };
   const int n = (D.vocab + kRD - 1) / kRD;
   issue_first<Dense<DT, kRD, kUD>, DT, kRD>(n, D.d, D.group, g, rows_of);
 }
-template <int DT, bool N>
-__device__ __forceinline__ void phase_head(DevRef D, const StepArgs &A, const Ctl &ctl, float *lds, Pre<DT, N> &pre) {
+template <int DT, int V>
+__device__ __forceinline__ void phase_head(DevRef D, const StepArgs &A, const Ctl &ctl, float *lds, Pre<DT, V> &pre) {
   float *red = lds_red(D, lds);
   const float *h = D.hidden + (size_t)D.L * D.d;
   const bool rec_s = !ctl.river && A.rec_slot >= 0;       // similarity of the last backbone block: recorded, never tested
   NormIn<DT> in;
   float r;
-  const float s = norm_and_similarity<DT>(D, rec_s, h, D.final_norm, in, r, red);
+  const float s = norm_and_similarity<DT, true>(D, rec_s, h, D.final_norm, in, r, red);
   if (rec_s && blockIdx.x == 0 && threadIdx.x == 0) pub(rec_sims(D, A) + (D.L - 1), s);
-  in.put(h, D.final_norm, D.d, r, run_log2<DT>(false, D.d), lds, lds_half(D, lds));
+  in.template put<true>(h, D.final_norm, D.d, r, run_log2<DT, V>(false, D.d), lds, lds_half(D, lds));
   lds_barrier();
   const int lane = pre.lane;
   float best = -INFINITY;
