@@ -15,7 +15,8 @@
  *    caller (for example through torch) and handed over.  The one exception:
  *    the first river_create on a device allocates 256 KiB of uncached device
  *    memory for the counters of the device-wide barrier (4 KiB per live
- *    context, at most 64 contexts per device); it is kept until the process
+ *    context, at most 64 contexts per device), and 1.2 MB of pinned host memory that
+ *    synchronous calls return their results through; both are kept until the process
  *    ends.  The context borrows weights and workspace: they must outlive it.
  *  - All calls return RIVER_OK (0) or a negative RIVER_E* code, never throw and
  *    never abort.  river_last_error() gives a text for the last failure.
@@ -78,8 +79,10 @@ typedef struct {
   int32_t spin_limit;     /* PERSISTENT: polls before a barrier wait gives up (0 = default) */
   int32_t prefill_gemm_min_tokens; /* prompts of at least this many tokens are prefilled with MFMA GEMMs
                                       (RIVER_BF16, d_model, d_ffn and river_group multiples of 64); shorter
-                                      ones, and all other configurations, run the decode kernels per prompt
-                                      position.  0 = default (32); negative = never */
+                                      ones keep the decode kernels' precision (models with blocks of 64 MB and
+                                      more: passes of 32 positions from 3 tokens on; others, and all other
+                                      configurations: one prompt position after the other).  0 = default (32);
+                                      negative = never a GEMM */
   int32_t batch_exit_rule; /* batched contexts, when Eq. 1 decides: 0 = every sequence for itself
                               (s_b > tau); 1 = Eq. 1 as printed: the whole batch leaves the backbone together at
                               the first block with min over the batch of s_b > tau */

@@ -949,6 +949,8 @@ static int create_impl(const river_config *cfg, const river_weights *w, const ri
           {(const void *)pf::k_pf_gemm<pf::TileM, false, pf::PF_SWIGLU>, pf::TileM::LDS_BYTES},
           {(const void *)pf::k_pf_gemm<pf::TileM, true, pf::PF_STORE>, pf::TileM::LDS_BYTES},
           {(const void *)pf::k_pf_gemm<pf::TileM, true, pf::PF_SWIGLU>, pf::TileM::LDS_BYTES},
+          {(const void *)pf::k_pf_gemm<pf::TileM, false, pf::PF_STORE, true>, pf::TileM::LDS_BYTES},
+          {(const void *)pf::k_pf_gemm<pf::TileM, true, pf::PF_STORE, true>, pf::TileM::LDS_BYTES},
           {(const void *)pf::k_pf_gemm<pf::TileN, false, pf::PF_STORE>, pf::TileN::LDS_BYTES},
           {(const void *)pf::k_pf_gemm<pf::TileN, false, pf::PF_SWIGLU>, pf::TileN::LDS_BYTES},
           {(const void *)pf::k_pf_gemm<pf::TileN, true, pf::PF_STORE>, pf::TileN::LDS_BYTES},
@@ -1082,11 +1084,11 @@ constexpr PfTile kPfTiles[3] = {{pf::TileM::TM, pf::TileM::TN, 0.5, 0.67},
                                 {pf::TileN::TM, pf::TileN::TN, 0.85, 1.15},
                                 {pf::TileL::TM, pf::TileL::TN, 1.4, 2.05}};
 struct PfPlan { int tile, split; };
-static PfPlan pf_plan(const river_ctx *x, int N, int K, int m, bool may_split) {
+static PfPlan pf_plan(const river_ctx *x, int N, int K, int m, bool may_split, int tiles_used = 3) {
   PfPlan best{0, 1};
   double best_us = 1e30;
   const int nk = K / pf::TK, cus = x->grid_persist;
-  for (int i = 0; i < 3; ++i) {
+  for (int i = 0; i < tiles_used; ++i) {
     const PfTile &t = kPfTiles[i];
     const long long tiles = (long long)((N + t.tn - 1) / t.tn) * ((m + t.tm - 1) / t.tm);
     for (int sp = 1; sp <= (may_split ? 16 : 1); ++sp) {
@@ -1102,26 +1104,31 @@ static PfPlan pf_plan(const river_ctx *x, int N, int K, int m, bool may_split) {
 
 // GEMM of the prefill over the stacked matrices ms[0..nm) of block l: fp32 planes of partial sums in
 // C (returns how many), or with EPI = PF_SWIGLU the fp16 activation of the down projection.
-template <class T, bool W4, int EPI>
+template <class T, bool W4, int EPI, bool EXACT = false>
 static void launch_gemm_t(river_ctx *x, const pf::GemmB &B, int N, const _Float16 *A, int K, void *C, int ldc, int m, int split) {
   const int n_tiles = (N + T::TN - 1) / T::TN, m_tiles = (m + T::TM - 1) / T::TM;
   const dim3 grid((n_tiles * split + 7) / 8 * 8 * m_tiles);      // (see the kernel's workgroup -> tile mapping)
-  pf::k_pf_gemm<T, W4, EPI><<<grid, dim3(T::NT), T::LDS_BYTES, x->stream>>>(A, K, B, N, K, x->cfg.river_group, C, ldc, m,
+  pf::k_pf_gemm<T, W4, EPI, EXACT><<<grid, dim3(T::NT), T::LDS_BYTES, x->stream>>>(A, K, B, N, K, x->cfg.river_group, C, ldc, m,
                                                                            m_tiles, split);
 }
-template <int EPI>
-static int launch_gemm(river_ctx *x, int l, bool w4, const int *ms, int nm, const _Float16 *A, int K, void *C, int m) {
-  pf::GemmB B{};
+// the stacked matrices ms[0..nm) of block l; returns their rows
+static int gemm_operand(const river_ctx *x, int l, bool w4, const int *ms, int nm, pf::GemmB *B) {
   int N = 0;
   for (int i = 0; i < nm; ++i) {
     long long r, c;
     matrix_shape(&x->cfg, ms[i], &r, &c);
-    B.w[i] = w4 ? (const void *)x->layers_h[l].qc[ms[i]] : x->layers_h[l].w[ms[i]];
-    B.sz[i] = x->layers_h[l].qsz[ms[i]];
-    B.rows[i] = (int)r;
+    B->w[i] = w4 ? (const void *)x->layers_h[l].qc[ms[i]] : x->layers_h[l].w[ms[i]];
+    B->sz[i] = x->layers_h[l].qsz[ms[i]];
+    B->rows[i] = (int)r;
     N += (int)r;
   }
-  for (int i = nm; i < 3; ++i) { B.w[i] = B.w[0]; B.sz[i] = B.sz[0]; B.rows[i] = 0; }
+  for (int i = nm; i < 3; ++i) { B->w[i] = B->w[0]; B->sz[i] = B->sz[0]; B->rows[i] = 0; }
+  return N;
+}
+template <int EPI>
+static int launch_gemm(river_ctx *x, int l, bool w4, const int *ms, int nm, const _Float16 *A, int K, void *C, int m) {
+  pf::GemmB B{};
+  const int N = gemm_operand(x, l, w4, ms, nm, &B);
   const PfPlan p = pf_plan(x, N, K, m, EPI == pf::PF_STORE);
   const int ldc = EPI == pf::PF_SWIGLU ? B.rows[0] : N;
   auto launch = [&](auto tile) {
@@ -1133,6 +1140,95 @@ static int launch_gemm(river_ctx *x, int l, bool w4, const int *ms, int nm, cons
   else if (p.tile == 1) launch(pf::TileN{});
   else launch(pf::TileL{});
   return p.split;
+}
+
+// GEMM of a pass over a short prompt (EXACT, see pf::k_pf_gemm): planes of kShort rows in C; returns how many.
+static int launch_gemm_exact(river_ctx *x, int l, bool w4, const int *ms, int nm, const _Float16 *A, int K, float *C) {
+  pf::GemmB B{};
+  const int N = gemm_operand(x, l, w4, ms, nm, &B), M = w4 ? pf::kShort : 3 * pf::kShort;
+  const int split = pf_plan(x, N, w4 ? 2 * K : K, M, true, 1).split;
+  if (w4) launch_gemm_t<pf::TileM, true, pf::PF_STORE, true>(x, B, N, A, K, C, N, M, split);
+  else launch_gemm_t<pf::TileM, false, pf::PF_STORE, true>(x, B, N, A, K, C, N, M, split);
+  return split * (w4 ? 1 : 3);
+}
+
+// Original final norm + LM head + argmax on the last prompt position, whose h(L) is in Dev::hidden (the decode
+// path's kernel), and the call's results on the host.
+static void launch_prefill_head(river_ctx *x, int n, int ep) {
+  StepArgs A{};
+  A.pos = n - 1; A.token = -1; A.forced_e = ep; A.want_head = 1; A.rec_slot = -1; A.n_splits = 1; A.bar_base = 0;
+  A.host_row = x->host ? x->host->rec : nullptr;
+  k_head<1><<<dim3(x->grid_gemv), dim3(x->block), x->lds_bytes, x->stream>>>(x->dev_d, A);
+}
+
+// Short prompts (see river_prefill.h): passes of up to kShort positions, from kShortMin positions on (a position
+// through the decode kernels costs one stream of the weights, a pass two to three), for models with
+// blocks of at least kShortBlockBytes.  Smaller ones would gain as well (a 23 MB block 26 us per position, 50 per
+// pass), but their prompts have always agreed bit for bit with those of contexts that never use GEMMs
+// (prefill_gemm_min_tokens < 0), and callers compare the two; at these sizes that costs a prompt 2 ms at most.
+constexpr int kShortMin = 3;
+constexpr size_t kShortBlockBytes = (size_t)64 << 20;
+static bool prefill_short_ok(const river_ctx *x, int n) {
+  const river_config &c = x->cfg;
+  if (x->lay.pf_rows == 0 || n < kShortMin) return false;
+  size_t block = 0;
+  for (int m = 0; m < 7; ++m) {
+    long long r, k;
+    matrix_shape(&c, m, &r, &k);
+    block += (size_t)(r * k) * 2;
+  }
+  // (the gate/up GEMM's planes are the largest: three of kShort rows)
+  return block >= kShortBlockBytes && (size_t)3 * pf::kShort * 2 * c.d_ffn * 4 <= x->lay.pf_big_bytes;
+}
+static int prefill_short(river_ctx *x, const int32_t *tokens, int n, int ep) {
+  const river_config &c = x->cfg;
+  const Dev &D = x->dev;
+  const Layout &y = x->lay;
+  hipStream_t s = x->stream;
+  const int L = c.n_layers, d = c.d_model, qd = c.n_q_heads * c.head_dim, ffn = c.d_ffn;
+  int *tok = (int *)(x->ws + y.pf_tok);
+  float *h = (float *)(x->ws + y.pf_h), *big = (float *)(x->ws + y.pf_big);
+  _Float16 *x16 = (_Float16 *)(x->ws + y.pf_x16), *q32 = (_Float16 *)(x->ws + y.pf_q16), *a16 = (_Float16 *)(x->ws + y.pf_a16);
+  const int m_qkv[3] = {M_WQ, M_WK, M_WV}, m_o[1] = {M_WO}, m_gu[2] = {M_GATE, M_UP}, m_d[1] = {M_DOWN};
+  const dim3 blk(512);
+  auto attn = c.head_dim == 128 ? pf::k_pf_attn_rows<128> : pf::k_pf_attn_rows<64>;
+  for (int c0 = 0; c0 < n; c0 += pf::kShort) {
+    const int m = std::min(pf::kShort, n - c0), last = c0 + m == n ? m - 1 : -1;
+    const int *tok_src = tok;
+    if (x->host && n <= kHostTok) {
+      std::memcpy(x->host->tok + c0, tokens + c0, (size_t)m * 4);
+      tok_src = x->host->tok + c0;
+    } else {
+      HIP_TRY(x, hipMemcpyAsync(tok, tokens + c0, (size_t)m * 4, hipMemcpyHostToDevice, s));
+    }
+    int parts = 0;
+    auto norm = [&](bool river, const int *tk, const void *gain, float *row_out, int row) {
+      (river ? pf::k_pf_norm<false> : pf::k_pf_norm<true>)<<<dim3(m), blk, 0, s>>>(
+          h, tk, D.tok_emb, big, parts, pf::kShort, gain, d, c.rms_eps, gain ? x16 : nullptr, row_out, row, 0);
+    };
+    for (int l = 0; l < L; ++l) {
+      const bool river = l >= ep;
+      const DevLayer &W = x->layers_h[l];
+      norm(river, l ? nullptr : tok_src, W.attn_norm, D.hidden + (size_t)l * d, last);
+      parts = launch_gemm_exact(x, l, river, m_qkv, 3, x16, d, big);
+      pf::k_pf_rope_store<true><<<dim3(m), blk, 0, s>>>(big, parts, pf::kShort, D.rope, c.n_q_heads, c.n_kv_heads, c.head_dim, c0, l,
+                                                        c.max_seq, D.kcache, D.vcache, D.kv_f16, q32);
+      if (l == L - 1 && last < 0) break;                     // (a pass before the last: its keys and values are all that is read)
+      attn<<<dim3((c.n_q_heads + 3) / 4, m), dim3(256), 0, s>>>((const float *)q32, D.kcache, D.vcache, D.kv_f16, c.n_q_heads,
+                                                                 c.n_kv_heads, l, c.max_seq, c0, !river, x16);
+      parts = launch_gemm_exact(x, l, river, m_o, 1, x16, qd, big);
+      norm(river, nullptr, W.ffn_norm, nullptr, -1);
+      parts = launch_gemm_exact(x, l, river, m_gu, 2, x16, d, big);
+      pf::k_pf_swiglu_rows<<<dim3((ffn + 2047) / 2048, m), dim3(256), 0, s>>>(big, parts, ffn, !river, a16);
+      parts = launch_gemm_exact(x, l, river, m_d, 1, a16, ffn, big);
+    }
+    if (last >= 0) norm(true, nullptr, nullptr, D.hidden + (size_t)L * d, last);
+    HIP_TRY(x, hipGetLastError());
+  }
+  launch_prefill_head(x, n, ep);
+  HIP_TRY(x, hipGetLastError());
+  x->pos = n;
+  return RIVER_OK;
 }
 
 // Prefill phase on the matrix cores: the prompt in equal chunks of up to pf_rows tokens, every block
@@ -1165,10 +1261,10 @@ static int prefill_gemm(river_ctx *x, int seq, const int32_t *tokens, int n, int
     for (int l = 0; l < L; ++l) {
       const bool river = l >= ep;
       const DevLayer &W = x->layers_h[l];
-      pf::k_pf_norm<<<dim3(m), rowwise, 0, s>>>(h, l ? nullptr : tok_src, D.tok_emb, big, parts, W.attn_norm, d, c.rms_eps, x16,
+      pf::k_pf_norm<false><<<dim3(m), rowwise, 0, s>>>(h, l ? nullptr : tok_src, D.tok_emb, big, parts, m, W.attn_norm, d, c.rms_eps, x16,
                                                 D.hidden + (size_t)l * d, last, 0);
       parts = launch_gemm<pf::PF_STORE>(x, l, river, m_qkv, 3, x16, d, big, m);
-      pf::k_pf_rope_store<<<dim3(m), rowwise, 0, s>>>(big, parts, m, D.rope, c.n_q_heads, c.n_kv_heads, c.head_dim, c0, l,
+      pf::k_pf_rope_store<false><<<dim3(m), rowwise, 0, s>>>(big, parts, m, D.rope, c.n_q_heads, c.n_kv_heads, c.head_dim, c0, l,
                                                       c.max_seq, kc, vc, D.kv_f16, q16);
       // Behind the last block's keys and values only the last prompt position goes on (its h(L) is the
       // head's input, nobody reads the others'): from there on the last block is one row of the last
@@ -1185,23 +1281,19 @@ static int prefill_gemm(river_ctx *x, int seq, const int32_t *tokens, int n, int
       attn<<<dim3(c.n_q_heads / hg, (m - qt0 + qt - 1) / qt), dim3(512), 0, s>>>(q16, kc, vc, D.kv_f16, c.n_q_heads, c.n_kv_heads,
                                                                                  l, c.max_seq, c0, m, qt0, x16);
       parts = launch_gemm<pf::PF_STORE>(x, l, river, m_o, 1, x16 + (size_t)t0 * qd, qd, big, rows);
-      pf::k_pf_norm<<<dim3(rows), rowwise, 0, s>>>(h, nullptr, nullptr, big, parts, W.ffn_norm, d, c.rms_eps, x16, nullptr, -1, t0);
+      pf::k_pf_norm<false><<<dim3(rows), rowwise, 0, s>>>(h, nullptr, nullptr, big, parts, rows, W.ffn_norm, d, c.rms_eps, x16, nullptr, -1, t0);
       (void)launch_gemm<pf::PF_SWIGLU>(x, l, river, m_gu, 2, x16 + (size_t)t0 * d, d, a16, rows);
       parts = launch_gemm<pf::PF_STORE>(x, l, river, m_d, 1, a16, ffn, big, rows);
     }
     // h(L) of the last prompt position, the head's input
     if (last >= 0) {
       const int t0 = m > pf::TileM::TM ? last : 0;
-      pf::k_pf_norm<<<dim3(last + 1 - t0), dim3(512), 0, s>>>(h, nullptr, nullptr, big, parts, nullptr, d, c.rms_eps, nullptr,
+      pf::k_pf_norm<false><<<dim3(last + 1 - t0), dim3(512), 0, s>>>(h, nullptr, nullptr, big, parts, last + 1 - t0, nullptr, d, c.rms_eps, nullptr,
                                                               D.hidden + (size_t)L * d, last, t0);
     }
     HIP_TRY(x, hipGetLastError());
   }
-  // the original final norm + LM head + argmax on the last prompt position (the decode path's kernel)
-  StepArgs A{};
-  A.pos = n - 1; A.token = -1; A.forced_e = ep; A.want_head = 1; A.rec_slot = -1; A.n_splits = 1; A.bar_base = 0;
-  A.host_row = x->host ? x->host->rec : nullptr;
-  k_head<1><<<dim3(x->grid_gemv), dim3(x->block), x->lds_bytes, s>>>(x->dev_d, A);
+  launch_prefill_head(x, n, ep);
   if (c.max_batch > 1)
     bd::k_bd_after_prefill<<<dim3(1), dim3(64), 0, s>>>(x->st_b, seq, &D.st->cur_token);
   HIP_TRY(x, hipGetLastError());
@@ -1237,8 +1329,11 @@ extern "C" int river_prefill(river_ctx *x, int32_t seq, const int32_t *tokens, i
   if (x->lay.pf_rows > 0 && (n_tokens >= min_gemm || x->cfg.max_batch > 1)) {
     rc = prefill_gemm(x, seq, tokens, n_tokens, ep);
     if (rc) return rc;
+  } else if (prefill_short_ok(x, n_tokens)) {
+    rc = prefill_short(x, tokens, n_tokens, ep);
+    if (rc) return rc;
   } else {
-    // short prompts, fp32 models and shapes the GEMM path does not take: the decode kernels,
+    // one or two tokens, fp32 models and shapes the GEMM path does not take: the decode kernels,
     // one prompt position after the other
     for (int i = 0; i < n_tokens; ++i) {
       rc = enqueue(x, tokens[i], ep, i == n_tokens - 1, -1, i == n_tokens - 1);

@@ -39,6 +39,10 @@ constexpr int LDK = TK + 8;           // LDS row stride in halfs: 144 B, rows 4 
 __device__ __forceinline__ f32x16 mfma16(half8 a, half8 b, f32x16 c) {
   return __builtin_amdgcn_mfma_f32_32x32x16_f16(a, b, c, 0, 0, 0);
 }
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+__device__ __forceinline__ f32x16 mfma16_bf16(half8 a, half8 b, f32x16 c) {     // (the registers hold bf16 values)
+  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
+}
 __device__ __forceinline__ int c_row(int r, int lane) { return (r >> 2) * 8 + (lane >> 5) * 4 + (r & 3); }
 
 __device__ __forceinline__ float bf16_lo(uint32_t w) { return __uint_as_float(w << 16); }
@@ -66,6 +70,44 @@ __device__ __forceinline__ half8 dequant8(uint32_t w, float s, float zero) {
     h[k + 4] = (_Float16)(fmaf((float)q[1], 0x1p18f, -zero) * s);
   }
   return h;
+}
+
+// The same weights as a sum of two fp16 numbers (22 bits): the first, or (low) what it leaves.
+__device__ __forceinline__ half8 dequant8_part(uint32_t w, float s, float zero, bool low) {
+  half8 h;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    const uint32_t sh = k < 2 ? w << (6 - 4 * k) : w >> (4 * k - 6);
+    const half2v q = __builtin_bit_cast(half2v, sh & 0x03c003c0u);
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+      const float t = fmaf((float)q[e], 0x1p18f, -zero) * s;
+      const _Float16 hi = (_Float16)t;
+      h[k + 4 * e] = low ? (_Float16)(t - (float)hi) : hi;
+    }
+  }
+  return h;
+}
+// x as a sum of three bf16 numbers (24 bits, exact but for what lies below the smallest of them)
+__device__ __forceinline__ void split3(float x, uint16_t (&p)[3]) {
+#pragma unroll
+  for (int i = 0; i < 3; ++i) {
+    p[i] = Store<1>::rne(x);
+    x -= __uint_as_float((uint32_t)p[i] << 16);
+  }
+}
+__device__ __forceinline__ void store_split3(uint16_t *dst, size_t plane, const float (&x)[8]) {
+  uint32_t w[3][4];
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    uint16_t a[3], b[3];
+    split3(x[2 * e], a);
+    split3(x[2 * e + 1], b);
+#pragma unroll
+    for (int i = 0; i < 3; ++i) w[i][e] = a[i] | (uint32_t)b[i] << 16;
+  }
+#pragma unroll
+  for (int i = 0; i < 3; ++i) *(uint4 *)(dst + i * plane) = make_uint4(w[i][0], w[i][1], w[i][2], w[i][3]);
 }
 
 // A 16-bit KV cache holds bf16 values, or IEEE half values when the context keeps its cache in
@@ -114,6 +156,11 @@ __device__ __forceinline__ void gemm_b_row(const GemmB &B, int n, int N, int &ma
 // because it is converted on the way (bf16 -> fp16, codes -> fp16); one conversion serves all
 // wavefronts of the tile.
 //
+// EXACT (short prompts, whose activations stay in 32 bits): dense -- A holds bf16 rows, the three parts of the
+// activations one under the other (see split3), multiplied with the bf16 weights as they are, every product exact; codes
+// -- A holds fp16 rows, as the decode kernels round them, and every K tile comes twice, with the first and
+// with the second fp16 part of the weights.
+//
 // Tile of C per workgroup (TM x TN), its WM x WN wavefronts, K tiles in flight in registers (PF) and
 // workgroups per CU (OCC, bounds the registers).
 template <int TM_, int TN_, int WM_, int WN_, int PF_, int OCC_> struct GemmTile {
@@ -150,7 +197,7 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t gemm_rsrc(const void *p) {
   return __builtin_amdgcn_make_buffer_rsrc((void *)p, 0, 0x7ffffff0, 0x00020000);
 }
 
-template <class T, bool W4, int EPI>
+template <class T, bool W4, int EPI, bool EXACT = false>
 __global__ __launch_bounds__(T::NT, T::OCC) void k_pf_gemm(const _Float16 *__restrict__ A, int lda, GemmB B, int N,
                                                            int K, int group, void *C, int ldc, int M, int m_tiles,
                                                            int k_split) {
@@ -167,7 +214,8 @@ __global__ __launch_bounds__(T::NT, T::OCC) void k_pf_gemm(const _Float16 *__res
   if (col >= n_tiles * k_split) return;
   const int n_tile = col / k_split, ks_i = col % k_split;
   const int m0 = m_tile * TM;
-  const int nk_all = K / TK, kt0 = (int)((long long)nk_all * ks_i / k_split);
+  constexpr bool TWICE = EXACT && W4;
+  const int nk_all = K / TK * (TWICE ? 2 : 1), kt0 = (int)((long long)nk_all * ks_i / k_split);
   const int nk = (int)((long long)nk_all * (ks_i + 1) / k_split) - kt0;
 
   // what this thread stages per K tile: a 16-byte segment of A per round; of B one per round (dense)
@@ -177,7 +225,7 @@ __global__ __launch_bounds__(T::NT, T::OCC) void k_pf_gemm(const _Float16 *__res
   unsigned a_off[RA];
 #pragma unroll
   for (int i = 0; i < RA; ++i) a_off[i] = (unsigned)min(m0 + i * GR + srow, M - 1) * (unsigned)lda * 2u + sk * 16u;
-  const __amdgpu_buffer_rsrc_t a_rsrc = gemm_rsrc((const char *)A + (size_t)kt0 * TK * 2);
+  const __amdgpu_buffer_rsrc_t a_rsrc = gemm_rsrc((const char *)A + (TWICE ? 0 : (size_t)kt0 * TK * 2));
   const int s_dst = srow * LDK + sk * 8;                       // + i * GR * LDK
   __amdgpu_buffer_rsrc_t b_rsrc[W4 ? 1 : RB];
   unsigned b_off = 0;
@@ -188,7 +236,7 @@ __global__ __launch_bounds__(T::NT, T::OCC) void k_pf_gemm(const _Float16 *__res
     int mat, row;
     gemm_b_row8<T, EPI>(B, n_tile, row_l & ~7, N, mat, row);
     row += row_l & 7;
-    b_src = (const char *)B.w[mat] + (size_t)row * (K >> 1) + q * RB * 4 + kt0 * (TK / 2);
+    b_src = (const char *)B.w[mat] + (size_t)row * (K >> 1) + q * RB * 4 + (TWICE ? 0 : kt0 * (TK / 2));
     b_sz = (const char *)B.sz[mat] + (size_t)row * ((K + group - 1) / group) * 4;   // (the last group may be shorter)
     b_dst = row_l * LDK + q * RB * 8;
   } else {
@@ -208,6 +256,10 @@ __global__ __launch_bounds__(T::NT, T::OCC) void k_pf_gemm(const _Float16 *__res
   const int tiles_per_group = group / TK;
   int g_at = W4 ? kt0 / tiles_per_group : 0, g_left = W4 ? tiles_per_group - kt0 % tiles_per_group : 0;
   auto load_part = [&](int kt, int u, int i) {   // part i of tile kt into set u
+    if constexpr (TWICE) {
+      kt = (kt0 + kt) >> 1;
+      g_at = kt / tiles_per_group; g_left = 2;
+    }
     fa[u][i] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(a_rsrc, a_off[i], kt * (TK * 2), 0));
     if constexpr (W4) {
       if (i == RA - 1) {                          // (all parts of the set have been staged)
@@ -225,16 +277,18 @@ __global__ __launch_bounds__(T::NT, T::OCC) void k_pf_gemm(const _Float16 *__res
       fb[u][i & n] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(b_rsrc[i & n], b_off, kt * (TK * 2), 0));
     }
   };
-  auto stage_part = [&](int u, int i, int buf) {  // part i of set u into LDS buffer buf
+  auto stage_part = [&](int u, int i, int buf, int kt) {  // part i of set u, tile kt, into LDS buffer buf
     _Float16 *const As = pf_lds + buf * TM * LDK, *const Bs = pf_lds + 2 * TM * LDK + buf * TN * LDK;
     *(u32x4 *)(As + s_dst + i * GR * LDK) = fa[u][i];
     if (i >= RB) return;
     if constexpr (W4) {
       const uint32_t w = i == 0 ? fb[u][0].x : i == 1 ? fb[u][0].y : i == 2 ? fb[u][0].z : fb[u][0].w;
-      *(half8 *)(Bs + b_dst + i * 8) = dequant8(w, bf16_lo(fsz[u]), bf16_hi(fsz[u]));
+      *(half8 *)(Bs + b_dst + i * 8) = TWICE ? dequant8_part(w, bf16_lo(fsz[u]), bf16_hi(fsz[u]), (kt0 + kt) & 1)
+                                             : dequant8(w, bf16_lo(fsz[u]), bf16_hi(fsz[u]));
     } else {
       const u32x4 w = fb[u][i & (RB - 1)];
-      *(half8 *)(Bs + s_dst + i * GR * LDK) = bf16x8_to_half8(make_uint4(w.x, w.y, w.z, w.w));
+      if constexpr (EXACT) *(u32x4 *)(Bs + s_dst + i * GR * LDK) = w;
+      else *(half8 *)(Bs + s_dst + i * GR * LDK) = bf16x8_to_half8(make_uint4(w.x, w.y, w.z, w.w));
     }
   };
 
@@ -271,13 +325,14 @@ __global__ __launch_bounds__(T::NT, T::OCC) void k_pf_gemm(const _Float16 *__res
 #pragma unroll
       for (int i = 0; i < RA; ++i) {                           // parts 0, 1 | 2 | 3, or 0 | 1
         if (ks != (RA == 2 ? i : i < 1 ? 0 : i - 1)) continue;
-        if (stage) stage_part(u1, i, cur ^ 1);
+        if (stage) stage_part(u1, i, cur ^ 1, kt + 1);
         if (load) load_part(kt + 1 + PF, u1, i);
       }
 #pragma unroll
       for (int i = 0; i < T::MB; ++i)
 #pragma unroll
-        for (int j = 0; j < T::NB; ++j) acc[i][j] = mfma16(xa[ks & 1][i], xb[ks & 1][j], acc[i][j]);
+        for (int j = 0; j < T::NB; ++j)
+          acc[i][j] = EXACT && !W4 ? mfma16_bf16(xa[ks & 1][i], xb[ks & 1][j], acc[i][j]) : mfma16(xa[ks & 1][i], xb[ks & 1][j], acc[i][j]);
       // the step's conversions, LDS writes and loads go between its MFMAs, not in front of them
 #pragma unroll
       for (int q = 0; q < T::MB * T::NB; ++q) {
@@ -296,7 +351,7 @@ __global__ __launch_bounds__(T::NT, T::OCC) void k_pf_gemm(const _Float16 *__res
       for (int i = 0; i < RA; ++i) load_part(u, u, i);
     }
 #pragma unroll
-  for (int i = 0; i < RA; ++i) stage_part(0, i, 0);
+  for (int i = 0; i < RA; ++i) stage_part(0, i, 0, 0);
   if (PF < nk) {
 #pragma unroll
     for (int i = 0; i < RA; ++i) load_part(PF, 0, i);
@@ -387,12 +442,15 @@ __device__ __forceinline__ void add_planes(const float *p, size_t stride, int n,
 // row_out: the row of the last prompt position (t == row_t) is also kept there, the debug view of
 // h(0..L) and the head's input.  d % 8 == 0, rows 16-byte aligned.  A row of up to 8192 columns is
 // read once and kept in registers between the reduction and the scaling.  256 threads, or 512 for few
-// rows, which then leave CUs idle (the host chooses).
+// rows, which then leave CUs idle (the host chooses).  plane_rows: rows of a plane.  SPLIT (short prompts): the
+// norm is stored as its three bf16 parts, kShort rows below each other (see split3).
 constexpr int kNormKeep = 4;
+constexpr int kShort = 32;             // rows of a pass over a short prompt
+template <bool SPLIT>
 __global__ __launch_bounds__(512) void k_pf_norm(float *__restrict__ h, const int *__restrict__ tokens,
                                                  const void *tok_emb, const float *__restrict__ part, int n_part,
-                                                 const void *gain, int d, float eps, _Float16 *x16, float *row_out,
-                                                 int row_t, int t0) {
+                                                 int plane_rows, const void *gain, int d, float eps, _Float16 *x16,
+                                                 float *row_out, int row_t, int t0) {
   __shared__ float red[16];
   const int t = t0 + blockIdx.x;
   float *const row = h + (size_t)t * d;
@@ -408,7 +466,7 @@ __global__ __launch_bounds__(512) void k_pf_norm(float *__restrict__ h, const in
       for (int e = 0; e < 8; ++e) x.v[e] = Store<1>::ld(tok_emb, emb + k + e);
     } else {
       x = ld_run8(row + k);
-      add_planes(part + (size_t)blockIdx.x * d + k, (size_t)gridDim.x * d, n_part, [&](const float *p, bool ok) {
+      add_planes(part + (size_t)blockIdx.x * d + k, (size_t)plane_rows * d, n_part, [&](const float *p, bool ok) {
         const Run8 q = ld_run8(p);
 #pragma unroll
         for (int e = 0; e < 8; ++e) x.v[e] += ok ? q.v[e] : 0.f;
@@ -431,10 +489,17 @@ __global__ __launch_bounds__(512) void k_pf_norm(float *__restrict__ h, const in
   const float r = 1.0f / sqrtf(block_sum(ss, red) / (float)d + eps);
   auto put = [&](int k, const Run8 &x) {
     const Run8 g = ld_run8_16(gain, k);
+    float v[8];
     half8 o;
 #pragma unroll
-    for (int e = 0; e < 8; ++e) o[e] = (_Float16)(x.v[e] * r * g.v[e]);
-    *(half8 *)(x16 + (size_t)t * d + k) = o;
+    for (int e = 0; e < 8; ++e) v[e] = x.v[e] * r * g.v[e];
+    if constexpr (SPLIT) {
+      store_split3((uint16_t *)x16 + (size_t)t * d + k, (size_t)kShort * d, v);
+    } else {
+#pragma unroll
+      for (int e = 0; e < 8; ++e) o[e] = (_Float16)v[e];
+      *(half8 *)(x16 + (size_t)t * d + k) = o;
+    }
   };
 #pragma unroll
   for (int i = 0; i < kNormKeep; ++i) {
@@ -448,7 +513,8 @@ __global__ __launch_bounds__(512) void k_pf_norm(float *__restrict__ h, const in
 // the attention kernel; k (rotated) and v rounded to the cache dtype and written to slot
 // (l, pos0 + t) of the shared cache.  qkv: n_part fp32 planes [m, qd + 2 kvd] of the QKV GEMM, added
 // in order.  One workgroup per token; a thread handles four rotation pairs (i, i + hd/2) of one head,
-// or four columns of v.
+// or four columns of v.  m: rows of a plane.  Q32: q in fp32 (short prompts).
+template <bool Q32>
 __global__ __launch_bounds__(512) void k_pf_rope_store(const float *__restrict__ qkv, int n_part, int m,
                                                        const float2 *__restrict__ rope, int nq, int nkv, int hd, int pos0,
                                                        int l, int max_seq, void *kcache, void *vcache, int kv_f16,
@@ -481,7 +547,11 @@ __global__ __launch_bounds__(512) void k_pf_rope_store(const float *__restrict__
     const float4 a = get(head * hd + e), b = get(head * hd + e + half);     // q heads, then k heads: contiguous in qkv
     const float lo[4] = {a.x * c01.x - b.x * c01.y, a.y * c01.z - b.y * c01.w, a.z * c23.x - b.z * c23.y, a.w * c23.z - b.w * c23.w};
     const float hi[4] = {a.x * c01.y + b.x * c01.x, a.y * c01.w + b.y * c01.z, a.z * c23.y + b.z * c23.x, a.w * c23.w + b.w * c23.z};
-    if (head < nq) {
+    if (Q32 && head < nq) {
+      float *const q = (float *)q16 + (size_t)t * qd + head * hd + e;
+      *(float4 *)q = make_float4(lo[0] * qs, lo[1] * qs, lo[2] * qs, lo[3] * qs);
+      *(float4 *)(q + half) = make_float4(hi[0] * qs, hi[1] * qs, hi[2] * qs, hi[3] * qs);
+    } else if (head < nq) {
       half4 ql, qh;
 #pragma unroll
       for (int j = 0; j < 4; ++j) { ql[j] = (_Float16)(lo[j] * qs); qh[j] = (_Float16)(hi[j] * qs); }
@@ -669,6 +739,118 @@ __global__ __launch_bounds__(512, 1) void k_pf_attn(const _Float16 *__restrict__
         for (int e = 0; e < 4; ++e) o[e] = (_Float16)(oacc[b][4 * i + e] * inv);
         *(half4 *)(o16 + (size_t)(q0 + r32) * qd + h * HD + b * 32 + c_row(4 * i, lane)) = o;
       }
+  }
+}
+
+// ------------------------------------------------------------- short prompts
+//
+// Prompts below the GEMM prefill's smallest keep the decode kernels' precision: 32-bit activations in backbone
+// blocks, fp16 inputs and exact codes in river blocks, fp32 queries, scores and probabilities.  They
+// went through the decode kernels one position at a time, a stream of all weights each (section of four
+// 8B blocks: 31 tokens 10.5 ms); now up to kShort positions share a pass of the GEMMs above in their
+// EXACT form, with the two kernels below between them (31 tokens: 0.7 ms).
+
+// Causal attention of a few rows over the cache (which holds their own keys and values already): one
+// wavefront per (row, query head), 16 lanes per cached position, four positions at a time, a running
+// softmax (base 2) per lane group.  Bound by latency: a few hundred wavefronts, a few positions each.
+// q32: [m][nq hd] fp32, scaled; out: rows of nq hd, three bf16 parts (split) or fp16.
+template <int HD>
+__global__ __launch_bounds__(256) void k_pf_attn_rows(const float *__restrict__ q32, const void *kcache, const void *vcache,
+                                                      int kv_f16, int nq, int nkv, int l, int max_seq, int pos0, bool split,
+                                                      void *out) {
+  constexpr int EL = HD / 16, NW = EL / 2;
+  const int lane = threadIdx.x & 63, slot = lane >> 4, dl = lane & 15;
+  const int t = blockIdx.y, h = blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (h >= nq) return;
+  const int P = pos0 + t, qd = nq * HD, kvd = nkv * HD;
+  const size_t base = (size_t)l * max_seq * kvd + (size_t)(h / (nq / nkv)) * HD + dl * EL;
+  float q[EL], o[EL], m = -1.0e30f, ls = 0.f;
+#pragma unroll
+  for (int e = 0; e < EL; ++e) { q[e] = q32[(size_t)t * qd + h * HD + dl * EL + e]; o[e] = 0.f; }
+  for (int p0 = 0; p0 <= P; p0 += 16) {
+    uint32_t kw[4][NW], vw[4][NW];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {                            // (positions beyond the last read it again, masked below)
+      const size_t off = (base + (size_t)min(p0 + u * 4 + slot, P) * kvd) * 2;
+#pragma unroll
+      for (int w = 0; w < NW; w += 2) {
+        const u32x2 a = *RIVER_GLOBAL(u32x2, (const char *)kcache + off + w * 4), b = *RIVER_GLOBAL(u32x2, (const char *)vcache + off + w * 4);
+        kw[u][w] = a.x; kw[u][w + 1] = a.y; vw[u][w] = b.x; vw[u][w + 1] = b.y;
+      }
+    }
+    float sc[4], mn = m;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      float d = 0.f;
+#pragma unroll
+      for (int w = 0; w < NW; ++w) d = fmaf(cache_hi(kw[u][w], kv_f16), q[2 * w + 1], fmaf(cache_lo(kw[u][w], kv_f16), q[2 * w], d));
+      sc[u] = row16_sum(d);
+      if (p0 + u * 4 + slot > P) sc[u] = -1.0e30f;
+      mn = fmaxf(mn, sc[u]);
+    }
+    const float cg = __builtin_amdgcn_exp2f(m - mn);
+    m = mn;
+    ls *= cg;
+#pragma unroll
+    for (int e = 0; e < EL; ++e) o[e] *= cg;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const float pg = sc[u] > -0.5e30f ? __builtin_amdgcn_exp2f(sc[u] - mn) : 0.f;
+      ls += pg;
+#pragma unroll
+      for (int w = 0; w < NW; ++w) {
+        o[2 * w] = fmaf(pg, cache_lo(vw[u][w], kv_f16), o[2 * w]);
+        o[2 * w + 1] = fmaf(pg, cache_hi(vw[u][w], kv_f16), o[2 * w + 1]);
+      }
+    }
+  }
+#pragma unroll
+  for (int off = 16; off <= 32; off <<= 1) {
+    const float m2 = __shfl_xor(m, off), l2 = __shfl_xor(ls, off), mn = fmaxf(m, m2);
+    const float c1 = __builtin_amdgcn_exp2f(m - mn), c2 = __builtin_amdgcn_exp2f(m2 - mn);
+    ls = ls * c1 + l2 * c2;
+#pragma unroll
+    for (int e = 0; e < EL; ++e) o[e] = o[e] * c1 + __shfl_xor(o[e], off) * c2;
+    m = mn;
+  }
+  if (slot != 0) return;
+  const size_t at = (size_t)t * qd + h * HD + dl * EL;
+#pragma unroll
+  for (int e = 0; e < EL; ++e) {
+    const float v = o[e] / ls;
+    if (split) {
+      uint16_t p[3];
+      split3(v, p);
+#pragma unroll
+      for (int i = 0; i < 3; ++i) ((uint16_t *)out)[i * (size_t)kShort * qd + at + e] = p[i];
+    } else {
+      ((_Float16 *)out)[at + e] = (_Float16)v;
+    }
+  }
+}
+
+// a = silu(gate) * up from the planes [n_part][kShort][2 ffn] of the gate/up GEMM, added in order; out: rows of
+// ffn, three bf16 parts (split) or fp16.  One thread per eight columns (ffn % 8 == 0).
+__global__ __launch_bounds__(256) void k_pf_swiglu_rows(const float *__restrict__ part, int n_part, int ffn, bool split, void *out) {
+  const int t = blockIdx.y, k = (blockIdx.x * 256 + (int)threadIdx.x) * 8;
+  if (k >= ffn) return;
+  const size_t stride = (size_t)kShort * 2 * ffn, row = (size_t)t * 2 * ffn;
+  Run8 g{}, u{};
+  add_planes(part + row + k, stride, n_part, [&](const float *p, bool ok) {
+    const Run8 a = ld_run8(p), b = ld_run8(p + ffn);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) { g.v[e] += ok ? a.v[e] : 0.f; u.v[e] += ok ? b.v[e] : 0.f; }
+  });
+  float v[8];
+#pragma unroll
+  for (int e = 0; e < 8; ++e) v[e] = g.v[e] / (1.0f + expf(-g.v[e])) * u.v[e];
+  if (split) {
+    store_split3((uint16_t *)out + (size_t)t * ffn + k, (size_t)kShort * ffn, v);
+  } else {
+    half8 o;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) o[e] = (_Float16)v[e];
+    *(half8 *)((_Float16 *)out + (size_t)t * ffn + k) = o;
   }
 }
 

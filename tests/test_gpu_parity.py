@@ -856,3 +856,75 @@ def test_river_quantised_elsewhere_integer_zero_points(mode):
             tok, _, _ = pair.step(tok, forced, f"foreign river step {step}")
         pair.compare_cache(44)
         pair.close()
+
+
+# Around the line between the step kernel's shapes for narrow models and the others (rows of 4 KiB: 2048
+# columns), with column counts that are and are not multiples of 32 (the 4-bit formats)
+SHAPE_LINE = [configs.ModelConfig("narrow-2048", 2, 2048, 16, 4, 128, 2080, 1002, 500000.0, 1e-5, configs.DTYPE_BF16, 64, 1, 2.0),
+              configs.ModelConfig("wide-2080", 2, 2080, 36, 4, 64, 2816, 1002, 500000.0, 1e-5, configs.DTYPE_BF16, 64, 1, 2.0),
+              configs.ModelConfig("wide-2064", 2, 2064, 36, 4, 64, 2832, 1002, 500000.0, 1e-5, configs.DTYPE_BF16, 64, 1, 2.0)]
+
+
+@pytest.mark.parametrize("mode", MODES, ids=MODE_IDS)
+@pytest.mark.parametrize("cfg", SHAPE_LINE, ids=lambda c: c.name)
+def test_step_shapes_around_the_narrow_line(mode, cfg):
+    say(f"{cfg.name} mode={mode}")
+    w = inputs.make_weights(cfg, 81, gain_std=0.1)
+    pair = Pair(cfg, w, mode, prefill_gemm_min_tokens=-1)
+    run_teacher_forced(pair, inputs.make_prompt(cfg.vocab, 7, 82), 4, forced=[1, 2, 1, 2], label=cfg.name)
+    pair.g.close()
+
+
+# Prompts below the GEMM prefill's smallest, in passes of up to 32 positions: blocks of 64 MB and more (the
+# smallest such shapes: ragged quantisation groups, ffn an odd multiple of 64, both head sizes)
+SHORT_64 = configs.ModelConfig("short-hd64", 3, 2048, 32, 8, 64, 4160, 1002, 500000.0, 1e-5, configs.DTYPE_BF16, 96, 1, 2.0,
+                               river_group=128)
+SHORT_128 = SHORT_64.with_(name="short-hd128", n_q_heads=18, n_kv_heads=9, head_dim=128, d_model=2112, river_group=64)
+
+
+@pytest.mark.parametrize("kv", [configs.KV_SAME, configs.KV_F16], ids=["kv-bf16", "kv-f16"])
+@pytest.mark.parametrize("cfg0,min_tokens,n_prompt,ep", [
+    (SHORT_64, 0, 3, 3), (SHORT_64, 0, 31, 2), (SHORT_128, 0, 16, 1), (SHORT_128, 0, 17, 3), (SHORT_64, 90, 32, 1), (SHORT_128, 90, 70, 2)],
+    ids=lambda v: v.name if hasattr(v, "name") else str(v))
+def test_short_prompts_keep_the_decode_kernels_precision(cfg0, min_tokens, n_prompt, ep, kv):
+    """Against the oracle and against a context that never uses GEMMs.  The two contexts differ by the order of
+    32-bit sums, which now and then turns a rounding of a cached key or value by one unit: 2^-8 (bf16) or
+    2^-11 (fp16 cache) of one element in thousands.  In the first block (backbone) their words may
+    differ by that only; behind it both are held to a quarter of the parity bar against the oracle, fp16
+    inputs of the river blocks included (2^-11 per element)."""
+    cfg = cfg0.with_(kv_dtype=kv)
+    say(f"{cfg.name} min={min_tokens} n={n_prompt} ep={ep} kv={kv}")
+    w = inputs.make_weights(cfg, 91, gain_std=0.1)
+    o = ro.Oracle(cfg, w, ro.quantize_river(cfg, w))
+    prompt = inputs.make_prompt(cfg.vocab, n_prompt, 92)
+    to = o.prefill(prompt, ep)
+    dw = binding.upload_weights(w)
+    dr = binding.quantize_river(cfg, dw)
+    g = binding.River(cfg, dw, dr, prefill_gemm_min_tokens=min_tokens)
+    never = binding.River(cfg, dw, dr, prefill_gemm_min_tokens=-1)
+    other = inputs.make_prompt(cfg.vocab, n_prompt, 93)
+    for _ in range(2):                                  # the second time behind another prompt: nothing is left over
+        tg, tn = g.prefill(prompt, ep), never.prefill(prompt, ep)
+        check_token(cfg, tg, to, o.logits(), cfg.name)
+        check_token(cfg, tn, to, o.logits(), cfg.name)
+        ho, hg, hn = o.hidden(), g.hidden(), never.hidden()
+        for l in range(cfg.n_layers + 1):
+            assert relerr(hg[l], ho[l]) <= 5e-3 and relerr(hn[l], ho[l]) <= 5e-3
+        assert relerr(g.logits(), o.logits()) <= 5e-3
+        unit = 2.0 ** -7 if kv == configs.KV_SAME else 2.0 ** -10
+        for a, b in ((g.kcache(), never.kcache()), (g.vcache(), never.vcache())):
+            a, b = a[0, :n_prompt], b[0, :n_prompt]
+            assert np.abs(a - b).max() <= unit * np.abs(b).max()
+            assert (np.abs(a - b) <= unit * np.abs(b) + 1e-6 * np.abs(b).max()).all() and (a != b).mean() <= 2e-3
+        g.prefill(other, ep)
+    # and the sequence goes on from there
+    tg, tn = g.prefill(prompt, ep), never.prefill(prompt, ep)
+    to = o.prefill(prompt, ep)
+    for e in (1, 3):
+        to2, eo, so = o.decode_step(to, e)
+        t2, e2, s2 = g.decode_step(to, e)
+        assert e2 == eo and relerr(g.logits(), o.logits()) <= TOL[cfg.dtype]
+        to = to2
+    g.close()
+    never.close()
+    o.close()
