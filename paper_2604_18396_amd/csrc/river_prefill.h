@@ -425,6 +425,13 @@ __device__ __forceinline__ Run8 ld_run8_16(const void *p, size_t i) {       // e
   return Run8{{f[0], f[1], f[2], f[3], f[4], f[5], f[6], f[7]}};
 }
 
+// eight norm gains; wide: the pointer is 16-byte aligned (the final norm's need not be)
+__device__ __forceinline__ Run8 ld_gain8(const void *gain, int k, bool wide) {
+  if (wide) return ld_run8_16(gain, k);
+  Run8 x;
+  for (int e = 0; e < 8; ++e) x.v[e] = Store<1>::ld(gain, k + e);
+  return x;
+}
 // f(element, exists) for every one of n planes, in order, four at a time so that their loads go out
 // together (an element beyond the last plane is plane 0's again, for f to leave out)
 template <class F>
@@ -478,17 +485,18 @@ __global__ __launch_bounds__(512) void k_pf_norm(float *__restrict__ h, const in
     for (int e = 0; e < 8; ++e) ss = fmaf(x.v[e], x.v[e], ss);
     return x;
   };
-  Run8 keep[kNormKeep];
+  // (the gains are fetched with the row: behind the reduction they are one more round trip)
+  Run8 keep[kNormKeep], kg[kNormKeep];
 #pragma unroll
   for (int i = 0; i < kNormKeep; ++i) {
     const int k = threadIdx.x * 8 + i * (int)blockDim.x * 8;
+    if (k < d && x16) kg[i] = ld_run8_16(gain, k);
     if (k < d) keep[i] = take(k);
   }
   for (int k = threadIdx.x * 8 + kNormKeep * (int)blockDim.x * 8; k < d; k += (int)blockDim.x * 8) (void)take(k);
   if (!x16) return;
   const float r = 1.0f / sqrtf(block_sum(ss, red) / (float)d + eps);
-  auto put = [&](int k, const Run8 &x) {
-    const Run8 g = ld_run8_16(gain, k);
+  auto put = [&](int k, const Run8 &x, const Run8 &g) {
     float v[8];
     half8 o;
 #pragma unroll
@@ -504,9 +512,9 @@ __global__ __launch_bounds__(512) void k_pf_norm(float *__restrict__ h, const in
 #pragma unroll
   for (int i = 0; i < kNormKeep; ++i) {
     const int k = threadIdx.x * 8 + i * (int)blockDim.x * 8;
-    if (k < d) put(k, keep[i]);
+    if (k < d) put(k, keep[i], kg[i]);
   }
-  for (int k = threadIdx.x * 8 + kNormKeep * (int)blockDim.x * 8; k < d; k += (int)blockDim.x * 8) put(k, ld_run8(row + k));   // (this thread's own)
+  for (int k = threadIdx.x * 8 + kNormKeep * (int)blockDim.x * 8; k < d; k += (int)blockDim.x * 8) put(k, ld_run8(row + k), ld_run8_16(gain, k));   // (this thread's own)
 }
 
 // RoPE on q and k at position pos0 + t; q scaled by log2(e) / sqrt(hd) and stored as fp16 for
@@ -1021,10 +1029,10 @@ __device__ __forceinline__ Run8 load_run8(float *row, const float *part, int n_p
   }
   return Run8{{a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w}};
 }
-__device__ __forceinline__ void norm_store_run8(const Run8 &x, float r, const void *gain, _Float16 *xf, int d, int t, int k) {
+__device__ __forceinline__ void norm_store_run8(const Run8 &x, float r, const Run8 &g, _Float16 *xf, int t, int k) {
   half8 o;
 #pragma unroll
-  for (int j = 0; j < 8; ++j) o[j] = (_Float16)(x.v[j] * r * Store<1>::ld(gain, k + j));
+  for (int j = 0; j < 8; ++j) o[j] = (_Float16)(x.v[j] * r * g.v[j]);
   frag_store8(xf, t, k, o);
 }
 
@@ -1059,10 +1067,12 @@ __global__ __launch_bounds__(256) void k_bd_begin(StepIn in, SeqState st, const 
     for (int j = 0; j < 8; ++j) ss = fmaf(x.v[j], x.v[j], ss);
     return x;
   };
-  Run8 keep[kRowKeep];
+  const bool gain_wide = ((uintptr_t)gain & 15) == 0;
+  Run8 keep[kRowKeep], kg[kRowKeep];                           // (gains with the row: one round trip)
 #pragma unroll
   for (int i = 0; i < kRowKeep; ++i) {
     const int k = threadIdx.x * 8 + i * 2048;
+    if (k < d) kg[i] = ld_gain8(gain, k, gain_wide);
     if (k < d) keep[i] = take(k);
   }
   for (int k = threadIdx.x * 8 + kRowKeep * 2048; k < d; k += 2048) (void)take(k);
@@ -1078,10 +1088,10 @@ __global__ __launch_bounds__(256) void k_bd_begin(StepIn in, SeqState st, const 
 #pragma unroll
   for (int i = 0; i < kRowKeep; ++i) {
     const int k = threadIdx.x * 8 + i * 2048;
-    if (k < d) norm_store_run8(keep[i], r, gain, xf, d, b, k);
+    if (k < d) norm_store_run8(keep[i], r, kg[i], xf, b, k);
   }
   for (int k = threadIdx.x * 8 + kRowKeep * 2048; k < d; k += 2048)    // stored by this thread itself above
-    norm_store_run8(ld_run8(h + (size_t)b * d + k), r, gain, xf, d, b, k);
+    norm_store_run8(ld_run8(h + (size_t)b * d + k), r, ld_gain8(gain, k, gain_wide), xf, b, k);
 }
 
 // C[rows, N] (op)= A[rows, K] B^T for the rows r < n_rows with river[r] == want (want < 0: all
@@ -1169,6 +1179,20 @@ __device__ __forceinline__ void bd_gemm_pass(const _Float16 *__restrict__ Af, co
   float ssq[MB];                                              // EPI_ADD_NORM: this thread's sum of h^2, row i * 16 + (tid % 256) / 16
 #pragma unroll
   for (int i = 0; i < MB; ++i) ssq[i] = 0.f;
+  // EPI_ADD_NORM with one row block per pass (d_model of up to 16 rows per CU): h and the gains of this thread's
+  // elements of the first pass, at most two, are fetched here, their latency is the K loop's
+  constexpr bool kPre = RBW == 1;
+  float pre_h[2] = {0.f, 0.f}, pre_g[2] = {0.f, 0.f};
+  if (kPre && epi == EPI_ADD_NORM) {
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      const int e = tid + q * nw * 64, row = (e / 256) * 16 + ((e & 255) >> 4), n = wg_r0 + (e & 15);
+      if (e < MB * 256 && row < n_rows && n < wg_r1) {
+        pre_h[q] = ((const float *)C)[(size_t)row * ldc + n];
+        pre_g[q] = Store<1>::ld(nrm.gain, n);
+      }
+    }
+  }
   for (int p0 = wg_r0; p0 < wg_r1; p0 += RBW * 16) {
     // Stream order (see BdB): this lane's 16-byte piece of K tile 0 of row block 0 lies in unit p0 / 8
     // or the next one, at [g][row % 8]; a row block further is 2 units, a K tile further one tile.
@@ -1296,7 +1320,8 @@ __device__ __forceinline__ void bd_gemm_pass(const _Float16 *__restrict__ Af, co
           red[((wv * RBW + rb) * MB + i) * 256 + (kg * 4 + r) * 16 + r16] = acc[rb][i][r];
     __syncthreads();
     constexpr int TILE_F = RBW * MB * 256;
-    for (int e = tid; e < TILE_F; e += nw * 64) {
+    int ord = kPre && p0 == wg_r0 ? 0 : 2;                            // which of this thread's elements
+    for (int e = tid; e < TILE_F; e += nw * 64, ++ord) {
       const int rb = e / (MB * 256), i = (e / 256) % MB, row = i * 16 + ((e & 255) >> 4), n = p0 + rb * 16 + (e & 15);
       int f = flag[0];                                        // (rows i * 16 + (tid % 256) / 16: see k_bd_gemm)
 #pragma unroll
@@ -1317,9 +1342,9 @@ __device__ __forceinline__ void bd_gemm_pass(const _Float16 *__restrict__ Af, co
         float *p = (float *)C + (size_t)(k_split > 1 ? ks * kRows + row : row) * ldc + n;
         const float v = total(e);
         if (epi == EPI_ADD_NORM) {
-          const float hv = *p + v;
+          const float hv = (ord == 0 ? pre_h[0] : ord == 1 ? pre_h[1] : *p) + v;
           *p = hv;
-          frag_store(nrm.xnext, row, n, (_Float16)(hv * Store<1>::ld(nrm.gain, n)));
+          frag_store(nrm.xnext, row, n, (_Float16)(hv * (ord == 0 ? pre_g[0] : ord == 1 ? pre_g[1] : Store<1>::ld(nrm.gain, n))));
 #pragma unroll
           for (int i2 = 0; i2 < MB; ++i2)
             if (i2 == i) ssq[i2] = fmaf(hv, hv, ssq[i2]);
@@ -1686,10 +1711,12 @@ __global__ __launch_bounds__(512) void k_bd_block_end(float *h_prev, float *__re
     *(float4 *)(hist + (size_t)b * d + k) = c0; *(float4 *)(hist + (size_t)b * d + k + 4) = c1;
     return c;
   };
-  Run8 keep[kRowKeep];
+  const bool gain_wide = ((uintptr_t)next_gain & 15) == 0;
+  Run8 keep[kRowKeep], kg[kRowKeep];                           // (gains with the row: one round trip)
 #pragma unroll
   for (int i = 0; i < kRowKeep; ++i) {
     const int k = threadIdx.x * 8 + i * (int)blockDim.x * 8;
+    if (k < d) kg[i] = ld_gain8(next_gain, k, gain_wide);
     if (k < d) keep[i] = take(k);
   }
   for (int k = threadIdx.x * 8 + kRowKeep * (int)blockDim.x * 8; k < d; k += (int)blockDim.x * 8) (void)take(k);
@@ -1708,10 +1735,10 @@ __global__ __launch_bounds__(512) void k_bd_block_end(float *h_prev, float *__re
 #pragma unroll
   for (int i = 0; i < kRowKeep; ++i) {
     const int k = threadIdx.x * 8 + i * (int)blockDim.x * 8;
-    if (k < d) norm_store_run8(keep[i], r, next_gain, xf, d, b, k);
+    if (k < d) norm_store_run8(keep[i], r, kg[i], xf, b, k);
   }
   for (int k = threadIdx.x * 8 + kRowKeep * (int)blockDim.x * 8; k < d; k += (int)blockDim.x * 8)    // updated by this thread itself above
-    norm_store_run8(load_run8(row, nullptr, 0, b, d, k), r, next_gain, xf, d, b, k);
+    norm_store_run8(load_run8(row, nullptr, 0, b, d, k), r, ld_gain8(next_gain, k, gain_wide), xf, b, k);
 }
 
 // The exit decision after backbone block l1 from the similarities k_bd_block_end left (launched
