@@ -1668,13 +1668,27 @@ __global__ __launch_bounds__(256) void k_bd_attn(const float *__restrict__ qkv, 
   for (int t = tid; t < REP * HD; t += 256) {
     const int r = t / HD, e = t % HD;
     const size_t pb = ((size_t)b * nq + h0 + r) * kBdAttnMaxSplits;
+    // every split's numbers are fetched before the first is used (in a loop over the splits each one was a
+    // round trip, twice: 4 us of 22 with four splits)
+    float mj[kBdAttnMaxSplits], lj[kBdAttnMaxSplits], oj[kBdAttnMaxSplits];
+#pragma unroll
+    for (int j = 0; j < kBdAttnMaxSplits; ++j) {
+      mj[j] = -1.0e30f; lj[j] = oj[j] = 0.f;
+      if (j < n_splits) {                                      // (uniform)
+        mj[j] = sub(part_ml + (pb + j) * 2);
+        lj[j] = sub(part_ml + (pb + j) * 2 + 1);
+        oj[j] = sub(part_o + (pb + j) * HD + e);
+      }
+    }
     float Mg = -1.0e30f;
-    for (int j = 0; j < n_splits; ++j) Mg = fmaxf(Mg, sub(part_ml + (pb + j) * 2));
+#pragma unroll
+    for (int j = 0; j < kBdAttnMaxSplits; ++j) Mg = fmaxf(Mg, mj[j]);
     float Lg = 0.f, Og = 0.f;
-    for (int j = 0; j < n_splits; ++j) {
-      const float cj = __builtin_amdgcn_exp2f(sub(part_ml + (pb + j) * 2) - Mg);   // an empty split has sum 0
-      Lg = fmaf(sub(part_ml + (pb + j) * 2 + 1), cj, Lg);
-      Og = fmaf(sub(part_o + (pb + j) * HD + e), cj, Og);
+#pragma unroll
+    for (int j = 0; j < kBdAttnMaxSplits; ++j) {
+      const float cj = __builtin_amdgcn_exp2f(mj[j] - Mg);     // an empty split has sum 0
+      Lg = fmaf(lj[j], cj, Lg);
+      Og = fmaf(oj[j], cj, Og);
     }
     frag_store(o16, b, (h0 + r) * HD + e, (_Float16)(Og / Lg));
   }
@@ -1794,13 +1808,22 @@ __global__ __launch_bounds__(256) void k_bd_argmax(const float *__restrict__ log
   float *mine = part + ((size_t)b * kBdArgmaxChunks + c) * 2;
   if (threadIdx.x == 0) { pub(mine, best); pub(mine + 1, __int_as_float(besti)); }
   if (!last_arriver(tickets + b, kBdArgmaxChunks, &flag)) return;
-  if (threadIdx.x == 0) {
-    best = -INFINITY;
-    besti = 0x7fffffff;
-    for (int j = 0; j < kBdArgmaxChunks; ++j) {
-      const float *pj = part + ((size_t)b * kBdArgmaxChunks + j) * 2;
+  // the chunks' maxima, a lane each (one thread after the other's round trip: 16 of them)
+  best = -INFINITY;
+  besti = 0x7fffffff;
+  if (threadIdx.x < 64) {
+    if (threadIdx.x < kBdArgmaxChunks) {
+      const float *pj = part + ((size_t)b * kBdArgmaxChunks + threadIdx.x) * 2;
       argmax_take(best, besti, sub(pj), __float_as_int(sub(pj + 1)));
     }
+#pragma unroll
+    for (int o = kBdArgmaxChunks / 2; o > 0; o >>= 1) {
+      const float v2 = __shfl_xor(best, o);
+      const int i2 = __shfl_xor(besti, o);
+      argmax_take(best, besti, v2, i2);
+    }
+  }
+  if (threadIdx.x == 0) {
     st.token[b] = besti;
     rec_token[b] = besti;
     rec_exit[b] = st.exit_pos[b];
