@@ -1508,13 +1508,17 @@ extern "C" int river_decode_batch(river_ctx *x, int32_t n_seq, const int32_t *in
                                                x->layers_h[0].attn_norm, c.rms_eps, x16);
   const size_t seq_stride = y.cache_bytes / 2;               // elements (bf16)
   // attention: one workgroup per (sequence, kv head, group of query heads, split of the positions);
-  // splits so that every CU has two workgroups (measured best) of at least 128 positions
+  // splits so that every CU has two workgroups (measured best) of at least 128 positions, or 256 where half the
+  // CUs have one without: a split more is a merge behind another workgroup's publication, about as long as two
+  // batches of 64 positions (128 / 256, 8 steps of four blocks: 8B, 32 sequences at 200 positions 4249 / 4154 us; 1B, 16
+  // at 400 2428 / 2400; mid-size shape, 8 at 200, 16 workgroups unsplit: 1669 / 1692)
   const int rep = c.n_q_heads / c.n_kv_heads, arep = rep % 4 == 0 ? 4 : 1;
   int t_max = 1;
   for (int b = 0; b < n; ++b) t_max = std::max(t_max, x->pos_b[b] + 1);
   const int hgs = rep / arep, groups = n * c.n_kv_heads * hgs;
+  const int per_split = 2 * groups >= x->grid_persist ? 256 : 128;
   int n_splits = (2 * x->grid_persist + groups - 1) / groups;
-  n_splits = std::max(1, std::min({n_splits, bd::kBdAttnMaxSplits, (t_max + 127) / 128}));
+  n_splits = std::max(1, std::min({n_splits, bd::kBdAttnMaxSplits, (t_max + per_split - 1) / per_split}));
   const size_t attn_lds = bd::bd_attn_lds_bytes(arep, c.head_dim);
   const int qkv_ld = qd + 2 * c.n_kv_heads * c.head_dim;
   for (int l = 0; l < L; ++l) {
