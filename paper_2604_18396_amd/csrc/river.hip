@@ -1251,8 +1251,8 @@ static int prefill_gemm(river_ctx *x, int seq, const int32_t *tokens, int n, int
     const int last = c0 + m == n ? m - 1 : -1;              // the row whose h(0..L) is kept
     const int *tok_src = tok;
     if (x->host && n <= kHostTok) {      // (the call waits for the stream: the slot is free)
-      std::memcpy(x->host->tok, tokens, (size_t)n * 4);
-      tok_src = x->host->tok;
+      std::memcpy(x->host->tok + c0, tokens + c0, (size_t)m * 4);
+      tok_src = x->host->tok + c0;
     } else {
       HIP_TRY(x, hipMemcpyAsync(tok, tokens + c0, (size_t)m * 4, hipMemcpyHostToDevice, s));
     }
