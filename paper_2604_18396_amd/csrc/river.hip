@@ -950,7 +950,7 @@ static int create_impl(const river_config *cfg, const river_weights *w, const ri
           {(const void *)pf::k_pf_gemm<pf::TileM, true, pf::PF_STORE>, pf::TileM::LDS_BYTES},
           {(const void *)pf::k_pf_gemm<pf::TileM, true, pf::PF_SWIGLU>, pf::TileM::LDS_BYTES},
           {(const void *)pf::k_pf_gemm<pf::TileM, false, pf::PF_STORE, true>, pf::TileM::LDS_BYTES},
-          {(const void *)pf::k_pf_gemm<pf::TileM, true, pf::PF_STORE, true>, pf::TileM::LDS_BYTES},
+          {(const void *)pf::k_pf_gemm<pf::TileM, true, pf::PF_STORE, true>, pf::TileM::LDS_FOLD},
           {(const void *)pf::k_pf_gemm<pf::TileN, false, pf::PF_STORE>, pf::TileN::LDS_BYTES},
           {(const void *)pf::k_pf_gemm<pf::TileN, false, pf::PF_SWIGLU>, pf::TileN::LDS_BYTES},
           {(const void *)pf::k_pf_gemm<pf::TileN, true, pf::PF_STORE>, pf::TileN::LDS_BYTES},
@@ -1108,8 +1108,8 @@ template <class T, bool W4, int EPI, bool EXACT = false>
 static void launch_gemm_t(river_ctx *x, const pf::GemmB &B, int N, const _Float16 *A, int K, void *C, int ldc, int m, int split) {
   const int n_tiles = (N + T::TN - 1) / T::TN, m_tiles = (m + T::TM - 1) / T::TM;
   const dim3 grid((n_tiles * split + 7) / 8 * 8 * m_tiles);      // (see the kernel's workgroup -> tile mapping)
-  pf::k_pf_gemm<T, W4, EPI, EXACT><<<grid, dim3(T::NT), T::LDS_BYTES, x->stream>>>(A, K, B, N, K, x->cfg.river_group, C, ldc, m,
-                                                                           m_tiles, split);
+  const size_t lds = EXACT && W4 ? T::LDS_FOLD : T::LDS_BYTES;
+  pf::k_pf_gemm<T, W4, EPI, EXACT><<<grid, dim3(T::NT), lds, x->stream>>>(A, K, B, N, K, x->cfg.river_group, C, ldc, m, m_tiles, split);
 }
 // the stacked matrices ms[0..nm) of block l; returns their rows
 static int gemm_operand(const river_ctx *x, int l, bool w4, const int *ms, int nm, pf::GemmB *B) {
@@ -1146,7 +1146,7 @@ static int launch_gemm(river_ctx *x, int l, bool w4, const int *ms, int nm, cons
 static int launch_gemm_exact(river_ctx *x, int l, bool w4, const int *ms, int nm, const _Float16 *A, int K, float *C) {
   pf::GemmB B{};
   const int N = gemm_operand(x, l, w4, ms, nm, &B), M = w4 ? pf::kShort : 3 * pf::kShort;
-  const int split = pf_plan(x, N, w4 ? 2 * K : K, M, true, 1).split;
+  const int split = pf_plan(x, N, K, M, true, 1).split;
   if (w4) launch_gemm_t<pf::TileM, true, pf::PF_STORE, true>(x, B, N, A, K, C, N, M, split);
   else launch_gemm_t<pf::TileM, false, pf::PF_STORE, true>(x, B, N, A, K, C, N, M, split);
   return split * (w4 ? 1 : 3);

@@ -72,19 +72,14 @@ __device__ __forceinline__ half8 dequant8(uint32_t w, float s, float zero) {
   return h;
 }
 
-// The same weights as a sum of two fp16 numbers (22 bits): the first, or (low) what it leaves.
-__device__ __forceinline__ half8 dequant8_part(uint32_t w, float s, float zero, bool low) {
+// The eight codes themselves: a nibble in the low bits of 1024.0 is 1024 + code.
+__device__ __forceinline__ half8 codes8(uint32_t w) {
   half8 h;
 #pragma unroll
-  for (int k = 0; k < 4; ++k) {
-    const uint32_t sh = k < 2 ? w << (6 - 4 * k) : w >> (4 * k - 6);
-    const half2v q = __builtin_bit_cast(half2v, sh & 0x03c003c0u);
-#pragma unroll
-    for (int e = 0; e < 2; ++e) {
-      const float t = fmaf((float)q[e], 0x1p18f, -zero) * s;
-      const _Float16 hi = (_Float16)t;
-      h[k + 4 * e] = low ? (_Float16)(t - (float)hi) : hi;
-    }
+  for (int k = 0; k < 4; ++k) {                // nibbles k and k + 4
+    const half2v q = __builtin_bit_cast(half2v, ((w >> (4 * k)) & 0x000f000fu) | 0x64006400u) - (_Float16)1024.f;
+    h[k] = q[0];
+    h[k + 4] = q[1];
   }
   return h;
 }
@@ -158,8 +153,11 @@ __device__ __forceinline__ void gemm_b_row(const GemmB &B, int n, int N, int &ma
 //
 // EXACT (short prompts, whose activations stay in 32 bits): dense -- A holds bf16 rows, the three parts of the
 // activations one under the other (see split3), multiplied with the bf16 weights as they are, every product exact; codes
-// -- A holds fp16 rows, as the decode kernels round them, and every K tile comes twice, with the first and
-// with the second fp16 part of the weights.
+// -- A holds fp16 rows, as the decode kernels round them, multiplied with the codes as they are; a K tile's
+// sums S and the sum X of its inputs (a product with ones) go into the result as scale (S - zero X) in fp32,
+// the form in which the decode kernels take the scale and the zero point.  (The weights as two fp16 numbers, the
+// K tiles taken twice, lost bits of weights below 2e-3 and turned those beyond 65504 into NaN; four 8B river
+// blocks and 3 tokens took 900 us that way, 563 now.)
 //
 // Tile of C per workgroup (TM x TN), its WM x WN wavefronts, K tiles in flight in registers (PF) and
 // workgroups per CU (OCC, bounds the registers).
@@ -171,6 +169,7 @@ template <int TM_, int TN_, int WM_, int WN_, int PF_, int OCC_> struct GemmTile
   static constexpr int GR = NT / 8;                            // rows a staging round of the workgroup covers
   static constexpr int RA = TM / GR, RB = TN / GR;             // staging rounds per K tile
   static constexpr int LDS_BYTES = 2 * (TM + TN) * LDK * 2;    // two buffers each of A and B
+  static constexpr int LDS_FOLD = LDS_BYTES + 2 * TN * 4;      // ... and of the pairs of B's rows (codes, EXACT)
   static_assert((RA == 2 || RA == 4) && (RB == 2 || RB == 4) && RA >= RB && RA * GR == TM && RB * GR == TN,
                 "two or four staging rounds");
 };
@@ -203,6 +202,8 @@ __global__ __launch_bounds__(T::NT, T::OCC) void k_pf_gemm(const _Float16 *__res
                                                            int k_split) {
   extern __shared__ __attribute__((aligned(16))) _Float16 pf_lds[];
   constexpr int TM = T::TM, TN = T::TN, PF = T::PF, GR = T::GR;
+  constexpr bool FOLD = EXACT && W4;
+  uint32_t *const pf_sz = (uint32_t *)((char *)pf_lds + T::LDS_BYTES);         // FOLD: two buffers of TN (scale, zero) pairs
   const int tid = threadIdx.x, lane = tid & 63;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6), wm = wv / T::WN, wn = wv % T::WN;
   // Workgroup -> (tile of C, slice of K).  Consecutive workgroup ids go round the 8 XCDs; the
@@ -214,8 +215,7 @@ __global__ __launch_bounds__(T::NT, T::OCC) void k_pf_gemm(const _Float16 *__res
   if (col >= n_tiles * k_split) return;
   const int n_tile = col / k_split, ks_i = col % k_split;
   const int m0 = m_tile * TM;
-  constexpr bool TWICE = EXACT && W4;
-  const int nk_all = K / TK * (TWICE ? 2 : 1), kt0 = (int)((long long)nk_all * ks_i / k_split);
+  const int nk_all = K / TK, kt0 = (int)((long long)nk_all * ks_i / k_split);
   const int nk = (int)((long long)nk_all * (ks_i + 1) / k_split) - kt0;
 
   // what this thread stages per K tile: a 16-byte segment of A per round; of B one per round (dense)
@@ -225,7 +225,7 @@ __global__ __launch_bounds__(T::NT, T::OCC) void k_pf_gemm(const _Float16 *__res
   unsigned a_off[RA];
 #pragma unroll
   for (int i = 0; i < RA; ++i) a_off[i] = (unsigned)min(m0 + i * GR + srow, M - 1) * (unsigned)lda * 2u + sk * 16u;
-  const __amdgpu_buffer_rsrc_t a_rsrc = gemm_rsrc((const char *)A + (TWICE ? 0 : (size_t)kt0 * TK * 2));
+  const __amdgpu_buffer_rsrc_t a_rsrc = gemm_rsrc((const char *)A + (size_t)kt0 * TK * 2);
   const int s_dst = srow * LDK + sk * 8;                       // + i * GR * LDK
   __amdgpu_buffer_rsrc_t b_rsrc[W4 ? 1 : RB];
   unsigned b_off = 0;
@@ -236,7 +236,7 @@ __global__ __launch_bounds__(T::NT, T::OCC) void k_pf_gemm(const _Float16 *__res
     int mat, row;
     gemm_b_row8<T, EPI>(B, n_tile, row_l & ~7, N, mat, row);
     row += row_l & 7;
-    b_src = (const char *)B.w[mat] + (size_t)row * (K >> 1) + q * RB * 4 + (TWICE ? 0 : kt0 * (TK / 2));
+    b_src = (const char *)B.w[mat] + (size_t)row * (K >> 1) + q * RB * 4 + kt0 * (TK / 2);
     b_sz = (const char *)B.sz[mat] + (size_t)row * ((K + group - 1) / group) * 4;   // (the last group may be shorter)
     b_dst = row_l * LDK + q * RB * 8;
   } else {
@@ -256,10 +256,6 @@ __global__ __launch_bounds__(T::NT, T::OCC) void k_pf_gemm(const _Float16 *__res
   const int tiles_per_group = group / TK;
   int g_at = W4 ? kt0 / tiles_per_group : 0, g_left = W4 ? tiles_per_group - kt0 % tiles_per_group : 0;
   auto load_part = [&](int kt, int u, int i) {   // part i of tile kt into set u
-    if constexpr (TWICE) {
-      kt = (kt0 + kt) >> 1;
-      g_at = kt / tiles_per_group; g_left = 2;
-    }
     fa[u][i] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(a_rsrc, a_off[i], kt * (TK * 2), 0));
     if constexpr (W4) {
       if (i == RA - 1) {                          // (all parts of the set have been staged)
@@ -277,14 +273,14 @@ __global__ __launch_bounds__(T::NT, T::OCC) void k_pf_gemm(const _Float16 *__res
       fb[u][i & n] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(b_rsrc[i & n], b_off, kt * (TK * 2), 0));
     }
   };
-  auto stage_part = [&](int u, int i, int buf, int kt) {  // part i of set u, tile kt, into LDS buffer buf
+  auto stage_part = [&](int u, int i, int buf) {  // part i of set u into LDS buffer buf
     _Float16 *const As = pf_lds + buf * TM * LDK, *const Bs = pf_lds + 2 * TM * LDK + buf * TN * LDK;
     *(u32x4 *)(As + s_dst + i * GR * LDK) = fa[u][i];
     if (i >= RB) return;
     if constexpr (W4) {
       const uint32_t w = i == 0 ? fb[u][0].x : i == 1 ? fb[u][0].y : i == 2 ? fb[u][0].z : fb[u][0].w;
-      *(half8 *)(Bs + b_dst + i * 8) = TWICE ? dequant8_part(w, bf16_lo(fsz[u]), bf16_hi(fsz[u]), (kt0 + kt) & 1)
-                                             : dequant8(w, bf16_lo(fsz[u]), bf16_hi(fsz[u]));
+      *(half8 *)(Bs + b_dst + i * 8) = FOLD ? codes8(w) : dequant8(w, bf16_lo(fsz[u]), bf16_hi(fsz[u]));
+      if (FOLD && i == 0 && tid % (8 / RB) == 0) pf_sz[buf * TN + tid / (8 / RB)] = fsz[u];
     } else {
       const u32x4 w = fb[u][i & (RB - 1)];
       if constexpr (EXACT) *(u32x4 *)(Bs + s_dst + i * GR * LDK) = w;
@@ -317,6 +313,12 @@ __global__ __launch_bounds__(T::NT, T::OCC) void k_pf_gemm(const _Float16 *__res
   };
   auto body = [&](int kt, int u1, bool stage, bool load) {     // u1: the set of tile kt + 1
     const int cur = kt & 1;
+    f32x16 part[FOLD ? T::MB : 1][FOLD ? T::NB : 1], xsum[FOLD ? T::MB : 1];   // FOLD: the tile's sums
+    uint32_t sz[T::NB];
+    if constexpr (FOLD) {                          // (in front of the barrier, behind which the buffer may be written)
+#pragma unroll
+      for (int j = 0; j < T::NB; ++j) sz[j] = pf_sz[cur * TN + wn * T::NW + j * 32 + r32];
+    }
 #pragma unroll
     for (int ks = 0; ks < 4; ++ks) {
       if (ks == 3) lds_barrier();
@@ -325,14 +327,22 @@ __global__ __launch_bounds__(T::NT, T::OCC) void k_pf_gemm(const _Float16 *__res
 #pragma unroll
       for (int i = 0; i < RA; ++i) {                           // parts 0, 1 | 2 | 3, or 0 | 1
         if (ks != (RA == 2 ? i : i < 1 ? 0 : i - 1)) continue;
-        if (stage) stage_part(u1, i, cur ^ 1, kt + 1);
+        if (stage) stage_part(u1, i, cur ^ 1);
         if (load) load_part(kt + 1 + PF, u1, i);
       }
 #pragma unroll
       for (int i = 0; i < T::MB; ++i)
 #pragma unroll
-        for (int j = 0; j < T::NB; ++j)
-          acc[i][j] = EXACT && !W4 ? mfma16_bf16(xa[ks & 1][i], xb[ks & 1][j], acc[i][j]) : mfma16(xa[ks & 1][i], xb[ks & 1][j], acc[i][j]);
+        for (int j = 0; j < T::NB; ++j) {
+          const half8 &a = xa[ks & 1][i], &b = xb[ks & 1][j];
+          if constexpr (FOLD) part[i][j] = mfma16(a, b, ks ? part[i][j] : f32x16{});
+          else acc[i][j] = EXACT ? mfma16_bf16(a, b, acc[i][j]) : mfma16(a, b, acc[i][j]);
+        }
+      if constexpr (FOLD) {
+        const half8 ones = (half8)(_Float16)1.f;
+#pragma unroll
+        for (int i = 0; i < T::MB; ++i) xsum[i] = mfma16(xa[ks & 1][i], ones, ks ? xsum[i] : f32x16{});
+      }
       // the step's conversions, LDS writes and loads go between its MFMAs, not in front of them
 #pragma unroll
       for (int q = 0; q < T::MB * T::NB; ++q) {
@@ -343,6 +353,15 @@ __global__ __launch_bounds__(T::NT, T::OCC) void k_pf_gemm(const _Float16 *__res
       }
       __builtin_amdgcn_sched_barrier(0);
     }
+    if constexpr (FOLD) {
+#pragma unroll
+      for (int i = 0; i < T::MB; ++i)
+#pragma unroll
+        for (int j = 0; j < T::NB; ++j)
+#pragma unroll
+          for (int r = 0; r < 16; ++r)
+            acc[i][j][r] = fmaf(bf16_lo(sz[j]), fmaf(-bf16_hi(sz[j]), xsum[i][r], part[i][j][r]), acc[i][j][r]);
+    }
   };
 #pragma unroll
   for (int u = 0; u < PF; ++u)
@@ -351,7 +370,7 @@ __global__ __launch_bounds__(T::NT, T::OCC) void k_pf_gemm(const _Float16 *__res
       for (int i = 0; i < RA; ++i) load_part(u, u, i);
     }
 #pragma unroll
-  for (int i = 0; i < RA; ++i) stage_part(0, i, 0, 0);
+  for (int i = 0; i < RA; ++i) stage_part(0, i, 0);
   if (PF < nk) {
 #pragma unroll
     for (int i = 0; i < RA; ++i) load_part(PF, 0, i);

@@ -928,3 +928,31 @@ def test_short_prompts_keep_the_decode_kernels_precision(cfg0, min_tokens, n_pro
     g.close()
     never.close()
     o.close()
+
+
+@pytest.mark.parametrize("size", [1e-6, 1.5e5], ids=["1e-6", "1.5e5"])
+def test_short_prompts_river_weights_of_any_size(size):
+    """Groups whose weights are all the same (scale 1, zero point minus the weight, code 0), of a size that has no
+    bits left as a sum of fp16 numbers, or does not fit one: a river block of a short prompt takes the scale and the
+    zero point in 32 bits.  Keys and values of a river block against the oracle's, every row by itself: at
+    most 2^-9 of it is the cache's rounding to bf16, 2^-11 the inputs' rounding to fp16."""
+    cfg = SHORT_64.with_(min_exit_layer=0, n_layers=1)
+    w = inputs.make_weights(cfg, 95, gain_std=0.1)
+    gen = torch.Generator().manual_seed(96)
+    for name in ("wk", "wv"):
+        rows, cols = w["layers"][0][name].shape
+        v = size * (1 + torch.rand(rows, -(-cols // cfg.river_group), generator=gen))
+        v *= torch.where(torch.rand(v.shape, generator=gen) < 0.5, -1.0, 1.0)
+        w["layers"][0][name] = v.to(torch.bfloat16).repeat_interleave(cfg.river_group, 1)[:, :cols].contiguous()
+    say(f"short prompt, constant groups of {size}")
+    pair = Pair(cfg, w, None)
+    prompt = inputs.make_prompt(cfg.vocab, 31, 97)
+    pair.o.prefill(prompt, 0)
+    pair.g.prefill(prompt, 0)
+    for got, want in ((pair.g.kcache(), pair.o.kcache()), (pair.g.vcache(), pair.o.vcache())):
+        got, want = (np.asarray(a, np.float64)[0, :31] for a in (got, want))
+        assert np.isfinite(got).all()
+        err = np.linalg.norm(got - want, axis=-1) / np.linalg.norm(want, axis=-1)
+        say(f"largest row error {err.max():.1e}")
+        assert err.max() <= 2.0 ** -8
+    pair.close()
