@@ -83,10 +83,15 @@ __device__ __forceinline__ half8 codes8(uint32_t w) {
   }
   return h;
 }
-// x as a sum of three bf16 numbers (24 bits, exact but for what lies below the smallest of them)
+// x as a sum of three bf16 numbers (24 bits, exact but for what lies below the smallest of them).  An infinity or NaN
+// is the first one, the others 0; a finite x that rounds to an infinity is cut off instead.
 __device__ __forceinline__ void split3(float x, uint16_t (&p)[3]) {
+  const bool finite = __builtin_isfinite(x);
+  p[0] = Store<1>::rne(x);
+  if (finite && (p[0] & 0x7fffu) == 0x7f80u) p[0] -= 1;
+  x = finite ? x - __uint_as_float((uint32_t)p[0] << 16) : 0.f;
 #pragma unroll
-  for (int i = 0; i < 3; ++i) {
+  for (int i = 1; i < 3; ++i) {
     p[i] = Store<1>::rne(x);
     x -= __uint_as_float((uint32_t)p[i] << 16);
   }

@@ -956,3 +956,25 @@ def test_short_prompts_river_weights_of_any_size(size):
         say(f"largest row error {err.max():.1e}")
         assert err.max() <= 2.0 ** -8
     pair.close()
+
+
+def test_short_prompts_keep_infinities():
+    """A feed-forward activation beyond the range of 32 bits: infinity times a weight is an infinity of the weight's sign,
+    as in the decode kernels.  (Behind it every norm gives NaN, on both routes.)"""
+    say("short prompt, infinite activations")
+    w = inputs.make_weights(SHORT_64, 98)
+    blk = w["layers"][0]
+    blk["w_gate"][:64] *= 1e20                          # silu(g) g: infinite where g > 0, else 0
+    blk["w_up"][:64] = blk["w_gate"][:64]
+    blk["w_down"][0::2, :64] = 0.01
+    blk["w_down"][1::2, :64] = -0.01
+    dw = binding.upload_weights(w)
+    prompt = inputs.make_prompt(SHORT_64.vocab, 5, 99)
+    h1 = []
+    for min_tokens in (0, -1):
+        g = binding.River(SHORT_64, dw, None, prefill_gemm_min_tokens=min_tokens)
+        g.prefill(prompt)
+        h1.append(g.hidden()[1])
+        g.close()
+    want = np.where(np.arange(SHORT_64.d_model) % 2 == 0, np.inf, -np.inf)
+    assert np.array_equal(h1[1], want) and np.array_equal(h1[0], want)
