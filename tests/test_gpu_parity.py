@@ -875,6 +875,25 @@ def test_step_shapes_around_the_narrow_line(mode, cfg):
     pair.g.close()
 
 
+# Vectors that are staged in more than one trip of a workgroup: 16384 columns of an activation, 8192 of a norm's
+# input (the last trip covers 32 columns, a quad of threads)
+TRIPS = [configs.ModelConfig("ffn-16416", 2, 256, 4, 2, 64, 16416, 514, 10000.0, 1e-5, configs.DTYPE_BF16, 16, 0, 2.0),
+         configs.ModelConfig("model-8224", 2, 8224, 4, 2, 64, 288, 514, 10000.0, 1e-5, configs.DTYPE_BF16, 16, 0, 2.0)]
+
+
+@pytest.mark.parametrize("mode", MODES, ids=MODE_IDS)
+@pytest.mark.parametrize("dtype", [configs.DTYPE_BF16, configs.DTYPE_F32], ids=["bf16", "fp32"])
+@pytest.mark.parametrize("cfg0", TRIPS, ids=lambda c: c.name)
+def test_vectors_staged_in_several_trips(cfg0, dtype, mode):
+    cfg = cfg0.with_(dtype=dtype)
+    needs_mode(cfg, mode)
+    say(f"{cfg.name} dtype={dtype} mode={mode}")
+    pair = Pair(cfg, inputs.make_weights(cfg, 85, gain_std=0.1), mode)
+    run_teacher_forced(pair, inputs.make_prompt(cfg.vocab, 3, 86), 4, forced=[2, 0, 1, 2], label=cfg.name)
+    pair.compare_cache(7)
+    pair.g.close()
+
+
 # Prompts below the GEMM prefill's smallest, in passes of up to 32 positions: blocks of 64 MB and more (the
 # smallest such shapes: ragged quantisation groups, ffn an odd multiple of 64, both head sizes)
 SHORT_64 = configs.ModelConfig("short-hd64", 3, 2048, 32, 8, 64, 4160, 1002, 500000.0, 1e-5, configs.DTYPE_BF16, 96, 1, 2.0,
@@ -884,15 +903,17 @@ SHORT_128 = SHORT_64.with_(name="short-hd128", n_q_heads=18, n_kv_heads=9, head_
 
 @pytest.mark.parametrize("kv", [configs.KV_SAME, configs.KV_F16], ids=["kv-bf16", "kv-f16"])
 @pytest.mark.parametrize("cfg0,min_tokens,n_prompt,ep", [
-    (SHORT_64, 0, 3, 3), (SHORT_64, 0, 31, 2), (SHORT_128, 0, 16, 1), (SHORT_128, 0, 17, 3), (SHORT_64, 90, 32, 1), (SHORT_128, 90, 70, 2)],
+    (SHORT_64, 0, 3, 3), (SHORT_64, 0, 31, 2), (SHORT_128, 0, 16, 1), (SHORT_128, 0, 17, 3), (SHORT_64, 90, 32, 1), (SHORT_128, 90, 70, 2),
+    (SHORT_64, 0, 29, 0), (SHORT_128, 90, 75, 0)],
     ids=lambda v: v.name if hasattr(v, "name") else str(v))
 def test_short_prompts_keep_the_decode_kernels_precision(cfg0, min_tokens, n_prompt, ep, kv):
     """Against the oracle and against a context that never uses GEMMs.  The two contexts differ by the order of
     32-bit sums, which now and then turns a rounding of a cached key or value by one unit: 2^-8 (bf16) or
     2^-11 (fp16 cache) of one element in thousands.  In the first block (backbone) their words may
-    differ by that only; behind it both are held to a quarter of the parity bar against the oracle, fp16
-    inputs of the river blocks included (2^-11 per element)."""
-    cfg = cfg0.with_(kv_dtype=kv)
+    differ by that only; hidden states and logits of both are held to a quarter of the parity bar against the oracle, fp16
+    inputs of the river blocks included (2^-11 per element), and the keys and values of every block and position, row
+    by row, to 2^-8: the cache's rounding is at most 2^-9 of a row, the inputs' 2^-11 in each of three blocks."""
+    cfg = cfg0.with_(kv_dtype=kv, min_exit_layer=min(cfg0.min_exit_layer, ep))
     say(f"{cfg.name} min={min_tokens} n={n_prompt} ep={ep} kv={kv}")
     w = inputs.make_weights(cfg, 91, gain_std=0.1)
     o = ro.Oracle(cfg, w, ro.quantize_river(cfg, w))
@@ -913,9 +934,16 @@ def test_short_prompts_keep_the_decode_kernels_precision(cfg0, min_tokens, n_pro
         assert relerr(g.logits(), o.logits()) <= 5e-3
         unit = 2.0 ** -7 if kv == configs.KV_SAME else 2.0 ** -10
         for a, b in ((g.kcache(), never.kcache()), (g.vcache(), never.vcache())):
+            if ep == 0:
+                continue
             a, b = a[0, :n_prompt], b[0, :n_prompt]
             assert np.abs(a - b).max() <= unit * np.abs(b).max()
             assert (np.abs(a - b) <= unit * np.abs(b) + 1e-6 * np.abs(b).max()).all() and (a != b).mean() <= 2e-3
+        for want, *both in ((o.kcache(), g.kcache(), never.kcache()), (o.vcache(), g.vcache(), never.vcache())):
+            want = np.asarray(want, np.float64).reshape(cfg.n_layers, cfg.max_seq, -1)[:, :n_prompt]
+            err = [np.linalg.norm(c[:, :n_prompt] - want, axis=-1) / np.linalg.norm(want, axis=-1) for c in both]
+            say("largest row error per block " + "; ".join(" ".join(f"{x:.1e}" for x in e.max(-1)) for e in err))
+            assert max(e.max() for e in err) <= 2.0 ** -8
         g.prefill(other, ep)
     # and the sequence goes on from there
     tg, tn = g.prefill(prompt, ep), never.prefill(prompt, ep)
