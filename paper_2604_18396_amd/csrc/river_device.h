@@ -226,6 +226,24 @@ __device__ __forceinline__ void publish_barrier() {
   asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
 }
 
+// Thread and lane id passed through an empty asm: with all phases of all blocks inlined into one kernel the
+// compiler would otherwise derive every offset that depends on them once at kernel entry and keep (spill) them
+// all; this way they are re-derived per phase.  A spilled one is read back behind the prefetch its wavefront has
+// in flight, since loads return in order: with fourteen of them (the staging's offsets) a token of the 8B shape
+// at 4096 positions took 2998 us (backbone) / 1906 (river), without 2904 / 1859; at 768 2702 / 1666, 2654 / 1642.
+// (The lane's range is left unknown: 1B, 256 positions 628 us, with it 637.)
+__device__ __forceinline__ int fresh_tid() {
+  int t = threadIdx.x;
+  asm volatile("" : "+v"(t));
+  __builtin_assume(t >= 0 && t < 1024);
+  return t;
+}
+__device__ __forceinline__ int fresh_lane() {
+  int t = threadIdx.x & 63;
+  asm volatile("" : "+v"(t));
+  return t;
+}
+
 // ------------------------------------------------------------ reductions
 
 
@@ -255,13 +273,18 @@ __device__ __forceinline__ float wave_sum(float v) {
   return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), 63));
 }
 
+// The value of the lane with byte offset `at` (4 times its id)
+__device__ __forceinline__ float lane_get(float v, int at) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_ds_bpermute(at, __builtin_bit_cast(int, v)));
+}
+
 // Sum over the workgroup in a fixed order; every thread gets the result.
 // red: LDS scratch of at least 16 floats.
 __device__ __forceinline__ float block_sum(float v, float *red) {
   v = wave_sum(v);
-  const int w = threadIdx.x >> 6, nw = blockDim.x >> 6;
+  const int t0 = fresh_tid(), w = t0 >> 6, nw = blockDim.x >> 6;
   lds_barrier();
-  if ((threadIdx.x & 63) == 0) red[w] = v;
+  if ((t0 & 63) == 0) red[w] = v;
   lds_barrier();
   float t = 0.f;
   for (int i = 0; i < nw; ++i) t += red[i];
@@ -274,9 +297,9 @@ template <int K, bool FREE = false>
 __device__ __forceinline__ void block_sum_k(float (&v)[K], float *red) {
 #pragma unroll
   for (int k = 0; k < K; ++k) v[k] = wave_sum(v[k]);
-  const int w = threadIdx.x >> 6, nw = blockDim.x >> 6;
+  const int t0 = fresh_tid(), w = t0 >> 6, nw = blockDim.x >> 6;
   if constexpr (!FREE) lds_barrier();
-  if ((threadIdx.x & 63) == 0) {
+  if ((t0 & 63) == 0) {
 #pragma unroll
     for (int k = 0; k < K; ++k) red[w * K + k] = v[k];
   }
@@ -501,17 +524,18 @@ __device__ __forceinline__ void stage_norm_embed(DevRef D, int tok, const void *
 constexpr int kCopyRuns = 4;         // runs per thread and trip: 16384 columns
 template <class Put>
 __device__ __forceinline__ void fetch_runs(const float *src, int n, Put put) {
+  const int tid = fresh_tid();
   for (int base = 0; base < n; base += kCopyRuns * kBlock * 8) {
     float4 a[kCopyRuns][2];
 #pragma unroll
     for (int k = 0; k < kCopyRuns; ++k) {
-      const int i = base + (k * kBlock + (int)threadIdx.x) * 8;
+      const int i = base + (k * kBlock + tid) * 8;
       a[k][0] = i < n ? sub4(src, i) : make_float4(0.f, 0.f, 0.f, 0.f);
       a[k][1] = i < n ? sub4(src, i + 4) : make_float4(0.f, 0.f, 0.f, 0.f);
     }
 #pragma unroll
     for (int k = 0; k < kCopyRuns; ++k) {
-      const int i = base + (k * kBlock + (int)threadIdx.x) * 8;
+      const int i = base + (k * kBlock + tid) * 8;
       if (i < n) put(i, a[k][0], a[k][1]);
     }
   }
@@ -572,12 +596,13 @@ constexpr int kNormRuns = 2;
 template <int DT> struct NormIn {
   float4 v[kNormRuns][2];
   float g[kNormRuns][8];
+  int tid = fresh_tid();
   // ANY: gains of any alignment (the final norm's; the blocks' are 16-byte aligned)
   template <bool ANY>
   __device__ __forceinline__ void load(const float *h, const void *gain, int base, int n) {
 #pragma unroll
     for (int k = 0; k < kNormRuns; ++k) {
-      const int i = base + (k * kBlock + (int)threadIdx.x) * 8;
+      const int i = base + (k * kBlock + tid) * 8;
       if (i < n) {
         v[k][0] = sub4(h, i);
         v[k][1] = sub4(h, i + 4);
@@ -606,7 +631,7 @@ template <int DT> struct NormIn {
       load<ANY>(h, gain, base, n);
 #pragma unroll
       for (int k = 0; k < kNormRuns; ++k)
-        if (base + (k * kBlock + (int)threadIdx.x) * 8 < n) {
+        if (base + (k * kBlock + tid) * 8 < n) {
           float q2[2];
 #pragma unroll
           for (int q = 0; q < 2; ++q)
@@ -625,7 +650,7 @@ template <int DT> struct NormIn {
       if (!one_trip) load<ANY>(h, gain, base, n);
 #pragma unroll
       for (int k = 0; k < kNormRuns; ++k) {
-        const int i = base + (k * kBlock + (int)threadIdx.x) * 8;
+        const int i = base + (k * kBlock + tid) * 8;
         if (i < n) {
           float x[8] = {v[k][0].x, v[k][0].y, v[k][0].z, v[k][0].w, v[k][1].x, v[k][1].y, v[k][1].z, v[k][1].w};
 #pragma unroll
@@ -840,14 +865,6 @@ template <int DT, int R, int U, int CPL> struct W4 {
 // step needs at most kNL / 2 loads (F::SUB == 2) -- then twice as many elements are in
 // flight for the same registers.  While one slot is consumed the others are in flight.
 // The first elements are issued before the barrier in front of the phase.
-// `lane` is the lane id passed through an empty asm: with all phases of all blocks inlined
-// into one kernel the compiler would otherwise derive every lane-offset variant once at
-// kernel entry and keep (spill) them all; this way they are re-derived per phase.
-__device__ __forceinline__ int fresh_lane() {
-  int t = threadIdx.x & 63;
-  asm volatile("" : "+v"(t));
-  return t;
-}
 constexpr int kSets = 2;           // register sets of the streaming pipeline (a third one only delayed the phases)
 // V: what a kernel is built for, bit 0 the phases' shapes for narrow models (see Shape), bit 1 column
 // counts that are all multiples of 32 (no other 4-bit format).  The one-launch step kernel is built per
@@ -1124,7 +1141,7 @@ __device__ __forceinline__ float4 similarity_part(DevRef D, int i) {
 template <int DT, bool ANY = false>
 __device__ __forceinline__ float norm_and_similarity(DevRef D, bool want_s, const float *h, const void *gain,
                                                      NormIn<DT> &in, float &r, float *red) {
-  const float4 p = want_s ? similarity_part(D, threadIdx.x) : make_float4(0.f, 0.f, 0.f, 0.f);
+  const float4 p = want_s ? similarity_part(D, in.tid) : make_float4(0.f, 0.f, 0.f, 0.f);
   const float ss = in.template fetch<ANY>(h, gain, D.d);
   float s = 0.f, tot;
   if (want_s) {
@@ -1148,7 +1165,7 @@ __device__ __forceinline__ bool exit_by_similarity(const StepArgs &A, const Ctl 
 __device__ __forceinline__ void exit_test(DevRef D, const StepArgs &A, int l1, float s, Ctl &ctl) {
   if (ctl.river) return;
   const bool may = l1 >= D.min_exit && l1 < D.L;
-  if (A.forced_e < 0 && blockIdx.x == 0 && threadIdx.x == 0 && A.rec_slot >= 0) pub(rec_sims(D, A) + (l1 - 1), s);
+  if (A.forced_e < 0 && blockIdx.x == 0 && fresh_tid() == 0 && A.rec_slot >= 0) pub(rec_sims(D, A) + (l1 - 1), s);
   if (may && (A.forced_e >= 0 ? A.forced_e == l1 : s > D.tau)) {
     ctl.river = true;
     ctl.exit_pos = l1;
@@ -1441,7 +1458,7 @@ __device__ __forceinline__ void stage_attn_out(DevRef D, const StepArgs &A, int 
     return;
   }
   lds_barrier();
-  for (int i = threadIdx.x * 8; i < n; i += blockDim.x * 8) {
+  for (int i = fresh_tid() * 8; i < n; i += blockDim.x * 8) {
     float v[8];
     combine_splits8(D, S, i / D.hd, i % D.hd, v);
     if (lp < 0) {
@@ -1566,12 +1583,13 @@ __device__ __forceinline__ void attn_items(DevRef D, const StepArgs &A, int l, f
     // the four lane groups of the wavefront -> one (lanes 16, 32 apart hold the same elements)
 #pragma unroll
     for (int off = 16; off <= 32; off <<= 1) {
-      const float m2 = __shfl_xor(m, off), l2 = __shfl_xor(ls, off);
+      const int other = (lane ^ off) * 4;
+      const float m2 = lane_get(m, other), l2 = lane_get(ls, other);
       const float mn = fmaxf(m, m2);
       const float c1 = __builtin_amdgcn_exp2f(m - mn), c2 = __builtin_amdgcn_exp2f(m2 - mn);
       ls = ls * c1 + l2 * c2;
 #pragma unroll
-      for (int e = 0; e < EL; ++e) o[e] = o[e] * c1 + __shfl_xor(o[e], off) * c2;
+      for (int e = 0; e < EL; ++e) o[e] = o[e] * c1 + lane_get(o[e], other) * c2;
       m = mn;
     }
     lds_barrier();                        // merge area free (previous item fully consumed)
@@ -1585,8 +1603,8 @@ __device__ __forceinline__ void attn_items(DevRef D, const StepArgs &A, int l, f
     lds_barrier();
     RIVER_MARK(D, 3);
     // the wavefronts -> one partial per (head, split), fixed order
-    if ((int)threadIdx.x < hd) {
-      const int e = threadIdx.x;
+    const int e = wv * 64 + lane;
+    if (e < hd) {
       float2 ml[kWaves];
       float ov[kWaves];
       float M = kNegBig;
