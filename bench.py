@@ -95,7 +95,7 @@ def phase_trace(ctx_len):
     L = cfg.n_layers
     names = ["QKV", "attention", "O-proj", "gate/up", "down"]
     mats = [("wq", "wk", "wv"), (), ("wo",), ("w_gate", "w_up"), ("w_down",)]
-    print(f"# phase timeline of k_step_persistent<1>, 8B shape, context {ctx_len}, mean over blocks 2..{L}, microseconds")
+    print(f"# phase timeline of k_step_persistent, 8B shape, context {ctx_len}, mean over blocks 2..{L}, microseconds")
     for which, fe in (("dense token (backbone blocks)", L), ("all-river token (4-bit twins)", 0)):
         for _ in range(4):
             g.decode_step(None, fe, sync=False)
@@ -391,7 +391,7 @@ def main():
                    "resident_parameter_GiB": resident / 2**30},
         "roofline": {"bound": "hbm", "achieved": gbs, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": gbs / HBM_PEAK_GBS, "traffic": traffic,
-                     "kernel": "k_step_persistent<1, false>" if args.mode == "persistent" else "all step kernels",
+                     "kernel": "k_step_persistent" if args.mode == "persistent" else "all step kernels",
                      "algorithmic_bytes_per_launch": float(np.mean(bytes_river)),
                      "traffic_detail": traffic_detail},
         "dense": {"value": tok_s_dense, "unit": "tokens/s", "ms_per_step": ms_dense / K,

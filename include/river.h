@@ -81,8 +81,9 @@ typedef struct {
                                       (RIVER_BF16, d_model, d_ffn and river_group multiples of 64); shorter
                                       ones keep the decode kernels' precision (models with blocks of 64 MB and
                                       more: passes of 32 positions from 3 tokens on; others, and all other
-                                      configurations: one prompt position after the other).  0 = default (32);
-                                      negative = never a GEMM */
+                                      configurations: one prompt position after the other).  The routes add
+                                      in different orders: results agree within the precision of the types,
+                                      not bit for bit.  0 = default (32); negative = never a GEMM */
   int32_t batch_exit_rule; /* batched contexts, when Eq. 1 decides: 0 = every sequence for itself
                               (s_b > tau); 1 = Eq. 1 as printed: the whole batch leaves the backbone together at
                               the first block with min over the batch of s_b > tau */

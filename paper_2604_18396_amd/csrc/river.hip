@@ -431,7 +431,10 @@ struct river_ctx {
 
 static thread_local std::string g_create_err;
 
-// rows of d_model and n_q * head_dim columns of at most four 1 KiB granules (see Shape)
+// Rows of d_model and n_q * head_dim columns of at most four 1 KiB granules (see Shape).  Sections of four bf16
+// blocks of head size 64, d_model 512 / 1024 / 1536 / 2048 / 2304 / 2560 / 3072 / 4096, us per step with the
+// narrow shapes and without: backbone 108 / 119 / 142 / 168 / 207 / 228 / 262 / 368 and 108 / 123 / 145 / 171 / 200 / 218 /
+// 257 / 360, river 110 / 115 / 124 / 132 / 163 / 185 / 199 / 231 and 114 / 122 / 130 / 140 / 166 / 177 / 190 / 223.
 static bool narrow_model(const river_config &c) {
   return std::max(c.d_model, c.n_q_heads * c.head_dim) * (c.dtype == RIVER_BF16 ? 2 : 4) <= 4096;
 }
@@ -729,7 +732,7 @@ static int create_impl(const river_config *cfg, const river_weights *w, const ri
     return RIVER_EHIP;
   }
   const int cus = prop.multiProcessorCount;
-  // one workgroup per CU, a multiple of 8 (the device-wide barrier counts in 8 groups)
+  // one workgroup per CU, a multiple of 8 (the XCDs)
   x->grid_persist = std::max(8, std::min(cus, kMaxGrid) / 8 * 8);
   // One launch per phase: no more workgroups than the widest phase has tasks for (a task is one or two
   // rows per wavefront; attention: a query head and split), a multiple of 8.  Small models only: the
@@ -1161,11 +1164,13 @@ static void launch_prefill_head(river_ctx *x, int n, int ep) {
   k_head<1><<<dim3(x->grid_gemv), dim3(x->block), x->lds_bytes, x->stream>>>(x->dev_d, A);
 }
 
-// Short prompts (see river_prefill.h): passes of up to kShort positions, from kShortMin positions on (a position
-// through the decode kernels costs one stream of the weights, a pass two to three), for models with
-// blocks of at least kShortBlockBytes.  Smaller ones would gain as well (a 23 MB block 26 us per position, 50 per
-// pass), but their prompts have always agreed bit for bit with those of contexts that never use GEMMs
-// (prefill_gemm_min_tokens < 0), and callers compare the two; at these sizes that costs a prompt 2 ms at most.
+// Short prompts (see river_prefill.h): passes of up to kShort positions, from kShortMin positions on, for models with
+// blocks of at least kShortBlockBytes.  us per prompt of 2 / 3 / 31 tokens through the decode kernels, and of
+// 3 / 31 in a pass: four 8B blocks, backbone 702 / 1030 / 10317 and 618 / 655, river 426 / 618 / 6036 and 563 / 577;
+// three blocks of 72 MB 199 / 287 / 2763 and 226 / 248, river 166 / 237 / 2246 and 210 / 223; three of 23 MB
+// 166 / 237 / 2257 and 202 / 220, river 164 / 235 / 2222 and 184 / 193.  So a pass costs two to three positions at
+// every size, and the line in block size is not where passes begin to pay: below it a prompt equals,
+// bit for bit, that of a context that never uses GEMMs (prefill_gemm_min_tokens < 0), and only that holds it there.
 constexpr int kShortMin = 3;
 constexpr size_t kShortBlockBytes = (size_t)64 << 20;
 static bool prefill_short_ok(const river_ctx *x, int n) {
