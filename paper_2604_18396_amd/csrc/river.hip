@@ -947,13 +947,11 @@ static int create_impl(const river_config *cfg, const river_weights *w, const ri
       if ((e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, lb)) != hipSuccess)
         return fail("hipFuncSetAttribute(max dynamic LDS)", e);
     if (gemm_prefill_ok(cfg)) {
-      const std::pair<const void *, int> pfg[] = {
+      std::vector<std::pair<const void *, int>> pfg = {
           {(const void *)pf::k_pf_gemm<pf::TileM, false, pf::PF_STORE>, pf::TileM::LDS_BYTES},
           {(const void *)pf::k_pf_gemm<pf::TileM, false, pf::PF_SWIGLU>, pf::TileM::LDS_BYTES},
           {(const void *)pf::k_pf_gemm<pf::TileM, true, pf::PF_STORE>, pf::TileM::LDS_BYTES},
           {(const void *)pf::k_pf_gemm<pf::TileM, true, pf::PF_SWIGLU>, pf::TileM::LDS_BYTES},
-          {(const void *)pf::k_pf_gemm<pf::TileM, false, pf::PF_STORE, true>, pf::TileM::LDS_BYTES},
-          {(const void *)pf::k_pf_gemm<pf::TileM, true, pf::PF_STORE, true>, pf::TileM::LDS_FOLD},
           {(const void *)pf::k_pf_gemm<pf::TileN, false, pf::PF_STORE>, pf::TileN::LDS_BYTES},
           {(const void *)pf::k_pf_gemm<pf::TileN, false, pf::PF_SWIGLU>, pf::TileN::LDS_BYTES},
           {(const void *)pf::k_pf_gemm<pf::TileN, true, pf::PF_STORE>, pf::TileN::LDS_BYTES},
@@ -962,6 +960,17 @@ static int create_impl(const river_config *cfg, const river_weights *w, const ri
           {(const void *)pf::k_pf_gemm<pf::TileL, false, pf::PF_SWIGLU>, pf::TileL::LDS_BYTES},
           {(const void *)pf::k_pf_gemm<pf::TileL, true, pf::PF_STORE>, pf::TileL::LDS_BYTES},
           {(const void *)pf::k_pf_gemm<pf::TileL, true, pf::PF_SWIGLU>, pf::TileL::LDS_BYTES}};
+      auto rows = [&](auto mb) {
+        constexpr int MB = decltype(mb)::value;
+        const int dense = pf::RowsTile<MB, false>::LDS_BYTES, codes = pf::RowsTile<MB, true>::LDS_BYTES;
+        pfg.push_back({(const void *)pf::k_pf_gemm_rows<MB, false, pf::PF_STORE, false>, dense});
+        pfg.push_back({(const void *)pf::k_pf_gemm_rows<MB, false, pf::PF_SWIGLU, false>, dense});
+        pfg.push_back({(const void *)pf::k_pf_gemm_rows<MB, true, pf::PF_STORE, false>, codes});
+        pfg.push_back({(const void *)pf::k_pf_gemm_rows<MB, true, pf::PF_SWIGLU, false>, codes});
+      };
+      rows(IC<1>{}); rows(IC<2>{}); rows(IC<3>{}); rows(IC<4>{});
+      pfg.push_back({(const void *)pf::k_pf_gemm_rows<3, false, pf::PF_STORE, true>, pf::RowsTile<3, false>::LDS_BYTES});
+      pfg.push_back({(const void *)pf::k_pf_gemm_rows<1, true, pf::PF_STORE, true>, pf::RowsTile<1, true>::LDS_BYTES});
       for (const auto &f : pfg)
         if ((e = hipFuncSetAttribute(f.first, hipFuncAttributeMaxDynamicSharedMemorySize, f.second)) != hipSuccess)
           return fail("hipFuncSetAttribute(prefill GEMM LDS)", e);
@@ -1082,16 +1091,20 @@ static int check_device_error(river_ctx *x) {
 // TileM / TileN / TileL: N 3072 K 2048, 255 rows 10 / 12 / 15; N 6144 K 4096, 512 rows 40 / 36 / 36, and 41
 // for TileM unsliced, which the rule takes: 44 in a prefill; N 4096 K 14336, 512 rows 75 / 64 / 64, one
 // slice 132 / 187 / 272; N 28672 K 4096, 512 rows 147 / 132 / 114, 4096 rows 1199 / 1144 / 903.)
+// Up to kRowsMost rows the tiles are k_pf_gemm_rows', with TileM's count of slices (four blocks of the 8B shape, half of them
+// river, 77 tokens: 624 us with TileM, 563 with it; beyond, its one tile of 128 rows per CU is the slower one: N 6144
+// K 4096, 512 rows 48 us, N 28672 190).
 struct PfTile { int tm, tn; double alone, full; };
 constexpr PfTile kPfTiles[3] = {{pf::TileM::TM, pf::TileM::TN, 0.5, 0.67},
                                 {pf::TileN::TM, pf::TileN::TN, 0.85, 1.15},
                                 {pf::TileL::TM, pf::TileL::TN, 1.4, 2.05}};
 struct PfPlan { int tile, split; };
-static PfPlan pf_plan(const river_ctx *x, int N, int K, int m, bool may_split, int tiles_used = 3) {
+static PfPlan pf_plan(const river_ctx *x, int N, int K, int m, bool may_split) {
   PfPlan best{0, 1};
   double best_us = 1e30;
   const int nk = K / pf::TK, cus = x->grid_persist;
-  for (int i = 0; i < tiles_used; ++i) {
+  const bool rows = m <= pf::kRowsMost;
+  for (int i = 0; i < (rows ? 1 : 3); ++i) {
     const PfTile &t = kPfTiles[i];
     const long long tiles = (long long)((N + t.tn - 1) / t.tn) * ((m + t.tm - 1) / t.tm);
     for (int sp = 1; sp <= (may_split ? 16 : 1); ++sp) {
@@ -1099,7 +1112,7 @@ static PfPlan pf_plan(const river_ctx *x, int N, int K, int m, bool may_split, i
       const double load = (double)(tiles * sp) / cus, whole = std::floor(load), part = load - whole;
       const double k_tile_us = whole * t.full + (part > 0.0 ? t.alone + (t.full - t.alone) * part : 0.0);
       const double us = (nk + sp - 1) / sp * k_tile_us + (sp > 1 ? 2.0 * sp * m * N * 4 / 4e6 : 0.0);
-      if (us < best_us) { best_us = us; best = PfPlan{i, sp}; }
+      if (us < best_us) { best_us = us; best = PfPlan{rows ? 3 : i, sp}; }
     }
   }
   return best;
@@ -1107,12 +1120,20 @@ static PfPlan pf_plan(const river_ctx *x, int N, int K, int m, bool may_split, i
 
 // GEMM of the prefill over the stacked matrices ms[0..nm) of block l: fp32 planes of partial sums in
 // C (returns how many), or with EPI = PF_SWIGLU the fp16 activation of the down projection.
-template <class T, bool W4, int EPI, bool EXACT = false>
+template <class T, bool W4, int EPI>
 static void launch_gemm_t(river_ctx *x, const pf::GemmB &B, int N, const _Float16 *A, int K, void *C, int ldc, int m, int split) {
   const int n_tiles = (N + T::TN - 1) / T::TN, m_tiles = (m + T::TM - 1) / T::TM;
   const dim3 grid((n_tiles * split + 7) / 8 * 8 * m_tiles);      // (see the kernel's workgroup -> tile mapping)
-  const size_t lds = EXACT && W4 ? T::LDS_FOLD : T::LDS_BYTES;
-  pf::k_pf_gemm<T, W4, EPI, EXACT><<<grid, dim3(T::NT), lds, x->stream>>>(A, K, B, N, K, x->cfg.river_group, C, ldc, m, m_tiles, split);
+  pf::k_pf_gemm<T, W4, EPI><<<grid, dim3(T::NT), T::LDS_BYTES, x->stream>>>(A, K, B, N, K, x->cfg.river_group, C, ldc, m, m_tiles, split);
+}
+template <int MB, bool W4, int EPI, bool EXACT = false>
+static void launch_rows_t(river_ctx *x, const pf::GemmB &B, int N, const _Float16 *A, int K, void *C, int ldc, int m, int split, int rows32 = 32) {
+  typedef pf::RowsTile<MB, W4> T;
+  const int n_tiles = (N + T::TN - 1) / T::TN;
+  const int stages = (K + T::COLS - 1) / T::COLS;
+  const pf::RowsDeal deal{rows32, n_tiles, split, (uint32_t)(((1ull << 32) + split - 1) / split), stages / split, stages % split};
+  const dim3 grid((n_tiles * split + 7) / 8 * 8);
+  pf::k_pf_gemm_rows<MB, W4, EPI, EXACT><<<grid, dim3(T::NT), T::LDS_BYTES, x->stream>>>(A, K, B, N, K, x->cfg.river_group, C, ldc, m, deal);
 }
 // the stacked matrices ms[0..nm) of block l; returns their rows
 static int gemm_operand(const river_ctx *x, int l, bool w4, const int *ms, int nm, pf::GemmB *B) {
@@ -1139,19 +1160,30 @@ static int launch_gemm(river_ctx *x, int l, bool w4, const int *ms, int nm, cons
     if (w4) launch_gemm_t<T, true, EPI>(x, B, N, A, K, C, ldc, m, p.split);
     else launch_gemm_t<T, false, EPI>(x, B, N, A, K, C, ldc, m, p.split);
   };
-  if (p.tile == 0) launch(pf::TileM{});
+  auto rows = [&](auto mb) {
+    constexpr int MB = decltype(mb)::value;
+    if (w4) launch_rows_t<MB, true, EPI>(x, B, N, A, K, C, ldc, m, p.split);
+    else launch_rows_t<MB, false, EPI>(x, B, N, A, K, C, ldc, m, p.split);
+  };
+  if (p.tile == 3) {
+    const int mb = (m + 31) / 32;
+    if (mb == 1) rows(IC<1>{});
+    else if (mb == 2) rows(IC<2>{});
+    else if (mb == 3) rows(IC<3>{});
+    else rows(IC<4>{});
+  } else if (p.tile == 0) launch(pf::TileM{});
   else if (p.tile == 1) launch(pf::TileN{});
   else launch(pf::TileL{});
   return p.split;
 }
 
 // GEMM of a pass over a short prompt (EXACT, see pf::k_pf_gemm): planes of kShort rows in C; returns how many.
-static int launch_gemm_exact(river_ctx *x, int l, bool w4, const int *ms, int nm, const _Float16 *A, int K, float *C) {
+static int launch_gemm_exact(river_ctx *x, int l, bool w4, const int *ms, int nm, const _Float16 *A, int K, float *C, int m) {
   pf::GemmB B{};
   const int N = gemm_operand(x, l, w4, ms, nm, &B), M = w4 ? pf::kShort : 3 * pf::kShort;
-  const int split = pf_plan(x, N, K, M, true, 1).split;
-  if (w4) launch_gemm_t<pf::TileM, true, pf::PF_STORE, true>(x, B, N, A, K, C, N, M, split);
-  else launch_gemm_t<pf::TileM, false, pf::PF_STORE, true>(x, B, N, A, K, C, N, M, split);
+  const int split = pf_plan(x, N, K, M, true).split;
+  if (w4) launch_rows_t<1, true, pf::PF_STORE, true>(x, B, N, A, K, C, N, M, split, m);
+  else launch_rows_t<3, false, pf::PF_STORE, true>(x, B, N, A, K, C, N, M, split, m);
   return split * (w4 ? 1 : 3);
 }
 
@@ -1215,17 +1247,17 @@ static int prefill_short(river_ctx *x, const int32_t *tokens, int n, int ep) {
       const bool river = l >= ep;
       const DevLayer &W = x->layers_h[l];
       norm(river, l ? nullptr : tok_src, W.attn_norm, D.hidden + (size_t)l * d, last);
-      parts = launch_gemm_exact(x, l, river, m_qkv, 3, x16, d, big);
+      parts = launch_gemm_exact(x, l, river, m_qkv, 3, x16, d, big, m);
       pf::k_pf_rope_store<true><<<dim3(m), blk, 0, s>>>(big, parts, pf::kShort, D.rope, c.n_q_heads, c.n_kv_heads, c.head_dim, c0, l,
                                                         c.max_seq, D.kcache, D.vcache, D.kv_f16, q32);
       if (l == L - 1 && last < 0) break;                     // (a pass before the last: its keys and values are all that is read)
       attn<<<dim3((c.n_q_heads + 3) / 4, m), dim3(256), 0, s>>>((const float *)q32, D.kcache, D.vcache, D.kv_f16, c.n_q_heads,
                                                                  c.n_kv_heads, l, c.max_seq, c0, !river, x16);
-      parts = launch_gemm_exact(x, l, river, m_o, 1, x16, qd, big);
+      parts = launch_gemm_exact(x, l, river, m_o, 1, x16, qd, big, m);
       norm(river, nullptr, W.ffn_norm, nullptr, -1);
-      parts = launch_gemm_exact(x, l, river, m_gu, 2, x16, d, big);
+      parts = launch_gemm_exact(x, l, river, m_gu, 2, x16, d, big, m);
       pf::k_pf_swiglu_rows<<<dim3((ffn + 2047) / 2048, m), dim3(256), 0, s>>>(big, parts, ffn, !river, a16);
-      parts = launch_gemm_exact(x, l, river, m_d, 1, a16, ffn, big);
+      parts = launch_gemm_exact(x, l, river, m_d, 1, a16, ffn, big, m);
     }
     if (last >= 0) norm(true, nullptr, nullptr, D.hidden + (size_t)L * d, last);
     HIP_TRY(x, hipGetLastError());

@@ -59,15 +59,18 @@ __device__ __forceinline__ half8 bf16x8_to_half8(const uint4 &w) {
 
 // Eight 4-bit codes of a row-major word (nibble i = column i) -> fp16 of (code - zero) * scale, taken in
 // fp32 as the decode kernels and the oracle take it.  A nibble in bits 6..9 of an fp16 word is the
-// subnormal number code * 2^-18, which the mixed-precision fma reads exactly.
+// subnormal number code * 2^-18, which the mixed-precision fma reads exactly; the product of the zero point
+// and the scale, bf16 both, is exact in fp32, so code * scale - zero * scale is rounded once and one
+// instruction a weight makes it (the difference first, then its product: three).
 __device__ __forceinline__ half8 dequant8(uint32_t w, float s, float zero) {
+  const float s18 = s * 0x1p18f, zs = -zero * s;
   half8 h;
 #pragma unroll
   for (int k = 0; k < 4; ++k) {                // nibbles k and k + 4
     const uint32_t sh = k < 2 ? w << (6 - 4 * k) : w >> (4 * k - 6);
     const half2v q = __builtin_bit_cast(half2v, sh & 0x03c003c0u);
-    h[k] = (_Float16)(fmaf((float)q[0], 0x1p18f, -zero) * s);
-    h[k + 4] = (_Float16)(fmaf((float)q[1], 0x1p18f, -zero) * s);
+    h[k] = (_Float16)fmaf((float)q[0], s18, zs);
+    h[k + 4] = (_Float16)fmaf((float)q[1], s18, zs);
   }
   return h;
 }
@@ -150,19 +153,10 @@ __device__ __forceinline__ void gemm_b_row(const GemmB &B, int n, int N, int &ma
 
 // What bounds it: many rows -- the matrix cores (at the clock the power limit leaves: 68 % of the
 // cycles issue MFMAs at 4096 x 28672 x 4096, 1.05 PFLOP/s, where the 128 x 128 tile with one K tile in
-// flight reached 0.85); few rows -- the weight stream and, before the K slices, the chain of K tiles of
-// the few workgroups there are (512 x 4096 x 14336: 209 us without slices and one tile in flight, 63
-// now).  A 256 x 256 tile halves the LDS reads per MFMA of a 128 x 128 one.  B goes through registers
+// flight reached 0.85); a few hundred rows -- the chain of K tiles of the few workgroups there are (512 x 4096 x
+// 14336: 209 us without slices and one tile in flight, 63 now); up to 128 rows: k_pf_gemm_rows.  A 256 x 256 tile halves the LDS reads per MFMA of a 128 x 128 one.  B goes through registers
 // because it is converted on the way (bf16 -> fp16, codes -> fp16); one conversion serves all
 // wavefronts of the tile.
-//
-// EXACT (short prompts, whose activations stay in 32 bits): dense -- A holds bf16 rows, the three parts of the
-// activations one under the other (see split3), multiplied with the bf16 weights as they are, every product exact; codes
-// -- A holds fp16 rows, as the decode kernels round them, multiplied with the codes as they are; a K tile's
-// sums S and the sum X of its inputs (a product with ones) go into the result as scale (S - zero X) in fp32,
-// the form in which the decode kernels take the scale and the zero point.  (The weights as two fp16 numbers, the
-// K tiles taken twice, lost bits of weights below 2e-3 and turned those beyond 65504 into NaN; four 8B river
-// blocks and 3 tokens took 900 us that way, 563 now.)
 //
 // Tile of C per workgroup (TM x TN), its WM x WN wavefronts, K tiles in flight in registers (PF) and
 // workgroups per CU (OCC, bounds the registers).
@@ -174,7 +168,6 @@ template <int TM_, int TN_, int WM_, int WN_, int PF_, int OCC_> struct GemmTile
   static constexpr int GR = NT / 8;                            // rows a staging round of the workgroup covers
   static constexpr int RA = TM / GR, RB = TN / GR;             // staging rounds per K tile
   static constexpr int LDS_BYTES = 2 * (TM + TN) * LDK * 2;    // two buffers each of A and B
-  static constexpr int LDS_FOLD = LDS_BYTES + 2 * TN * 4;      // ... and of the pairs of B's rows (codes, EXACT)
   static_assert((RA == 2 || RA == 4) && (RB == 2 || RB == 4) && RA >= RB && RA * GR == TM && RB * GR == TN,
                 "two or four staging rounds");
 };
@@ -201,14 +194,12 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t gemm_rsrc(const void *p) {
   return __builtin_amdgcn_make_buffer_rsrc((void *)p, 0, 0x7ffffff0, 0x00020000);
 }
 
-template <class T, bool W4, int EPI, bool EXACT = false>
+template <class T, bool W4, int EPI>
 __global__ __launch_bounds__(T::NT, T::OCC) void k_pf_gemm(const _Float16 *__restrict__ A, int lda, GemmB B, int N,
                                                            int K, int group, void *C, int ldc, int M, int m_tiles,
                                                            int k_split) {
   extern __shared__ __attribute__((aligned(16))) _Float16 pf_lds[];
   constexpr int TM = T::TM, TN = T::TN, PF = T::PF, GR = T::GR;
-  constexpr bool FOLD = EXACT && W4;
-  uint32_t *const pf_sz = (uint32_t *)((char *)pf_lds + T::LDS_BYTES);         // FOLD: two buffers of TN (scale, zero) pairs
   const int tid = threadIdx.x, lane = tid & 63;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6), wm = wv / T::WN, wn = wv % T::WN;
   // Workgroup -> (tile of C, slice of K).  Consecutive workgroup ids go round the 8 XCDs; the
@@ -284,12 +275,10 @@ __global__ __launch_bounds__(T::NT, T::OCC) void k_pf_gemm(const _Float16 *__res
     if (i >= RB) return;
     if constexpr (W4) {
       const uint32_t w = i == 0 ? fb[u][0].x : i == 1 ? fb[u][0].y : i == 2 ? fb[u][0].z : fb[u][0].w;
-      *(half8 *)(Bs + b_dst + i * 8) = FOLD ? codes8(w) : dequant8(w, bf16_lo(fsz[u]), bf16_hi(fsz[u]));
-      if (FOLD && i == 0 && tid % (8 / RB) == 0) pf_sz[buf * TN + tid / (8 / RB)] = fsz[u];
+      *(half8 *)(Bs + b_dst + i * 8) = dequant8(w, bf16_lo(fsz[u]), bf16_hi(fsz[u]));
     } else {
       const u32x4 w = fb[u][i & (RB - 1)];
-      if constexpr (EXACT) *(u32x4 *)(Bs + s_dst + i * GR * LDK) = w;
-      else *(half8 *)(Bs + s_dst + i * GR * LDK) = bf16x8_to_half8(make_uint4(w.x, w.y, w.z, w.w));
+      *(half8 *)(Bs + s_dst + i * GR * LDK) = bf16x8_to_half8(make_uint4(w.x, w.y, w.z, w.w));
     }
   };
 
@@ -318,12 +307,6 @@ __global__ __launch_bounds__(T::NT, T::OCC) void k_pf_gemm(const _Float16 *__res
   };
   auto body = [&](int kt, int u1, bool stage, bool load) {     // u1: the set of tile kt + 1
     const int cur = kt & 1;
-    f32x16 part[FOLD ? T::MB : 1][FOLD ? T::NB : 1], xsum[FOLD ? T::MB : 1];   // FOLD: the tile's sums
-    uint32_t sz[T::NB];
-    if constexpr (FOLD) {                          // (in front of the barrier, behind which the buffer may be written)
-#pragma unroll
-      for (int j = 0; j < T::NB; ++j) sz[j] = pf_sz[cur * TN + wn * T::NW + j * 32 + r32];
-    }
 #pragma unroll
     for (int ks = 0; ks < 4; ++ks) {
       if (ks == 3) lds_barrier();
@@ -340,14 +323,8 @@ __global__ __launch_bounds__(T::NT, T::OCC) void k_pf_gemm(const _Float16 *__res
 #pragma unroll
         for (int j = 0; j < T::NB; ++j) {
           const half8 &a = xa[ks & 1][i], &b = xb[ks & 1][j];
-          if constexpr (FOLD) part[i][j] = mfma16(a, b, ks ? part[i][j] : f32x16{});
-          else acc[i][j] = EXACT ? mfma16_bf16(a, b, acc[i][j]) : mfma16(a, b, acc[i][j]);
+          acc[i][j] = mfma16(a, b, acc[i][j]);
         }
-      if constexpr (FOLD) {
-        const half8 ones = (half8)(_Float16)1.f;
-#pragma unroll
-        for (int i = 0; i < T::MB; ++i) xsum[i] = mfma16(xa[ks & 1][i], ones, ks ? xsum[i] : f32x16{});
-      }
       // the step's conversions, LDS writes and loads go between its MFMAs, not in front of them
 #pragma unroll
       for (int q = 0; q < T::MB * T::NB; ++q) {
@@ -357,15 +334,6 @@ __global__ __launch_bounds__(T::NT, T::OCC) void k_pf_gemm(const _Float16 *__res
         __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);      // global load
       }
       __builtin_amdgcn_sched_barrier(0);
-    }
-    if constexpr (FOLD) {
-#pragma unroll
-      for (int i = 0; i < T::MB; ++i)
-#pragma unroll
-        for (int j = 0; j < T::NB; ++j)
-#pragma unroll
-          for (int r = 0; r < 16; ++r)
-            acc[i][j][r] = fmaf(bf16_lo(sz[j]), fmaf(-bf16_hi(sz[j]), xsum[i][r], part[i][j][r]), acc[i][j][r]);
     }
   };
 #pragma unroll
@@ -424,6 +392,352 @@ done:
           }
         }
       }
+  }
+}
+
+// ---- GEMM of few rows
+//
+// The same product for up to 128 rows.  k_pf_gemm's 128 x 128 tile is bound there by neither the stream nor the
+// matrix cores but by the way of a K tile through the registers: load, convert, write to LDS, barrier, read
+// (1500 cycles for 128 x 128 x 64, of which 510 with the matrix cores at work, bf16 or codes alike).  Here
+//  * A and B go from global memory to LDS directly (buffer loads with the LDS as their destination), up to
+//    five stages of them in flight without a register: 64 KB of weights per CU and more;
+//  * a tile is 32 MB rows of A (no products for padding rows beyond 31; rows that do not exist are not
+//    loaded) x 128 rows of B; each of the eight wavefronts owns 32 rows of B and half of a stage's columns, so
+//    that B is converted once, in the registers its product reads it from;
+//  * the operands of a stage are read from LDS during the products of the one before; one barrier a stage.
+// A stage is 64 columns of bf16, or 128 of codes with their (scale, zero) pairs.  LDS rows are 128 bytes
+// of 16-byte pieces (codes: 64), the piece c of row r in place c ^ (r / 2) % 8 (codes: c ^ (r / 4) % 4): the
+// 16 lanes that a 16-byte read serves together then touch every bank once.
+// Measured (us in a prefill of 77 tokens at the 8B shape, 128 x 128 tile and now; bf16 / codes): QKV 18.2 / 16.6 and 15.7 /
+// 17.0, O 12.6 / 14.4 and 11.6 / 14.4, gate/up 49.0 / 47.8 and 45.3 / 39.2, down 28.2 / 25.5 and 23.8 / 22.4.  What bounds it now: bf16
+// -- the stream at the clock that is left beside the products (1.7 GHz: 5.2 TB/s in gate/up); codes -- nothing
+// alone: of 1900 cycles a stage the conversions take 770 of a SIMD, the products as many, the loads 1200 of the
+// CU's way to the L2 (30 bytes a cycle, also with 8 workgroups on the chip: a workgroup reads all of A).  A launch that
+// is short costs 3 us from its start to the first stage and 1 us behind the last one.  Tried: beginning at different
+// stages in different workgroups (no change), A kept in tiles of 64 columns (no
+// change).
+//
+// EXACT (short prompts, whose activations stay in 32 bits): dense -- A holds bf16 rows, the three parts of the
+// activations one under the other (see split3), multiplied with the bf16 weights as they are, every product exact; codes
+// -- A holds fp16 rows, as the decode kernels round them, multiplied with the codes as they are; a K tile's
+// sums S and the sum X of its inputs (a product with ones) go into the result as scale (S - zero X) in fp32,
+// the form in which the decode kernels take the scale and the zero point.  (The weights as two fp16 numbers, the
+// K tiles taken twice, lost bits of weights below 2e-3 and turned those beyond 65504 into NaN; four 8B river
+// blocks and 3 tokens took 900 us that way, 563 now.)
+//
+template <int MB_, bool W4> struct RowsTile {
+  static constexpr int MB = MB_, TM = 32 * MB, TN = 128, NT = 512;
+  static constexpr int COLS = W4 ? 128 : 64;                     // columns of a stage
+  static constexpr int A_BYTES = TM * COLS * 2, CODES = TN * COLS / 2, PAIRS = 2048;
+  static constexpr int STAGE = A_BYTES + (W4 ? CODES + PAIRS : TN * COLS * 2);
+  static constexpr int S = STAGE * 5 <= 160 * 1024 ? 5 : STAGE * 4 <= 160 * 1024 ? 4 : 3;
+  static constexpr int LDR = 136;                                // floats of a row of sums: rows 4 apart, half a wavefront each, do not meet in a bank
+  static constexpr int SUMS = 2 * TM * LDR * 4;
+  static constexpr int LDS_BYTES = S * STAGE > SUMS ? S * STAGE : SUMS;
+  static constexpr int A_ITEMS = A_BYTES / 1024;                 // loads of a wavefront that a stage of A is
+  static constexpr int ITEMS = A_ITEMS + 16;                     // ... and B's (codes: 8, their pairs: 8)
+  static_assert(LDS_BYTES <= 160 * 1024, "LDS of a CU");
+};
+
+// 64 lanes x 16 (4) bytes from rsrc + voff + soff to LDS at lds + 16 (4) * lane.  In assembly, because the
+// compiler makes every LDS read wait for all such loads in flight; rows_wait counts them instead.
+template <bool STREAM>
+__device__ __forceinline__ void load_lds16(unsigned lds, unsigned voff, const u32x4 &rsrc, unsigned soff) {
+  if constexpr (STREAM)
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen nt lds"
+                 :: "s"(lds), "v"(voff), "s"(rsrc), "s"(soff) : "memory", "m0");
+  else
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
+                 :: "s"(lds), "v"(voff), "s"(rsrc), "s"(soff) : "memory", "m0");
+}
+__device__ __forceinline__ void load_lds4(unsigned lds, unsigned voff, const u32x4 &rsrc, unsigned soff) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dword %1, %2, %3 offen lds"
+               :: "s"(lds), "v"(voff), "s"(rsrc), "s"(soff) : "memory", "m0");
+}
+// All but this wavefront's N last loads have landed and its LDS operations are done; then the workgroup.
+template <int N>
+__device__ __forceinline__ void rows_wait() {
+  static_assert(N < 64, "six bits");
+  asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" :: "n"(N) : "memory");
+}
+// ... the loads of `later` stages, N of them each (at most MOST stages)
+template <int N, int MOST>
+__device__ __forceinline__ void rows_wait_stages(int later) {
+  if constexpr (MOST > 0) {
+    if (later >= MOST) rows_wait<N * MOST>();
+    else rows_wait_stages<N, MOST - 1>(later);
+  } else {
+    rows_wait<0>();
+  }
+}
+__device__ __forceinline__ u32x4 uniform_rsrc(const void *p) {
+  const uint64_t a = (uint64_t)p;
+  return u32x4{(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)a),
+               (uint32_t)__builtin_amdgcn_readfirstlane((int)((uint32_t)(a >> 32) & 0xffffu)), 0x7ffffff0u, 0x00020000u};
+}
+
+// Row r of B's tile -> matrix and row, for `run` rows that start at r (8, or 16 of codes).  SwiGLU: 16 rows of the
+// gate and 16 of the up matrix in turn, so that lanes l and l + 16 of a wavefront hold the factors of an output.
+template <int EPI>
+__device__ __forceinline__ void rows_b_row(const GemmB &B, int n_tile, int r, int run, int N, int &mat, int &row) {
+  if constexpr (EPI == PF_SWIGLU) {
+    mat = (r >> 4) & 1;
+    row = min(n_tile * 64 + (r >> 5) * 16 + (r & 15), B.rows[0] - run);
+  } else {
+    gemm_b_row(B, min(n_tile * 128 + r, N - run), N, mat, row);
+  }
+}
+
+// How the host deals a product out (no division in front of the first load): one workgroup per (tile of N, slice of K).
+constexpr int kRowsMost = 128;  // rows of A that one tile takes
+struct RowsDeal {
+  int rows32;                 // rows that exist of every 32 (short prompts; else 32)
+  int n_tiles, k_split;
+  uint32_t split_inv;         // ceil(2^32 / k_split) (k_split = 1: not used): workgroup / k_split is a high product
+  int st_base, st_rem;        // stages of a slice: st_base, and one more for the first st_rem
+};
+template <int MB, bool W4, int EPI, bool EXACT>
+__global__ __launch_bounds__(512, 1) void k_pf_gemm_rows(const _Float16 *__restrict__ A, int lda, GemmB B, int N, int K,
+                                                         int group, void *C, int ldc, int M, RowsDeal deal) {
+  typedef RowsTile<MB, W4> T;
+  constexpr bool FOLD = EXACT && W4;
+  constexpr int S = T::S, KS = W4 ? 4 : 2;                      // MFMA steps of a wavefront per stage
+  constexpr int NJ = (T::ITEMS + 7) / 8, ODD = T::ITEMS % 8;    // loads per wavefront and stage (ODD: the first ODD wavefronts')
+  extern __shared__ __attribute__((aligned(16))) char rows_lds[];
+  const unsigned lds0 = (unsigned)(size_t)(__attribute__((address_space(3))) char *)rows_lds;
+  const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int nb = wv & 3, half = wv >> 2;                        // its rows of B, its half of a stage's columns
+  const int col = blockIdx.x;
+  if (col >= deal.n_tiles * deal.k_split) return;
+  const int n_tile = deal.k_split == 1 ? col : (int)__umulhi((uint32_t)col, deal.split_inv), ks_i = col - n_tile * deal.k_split;
+  const int st0 = ks_i * deal.st_base + min(ks_i, deal.st_rem), ns = deal.st_base + (ks_i < deal.st_rem ? 1 : 0);
+
+  // what this wavefront loads per stage: item wv + 8 j = 1 KB of the stage (A's rows, B's rows; the pairs last)
+  u32x4 rs[NJ];
+  unsigned vo[NJ];
+  const int gpr = W4 ? (K + group - 1) / group : 0;
+  int g_at = 0, g_left = 0;                                     // this lane's (scale, zero) pair of the next stage
+  const int tpg = W4 ? group / 64 : 1, pair_half = lane & 1;
+  if constexpr (W4) {                                           // (counted on from there, no division per stage)
+    g_at = st0 ? (2 * st0 + pair_half) / tpg : tpg == 1 ? pair_half : 0;
+    g_left = tpg - (2 * st0 + pair_half - g_at * tpg);
+  }
+#pragma unroll
+  for (int j = 0; j < NJ; ++j) {
+    const int it = wv + 8 * j;
+    if (it < T::A_ITEMS) {
+      const int sub = it / (4 * MB), r = (it % (4 * MB)) * 8 + (lane >> 3);         // W4: two tiles of 64 columns
+      const int piece = (lane & 7) ^ ((r >> 1) & 7);
+      rs[j] = uniform_rsrc((const char *)A + (size_t)st0 * T::COLS * 2);
+      // (rows that do not exist lie beyond the descriptor's range: zero, without an access)
+      vo[j] = r < M && (!EXACT || (r & 31) < deal.rows32) ? (unsigned)r * (unsigned)lda * 2u + sub * 128 + piece * 16 : 0xc0000000u;
+    } else if (!W4) {
+      const int r0 = (it - T::A_ITEMS) * 8, r = r0 + (lane >> 3), piece = (lane & 7) ^ ((r >> 1) & 7);
+      int mat, row;
+      rows_b_row<EPI>(B, n_tile, min(r0, 120), 8, N, mat, row);
+      rs[j] = uniform_rsrc((const char *)B.w[mat] + ((size_t)row * K + (size_t)st0 * 64) * 2);
+      vo[j] = (unsigned)(lane >> 3) * (unsigned)K * 2u + piece * 16;
+    } else {
+      const int q = (it - T::A_ITEMS) & 7;
+      int mat, row;
+      rows_b_row<EPI>(B, n_tile, q * 16, 16, N, mat, row);
+      if (it < T::A_ITEMS + 8) {                                // 16 rows x 64 bytes of codes
+        const int r = lane >> 2, piece = (lane & 3) ^ ((r >> 2) & 3);
+        rs[j] = uniform_rsrc((const char *)B.w[mat] + (size_t)row * (K >> 1) + (size_t)st0 * 64);
+        vo[j] = (unsigned)r * (unsigned)(K >> 1) + piece * 16;
+      } else {                                                  // their pairs: lane -> row lane / 2 % 16, 64 columns lane % 2
+        rs[j] = uniform_rsrc((const char *)B.sz[mat] + (size_t)row * gpr * 4);
+        vo[j] = (unsigned)((lane >> 1) & 15) * (unsigned)gpr * 4u;
+      }
+    }
+  }
+  int at = 0;                                                   // the next stage to load
+  // the slice's last stage has 64 columns only
+  const bool ragged = W4 && (K & 64) && ks_i == deal.k_split - 1;
+                              // this workgroup is the only reader of its rows of B
+  auto issue_as = [&](int buf, auto last) {                     // last: of a ragged row (codes)
+    constexpr bool CUT = decltype(last)::value;
+    const unsigned dst = lds0 + (unsigned)buf * T::STAGE;
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) {
+      const int it = wv + 8 * j;
+      if (ODD && j == NJ - 1 && wv >= ODD) continue;
+      if (W4 && j == NJ - 1) {                                  // (codes: whole rounds of eight; the last one is the pairs)
+        load_lds4(dst + T::A_BYTES + T::CODES + wv * 256, vo[j] + (unsigned)min(g_at, gpr - 1) * 4u, rs[j], 0);
+        continue;
+      }
+      unsigned v = vo[j];
+      if constexpr (CUT) {                                      // pieces beyond the row: its last 64 columns again
+        if (j < MB) v -= it >= 4 * MB ? 128u : 0u;
+        else v -= (v - (unsigned)(lane >> 2) * (unsigned)(K >> 1)) & 32u;
+      }
+      const unsigned along = (unsigned)at * (W4 && j >= MB ? 64u : T::COLS * 2u);          // columns, of codes or 16 bits
+      if (8 * j >= T::A_ITEMS) load_lds16<true>(dst + it * 1024u, v, rs[j], along);
+      else load_lds16<false>(dst + it * 1024u, v, rs[j], along);
+    }
+  };
+  auto issue = [&](int buf) {                                   // the next stage of the slice into LDS buffer buf
+    if (W4 && ragged && at == ns - 1) issue_as(buf, IC<1>{});
+    else issue_as(buf, IC<0>{});
+    if constexpr (W4) {                                         // (two steps of 64 columns)
+      g_left -= 2;
+      if (g_left <= 0) { g_left += tpg; ++g_at; }
+      if (g_left <= 0) { g_left += tpg; ++g_at; }
+    }
+    ++at;
+  };
+  // all loads of stage s have landed, everybody's reads of stage s - 1 are done (`later` stages are in flight behind it)
+  auto landed = [&](int later) {
+    if constexpr (ODD) {
+      if (wv < ODD) rows_wait_stages<NJ, S - 1>(later);
+      else rows_wait_stages<NJ - 1, S - 1>(later);
+    } else {
+      rows_wait_stages<NJ, S - 1>(later);
+    }
+  };
+
+  f32x16 acc[MB];
+#pragma unroll
+  for (int i = 0; i < MB; ++i)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[i][r] = 0.f;
+
+  // Operands: lane (r32, g) of step ks reads piece ks * 2 + g of a 64-column row, ks = 2 half, 2 half + 1; codes:
+  // columns 32 g + 8 ks .. + 7 of this half's 64, piece 4 g + ks of A, word ks of its 16-byte piece of codes.
+  const int r32 = lane & 31, g = lane >> 5, sx = (r32 >> 1) & 7;
+  unsigned pa[KS];
+#pragma unroll
+  for (int k = 0; k < KS; ++k)
+    pa[k] = r32 * 128u + (((W4 ? 4 * g + k : (2 * half + k) * 2 + g) ^ sx) * 16u) + (W4 ? half * (MB * 4096u) : 0u);
+  const unsigned pc = T::A_BYTES + (nb * 32 + r32) * 64u + (((2 * half + g) ^ ((r32 >> 2) & 3)) * 16u);
+  const unsigned pz = T::A_BYTES + T::CODES + (2 * nb + (r32 >> 4)) * 256u + (r32 & 15) * 8u + half * 4u;
+  half8 xa[2][KS][MB], xb[2][W4 ? 1 : KS];
+  uint32_t sz[2];
+  auto frags = [&](unsigned at, int f) {
+    const char *const b = rows_lds + at;
+#pragma unroll
+    for (int k = 0; k < KS; ++k) {
+      if constexpr (!W4) xb[f][k] = *(const half8 *)(b + T::A_BYTES + nb * 4096 + pa[k]);
+      else if (k == 0) { xb[f][0] = *(const half8 *)(b + pc); sz[f] = *(const uint32_t *)(b + pz); }
+#pragma unroll
+      for (int i = 0; i < MB; ++i) xa[f][k][i] = *(const half8 *)(b + pa[k] + i * 4096);
+    }
+  };
+  // step k of stage set f: B's operand as the product wants it
+  auto operand = [&](int f, int k) -> half8 {
+    if constexpr (W4) {
+      const u32x4 w4 = __builtin_bit_cast(u32x4, xb[f][0]);
+      const uint32_t w = k == 0 ? w4.x : k == 1 ? w4.y : k == 2 ? w4.z : w4.w;
+      return FOLD ? codes8(w) : dequant8(w, bf16_lo(sz[f]), bf16_hi(sz[f]));
+    } else {
+      const u32x4 v = __builtin_bit_cast(u32x4, xb[f][k]);
+      return EXACT ? xb[f][k] : bf16x8_to_half8(make_uint4(v.x, v.y, v.z, v.w));
+    }
+  };
+  // The products of set f, beside each step's the conversion of the next one's operand (the last step: of set f ^ 1's
+  // first): two wavefronts share a SIMD and come out of the same barrier, so that one's conversions do not by
+  // themselves fall into the other's products.
+  half8 b;
+  auto products = [&](int f, bool more) {
+    f32x16 part[FOLD ? MB : 1], xsum[FOLD ? MB : 1];
+    const half8 ones = (half8)(_Float16)1.f;
+    const float s = bf16_lo(sz[f]), z = bf16_hi(sz[f]);
+#pragma unroll
+    for (int k = 0; k < KS; ++k) {
+      half8 nx = b;
+      if (k + 1 < KS) nx = operand(f, k + 1);
+      else if (more) nx = operand(f ^ 1, 0);
+#pragma unroll
+      for (int i = 0; i < MB; ++i) {
+        if constexpr (FOLD) {
+          part[i] = mfma16(xa[f][k][i], b, k ? part[i] : f32x16{});
+          xsum[i] = mfma16(xa[f][k][i], ones, k ? xsum[i] : f32x16{});
+        } else {
+          acc[i] = EXACT ? mfma16_bf16(xa[f][k][i], b, acc[i]) : mfma16(xa[f][k][i], b, acc[i]);
+        }
+      }
+      if constexpr (!EXACT) {
+#pragma unroll
+        for (int q = 0; q < MB; ++q) {
+          __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                    // one MFMA
+          __builtin_amdgcn_sched_group_barrier(0x002, (20 + MB - 1) / MB, 0);   // VALU
+        }
+      }
+      b = nx;
+    }
+    if constexpr (FOLD) {
+#pragma unroll
+      for (int i = 0; i < MB; ++i)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[i][r] = fmaf(s, fmaf(-z, xsum[i][r], part[i][r]), acc[i][r]);
+    }
+  };
+
+#pragma unroll
+  for (int s = 0; s < S; ++s)
+    if (s < ns) issue(s);
+  landed(min(ns - 1, S - 1));
+  frags(0, 0);
+  int buf = 0;                                                   // buffer of the stage at work
+  auto body = [&](int s, int f) {                                // (s + 1 < ns: no LDS read behind a branch, whose end would wait for all)
+    const int next = buf + 1 == S ? 0 : buf + 1;
+    if (s + S <= ns) landed(S - 2);
+    else landed(ns - 2 - s);
+    frags(next * T::STAGE, f ^ 1);
+    __builtin_amdgcn_sched_barrier(0);
+    if (s + S < ns) issue(buf);
+    __builtin_amdgcn_sched_barrier(0);
+    products(f, true);
+    __builtin_amdgcn_sched_barrier(0);
+    buf = next;
+  };
+  b = operand(0, 0);
+  const bool live = !(ragged && half);                           // (of the last stage: its second half does not exist)
+  int s = 0;
+  for (; s + 2 < ns; s += 2) { body(s, 0); body(s + 1, 1); }
+  if (s + 1 < ns) {
+    body(s, 0);
+    if (live) products(1, false);
+  } else if (live) {
+    products(0, false);
+  }
+
+  // The halves' sums meet in LDS, row-major, and leave in 16-byte stores.  (A loop, not unrolled: a launch fetches its
+  // code from the caches anew, and the sums of every register in their own instructions were most of it.)
+  constexpr int LDR = T::LDR;
+  rows_wait<0>();
+  {
+    float *const mine = (float *)rows_lds + (half * T::TM + (lane >> 5) * 4) * LDR + nb * 32 + r32;
+#pragma unroll
+    for (int i = 0; i < MB; ++i)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) mine[(i * 32 + (r >> 2) * 8 + (r & 3)) * LDR] = acc[i][r];
+  }
+  lds_barrier();
+  const float *const sums = (const float *)rows_lds;
+  auto sum4 = [&](int row, int c) {
+    const f32x4 p = *(const f32x4 *)(sums + row * LDR + c), q = *(const f32x4 *)(sums + (T::TM + row) * LDR + c);
+    return p + q;
+  };
+  if constexpr (EPI == PF_SWIGLU) {
+#pragma unroll 1
+    for (int e = tid; e < T::TM * 16; e += 512) {                // four outputs: 16 columns of gate, then of up, per wavefront's 32
+      const int row = e >> 4, c = (e & 15) * 4, at = (c >> 4) * 32 + (c & 15), cc = n_tile * 64 + c;
+      if (row >= M || cc >= ldc) continue;
+      const f32x4 gt = sum4(row, at), up = sum4(row, at + 16);
+      half4 o;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) o[q] = (_Float16)(gt[q] / (1.0f + expf(-gt[q])) * up[q]);
+      *(half4 *)((_Float16 *)C + (size_t)row * ldc + cc) = o;
+    }
+  } else {
+    float *const out = (float *)C + (size_t)ks_i * M * ldc;
+#pragma unroll 1
+    for (int e = tid; e < T::TM * 32; e += 512) {
+      const int row = e >> 5, c = (e & 31) * 4, cc = n_tile * 128 + c;
+      if (row < M && cc < N) *(f32x4 *)(out + (size_t)row * ldc + cc) = sum4(row, c);
+    }
   }
 }
 

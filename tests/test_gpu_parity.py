@@ -765,6 +765,23 @@ def test_gemm_prefill_tiles_and_k_slices_equal_serial_prefill_closely(cfg, n_pro
         assert relerr(a, np.asarray(b, np.float64)) <= tol
 
 
+@pytest.mark.parametrize("cfg0,n_prompt", [(GEMM_SHAPES[1], 32), (GEMM_SHAPES[3], 64), (GEMM_SHAPES[3], 65), (GEMM_SHAPES[3], 96),
+                                           (GEMM_SHAPES[4], 97), (GEMM_SHAPES[2], 128), (GEMM_SHAPES[0], 129)],
+                         ids=lambda v: v.name if hasattr(v, "name") else str(v))
+def test_gemm_prefill_few_rows_match_oracle(cfg0, n_prompt):
+    """The GEMM of up to 128 rows on both sides of its row blocks of 32, with rows of B that end in half a tile of
+    128 and contractions that end in half a stage of 128 codes."""
+    test_gemm_prefill_matches_oracle(cfg0, n_prompt)
+
+
+@pytest.mark.parametrize("cfg,n_prompt", [(DEEP_PF.with_(d_ffn=8256), 77), (DEEP_PF.with_(river_group=192), 128), (WIDE_PF, 40)],
+                         ids=["deep-77", "deep-g192-128", "wide-40"])
+def test_gemm_prefill_few_rows_in_k_slices_equal_serial_prefill_closely(cfg, n_prompt):
+    """... with more stages than fit in LDS at once, K slices of uneven length, the last one ending in half a
+    stage, and groups that are no power of two."""
+    test_gemm_prefill_tiles_and_k_slices_equal_serial_prefill_closely(cfg, n_prompt)
+
+
 # ------------------------------------------------------------ backbone offloading
 
 @pytest.mark.parametrize("mode", MODES, ids=MODE_IDS)
