@@ -969,6 +969,16 @@ static int create_impl(const river_config *cfg, const river_weights *w, const ri
         pfg.push_back({(const void *)pf::k_pf_gemm_rows<MB, true, pf::PF_SWIGLU, false>, codes});
       };
       rows(IC<1>{}); rows(IC<2>{}); rows(IC<3>{}); rows(IC<4>{});
+      auto attn = [&](auto hd) {
+        constexpr int HD = decltype(hd)::value;
+        pfg.push_back({(const void *)pf::k_pf_attn<HD, 1, 1>, pf::attn_lds_bytes(HD, 1)});
+        pfg.push_back({(const void *)pf::k_pf_attn<HD, 2, 1>, pf::attn_lds_bytes(HD, 1)});
+        pfg.push_back({(const void *)pf::k_pf_attn<HD, 4, 1>, pf::attn_lds_bytes(HD, 1)});
+        pfg.push_back({(const void *)pf::k_pf_attn<HD, 1, 2>, pf::attn_lds_bytes(HD, 2)});
+        pfg.push_back({(const void *)pf::k_pf_attn<HD, 2, 2>, pf::attn_lds_bytes(HD, 2)});
+        pfg.push_back({(const void *)pf::k_pf_attn<HD, 4, 2>, pf::attn_lds_bytes(HD, 2)});
+      };
+      attn(IC<64>{}); attn(IC<128>{});
       pfg.push_back({(const void *)pf::k_pf_gemm_rows<3, false, pf::PF_STORE, true>, pf::RowsTile<3, false>::LDS_BYTES});
       pfg.push_back({(const void *)pf::k_pf_gemm_rows<1, true, pf::PF_STORE, true>, pf::RowsTile<1, true>::LDS_BYTES});
       for (const auto &f : pfg)
@@ -1227,6 +1237,7 @@ static int prefill_short(river_ctx *x, const int32_t *tokens, int n, int ep) {
   float *h = (float *)(x->ws + y.pf_h), *big = (float *)(x->ws + y.pf_big);
   _Float16 *x16 = (_Float16 *)(x->ws + y.pf_x16), *q32 = (_Float16 *)(x->ws + y.pf_q16), *a16 = (_Float16 *)(x->ws + y.pf_a16);
   const int m_qkv[3] = {M_WQ, M_WK, M_WV}, m_o[1] = {M_WO}, m_gu[2] = {M_GATE, M_UP}, m_d[1] = {M_DOWN};
+  const int rope_wgs = ((c.n_q_heads + c.n_kv_heads) * (c.head_dim / 8) + c.n_kv_heads * c.head_dim / 4 + 255) / 256;   // (see k_pf_rope_store)
   const dim3 blk(512);
   auto attn = c.head_dim == 128 ? pf::k_pf_attn_rows<128> : pf::k_pf_attn_rows<64>;
   for (int c0 = 0; c0 < n; c0 += pf::kShort) {
@@ -1248,7 +1259,7 @@ static int prefill_short(river_ctx *x, const int32_t *tokens, int n, int ep) {
       const DevLayer &W = x->layers_h[l];
       norm(river, l ? nullptr : tok_src, W.attn_norm, D.hidden + (size_t)l * d, last);
       parts = launch_gemm_exact(x, l, river, m_qkv, 3, x16, d, big, m);
-      pf::k_pf_rope_store<true><<<dim3(m), blk, 0, s>>>(big, parts, pf::kShort, D.rope, c.n_q_heads, c.n_kv_heads, c.head_dim, c0, l,
+      pf::k_pf_rope_store<true><<<dim3(m, rope_wgs), dim3(256), 0, s>>>(big, parts, pf::kShort, D.rope, c.n_q_heads, c.n_kv_heads, c.head_dim, c0, l,
                                                         c.max_seq, D.kcache, D.vcache, D.kv_f16, q32);
       if (l == L - 1 && last < 0) break;                     // (a pass before the last: its keys and values are all that is read)
       attn<<<dim3((c.n_q_heads + 3) / 4, m), dim3(256), 0, s>>>((const float *)q32, D.kcache, D.vcache, D.kv_f16, c.n_q_heads,
@@ -1268,6 +1279,45 @@ static int prefill_short(river_ctx *x, const int32_t *tokens, int n, int ep) {
   return RIVER_OK;
 }
 
+// Attention of a chunk's queries: as many query heads of a kv head per workgroup (4, 2 or 1) as divide them, two tiles of
+// keys a step where one a step makes no more workgroups than there are CUs (us, one / two tiles, 32 heads on 8 of head size
+// 128: 77 rows 9.9 / 9.2, 512 25.2 / 18.5, 1024 43 / 31, 2048 80 / 67, 2560 98 / 106).  Passes of more than 2048 rows have that
+// few workgroups with few heads only (8 on 2: 3072 rows 105 / 69) and keep one tile all the same: a long prompt's cache
+// is held to the per-position prefill's to less than one rounding of its largest values, and that bar
+// is met by the probabilities as one chain rounds them.
+constexpr int kAttnPairRows = 2048;
+template <int HD, int HG>
+static void launch_attn_t(river_ctx *x, int l, const void *kc, const void *vc, int c0, int m, const _Float16 *q16, _Float16 *o16) {
+  const river_config &c = x->cfg;
+  auto go = [&](auto ks) {
+    constexpr int KS = decltype(ks)::value, QT = 256 / HG / KS;
+    pf::k_pf_attn<HD, HG, KS><<<dim3(c.n_q_heads / HG, (m + QT - 1) / QT), dim3(512), pf::attn_lds_bytes(HD, KS), x->stream>>>(
+        q16, kc, vc, x->dev.kv_f16, c.n_q_heads, c.n_kv_heads, l, c.max_seq, c0, m, o16);
+  };
+  const int wgs = c.n_q_heads / HG * ((m + 256 / HG - 1) / (256 / HG));
+  if (wgs <= x->grid_persist && m <= kAttnPairRows) go(IC<2>{});
+  else go(IC<1>{});
+}
+static int heads_per_group(const river_config &c) {
+  const int rep = c.n_q_heads / c.n_kv_heads;
+  return rep % 4 == 0 ? 4 : rep % 2 == 0 ? 2 : 1;
+}
+static void launch_attn(river_ctx *x, int l, const void *kc, const void *vc, int c0, int m, const _Float16 *q16, _Float16 *o16) {
+  const int hg = heads_per_group(x->cfg);
+  auto f = x->cfg.head_dim == 128 ? (hg == 4 ? launch_attn_t<128, 4> : hg == 2 ? launch_attn_t<128, 2> : launch_attn_t<128, 1>)
+                                  : (hg == 4 ? launch_attn_t<64, 4> : hg == 2 ? launch_attn_t<64, 2> : launch_attn_t<64, 1>);
+  f(x, l, kc, vc, c0, m, q16, o16);
+}
+// ... and of the last position P alone, in splits of at least 128 positions
+static void launch_attn_last(river_ctx *x, int l, const void *kc, const void *vc, int P, const _Float16 *q16, _Float16 *o16) {
+  const river_config &c = x->cfg;
+  const int hg = heads_per_group(c), splits = std::min(kMaxSplits, (P + 128) / 128);
+  auto k = c.head_dim == 128 ? (hg == 4 ? pf::k_pf_attn_last<128, 4> : hg == 2 ? pf::k_pf_attn_last<128, 2> : pf::k_pf_attn_last<128, 1>)
+                             : (hg == 4 ? pf::k_pf_attn_last<64, 4> : hg == 2 ? pf::k_pf_attn_last<64, 2> : pf::k_pf_attn_last<64, 1>);
+  k<<<dim3(c.n_q_heads / hg, splits), dim3(256 * hg), 0, x->stream>>>(q16, kc, vc, x->dev.kv_f16, c.n_q_heads, c.n_kv_heads, l, c.max_seq, P,
+                                                                splits, x->dev.part_o, x->dev.part_ml, o16);
+}
+
 // Prefill phase on the matrix cores: the prompt in equal chunks of up to pf_rows tokens, every block
 // as MFMA GEMMs over the chunk (see river_prefill.h); blocks above ep run as river twins.
 static int prefill_gemm(river_ctx *x, int seq, const int32_t *tokens, int n, int ep) {
@@ -1282,6 +1332,7 @@ static int prefill_gemm(river_ctx *x, int seq, const int32_t *tokens, int n, int
   _Float16 *a16 = (_Float16 *)(x->ws + y.pf_a16);
   char *kc = (char *)D.kcache + (size_t)seq * y.cache_bytes, *vc = (char *)D.vcache + (size_t)seq * y.cache_bytes;
   const int m_qkv[3] = {M_WQ, M_WK, M_WV}, m_o[1] = {M_WO}, m_gu[2] = {M_GATE, M_UP}, m_d[1] = {M_DOWN};
+  const int rope_wgs = ((c.n_q_heads + c.n_kv_heads) * (c.head_dim / 8) + c.n_kv_heads * c.head_dim / 4 + 255) / 256;   // (see k_pf_rope_store)
   const int chunks = (n + y.pf_rows - 1) / y.pf_rows, step = std::min(y.pf_rows, ((n + chunks - 1) / chunks + 255) / 256 * 256);
   for (int c0 = 0; c0 < n; c0 += step) {
     const int m = std::min(step, n - c0);
@@ -1301,7 +1352,7 @@ static int prefill_gemm(river_ctx *x, int seq, const int32_t *tokens, int n, int
       pf::k_pf_norm<false><<<dim3(m), rowwise, 0, s>>>(h, l ? nullptr : tok_src, D.tok_emb, big, parts, m, W.attn_norm, d, c.rms_eps, x16,
                                                 D.hidden + (size_t)l * d, last, 0);
       parts = launch_gemm<pf::PF_STORE>(x, l, river, m_qkv, 3, x16, d, big, m);
-      pf::k_pf_rope_store<false><<<dim3(m), rowwise, 0, s>>>(big, parts, m, D.rope, c.n_q_heads, c.n_kv_heads, c.head_dim, c0, l,
+      pf::k_pf_rope_store<false><<<dim3(m, rope_wgs), dim3(256), 0, s>>>(big, parts, m, D.rope, c.n_q_heads, c.n_kv_heads, c.head_dim, c0, l,
                                                       c.max_seq, kc, vc, D.kv_f16, q16);
       // Behind the last block's keys and values only the last prompt position goes on (its h(L) is the
       // head's input, nobody reads the others'): from there on the last block is one row of the last
@@ -1310,13 +1361,8 @@ static int prefill_gemm(river_ctx *x, int seq, const int32_t *tokens, int n, int
       const bool tail = l == L - 1 && m > pf::TileM::TM;
       if (l == L - 1 && last < 0) break;
       const int t0 = tail ? last : 0, rows = tail ? 1 : m;
-      // attention: as many query heads of a kv head per workgroup (4, 2 or 1) as divide them
-      const int rep = c.n_q_heads / c.n_kv_heads, hg = rep % 4 == 0 ? 4 : rep % 2 == 0 ? 2 : 1, qt = 256 / hg;
-      const int qt0 = t0 / qt * qt;
-      auto attn = c.head_dim == 128 ? (hg == 4 ? pf::k_pf_attn<128, 4> : hg == 2 ? pf::k_pf_attn<128, 2> : pf::k_pf_attn<128, 1>)
-                                    : (hg == 4 ? pf::k_pf_attn<64, 4> : hg == 2 ? pf::k_pf_attn<64, 2> : pf::k_pf_attn<64, 1>);
-      attn<<<dim3(c.n_q_heads / hg, (m - qt0 + qt - 1) / qt), dim3(512), 0, s>>>(q16, kc, vc, D.kv_f16, c.n_q_heads, c.n_kv_heads,
-                                                                                 l, c.max_seq, c0, m, qt0, x16);
+      if (tail) launch_attn_last(x, l, kc, vc, c0 + last, q16 + (size_t)last * qd, x16 + (size_t)last * qd);
+      else launch_attn(x, l, kc, vc, c0, m, q16, x16);
       parts = launch_gemm<pf::PF_STORE>(x, l, river, m_o, 1, x16 + (size_t)t0 * qd, qd, big, rows);
       pf::k_pf_norm<false><<<dim3(rows), rowwise, 0, s>>>(h, nullptr, nullptr, big, parts, rows, W.ffn_norm, d, c.rms_eps, x16, nullptr, -1, t0);
       (void)launch_gemm<pf::PF_SWIGLU>(x, l, river, m_gu, 2, x16 + (size_t)t0 * d, d, a16, rows);

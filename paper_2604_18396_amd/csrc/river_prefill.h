@@ -770,13 +770,19 @@ __device__ __forceinline__ Run8 ld_gain8(const void *gain, int k, bool wide) {
   for (int e = 0; e < 8; ++e) x.v[e] = Store<1>::ld(gain, k + e);
   return x;
 }
-// f(element, exists) for every one of n planes, in order, four at a time so that their loads go out
-// together (an element beyond the last plane is plane 0's again, for f to leave out)
-template <class F>
-__device__ __forceinline__ void add_planes(const float *p, size_t stride, int n, F f) {
-  for (int j = 0; j < n; j += 4) {
+// f(element, exists) for every one of n planes, in order, the loads of up to MOST together (one, four or eight
+// by what is left: an element beyond the last plane is plane 0's again, for f to leave out)
+template <int U, class F>
+__device__ __forceinline__ void add_some_planes(const float *p, size_t stride, int j, int n, F f) {
 #pragma unroll
-    for (int u = 0; u < 4; ++u) f(p + (j + u < n ? (size_t)(j + u) * stride : 0), j + u < n);
+  for (int u = 0; u < U; ++u) f(p + (j + u < n ? (size_t)(j + u) * stride : 0), j + u < n);
+}
+template <int MOST = 8, class F>
+__device__ __forceinline__ void add_planes(const float *p, size_t stride, int n, F f) {
+  for (int j = 0; j < n; j += MOST) {
+    if (MOST > 4 && n - j > 4) add_some_planes<8>(p, stride, j, n, f);
+    else if (n - j > 1) add_some_planes<4>(p, stride, j, n, f);
+    else add_some_planes<1>(p, stride, j, n, f);
   }
 }
 
@@ -811,7 +817,7 @@ __global__ __launch_bounds__(512) void k_pf_norm(float *__restrict__ h, const in
       for (int e = 0; e < 8; ++e) x.v[e] = Store<1>::ld(tok_emb, emb + k + e);
     } else {
       x = ld_run8(row + k);
-      add_planes(part + (size_t)blockIdx.x * d + k, (size_t)plane_rows * d, n_part, [&](const float *p, bool ok) {
+      add_planes<4>(part + (size_t)blockIdx.x * d + k, (size_t)plane_rows * d, n_part, [&](const float *p, bool ok) {
         const Run8 q = ld_run8(p);
 #pragma unroll
         for (int e = 0; e < 8; ++e) x.v[e] += ok ? q.v[e] : 0.f;
@@ -858,10 +864,12 @@ __global__ __launch_bounds__(512) void k_pf_norm(float *__restrict__ h, const in
 // RoPE on q and k at position pos0 + t; q scaled by log2(e) / sqrt(hd) and stored as fp16 for
 // the attention kernel; k (rotated) and v rounded to the cache dtype and written to slot
 // (l, pos0 + t) of the shared cache.  qkv: n_part fp32 planes [m, qd + 2 kvd] of the QKV GEMM, added
-// in order.  One workgroup per token; a thread handles four rotation pairs (i, i + hd/2) of one head,
-// or four columns of v.  m: rows of a plane.  Q32: q in fp32 (short prompts).
+// in order.  A thread has one item of a token: four rotation pairs (i, i + hd/2) of one head, or four columns of
+// v; grid (m, items / 256).  (One workgroup of 512 per token, two or three items a thread one after the
+// other: 7.1 us for 77 tokens of the 8B shape with five planes and 30 for 4096 with one, now 4.8 and 25.)
+// m: rows of a plane.  Q32: q in fp32 (short prompts).
 template <bool Q32>
-__global__ __launch_bounds__(512) void k_pf_rope_store(const float *__restrict__ qkv, int n_part, int m,
+__global__ __launch_bounds__(256) void k_pf_rope_store(const float *__restrict__ qkv, int n_part, int m,
                                                        const float2 *__restrict__ rope, int nq, int nkv, int hd, int pos0,
                                                        int l, int max_seq, void *kcache, void *vcache, int kv_f16,
                                                        _Float16 *q16) {
@@ -887,7 +895,8 @@ __global__ __launch_bounds__(512) void k_pf_rope_store(const float *__restrict__
     }
     *(u32x2 *)((char *)cache + i * 2) = v;
   };
-  for (int i = threadIdx.x; i < (nq + nkv) * per; i += blockDim.x) {
+  const int i = blockIdx.y * 256 + threadIdx.x, pairs = (nq + nkv) * per;
+  if (i < pairs) {
     const int head = i / per, e = (i % per) * 4;
     const float4 c01 = *(const float4 *)(rope + (size_t)p * half + e), c23 = *(const float4 *)(rope + (size_t)p * half + e + 2);
     const float4 a = get(head * hd + e), b = get(head * hd + e + half);     // q heads, then k heads: contiguous in qkv
@@ -910,9 +919,10 @@ __global__ __launch_bounds__(512) void k_pf_rope_store(const float *__restrict__
       to_cache(kcache, o + half, hi[0], hi[1], hi[2], hi[3]);
     }
   }
-  for (int i = threadIdx.x * 4; i < kvd; i += blockDim.x * 4) {
-    const float4 v = get(qd + kvd + i);
-    to_cache(vcache, ((size_t)l * max_seq + p) * kvd + i, v.x, v.y, v.z, v.w);
+  const int c = (i - pairs) * 4;
+  if (c >= 0 && c < kvd) {
+    const float4 v = get(qd + kvd + c);
+    to_cache(vcache, ((size_t)l * max_seq + p) * kvd + c, v.x, v.y, v.z, v.w);
   }
 }
 
@@ -935,20 +945,27 @@ __global__ __launch_bounds__(512) void k_pf_rope_store(const float *__restrict__
 // The scores carry log2(e)/sqrt(hd) (folded into q16): base-2 online softmax.  Bound by the matrix
 // cores and, per tile about as long, the vector units (32 exponentials per lane beside the 32 MFMAs).
 // Key 0 is visible to every query, so the running maximum is a real score after the first tile.
-template <int HD, int HG>
+// KS = 2 (few workgroups): a step is two tiles of 64 keys, and two wavefronts share 32 queries, one tile of a step
+// each; half as many queries per workgroup, twice the workgroups, half as many steps one after the other.  Their two
+// softmaxes meet in LDS behind the loop (figures and the line between the two: launch_attn_t).
+template <int HD, int HG, int KS>
 __global__ __launch_bounds__(512, 1) void k_pf_attn(const _Float16 *__restrict__ q16, const void *kcache,
                                                     const void *vcache, int kv_f16, int nq, int nkv, int l, int max_seq,
-                                                    int pos0, int m, int qt0, _Float16 *o16) {
+                                                    int pos0, int m, _Float16 *o16) {
   constexpr int LDH = HD + 8;                 // K tile row stride (halfs)
   constexpr int LDV = 64 + 8;                 // V^T tile row stride (halfs)
-  constexpr int QT = 256 / HG, NK = HD / 64;  // queries per workgroup; 16-byte K segments per thread
-  __shared__ __attribute__((aligned(16))) _Float16 Ks[2][64 * LDH];
-  __shared__ __attribute__((aligned(16))) _Float16 Vt[2][HD * LDV];
+  constexpr int QT = 256 / HG / KS, KT = 64 * KS;               // queries per workgroup, keys of a step
+  constexpr int NK = KT * HD / 8 / 512;       // 16-byte K segments per thread
+  constexpr int NV = (KT / 2 * HD / 8 + 511) / 512;             // ... pairs of V segments
+  extern __shared__ __attribute__((aligned(16))) _Float16 attn_lds[];
+  auto Ks = [&](int buf, int tile) { return attn_lds + (buf * KS + tile) * (64 * LDH); };
+  auto Vt = [&](int buf, int tile) { return attn_lds + 2 * KS * 64 * LDH + (buf * KS + tile) * (HD * LDV); };
   const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   // (the kv head changes fastest: with eight of them every XCD's L2 sees the K and V of one)
   const int kvh = blockIdx.x % nkv, h = kvh * (nq / nkv) + (blockIdx.x / nkv) * HG + wv % HG;
-  const int qt = qt0 + (int)(gridDim.y - 1 - blockIdx.y) * QT;   // the longest rows first; qt0: the first query at work
-  const int q0 = qt + (wv / HG) * 32;                       // first query (chunk-relative) of this wavefront
+  const int qt = (int)(gridDim.y - 1 - blockIdx.y) * QT;    // the longest rows first
+  const int q0 = qt + (wv / HG / KS) * 32;                  // first query (chunk-relative) of this wavefront
+  const int part = KS == 1 ? 0 : wv / HG % KS;              // its tile of a step
   const int r32 = lane & 31, g = lane >> 5;
   const int qd = nq * HD, kvd = nkv * HD;
   const int tq = min(q0 + r32, m - 1);                      // this lane's query row (clamped: rows >= m are don't-care)
@@ -972,20 +989,24 @@ __global__ __launch_bounds__(512, 1) void k_pf_attn(const _Float16 *__restrict__
   const size_t cbase = (size_t)l * max_seq * kvd + (size_t)kvh * HD;
   // A key tile on its way: K rows as 16-byte segments along d; of V two neighbouring keys' segments
   // per thread, which leave as eight 4-byte writes into the transposed tile.
-  const int v_key = 2 * (tid & 31), v_ds = tid >> 5;
-  const bool v_mine = v_ds < HD / 8;                        // (uniform per wavefront)
-  const int v_dst = v_ds * 8 * LDV + (v_key & ~15) + (((v_key >> 2) & 1) << 3) + (((v_key >> 3) & 1) << 2) + (v_key & 3);
-  u32x4 fk[NK], fv[2];
+  constexpr int VP = 32 * HD / 8;                           // ... of a tile of 64 keys
+  const int v_key = 2 * (tid & 31);
+  const int v_at = (v_key & ~15) + (((v_key >> 2) & 1) << 3) + (((v_key >> 3) & 1) << 2) + (v_key & 3);
+  u32x4 fk[NK], fv[NV][2];
   auto fetch = [&](int kt) {
 #pragma unroll
     for (int i = 0; i < NK; ++i) {
       const int seg = tid + 512 * i, key = seg / (HD / 8), ds = seg % (HD / 8);
       fk[i] = *RIVER_GLOBAL(u32x4, (const char *)kcache + (cbase + (size_t)min(kt + key, last_pos) * kvd + ds * 8) * 2);
     }
-    if (v_mine) {
 #pragma unroll
-      for (int j = 0; j < 2; ++j)
-        fv[j] = *RIVER_GLOBAL(u32x4, (const char *)vcache + (cbase + (size_t)min(kt + v_key + j, last_pos) * kvd + v_ds * 8) * 2);
+    for (int i = 0; i < NV; ++i) {
+      const int idx = tid + 512 * i, tile = idx / VP, ds = idx % VP / 32;         // (uniform per wavefront)
+      if (tile < KS) {
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+          fv[i][j] = *RIVER_GLOBAL(u32x4, (const char *)vcache + (cbase + (size_t)min(kt + tile * 64 + v_key + j, last_pos) * kvd + ds * 8) * 2);
+      }
     }
   };
   auto stage = [&](int buf) {
@@ -993,22 +1014,29 @@ __global__ __launch_bounds__(512, 1) void k_pf_attn(const _Float16 *__restrict__
     for (int i = 0; i < NK; ++i) {
       const int seg = tid + 512 * i, key = seg / (HD / 8), ds = seg % (HD / 8);
       const u32x4 w = fk[i];
-      *(half8 *)(Ks[buf] + key * LDH + ds * 8) = cache_half8(make_uint4(w.x, w.y, w.z, w.w), kv_f16);
+      *(half8 *)(Ks(buf, key >> 6) + (key & 63) * LDH + ds * 8) = cache_half8(make_uint4(w.x, w.y, w.z, w.w), kv_f16);
     }
-    if (v_mine) {
-      const u32x4 w0 = fv[0], w1 = fv[1];
-      const half8 a = cache_half8(make_uint4(w0.x, w0.y, w0.z, w0.w), kv_f16), b = cache_half8(make_uint4(w1.x, w1.y, w1.z, w1.w), kv_f16);
 #pragma unroll
-      for (int e = 0; e < 8; ++e) *(half2v *)(Vt[buf] + v_dst + e * LDV) = half2v{a[e], b[e]};
+    for (int i = 0; i < NV; ++i) {
+      const int idx = tid + 512 * i, tile = idx / VP, ds = idx % VP / 32;
+      if (tile < KS) {
+        const u32x4 w0 = fv[i][0], w1 = fv[i][1];
+        const half8 a = cache_half8(make_uint4(w0.x, w0.y, w0.z, w0.w), kv_f16), b = cache_half8(make_uint4(w1.x, w1.y, w1.z, w1.w), kv_f16);
+        _Float16 *const dst = Vt(buf, tile) + ds * 8 * LDV + v_at;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) *(half2v *)(dst + e * LDV) = half2v{a[e], b[e]};
+      }
     }
   };
   fetch(0);
   stage(0);
   lds_barrier();
   int buf = 0;
-  for (int kt = 0; kt <= last_pos; kt += 64, buf ^= 1) {
-    const bool more = kt + 64 <= last_pos;
-    if (more) fetch(kt + 64);
+  for (int kt0 = 0; kt0 <= last_pos; kt0 += KT, buf ^= 1) {
+    const bool more = kt0 + KT <= last_pos;
+    if (more) fetch(kt0 + KT);
+    const int kt = kt0 + part * 64;                          // this wavefront's tile
+    const _Float16 *const Kt = Ks(buf, part), *const Vp = Vt(buf, part);
     // wavefronts without queries, and those whose queries all lie before this tile, have nothing to add
     if (q0 < m && kt <= pos0 + q0 + 31) {
       // S^T for the two 32-key blocks of the tile
@@ -1021,7 +1049,7 @@ __global__ __launch_bounds__(512, 1) void k_pf_attn(const _Float16 *__restrict__
       for (int ks = 0; ks < HD / 16; ++ks)
 #pragma unroll
         for (int kb = 0; kb < 2; ++kb) {
-          const half8 ka = *(const half8 *)(Ks[buf] + (kb * 32 + r32) * LDH + ks * 16 + g * 8);
+          const half8 ka = *(const half8 *)(Kt + (kb * 32 + r32) * LDH + ks * 16 + g * 8);
           s[kb] = mfma16(ka, qb[ks], s[kb]);
         }
       if (kt + 63 > pos0 + q0) {                             // the tile reaches beyond the first query: mask
@@ -1066,7 +1094,7 @@ __global__ __launch_bounds__(512, 1) void k_pf_attn(const _Float16 *__restrict__
         for (int j = 0; j < 2; ++j)
 #pragma unroll
           for (int b = 0; b < HD / 32; ++b) {
-            const half8 va = *(const half8 *)(Vt[buf] + (b * 32 + r32) * LDV + kb * 32 + j * 16 + g * 8);
+            const half8 va = *(const half8 *)(Vp + (b * 32 + r32) * LDV + kb * 32 + j * 16 + g * 8);
             oacc[b] = mfma16(va, pb[kb][j], oacc[b]);
           }
     }
@@ -1074,17 +1102,186 @@ __global__ __launch_bounds__(512, 1) void k_pf_attn(const _Float16 *__restrict__
     lds_barrier();
   }
   // O^T[d, q] / l -> o16[q, h*HD + d]; registers 4i .. 4i+3 are four consecutive d
-  if (q0 + r32 < m) {
-    const float inv = 1.0f / (lrun + __shfl_xor(lrun, 32));
+  lrun += __shfl_xor(lrun, 32);
+  constexpr int NB = HD / 32 / KS;                          // blocks of 32 d that this wavefront finishes: part * NB on
+  if constexpr (KS == 2) {
+    // (the other wavefront of these queries: HG wavefronts on or back.  Keys a query does not see at all
+    // leave a maximum of -1e30, whose weight is 0 beside the first tile's.)
+    f32x4 *const box = (f32x4 *)attn_lds;
+    float *const ml = (float *)(box + 8 * NB * 4 * 64);
+    const int other = part ? wv - HG : wv + HG;
+    auto give = [&](auto O) {                               // the other's blocks
+      constexpr int b0 = decltype(O)::value * NB;
 #pragma unroll
-    for (int b = 0; b < HD / 32; ++b)
+      for (int b = 0; b < NB; ++b)
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          box[((wv * NB + b) * 4 + i) * 64 + lane] = f32x4{oacc[b0 + b][4 * i], oacc[b0 + b][4 * i + 1], oacc[b0 + b][4 * i + 2], oacc[b0 + b][4 * i + 3]};
+    };
+    if (part) give(IC<0>{});
+    else give(IC<1>{});
+    ml[wv * 128 + lane] = mrun;
+    ml[wv * 128 + 64 + lane] = lrun;
+    lds_barrier();
+    const float m2 = ml[other * 128 + lane], l2 = ml[other * 128 + 64 + lane], mx = fmaxf(mrun, m2);
+    const float c1 = __builtin_amdgcn_exp2f(mrun - mx), c2 = __builtin_amdgcn_exp2f(m2 - mx);
+    lrun = lrun * c1 + l2 * c2;
+    auto take = [&](auto P) {
+      constexpr int b0 = decltype(P)::value * NB;
+#pragma unroll
+      for (int b = 0; b < NB; ++b)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const f32x4 p = box[((other * NB + b) * 4 + i) * 64 + lane];
+          oacc[b][4 * i] = oacc[b0 + b][4 * i] * c1 + p.x * c2;
+          oacc[b][4 * i + 1] = oacc[b0 + b][4 * i + 1] * c1 + p.y * c2;
+          oacc[b][4 * i + 2] = oacc[b0 + b][4 * i + 2] * c1 + p.z * c2;
+          oacc[b][4 * i + 3] = oacc[b0 + b][4 * i + 3] * c1 + p.w * c2;
+        }
+    };
+    if (part) take(IC<1>{});
+    else take(IC<0>{});
+  }
+  if (q0 + r32 < m) {
+    const float inv = 1.0f / lrun;
+#pragma unroll
+    for (int b = 0; b < NB; ++b)
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         half4 o;
 #pragma unroll
         for (int e = 0; e < 4; ++e) o[e] = (_Float16)(oacc[b][4 * i + e] * inv);
-        *(half4 *)(o16 + (size_t)(q0 + r32) * qd + h * HD + b * 32 + c_row(4 * i, lane)) = o;
+        *(half4 *)(o16 + (size_t)(q0 + r32) * qd + h * HD + (part * NB + b) * 32 + c_row(4 * i, lane)) = o;
       }
+  }
+}
+constexpr int attn_lds_bytes(int hd, int ks) { return 2 * ks * (64 * (hd + 8) + hd * 72) * 2; }
+
+// The last prompt position alone (behind the last block's keys and values only it goes on) over positions 0 .. P: one
+// workgroup per (kv head, group of REP of its query heads, split of the positions), 16 lanes per cached
+// position, a running softmax (base 2) per lane group and head, everything but q in fp32.  The splits' results
+// meet in the last workgroup to arrive of a head group, in split order.  Bound by latency: 26 us at 4096 positions of the 8B shape, 11 at
+// 512, 8 at 255 of the 1B shape; the tiles above, one row of 32 at work, took 139, 26 and 11.7.  A head per
+// wavefront: with all heads of a kv head in every lane (each row fetched once) it took 46 and 16, the vector
+// instructions of one wavefront per SIMD in a chain.
+// part_o, part_ml: as the decode attention leaves them; word 2 of a head's first part_ml entry counts arrivals (zero
+// between launches).
+template <int HD, int REP>
+__global__ __launch_bounds__(256 * REP) void k_pf_attn_last(const _Float16 *__restrict__ q16, const void *kcache, const void *vcache,
+                                                            int kv_f16, int nq, int nkv, int l, int max_seq, int P, int n_splits,
+                                                            float *part_o, float *part_ml, _Float16 *o16) {
+  constexpr int EL = HD / 16, NW = EL / 2, RB = 4;             // elements and words of a lane's slice of a row; rows in a batch
+  __shared__ float part[4][REP][HD], wml[4][REP][2];
+  __shared__ int flag;
+  const int tid = threadIdx.x, dl = tid & 15, wv = tid >> 6, r = wv % REP, quarter = wv / REP;
+  const int hgs = nq / nkv / REP, kvh = blockIdx.x / hgs, h0 = kvh * (nq / nkv) + blockIdx.x % hgs * REP;
+  const int sp = blockIdx.y, chunk = (P + n_splits) / n_splits, p0 = sp * chunk, p1 = min(P + 1, p0 + chunk);
+  const int kvd = nkv * HD;
+  const size_t base = (size_t)l * max_seq * kvd + (size_t)kvh * HD + dl * EL;
+  float q[EL], o[EL], m = -1.0e30f, ls = 0.f;
+#pragma unroll
+  for (int e = 0; e < EL; ++e) { q[e] = (float)q16[(h0 + r) * HD + dl * EL + e]; o[e] = 0.f; }
+  struct Batch { uint32_t k[RB][NW], v[RB][NW]; };
+  auto load = [&](int j0, Batch &t) {                          // (rows beyond the last read it again, masked below)
+#pragma unroll
+    for (int u = 0; u < RB; ++u) {
+      const size_t off = (base + (size_t)min(j0 + 16 * u, p1 - 1) * kvd) * 2;
+#pragma unroll
+      for (int w = 0; w < NW; w += 2) {
+        const u32x2 a = *RIVER_GLOBAL(u32x2, (const char *)kcache + off + w * 4), c = *RIVER_GLOBAL(u32x2, (const char *)vcache + off + w * 4);
+        t.k[u][w] = a.x; t.k[u][w + 1] = a.y; t.v[u][w] = c.x; t.v[u][w + 1] = c.y;
+      }
+    }
+  };
+  auto consume = [&](int j0, const Batch &t) {
+    float sc[RB], mn = m;
+#pragma unroll
+    for (int u = 0; u < RB; ++u) {
+      float dot = 0.f;
+#pragma unroll
+      for (int w = 0; w < NW; ++w) dot = fmaf(cache_hi(t.k[u][w], kv_f16), q[2 * w + 1], fmaf(cache_lo(t.k[u][w], kv_f16), q[2 * w], dot));
+      sc[u] = row16_sum(dot);
+      if (j0 + 16 * u >= p1) sc[u] = -1.0e30f;
+      mn = fmaxf(mn, sc[u]);
+    }
+    const float cg = __builtin_amdgcn_exp2f(m - mn);
+    m = mn;
+    ls *= cg;
+#pragma unroll
+    for (int e = 0; e < EL; ++e) o[e] *= cg;
+#pragma unroll
+    for (int u = 0; u < RB; ++u) {
+      const float pg = sc[u] > -0.5e30f ? __builtin_amdgcn_exp2f(sc[u] - mn) : 0.f;
+      ls += pg;
+#pragma unroll
+      for (int w = 0; w < NW; ++w) {
+        o[2 * w] = fmaf(pg, cache_lo(t.v[u][w], kv_f16), o[2 * w]);
+        o[2 * w + 1] = fmaf(pg, cache_hi(t.v[u][w], kv_f16), o[2 * w + 1]);
+      }
+    }
+  };
+  Batch ba, bb;
+  constexpr int step = 16 * RB;                                // (16 lane groups of a head: four wavefronts)
+  int j0 = p0 + quarter * 4 + ((tid & 63) >> 4);
+  if (j0 < p1) load(j0, ba);
+  for (; j0 < p1; j0 += 2 * step) {
+    load(j0 + step, bb);
+    consume(j0, ba);
+    load(j0 + 2 * step, ba);
+    if (j0 + step < p1) consume(j0 + step, bb);
+  }
+  // the four lane groups of a wavefront by lane exchange, a head's wavefronts through LDS
+#pragma unroll
+  for (int off = 16; off <= 32; off <<= 1) {
+    const float m2 = __shfl_xor(m, off), l2 = __shfl_xor(ls, off), mn = fmaxf(m, m2);
+    const float c1 = __builtin_amdgcn_exp2f(m - mn), c2 = __builtin_amdgcn_exp2f(m2 - mn);
+    ls = ls * c1 + l2 * c2;
+#pragma unroll
+    for (int e = 0; e < EL; ++e) o[e] = o[e] * c1 + __shfl_xor(o[e], off) * c2;
+    m = mn;
+  }
+  if ((tid & 63) < 16) {
+#pragma unroll
+    for (int e = 0; e < EL; ++e) part[quarter][r][dl * EL + e] = o[e];
+    if (dl == 0) { wml[quarter][r][0] = m; wml[quarter][r][1] = ls; }
+  }
+  __syncthreads();
+  const size_t pb = (size_t)h0 * kMaxSplits;
+  const int hr = tid / HD, he = tid % HD;                      // (a thread per element of the heads: 256 REP >= REP HD)
+  if (hr < REP) {
+    float M = -1.0e30f, Ls = 0.f, O = 0.f;
+    for (int w = 0; w < 4; ++w) M = fmaxf(M, wml[w][hr][0]);
+    for (int w = 0; w < 4; ++w) {
+      const float c = __builtin_amdgcn_exp2f(wml[w][hr][0] - M);
+      Ls = fmaf(wml[w][hr][1], c, Ls);
+      O = fmaf(part[w][hr][he], c, O);
+    }
+    if (n_splits == 1) {
+      o16[(h0 + hr) * HD + he] = (_Float16)(O / Ls);
+    } else {
+      const size_t pi = pb + hr * kMaxSplits + sp;
+      pub(part_o + pi * HD + he, O);
+      if (he == 0) { pub(part_ml + pi * 4, M); pub(part_ml + pi * 4 + 1, Ls); }
+    }
+  }
+  if (n_splits == 1 || !last_arriver((unsigned int *)part_ml + pb * 4 + 2, (unsigned)n_splits, &flag)) return;
+  if (hr < REP) {
+    float mj[kMaxSplits], lj[kMaxSplits], oj[kMaxSplits], M = -1.0e30f, Ls = 0.f, O = 0.f;
+#pragma unroll
+    for (int j = 0; j < kMaxSplits; ++j) {                     // (all of them fetched before the first is used)
+      const size_t pi = pb + hr * kMaxSplits + j;
+      mj[j] = j < n_splits ? sub(part_ml + pi * 4) : -1.0e30f;
+      lj[j] = j < n_splits ? sub(part_ml + pi * 4 + 1) : 0.f;
+      oj[j] = j < n_splits ? sub(part_o + pi * HD + he) : 0.f;
+      M = fmaxf(M, mj[j]);
+    }
+#pragma unroll
+    for (int j = 0; j < kMaxSplits; ++j) {
+      const float c = __builtin_amdgcn_exp2f(mj[j] - M);       // (an empty split has sum 0)
+      Ls = fmaf(lj[j], c, Ls);
+      O = fmaf(oj[j], c, O);
+    }
+    o16[(h0 + hr) * HD + he] = (_Float16)(O / Ls);
   }
 }
 
@@ -1357,7 +1554,7 @@ constexpr int kRowKeep = 4;
 __device__ __forceinline__ Run8 load_run8(float *row, const float *part, int n_part, int t, int d, int k) {
   float4 a = *(const float4 *)(row + k), b = *(const float4 *)(row + k + 4);
   if (n_part > 0) {
-    add_planes(part + (size_t)t * d + k, (size_t)kRows * d, n_part, [&](const float *p, bool ok) {
+    add_planes<4>(part + (size_t)t * d + k, (size_t)kRows * d, n_part, [&](const float *p, bool ok) {
       const float4 pa = *(const float4 *)p, pb = *(const float4 *)(p + 4);
       a.x += ok ? pa.x : 0.f; a.y += ok ? pa.y : 0.f; a.z += ok ? pa.z : 0.f; a.w += ok ? pa.w : 0.f;
       b.x += ok ? pb.x : 0.f; b.y += ok ? pb.y : 0.f; b.z += ok ? pb.z : 0.f; b.w += ok ? pb.w : 0.f;
