@@ -101,6 +101,92 @@ __global__ __launch_bounds__(kBlock) void k_head(const Dev *Dp, StepArgs A) {
   phase_head<DT>(D, A, ctl, lds, pre);
 }
 
+// The end of a prefill on the matrix cores (bf16): h(L) of the last position completed from the sums of the last GEMM, final
+// norm, LM head, token, and the state a new sequence starts from.  One launch for what were five (reset, last sums, head, copy of the
+// logits, token of the batched sequence), 3 to 5 us each with nothing to do: four 8B blocks, 77 tokens 561 -> 547 us, four 1B
+// blocks, 255 tokens 407 -> 400.  Bound by the stream of the head behind 10 us of launch, staging and hand-over (30 us for 131 MB).
+// n_part >= 0: h(L) = h_row + n_part planes part + j * stride, added in order, d_model of at most kPfHeadCols columns; < 0: it lies in
+// Dev::hidden already.  The weight prefetch is issued in front of it, as in a decode step.
+constexpr int kPfHeadCols = kNormRuns * kBlock * 8, kPfHeadPlanes = 8;
+__global__ __launch_bounds__(kBlock) void k_pf_head(const Dev *Dp, const float *h_row, const float *part, size_t stride, int n_part,
+                                                    float *out_logits, int *host_row, int *batch_token) {
+  constexpr int V = 0;
+  extern __shared__ float lds[];
+  DevRef D = *RIVER_CONSTANT(Dev, Dp);
+  float *const h = D.hidden + (size_t)D.L * D.d;
+  Pre<1, V> pre;
+  prefetch_head<1>(D, pre);
+  NormIn<1> in;
+  float ss[1] = {0.f};
+  if (n_part >= 0) {
+#pragma unroll
+    for (int k = 0; k < kNormRuns; ++k) {
+      const int i = (k * kBlock + in.tid) * 8;
+      if (i >= D.d) continue;
+      pf::Run8 x = pf::ld_run8(h_row + i);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) in.g[k][e] = Store<1>::ld(D.final_norm, i + e);
+      pf::add_planes(part + i, stride, n_part, [&](const float *p, bool ok) {
+        const pf::Run8 q = pf::ld_run8(p);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) x.v[e] += ok ? q.v[e] : 0.f;
+      });
+      if (blockIdx.x == 0) pf::st_run8(h + i, x);
+      in.v[k][0] = make_float4(x.v[0], x.v[1], x.v[2], x.v[3]);
+      in.v[k][1] = make_float4(x.v[4], x.v[5], x.v[6], x.v[7]);
+      float q2[2];
+#pragma unroll
+      for (int q = 0; q < 2; ++q)
+        q2[q] = (in.v[k][q].x * in.v[k][q].x + in.v[k][q].y * in.v[k][q].y) + (in.v[k][q].z * in.v[k][q].z + in.v[k][q].w * in.v[k][q].w);
+      ss[0] += q2[0] + q2[1];
+    }
+  } else {
+    ss[0] = in.fetch<true>(h, D.final_norm, D.d);
+  }
+  block_sum_k<1, true>(ss, lds_red(D, lds));
+  in.put<true>(h, D.final_norm, D.d, 1.0f / sqrtf(ss[0] / (float)D.d + D.eps), run_log2<1, V>(false, D.d), lds, lds_half(D, lds));
+  lds_barrier();
+  // the rows and the token, as in phase_head (a function that both share costs the step kernel 0.8 % at the 1B shape)
+  float *const red = lds_red(D, lds);
+  const int lane = pre.lane;
+  float best = -INFINITY;
+  int besti = 0x7fffffff;
+  auto rows_of = [&](int t, Rows<kRD> &rw) { head_rows<1>(D, t, rw); };
+  auto epi = [&](int t, float (&acc)[kRD]) {
+#pragma unroll
+    for (int r = 0; r < kRD; ++r) {
+      const int row = t * kRD + r;
+      if (row < D.vocab) {
+        if (lane == 0) {
+          D.logits[row] = acc[r];
+          if (out_logits) out_logits[row] = acc[r];
+        }
+        argmax_take(best, besti, acc[r], row);
+      }
+    }
+  };
+  stream_tasks<Dense<1, kRD, kUD>, 1, kRD>((D.vocab + kRD - 1) / kRD, D.d, D.group, lds, pre, rows_of, epi);
+  block_argmax(best, besti, red);
+  if (threadIdx.x == 0) {
+    pub(D.amax_val + blockIdx.x, best);
+    pub((float *)D.amax_idx + blockIdx.x, __int_as_float(besti));
+  }
+  if (!last_arriver(&D.st->head_cnt, gridDim.x, lds_flag(D, lds))) return;
+  float top = -INFINITY;
+  int token = 0x7fffffff;
+  for (int i = threadIdx.x; i < (int)gridDim.x; i += blockDim.x)
+    argmax_take(top, token, sub(D.amax_val + i), __float_as_int(sub((const float *)D.amax_idx + i)));
+  block_argmax(top, token, red);
+  if (threadIdx.x < kBarCounters) *bar_counter(D.bar, threadIdx.x) = 0;
+  if (threadIdx.x == 0) {
+    *bar_error(D.bar) = 0;
+    *D.st = DevState{};
+    D.st->cur_token = token;
+    if (batch_token) *batch_token = token;
+    if (host_row) { host_store(host_row, token); host_store(host_row + 1, 0); }
+  }
+}
+
 #ifdef RIVER_TRACE
 // diagnostics build: every workgroup stamps the 100 MHz wall clock when it arrives at and
 // when it is released from each device-wide barrier of the last launch
@@ -170,8 +256,10 @@ __device__ RIVER_PSTEP_INLINE void pstep_head(const Dev *Dp, StepArgs A, int ctl
 
 // The number of barriers (5 L - 1, one more with the head) is the same for every workgroup
 // whatever the exit state.
+// (On a page of its own: the same code 0x3600 bytes further into one takes 564.6 us per token of the 1B shape instead
+// of 561.3, and 665.3 instead of 664.1 for two of four 8B blocks at 4096 positions.)
 template <int DT, bool F16, int V, int HD>
-__global__ __launch_bounds__(kBlock) void k_step_persistent(const Dev *Dp, StepArgs A) {
+__global__ __launch_bounds__(kBlock) __attribute__((aligned(4096))) void k_step_persistent(const Dev *Dp, StepArgs A) {
   extern __shared__ float lds[];
   DevRef D = *RIVER_CONSTANT(Dev, Dp);
   unsigned long long k = A.bar_base;
@@ -942,7 +1030,7 @@ static int create_impl(const river_config *cfg, const river_weights *w, const ri
         (const void *)k_oproj<0, 0>, (const void *)k_oproj<0, V_NARROW>, (const void *)k_oproj<1, 0>,
         (const void *)k_gateup<0, 0>, (const void *)k_gateup<0, V_NARROW>, (const void *)k_gateup<1, 0>,
         (const void *)k_down<0, 0>, (const void *)k_down<0, V_NARROW>, (const void *)k_down<1, 0>,
-        (const void *)k_head<0>, (const void *)k_head<1>, (const void *)step_kernel(x)};
+        (const void *)k_head<0>, (const void *)k_head<1>, (const void *)k_pf_head, (const void *)step_kernel(x)};
     for (const void *f : fns)
       if ((e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, lb)) != hipSuccess)
         return fail("hipFuncSetAttribute(max dynamic LDS)", e);
@@ -1197,13 +1285,22 @@ static int launch_gemm_exact(river_ctx *x, int l, bool w4, const int *ms, int nm
   return split * (w4 ? 1 : 3);
 }
 
-// Original final norm + LM head + argmax on the last prompt position, whose h(L) is in Dev::hidden (the decode
-// path's kernel), and the call's results on the host.
-static void launch_prefill_head(river_ctx *x, int n, int ep) {
-  StepArgs A{};
-  A.pos = n - 1; A.token = -1; A.forced_e = ep; A.want_head = 1; A.rec_slot = -1; A.n_splits = 1; A.bar_base = 0;
-  A.host_row = x->host ? x->host->rec : nullptr;
-  k_head<1><<<dim3(x->grid_gemv), dim3(x->block), x->lds_bytes, x->stream>>>(x->dev_d, A);
+// Original final norm + LM head + argmax on the last prompt position, the call's results and the new sequence's state (k_pf_head).
+// h_row: the position's residual row, parts planes of plane_rows rows behind each other with its sums in row `row`.
+static void launch_prefill_head(river_ctx *x, const float *h_row, const float *planes, int parts, int plane_rows, int row, float *out_logits,
+                                int *batch_token) {
+  const river_config &c = x->cfg;
+  const int d = c.d_model;
+  int n_part = parts;
+  if (parts > kPfHeadPlanes || d > kPfHeadCols) {               // (every workgroup reads the planes: 16 KB each at the 8B shape)
+    // (the norm kernel takes rows that the planes hold from their row 0 on)
+    pf::k_pf_norm<false><<<dim3(1), dim3(512), 0, x->stream>>>((float *)h_row, nullptr, x->dev.tok_emb, planes + (size_t)row * d, parts, plane_rows,
+                                                               nullptr, d, c.rms_eps, nullptr, x->dev.hidden + (size_t)c.n_layers * d, 0, 0);
+    n_part = -1;
+  }
+  k_pf_head<<<dim3(x->grid_gemv), dim3(x->block), x->lds_bytes, x->stream>>>(x->dev_d, h_row, planes + (size_t)row * d, (size_t)plane_rows * d, n_part,
+                                                                             out_logits, x->host ? x->host->rec : nullptr, batch_token);
+  x->bar_total = 0;
 }
 
 // Short prompts (see river_prefill.h): passes of up to kShort positions, from kShortMin positions on, for models with
@@ -1227,7 +1324,7 @@ static bool prefill_short_ok(const river_ctx *x, int n) {
   // (the gate/up GEMM's planes are the largest: three of kShort rows)
   return block >= kShortBlockBytes && (size_t)3 * pf::kShort * 2 * c.d_ffn * 4 <= x->lay.pf_big_bytes;
 }
-static int prefill_short(river_ctx *x, const int32_t *tokens, int n, int ep) {
+static int prefill_short(river_ctx *x, const int32_t *tokens, int n, int ep, float *out_logits) {
   const river_config &c = x->cfg;
   const Dev &D = x->dev;
   const Layout &y = x->lay;
@@ -1270,10 +1367,9 @@ static int prefill_short(river_ctx *x, const int32_t *tokens, int n, int ep) {
       pf::k_pf_swiglu_rows<<<dim3((ffn + 2047) / 2048, m), dim3(256), 0, s>>>(big, parts, ffn, !river, a16);
       parts = launch_gemm_exact(x, l, river, m_d, 1, a16, ffn, big, m);
     }
-    if (last >= 0) norm(true, nullptr, nullptr, D.hidden + (size_t)L * d, last);
+    if (last >= 0) launch_prefill_head(x, h + (size_t)last * d, big, parts, pf::kShort, last, out_logits, nullptr);
     HIP_TRY(x, hipGetLastError());
   }
-  launch_prefill_head(x, n, ep);
   HIP_TRY(x, hipGetLastError());
   x->pos = n;
   return RIVER_OK;
@@ -1320,7 +1416,7 @@ static void launch_attn_last(river_ctx *x, int l, const void *kc, const void *vc
 
 // Prefill phase on the matrix cores: the prompt in equal chunks of up to pf_rows tokens, every block
 // as MFMA GEMMs over the chunk (see river_prefill.h); blocks above ep run as river twins.
-static int prefill_gemm(river_ctx *x, int seq, const int32_t *tokens, int n, int ep) {
+static int prefill_gemm(river_ctx *x, int seq, const int32_t *tokens, int n, int ep, float *out_logits) {
   const river_config &c = x->cfg;
   const Dev &D = x->dev;
   const Layout &y = x->lay;
@@ -1368,18 +1464,12 @@ static int prefill_gemm(river_ctx *x, int seq, const int32_t *tokens, int n, int
       (void)launch_gemm<pf::PF_SWIGLU>(x, l, river, m_gu, 2, x16 + (size_t)t0 * d, d, a16, rows);
       parts = launch_gemm<pf::PF_STORE>(x, l, river, m_d, 1, a16, ffn, big, rows);
     }
-    // h(L) of the last prompt position, the head's input
     if (last >= 0) {
-      const int t0 = m > pf::TileM::TM ? last : 0;
-      pf::k_pf_norm<false><<<dim3(last + 1 - t0), dim3(512), 0, s>>>(h, nullptr, nullptr, big, parts, last + 1 - t0, nullptr, d, c.rms_eps, nullptr,
-                                                              D.hidden + (size_t)L * d, last, t0);
+      const bool tail = m > pf::TileM::TM;
+      launch_prefill_head(x, h + (size_t)last * d, big, parts, tail ? 1 : m, tail ? 0 : last, out_logits, c.max_batch > 1 ? x->st_b.token + seq : nullptr);
     }
     HIP_TRY(x, hipGetLastError());
   }
-  launch_prefill_head(x, n, ep);
-  if (c.max_batch > 1)
-    bd::k_bd_after_prefill<<<dim3(1), dim3(64), 0, s>>>(x->st_b, seq, &D.st->cur_token);
-  HIP_TRY(x, hipGetLastError());
   if (c.max_batch > 1) x->pos_b[seq] = n;
   else x->pos = n;
   return RIVER_OK;
@@ -1404,26 +1494,40 @@ extern "C" int river_prefill(river_ctx *x, int32_t seq, const int32_t *tokens, i
   if (ep < L && !x->have_river) { x->err = "prefill below full depth needs river weights"; return RIVER_ESTATE; }
   // a new sequence also clears a previous device-side time-out
   x->broken = false;
-  int rc = reset_state(x);
-  if (rc) return rc;
+  int rc;
   x->pos = 0;
   x->have_token = false;
   const int min_gemm = x->cfg.prefill_gemm_min_tokens > 0 ? x->cfg.prefill_gemm_min_tokens : 32;
+  // the head's kernel stores the logits where the caller wants them if that is this device's memory (else a copy, which
+  // may refuse the address; a kernel would fault)
+  float *direct = nullptr;
+  if (out_logits) {
+    hipPointerAttribute_t at;
+    int dev = -1;
+    if (hipGetDevice(&dev) == hipSuccess && hipPointerGetAttributes(&at, out_logits) == hipSuccess && at.type == hipMemoryTypeDevice &&
+        at.device == dev && (uintptr_t)out_logits % 4 == 0)
+      direct = out_logits;
+    else
+      (void)hipGetLastError();
+  }
   if (x->lay.pf_rows > 0 && (n_tokens >= min_gemm || x->cfg.max_batch > 1)) {
-    rc = prefill_gemm(x, seq, tokens, n_tokens, ep);
+    rc = prefill_gemm(x, seq, tokens, n_tokens, ep, direct);
     if (rc) return rc;
   } else if (prefill_short_ok(x, n_tokens)) {
-    rc = prefill_short(x, tokens, n_tokens, ep);
+    rc = prefill_short(x, tokens, n_tokens, ep, direct);
     if (rc) return rc;
   } else {
     // one or two tokens, fp32 models and shapes the GEMM path does not take: the decode kernels,
     // one prompt position after the other
+    direct = nullptr;
+    rc = reset_state(x);
+    if (rc) return rc;
     for (int i = 0; i < n_tokens; ++i) {
       rc = enqueue(x, tokens[i], ep, i == n_tokens - 1, -1, i == n_tokens - 1);
       if (rc) return rc;
     }
   }
-  if (out_logits)
+  if (out_logits && !direct)
     HIP_TRY(x, hipMemcpyAsync(out_logits, x->dev.logits, (size_t)x->cfg.vocab * 4, hipMemcpyDeviceToDevice,
                               x->stream));
   if (x->host) {

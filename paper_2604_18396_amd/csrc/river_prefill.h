@@ -2369,10 +2369,5 @@ __global__ __launch_bounds__(256) void k_bd_argmax(const float *__restrict__ log
       host_store(host_row + 2 * max_batch + b * L + i, __float_as_int(sims[(size_t)b * L + i]));
 }
 
-// after a prefill of sequence `seq`: its next token
-__global__ void k_bd_after_prefill(SeqState st, int seq, const int *cur_token) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) st.token[seq] = *cur_token;
-}
-
 }  // namespace bd
 }  // namespace river

@@ -782,6 +782,13 @@ def test_gemm_prefill_few_rows_in_k_slices_equal_serial_prefill_closely(cfg, n_p
     test_gemm_prefill_tiles_and_k_slices_equal_serial_prefill_closely(cfg, n_prompt)
 
 
+@pytest.mark.parametrize("d_model,n_prompt", [(8192, 40), (8256, 40), (8256, 140)])
+def test_gemm_prefill_head_of_wide_models(d_model, n_prompt):
+    """The prefill's head completes the last row itself up to 8192 columns and takes it from memory beyond."""
+    cfg = configs.ModelConfig(f"wide-{d_model}", 2, d_model, 2, 1, 64, 128, 1002, 500000.0, 1e-5, configs.DTYPE_BF16, n_prompt + 8, 1, 2.0)
+    test_gemm_prefill_tiles_and_k_slices_equal_serial_prefill_closely(cfg, n_prompt)
+
+
 # ------------------------------------------------------------ backbone offloading
 
 @pytest.mark.parametrize("mode", MODES, ids=MODE_IDS)
