@@ -1305,8 +1305,9 @@ static void launch_prefill_head(river_ctx *x, const float *h_row, const float *p
 
 // Short prompts (see river_prefill.h): passes of up to kShort positions, from kShortMin positions on, for models with
 // blocks of at least kShortBlockBytes.  us per prompt of 2 / 3 / 31 tokens through the decode kernels, and of
-// 3 / 31 in a pass: four 8B blocks, backbone 702 / 1030 / 10317 and 618 / 655, river 426 / 618 / 6036 and 563 / 577;
-// three blocks of 72 MB 199 / 287 / 2763 and 226 / 248, river 166 / 237 / 2246 and 210 / 223; three of 23 MB
+// 3 / 31 in a pass: four 8B blocks, backbone 702 / 1030 / 10317 and 564 / 630, river 426 / 618 / 6036 and 379 / 419;
+// three blocks of 72 MB 199 / 287 / 2763 and 233 / 267 (with 128 x 128 tiles 242 / 256), river 166 / 237 / 2246 and 175 / 189; three of 23 MB, by
+// 128 x 128 tiles,
 // 166 / 237 / 2257 and 202 / 220, river 164 / 235 / 2222 and 184 / 193.  So a pass costs two to three positions at
 // every size, and the line in block size is not where passes begin to pay: below it a prompt equals,
 // bit for bit, that of a context that never uses GEMMs (prefill_gemm_min_tokens < 0), and only that holds it there.

@@ -424,7 +424,7 @@ done:
 // sums S and the sum X of its inputs (a product with ones) go into the result as scale (S - zero X) in fp32,
 // the form in which the decode kernels take the scale and the zero point.  (The weights as two fp16 numbers, the
 // K tiles taken twice, lost bits of weights below 2e-3 and turned those beyond 65504 into NaN; four 8B river
-// blocks and 3 tokens took 900 us that way, 563 now.)
+// blocks and 3 tokens took 900 us that way, 379 now.)
 //
 template <int MB_, bool W4> struct RowsTile {
   static constexpr int MB = MB_, TM = 32 * MB, TN = 128, NT = 512;
@@ -779,10 +779,15 @@ __device__ __forceinline__ void add_some_planes(const float *p, size_t stride, i
 }
 template <int MOST = 8, class F>
 __device__ __forceinline__ void add_planes(const float *p, size_t stride, int n, F f) {
-  for (int j = 0; j < n; j += MOST) {
-    if (MOST > 4 && n - j > 4) add_some_planes<8>(p, stride, j, n, f);
-    else if (n - j > 1) add_some_planes<4>(p, stride, j, n, f);
-    else add_some_planes<1>(p, stride, j, n, f);
+  if (n == 1) {
+    add_some_planes<1>(p, stride, 0, n, f);
+  } else if constexpr (MOST == 4) {                            // (no choice in the loop: the 24 planes of a short prompt's norm 7.6 us, with it 9.4)
+    for (int j = 0; j < n; j += 4) add_some_planes<4>(p, stride, j, n, f);
+  } else {
+    for (int j = 0; j < n; j += 8) {
+      if (n - j > 4) add_some_planes<8>(p, stride, j, n, f);
+      else add_some_planes<4>(p, stride, j, n, f);
+    }
   }
 }
 
@@ -1291,7 +1296,7 @@ __global__ __launch_bounds__(256 * REP) void k_pf_attn_last(const _Float16 *__re
 // blocks, fp16 inputs and exact codes in river blocks, fp32 queries, scores and probabilities.  They
 // went through the decode kernels one position at a time, a stream of all weights each (section of four
 // 8B blocks: 31 tokens 10.5 ms); now up to kShort positions share a pass of the GEMMs above in their
-// EXACT form, with the two kernels below between them (31 tokens: 0.7 ms).
+// EXACT form, with the two kernels below between them (31 tokens: 0.63 ms).
 
 // Causal attention of a few rows over the cache (which holds their own keys and values already): one
 // wavefront per (row, query head), 16 lanes per cached position, four positions at a time, a running
