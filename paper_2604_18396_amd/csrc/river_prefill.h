@@ -1216,7 +1216,8 @@ __global__ __launch_bounds__(256 * REP) void k_pf_attn_last(const _Float16 *__re
     for (int e = 0; e < EL; ++e) o[e] *= cg;
 #pragma unroll
     for (int u = 0; u < RB; ++u) {
-      const float pg = sc[u] > -0.5e30f ? __builtin_amdgcn_exp2f(sc[u] - mn) : 0.f;
+      // (left out by its position, not by its value: a score that is NaN is one, as in the tiles)
+      const float pg = j0 + 16 * u < p1 ? __builtin_amdgcn_exp2f(sc[u] - mn) : 0.f;
       ls += pg;
 #pragma unroll
       for (int w = 0; w < NW; ++w) {

@@ -789,6 +789,33 @@ def test_gemm_prefill_head_of_wide_models(d_model, n_prompt):
     test_gemm_prefill_tiles_and_k_slices_equal_serial_prefill_closely(cfg, n_prompt)
 
 
+@pytest.mark.parametrize("head_dim", [64, 128])
+@pytest.mark.parametrize("n_prompt", [128, 129, 300])
+def test_gemm_prefill_score_without_a_value(n_prompt, head_dim):
+    """Most of one prompt token's keys are beyond the range of the cache's type: infinities of both signs, whose scores are NaN.
+    The last position attends to them, so its logits have no value either, whether it goes through the tiles with the
+    rest of a short chunk or alone through the kernel of the last row (from 129 tokens on)."""
+    say(f"GEMM prefill, NaN scores, {n_prompt} tokens, head size {head_dim}")
+    cfg = configs.ModelConfig("inf-key", 1, 256, 4, 2, head_dim, 256, 1002, 10000.0, 1e-5, configs.DTYPE_BF16, 304, 1, 2.0,
+                              kv_dtype=configs.KV_F16)
+    w = inputs.make_weights(cfg, 5)
+    w["tok_emb"][:, 7] = 0                                       # column 7 is this token's alone
+    w["tok_emb"][3] = 0
+    w["tok_emb"][3, 7] = 1
+    w["layers"][0]["wk"][:, 7] = 6e4
+    prompt = inputs.make_prompt(cfg.vocab, n_prompt, 6)
+    prompt = np.where(prompt == 3, 4, prompt)
+    g = binding.River(cfg, binding.upload_weights(w), None, prefill_gemm_min_tokens=1)
+    g.prefill(prompt)
+    assert np.isfinite(g.logits()).all()
+    prompt[69] = 3
+    g.prefill(prompt)
+    bad = ~np.isfinite(g.kcache()[0, :n_prompt])
+    assert bad[69].mean() > 0.5 and not np.delete(bad, 69, axis=0).any()     # (a rotated pair may cancel)
+    assert np.isnan(g.logits()).all()
+    g.close()
+
+
 # ------------------------------------------------------------ backbone offloading
 
 @pytest.mark.parametrize("mode", MODES, ids=MODE_IDS)
