@@ -1476,6 +1476,19 @@ static int prefill_gemm(river_ctx *x, int seq, const int32_t *tokens, int n, int
   return RIVER_OK;
 }
 
+// Are `bytes` bytes from p memory of the current device that one allocation holds?
+static bool device_memory(const void *p, size_t bytes) {
+  hipPointerAttribute_t at;
+  hipDeviceptr_t base = nullptr;
+  size_t size = 0;
+  int dev = -1;
+  if (hipGetDevice(&dev) != hipSuccess || hipPointerGetAttributes(&at, p) != hipSuccess || at.type != hipMemoryTypeDevice || at.device != dev ||
+      hipMemGetAddressRange(&base, &size, (hipDeviceptr_t)p) != hipSuccess)
+    return false;
+  const size_t before = (size_t)((const char *)p - (const char *)base);
+  return before <= size && bytes <= size - before;
+}
+
 extern "C" int river_prefill(river_ctx *x, int32_t seq, const int32_t *tokens, int32_t n_tokens,
                              int32_t prefill_exit_layer, int32_t *out_token, float *out_logits) {
   if (!x) return RIVER_EINVAL;
@@ -1499,17 +1512,12 @@ extern "C" int river_prefill(river_ctx *x, int32_t seq, const int32_t *tokens, i
   x->pos = 0;
   x->have_token = false;
   const int min_gemm = x->cfg.prefill_gemm_min_tokens > 0 ? x->cfg.prefill_gemm_min_tokens : 32;
-  // the head's kernel stores the logits where the caller wants them if that is this device's memory (else a copy, which
-  // may refuse the address; a kernel would fault)
+  // the head's kernel stores the logits where the caller wants them if all of that is this device's memory (else a copy, which
+  // refuses what it cannot write; a kernel would fault)
   float *direct = nullptr;
   if (out_logits) {
-    hipPointerAttribute_t at;
-    int dev = -1;
-    if (hipGetDevice(&dev) == hipSuccess && hipPointerGetAttributes(&at, out_logits) == hipSuccess && at.type == hipMemoryTypeDevice &&
-        at.device == dev && (uintptr_t)out_logits % 4 == 0)
-      direct = out_logits;
-    else
-      (void)hipGetLastError();
+    if (device_memory(out_logits, (size_t)x->cfg.vocab * 4) && (uintptr_t)out_logits % 4 == 0) direct = out_logits;
+    else (void)hipGetLastError();
   }
   if (x->lay.pf_rows > 0 && (n_tokens >= min_gemm || x->cfg.max_batch > 1)) {
     rc = prefill_gemm(x, seq, tokens, n_tokens, ep, direct);

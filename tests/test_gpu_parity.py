@@ -607,6 +607,40 @@ def test_prefill_outputs_and_argument_checks():
     dense.close()
 
 
+@pytest.mark.parametrize("missing", [1, 250, 500])
+def test_prefill_refuses_logits_that_end_beyond_their_allocation(missing):
+    """out_logits with fewer than vocab floats left in its allocation: refused, as a copy of the logits is, nothing
+    written, and the context takes the next prompt.  (The allocation ends 2 KB in front of a page.)"""
+    import ctypes as C
+    say(f"prefill, out_logits {missing} floats short")
+    cfg = MID.with_(max_seq=64)
+    g = binding.River(cfg, binding.upload_weights(inputs.make_weights(cfg, 3)), None, prefill_gemm_min_tokens=1)
+    prompt = np.ascontiguousarray(inputs.make_prompt(cfg.vocab, 40, 4), dtype=np.int32)
+    want = g.prefill(prompt)
+    logits = g.logits()
+    L, size = binding.load(), (1 << 20) - 2048
+    L.hipMalloc.argtypes = [C.c_void_p, C.c_size_t]              # (an allocation of its own: torch's are pieces of larger ones)
+    L.hipMemcpy.argtypes = [C.c_void_p, C.c_void_p, C.c_size_t, C.c_int]
+    L.hipFree.argtypes = [C.c_void_p]
+    at = C.c_void_p()
+    assert L.hipMalloc(C.byref(at), size) == 0
+    mark, back = np.full(size // 4, 7.0, np.float32), np.empty(size // 4, np.float32)
+    token = C.c_int32()
+
+    def call(p):
+        return L.river_prefill(g._h, 0, prompt.ctypes.data, 40, -1, C.byref(token), p)
+
+    assert L.hipMemcpy(at, mark.ctypes.data, size, 1) == 0
+    assert call(at.value + size - 4 * (cfg.vocab - missing)) == binding.RIVER_EHIP
+    assert L.hipMemcpy(back.ctypes.data, at, size, 2) == 0 and np.array_equal(back, mark)
+    L.hipGetLastError()                                          # (the runtime's note of the refusal)
+    assert call(at.value + size - 4 * cfg.vocab) == 0 and token.value == want           # ... and one that just fits
+    assert L.hipMemcpy(back.ctypes.data, at, size, 2) == 0
+    assert np.array_equal(back[-cfg.vocab:], logits) and np.array_equal(back[:-cfg.vocab], mark[:-cfg.vocab])
+    assert L.hipFree(at) == 0
+    g.close()
+
+
 def test_barrier_slot_pool_reuse_and_exhaustion():
     """Contexts take one of 64 barrier slots per device: 70 contexts created and destroyed one
     after the other reuse slots; the 65th simultaneous context is refused with RIVER_ENOSPC."""
