@@ -1516,8 +1516,9 @@ extern "C" int river_prefill(river_ctx *x, int32_t seq, const int32_t *tokens, i
   // refuses what it cannot write; a kernel would fault)
   float *direct = nullptr;
   if (out_logits) {
+    const hipError_t pending = hipPeekAtLastError();
     if (device_memory(out_logits, (size_t)x->cfg.vocab * 4) && (uintptr_t)out_logits % 4 == 0) direct = out_logits;
-    else (void)hipGetLastError();
+    else if (pending == hipSuccess) (void)hipGetLastError();     // (the look's own error, not one that was there before)
   }
   if (x->lay.pf_rows > 0 && (n_tokens >= min_gemm || x->cfg.max_batch > 1)) {
     rc = prefill_gemm(x, seq, tokens, n_tokens, ep, direct);

@@ -641,6 +641,30 @@ def test_prefill_refuses_logits_that_end_beyond_their_allocation(missing):
     g.close()
 
 
+@pytest.mark.parametrize("where", ["nowhere", "device", "pinned"])
+def test_prefill_reports_an_error_that_was_pending(where):
+    """An error of an earlier runtime call of this thread (a device that does not exist) fails the prefill's check of its
+    launches, wherever the logits go; the look at the logits' address does not take it away."""
+    say(f"prefill behind a failed runtime call, logits {where}")
+    cfg = MID.with_(max_seq=64)
+    g = binding.River(cfg, binding.upload_weights(inputs.make_weights(cfg, 3)), None, prefill_gemm_min_tokens=1)
+    prompt = np.ascontiguousarray(inputs.make_prompt(cfg.vocab, 40, 4), dtype=np.int32)
+    out = None if where == "nowhere" else torch.empty(cfg.vocab, device="cuda") if where == "device" else \
+        torch.empty(cfg.vocab, pin_memory=True)
+    L = binding.load()
+
+    def call():
+        return L.river_prefill(g._h, 0, prompt.ctypes.data, 40, -1, None, out.data_ptr() if out is not None else None)
+
+    assert call() == 0 and L.hipPeekAtLastError() == 0
+    assert L.hipSetDevice(12345) != 0 and L.hipPeekAtLastError() != 0
+    assert call() == binding.RIVER_EHIP
+    assert L.hipPeekAtLastError() == 0 and call() == 0           # reported, and over
+    if out is not None:
+        np.testing.assert_array_equal(out.cpu().numpy(), g.logits())
+    g.close()
+
+
 def test_barrier_slot_pool_reuse_and_exhaustion():
     """Contexts take one of 64 barrier slots per device: 70 contexts created and destroyed one
     after the other reuse slots; the 65th simultaneous context is refused with RIVER_ENOSPC."""
