@@ -1560,11 +1560,14 @@ constexpr int kRowKeep = 4;
 __device__ __forceinline__ Run8 load_run8(float *row, const float *part, int n_part, int t, int d, int k) {
   float4 a = *(const float4 *)(row + k), b = *(const float4 *)(row + k + 4);
   if (n_part > 0) {
-    add_planes<4>(part + (size_t)t * d + k, (size_t)kRows * d, n_part, [&](const float *p, bool ok) {
-      const float4 pa = *(const float4 *)p, pb = *(const float4 *)(p + 4);
-      a.x += ok ? pa.x : 0.f; a.y += ok ? pa.y : 0.f; a.z += ok ? pa.z : 0.f; a.w += ok ? pa.w : 0.f;
-      b.x += ok ? pb.x : 0.f; b.y += ok ? pb.y : 0.f; b.z += ok ? pb.z : 0.f; b.w += ok ? pb.w : 0.f;
-    });
+    // (not add_planes: with its branch for one plane, which a batched step never has, k_bd_block_end takes 142 registers instead of
+    // 124, and 5.9 us instead of 5.7 for 32 rows of the 8B shape)
+    for (int j = 0; j < n_part; j += 4)
+      add_some_planes<4>(part + (size_t)t * d + k, (size_t)kRows * d, j, n_part, [&](const float *p, bool ok) {
+        const float4 pa = *(const float4 *)p, pb = *(const float4 *)(p + 4);
+        a.x += ok ? pa.x : 0.f; a.y += ok ? pa.y : 0.f; a.z += ok ? pa.z : 0.f; a.w += ok ? pa.w : 0.f;
+        b.x += ok ? pb.x : 0.f; b.y += ok ? pb.y : 0.f; b.z += ok ? pb.z : 0.f; b.w += ok ? pb.w : 0.f;
+      });
     *(float4 *)(row + k) = a;
     *(float4 *)(row + k + 4) = b;
   }

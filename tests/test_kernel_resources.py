@@ -38,3 +38,10 @@ def test_step_kernels_keep_everything_in_registers(tmp_path):
     assert len(steps) == 12
     for name, f in steps.items():
         assert int(f["private_segment_fixed_size"]) == 0 and int(f["vgpr_spill_count"]) == 0, (name, f)
+
+
+def test_block_end_of_a_batched_step_takes_no_more_registers_than_it_did(tmp_path):
+    """The sums of partial results are shared with the prefill's row kernels: a branch that only those need made
+    this one 18 registers larger and slower, in every block of every batched step."""
+    (f,) = [f for n, f in kernels(tmp_path).items() if "k_bd_block_end" in n]
+    assert int(f["vgpr_count"]) <= 124 and int(f["private_segment_fixed_size"]) == 0, f
