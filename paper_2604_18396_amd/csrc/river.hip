@@ -1378,11 +1378,9 @@ static int prefill_short(river_ctx *x, const int32_t *tokens, int n, int ep, flo
 
 // Attention of a chunk's queries: as many query heads of a kv head per workgroup (4, 2 or 1) as divide them, two tiles of
 // keys a step where one a step makes no more workgroups than there are CUs (us, one / two tiles, 32 heads on 8 of head size
-// 128: 77 rows 9.9 / 9.2, 512 25.2 / 18.5, 1024 43 / 31, 2048 80 / 67, 2560 98 / 106).  Passes of more than 2048 rows have that
-// few workgroups with few heads only (8 on 2: 3072 rows 105 / 69) and keep one tile all the same: a long prompt's cache
-// is held to the per-position prefill's to less than one rounding of its largest values, and that bar
-// is met by the probabilities as one chain rounds them.
-constexpr int kAttnPairRows = 2048;
+// 128: 77 rows 9.9 / 9.2, 512 25.2 / 18.5, 1024 43 / 31, 2048 80 / 67, 2560 98 / 106; 8 on 2: 3072 rows 105 / 69, a prompt of 8300 in
+// three chunks and two blocks as a whole 1025 / 856).  Keys and values of the next block are as far from 64 bits either way:
+// 1.77e-3 of 3072 positions, 1.70e-3 of 8300 (their rounding to bf16).
 template <int HD, int HG>
 static void launch_attn_t(river_ctx *x, int l, const void *kc, const void *vc, int c0, int m, const _Float16 *q16, _Float16 *o16) {
   const river_config &c = x->cfg;
@@ -1392,7 +1390,7 @@ static void launch_attn_t(river_ctx *x, int l, const void *kc, const void *vc, i
         q16, kc, vc, x->dev.kv_f16, c.n_q_heads, c.n_kv_heads, l, c.max_seq, c0, m, o16);
   };
   const int wgs = c.n_q_heads / HG * ((m + 256 / HG - 1) / (256 / HG));
-  if (wgs <= x->grid_persist && m <= kAttnPairRows) go(IC<2>{});
+  if (wgs <= x->grid_persist) go(IC<2>{});
   else go(IC<1>{});
 }
 static int heads_per_group(const river_config &c) {

@@ -785,8 +785,22 @@ def test_gemm_prefill_in_chunks_equals_serial_prefill_closely():
         tok = g.prefill(prompt, 1)
         outs.append((tok, g.hidden(), g.logits(), g.kcache()[:, :n].copy(), g.vcache()[:, :n].copy()))
         g.close()
-    for a, b in zip(outs[1][1:], outs[0][1:]):
-        assert relerr(a, np.asarray(b, np.float64)) <= 5e-3
+    # 5e-3 for the half-precision operands; the caches hold bf16: values that differ by delta before
+    # the rounding differ by at most delta + 2^-9 (|a| + |b|) after it
+    for a, b, tol in zip(outs[1][1:], outs[0][1:], (5e-3, 5e-3, 5e-3 + 2.0 ** -8, 5e-3 + 2.0 ** -8)):
+        assert relerr(a, np.asarray(b, np.float64)) <= tol
+
+
+# one and two query heads per workgroup, both head sizes: 240 workgroups of 1536 rows and 280 (260) of 1537
+@pytest.mark.parametrize("n_prompt", [1536, 1537])
+@pytest.mark.parametrize("n_kv_heads,head_dim", [(40, 64), (40, 128), (20, 64), (20, 128)])
+def test_gemm_prefill_attention_on_both_sides_of_the_workgroup_line(n_kv_heads, head_dim, n_prompt):
+    """The prefill's attention takes two tiles of keys a step up to a workgroup per CU (256) and one beyond, where the
+    last tile of queries has a single row.  Block 1's attention is seen in block 2's keys and values, position by
+    position; against the per-position prefill as the GEMM tiles are."""
+    cfg = configs.ModelConfig(f"line-{n_kv_heads}x{head_dim}", 2, 256, 40, n_kv_heads, head_dim, 256, 1002, 500000.0, 1e-5,
+                              configs.DTYPE_BF16, n_prompt + 8, 1, 2.0)
+    test_gemm_prefill_tiles_and_k_slices_equal_serial_prefill_closely(cfg, n_prompt)
 
 
 WIDE_PF = configs.ModelConfig("wide-pf-bf16", 3, 256, 32, 8, 128, 7168, 1002, 500000.0, 1e-5, configs.DTYPE_BF16, 64, 1, 2.0)
