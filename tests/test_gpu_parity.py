@@ -4,6 +4,7 @@ Bars (from the benchmark spec): exit positions and token ids bit-exact under tea
 forcing except at steps whose similarity lies within 1e-3 of tau; hidden states and
 logits within max relative error 1e-4 (fp32) / 2e-2 (bf16), where the relative error of a
 vector is |a-b|_inf / |b|_inf with b the oracle's."""
+import ctypes as C
 import sys
 
 import numpy as np
@@ -498,6 +499,30 @@ def test_barrier_wait_is_bounded():
     g.close()
 
 
+@pytest.mark.parametrize("n_prompt", [40, 140])
+def test_gemm_prefill_behind_a_wait_that_gave_up(n_prompt):
+    """The GEMM prefill has no device-wide waits; its last workgroup clears what a step whose waits gave up has left (the
+    barrier's counters, its error flag, the token state), and the results are those of a context that never timed out."""
+    say(f"GEMM prefill of {n_prompt} tokens behind a time-out")
+    cfg = MID.with_(max_seq=160)
+    dw = binding.upload_weights(inputs.make_weights(cfg, 3))
+    prompt = inputs.make_prompt(cfg.vocab, n_prompt, 4)
+    ref = binding.River(cfg, dw, None)
+    g = binding.River(cfg, dw, None, spin_limit=1)
+    for give_up in (lambda: g.prefill([1, 2, 3, 4]), lambda: g.decode_step(5)):
+        with pytest.raises(binding.RiverError) as ei:
+            give_up()
+        assert ei.value.code == binding.RIVER_EHIP
+        with pytest.raises(binding.RiverError):
+            g.decode_step(5)                                     # closed until the next prompt
+        assert g.prefill(prompt) == ref.prefill(prompt)
+        np.testing.assert_array_equal(g.logits(), ref.logits())
+        np.testing.assert_array_equal(g.hidden(), ref.hidden())
+        np.testing.assert_array_equal(g.kcache()[:, :n_prompt], ref.kcache()[:, :n_prompt])
+    g.close()
+    ref.close()
+
+
 # ------------------------------------------- long context: 5 to 8 attention splits
 
 LONG = configs.ModelConfig("long-hd128-bf16", 2, 512, 8, 2, 128, 1408, 1002, 500000.0, 1e-5,
@@ -611,7 +636,6 @@ def test_prefill_outputs_and_argument_checks():
 def test_prefill_refuses_logits_that_end_beyond_their_allocation(missing):
     """out_logits with fewer than vocab floats left in its allocation: refused, as a copy of the logits is, nothing
     written, and the context takes the next prompt.  (The allocation ends 2 KB in front of a page.)"""
-    import ctypes as C
     say(f"prefill, out_logits {missing} floats short")
     cfg = MID.with_(max_seq=64)
     g = binding.River(cfg, binding.upload_weights(inputs.make_weights(cfg, 3)), None, prefill_gemm_min_tokens=1)
@@ -638,6 +662,37 @@ def test_prefill_refuses_logits_that_end_beyond_their_allocation(missing):
     assert L.hipMemcpy(back.ctypes.data, at, size, 2) == 0
     assert np.array_equal(back[-cfg.vocab:], logits) and np.array_equal(back[:-cfg.vocab], mark[:-cfg.vocab])
     assert L.hipFree(at) == 0
+    g.close()
+
+
+# every way a prefill's logits go to the caller: (way, shape, tokens, smallest GEMM prompt, sequences).  The head's kernel completes the
+# last row itself from up to 8 planes of sums of at most 8192 columns (DEEP_PF's down projection leaves 8, MID's 11).
+LOGIT_ROUTES = [("per position", MID, 9, -1, 1), ("head completes the row", "deep", 77, 1, 1), ("last row alone", "deep", 140, 1, 1),
+                ("more planes", MID, 40, 1, 1), ("more planes, last row alone", MID, 129, 1, 1), ("wider", "wide", 40, 1, 1),
+                ("short passes", "short", 40, 90, 1), ("short pass", "short", 5, 90, 1), ("batched", MID, 40, 1, 3),
+                ("batched, one token", MID, 1, 0, 3)]
+
+
+@pytest.mark.parametrize("where", ["device", "odd", "pinned"])
+@pytest.mark.parametrize("route,cfg,n_prompt,min_tokens,n_seq", LOGIT_ROUTES, ids=[r[0].replace(",", "").replace(" ", "-") for r in LOGIT_ROUTES])
+def test_prefill_logits_for_the_caller(route, cfg, n_prompt, min_tokens, n_seq, where):
+    """The logits in the caller's memory are those of the library's own buffer, bit for bit, with nothing around them
+    written: device memory (the head's kernel stores there), also where only its floats are aligned, and pinned host memory
+    (a copy).  The second prompt finds the first one's logits there."""
+    cfg = {"deep": DEEP_PF, "wide": WIDE_HEAD, "short": SHORT_64}.get(cfg, cfg).with_(max_seq=max(n_prompt, 8) + 8)
+    say(f"prefill logits, {route}, {where}")
+    g = binding.River(cfg, binding.upload_weights(inputs.make_weights(cfg, 3)), None, prefill_gemm_min_tokens=min_tokens, max_batch=n_seq)
+    first = 33 if where == "odd" else 32
+    buf = torch.full((cfg.vocab + 64,), -7.5, pin_memory=True) if where == "pinned" else torch.full((cfg.vocab + 64,), -7.5, device="cuda")
+    out = buf[first:first + cfg.vocab]
+    for seed in (4, 5):
+        prompt = np.ascontiguousarray(inputs.make_prompt(cfg.vocab, n_prompt, seed), dtype=np.int32)
+        token = C.c_int32(-1)
+        assert binding.load().river_prefill(g._h, n_seq - 1, prompt.ctypes.data, n_prompt, -1, C.byref(token), out.data_ptr()) == 0
+        got = buf.cpu().numpy()
+        np.testing.assert_array_equal(got[first:first + cfg.vocab], g.logits())
+        assert (got[:first] == -7.5).all() and (got[first + cfg.vocab:] == -7.5).all()
+        assert token.value == int(np.argmax(g.logits())) and np.isfinite(g.logits()).all()
     g.close()
 
 
@@ -804,6 +859,7 @@ def test_gemm_prefill_attention_on_both_sides_of_the_workgroup_line(n_kv_heads, 
 
 
 WIDE_PF = configs.ModelConfig("wide-pf-bf16", 3, 256, 32, 8, 128, 7168, 1002, 500000.0, 1e-5, configs.DTYPE_BF16, 64, 1, 2.0)
+WIDE_HEAD = configs.ModelConfig("wide-8256", 2, 8256, 2, 1, 64, 128, 1002, 500000.0, 1e-5, configs.DTYPE_BF16, 64, 1, 2.0)
 DEEP_PF = configs.ModelConfig("deep-pf-bf16", 3, 4096, 4, 2, 128, 8192, 1002, 500000.0, 1e-5, configs.DTYPE_BF16, 64, 1, 2.0)
 
 
@@ -857,7 +913,7 @@ def test_gemm_prefill_few_rows_in_k_slices_equal_serial_prefill_closely(cfg, n_p
 @pytest.mark.parametrize("d_model,n_prompt", [(8192, 40), (8256, 40), (8256, 140)])
 def test_gemm_prefill_head_of_wide_models(d_model, n_prompt):
     """The prefill's head completes the last row itself up to 8192 columns and takes it from memory beyond."""
-    cfg = configs.ModelConfig(f"wide-{d_model}", 2, d_model, 2, 1, 64, 128, 1002, 500000.0, 1e-5, configs.DTYPE_BF16, n_prompt + 8, 1, 2.0)
+    cfg = WIDE_HEAD.with_(name=f"wide-{d_model}", d_model=d_model, max_seq=n_prompt + 8)
     test_gemm_prefill_tiles_and_k_slices_equal_serial_prefill_closely(cfg, n_prompt)
 
 
@@ -915,6 +971,24 @@ def test_backbone_offloading_reads_deep_blocks_from_pinned_host_memory(mode):
         assert e2 == eo
     g2.close()
     pair.close()
+
+
+@pytest.mark.parametrize("cfg0,n_prompt,min_tokens", [(MID, 40, 1), (MID, 128, 1), (MID, 150, 1), ("short", 7, 0)],
+                         ids=["one-row-tile", "four-row-blocks", "two-row-tiles", "short-pass"])
+def test_prefill_gemms_read_offloaded_matrices(cfg0, n_prompt, min_tokens):
+    """... and so do the GEMMs of a prefill, whose operands go from there to LDS: bit for bit as from HBM."""
+    cfg = (SHORT_64.with_(n_layers=2) if cfg0 == "short" else cfg0).with_(min_exit_layer=0, max_seq=160)
+    say(f"offloaded matrices, prefill of {n_prompt}")
+    dw = binding.upload_weights(inputs.make_weights(cfg, 77, gain_std=0.05))
+    dr = binding.quantize_river(cfg, dw)
+    prompt = inputs.make_prompt(cfg.vocab, n_prompt, 78)
+    outs = []
+    for w in (dw, binding.offload_backbone(dw, 1)):
+        g = binding.River(cfg, w, dr, prefill_gemm_min_tokens=min_tokens)
+        outs.append((g.prefill(prompt), g.hidden(), g.logits(), g.kcache()[:, :n_prompt].copy(), g.vcache()[:, :n_prompt].copy()))
+        g.close()
+    for a, b in zip(*outs):
+        np.testing.assert_array_equal(a, b)
 
 
 # ------------------------------------------------------------------ FP16 KV cache
