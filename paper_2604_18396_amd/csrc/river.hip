@@ -256,10 +256,8 @@ __device__ RIVER_PSTEP_INLINE void pstep_head(const Dev *Dp, StepArgs A, int ctl
 
 // The number of barriers (5 L - 1, one more with the head) is the same for every workgroup
 // whatever the exit state.
-// (On a page of its own: the same code 0x3600 bytes further into one takes 564.6 us per token of the 1B shape instead
-// of 561.3, and 665.3 instead of 664.1 for two of four 8B blocks at 4096 positions.)
 template <int DT, bool F16, int V, int HD>
-__global__ __launch_bounds__(kBlock) __attribute__((aligned(4096))) void k_step_persistent(const Dev *Dp, StepArgs A) {
+__global__ __launch_bounds__(kBlock) void k_step_persistent(const Dev *Dp, StepArgs A) {
   extern __shared__ float lds[];
   DevRef D = *RIVER_CONSTANT(Dev, Dp);
   unsigned long long k = A.bar_base;
