@@ -104,7 +104,7 @@ __global__ __launch_bounds__(kBlock) void k_head(const Dev *Dp, StepArgs A) {
 // The end of a prefill on the matrix cores (bf16): h(L) of the last position completed from the sums of the last GEMM, final
 // norm, LM head, token, and the state a new sequence starts from.  One launch for what were five (reset, last sums, head, copy of the
 // logits, token of the batched sequence), 3 to 5 us each with nothing to do: four 8B blocks, 77 tokens 561 -> 547 us, four 1B
-// blocks, 255 tokens 407 -> 400.  Bound by the stream of the head behind 10 us of launch, staging and hand-over (30 us for 131 MB).
+// blocks, 255 tokens 407 -> 400 (there the last sums still have their launch, 5 us: see launch_prefill_head).  Bound by the stream of the head behind 10 us of launch, staging and hand-over (30 us for 131 MB).
 // n_part >= 0: h(L) = h_row + n_part planes part + j * stride, added in order, d_model of at most kPfHeadCols columns; < 0: it lies in
 // Dev::hidden already.  The weight prefetch is issued in front of it, as in a decode step.
 constexpr int kPfHeadCols = kNormRuns * kBlock * 8, kPfHeadPlanes = 8;
@@ -1187,9 +1187,12 @@ static int check_device_error(river_ctx *x) {
 // TileM / TileN / TileL: N 3072 K 2048, 255 rows 10 / 12 / 15; N 6144 K 4096, 512 rows 40 / 36 / 36, and 41
 // for TileM unsliced, which the rule takes: 44 in a prefill; N 4096 K 14336, 512 rows 75 / 64 / 64, one
 // slice 132 / 187 / 272; N 28672 K 4096, 512 rows 147 / 132 / 114, 4096 rows 1199 / 1144 / 903.)
-// Up to kRowsMost rows the tiles are k_pf_gemm_rows', with TileM's count of slices (four blocks of the 8B shape, half of them
-// river, 77 tokens: 624 us with TileM, 563 with it; beyond, its one tile of 128 rows per CU is the slower one: N 6144
-// K 4096, 512 rows 48 us, N 28672 190).
+// Up to kRowsMost rows the tiles are k_pf_gemm_rows', with TileM's count of slices, which is the best one there too (us
+// by slices, 77 rows: N 6144 K 4096 3 / 4 / 5 / 6 / 8 of them 17.8 / 15.6 / 14.5 / 21.7 / 20.1; N 4096 K 4096 4 / 6 / 8 / 9
+// 15.1 / 12.8 / 13.4 / 17.4; N 4096 K 14336 35.9 / 29.6 / 24.0 / 36.6; taken 5, 8 and 8).  Four blocks of the 8B shape, half of them river, 77
+// tokens: 624 us with TileM, 563 with it.  Beyond 128 rows it would take two tiles of rows (us in a prefill, the tiles
+// above / two of it): N 3072 K 2048, 255 rows 12.9 / 13.1, N 16384 28.4 / 28.6; N 6144 K 4096, 200 rows 26.9 / 27.2, N 28672
+// 72 / 95; with 2 x 96 rows, N 16384 K 2048, 160 rows 26.9 / 23.6, which has not been built.
 struct PfTile { int tm, tn; double alone, full; };
 constexpr PfTile kPfTiles[3] = {{pf::TileM::TM, pf::TileM::TN, 0.5, 0.67},
                                 {pf::TileN::TM, pf::TileN::TN, 0.85, 1.15},
@@ -1273,7 +1276,7 @@ static int launch_gemm(river_ctx *x, int l, bool w4, const int *ms, int nm, cons
   return p.split;
 }
 
-// GEMM of a pass over a short prompt (EXACT, see pf::k_pf_gemm): planes of kShort rows in C; returns how many.
+// GEMM of a pass over a short prompt (EXACT, see pf::k_pf_gemm_rows): planes of kShort rows in C; returns how many.
 static int launch_gemm_exact(river_ctx *x, int l, bool w4, const int *ms, int nm, const _Float16 *A, int K, float *C, int m) {
   pf::GemmB B{};
   const int N = gemm_operand(x, l, w4, ms, nm, &B), M = w4 ? pf::kShort : 3 * pf::kShort;
@@ -1284,7 +1287,8 @@ static int launch_gemm_exact(river_ctx *x, int l, bool w4, const int *ms, int nm
 }
 
 // Original final norm + LM head + argmax on the last prompt position, the call's results and the new sequence's state (k_pf_head).
-// h_row: the position's residual row, parts planes of plane_rows rows behind each other with its sums in row `row`.
+// h_row: the position's residual row, parts planes of plane_rows rows behind each other with its sums in row `row`.  More planes than
+// kPfHeadPlanes (the single row of a down projection to 2048 columns has up to 16) and wider rows are added up by k_pf_norm in front.
 static void launch_prefill_head(river_ctx *x, const float *h_row, const float *planes, int parts, int plane_rows, int row, float *out_logits,
                                 int *batch_token) {
   const river_config &c = x->cfg;
@@ -1375,10 +1379,10 @@ static int prefill_short(river_ctx *x, const int32_t *tokens, int n, int ep, flo
 }
 
 // Attention of a chunk's queries: as many query heads of a kv head per workgroup (4, 2 or 1) as divide them, two tiles of
-// keys a step where one a step makes no more workgroups than there are CUs (us, one / two tiles, 32 heads on 8 of head size
-// 128: 77 rows 9.9 / 9.2, 512 25.2 / 18.5, 1024 43 / 31, 2048 80 / 67, 2560 98 / 106; 8 on 2: 3072 rows 105 / 69, a prompt of 8300 in
-// three chunks and two blocks as a whole 1025 / 856).  Keys and values of the next block are as far from 64 bits either way:
-// 1.77e-3 of 3072 positions, 1.70e-3 of 8300 (their rounding to bf16).
+// keys a step where one a step makes no more workgroups than there are CUs (us in a prefill, one / two tiles, 32 heads on 8 of head
+// size 128: 77 rows 10.6 / 9.7, 512 28.9 / 20.2, 1024 46 / 33, 2048 89 / 69, beyond the line 2560 98 to 113 / 106 to
+// 109; 8 on 2: 3072 rows 110 / 74, a prompt of 8300 in three chunks and two blocks as a whole 1025 / 856).  Keys and values of the
+// next block are as far from 64 bits either way: 1.77e-3 of 3072 positions, 1.70e-3 of 8300 (their rounding to bf16).
 template <int HD, int HG>
 static void launch_attn_t(river_ctx *x, int l, const void *kc, const void *vc, int c0, int m, const _Float16 *q16, _Float16 *o16) {
   const river_config &c = x->cfg;

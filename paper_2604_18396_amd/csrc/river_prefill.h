@@ -400,19 +400,22 @@ done:
 // The same product for up to 128 rows.  k_pf_gemm's 128 x 128 tile is bound there by neither the stream nor the
 // matrix cores but by the way of a K tile through the registers: load, convert, write to LDS, barrier, read
 // (1500 cycles for 128 x 128 x 64, of which 510 with the matrix cores at work, bf16 or codes alike).  Here
-//  * A and B go from global memory to LDS directly (buffer loads with the LDS as their destination), up to
-//    five stages of them in flight without a register: 64 KB of weights per CU and more;
+//  * A and B go from global memory to LDS directly (buffer loads with the LDS as their destination), without a register:
+//    behind the stage at work up to four more are in flight per CU, of bf16 64 KB of weights,
+//    of codes 40, 40, 30 and 20 KB with up to 32, 64, 96 and 128 rows;
 //  * a tile is 32 MB rows of A (no products for padding rows beyond 31; rows that do not exist are not
 //    loaded) x 128 rows of B; each of the eight wavefronts owns 32 rows of B and half of a stage's columns, so
 //    that B is converted once, in the registers its product reads it from;
 //  * the operands of a stage are read from LDS during the products of the one before; one barrier a stage.
 // A stage is 64 columns of bf16, or 128 of codes with their (scale, zero) pairs.  LDS rows are 128 bytes
 // of 16-byte pieces (codes: 64), the piece c of row r in place c ^ (r / 2) % 8 (codes: c ^ (r / 4) % 4): the
-// 16 lanes that a 16-byte read serves together then touch every bank once.
+// 16 lanes that a 16-byte read serves together then touch every bank once (conflicts: 2 % of the LDS cycles with bf16,
+// 5 % with codes, whose pairs are read four bytes a lane).
 // Measured (us in a prefill of 77 tokens at the 8B shape, 128 x 128 tile and now; bf16 / codes): QKV 18.2 / 16.6 and 15.7 /
 // 17.0, O 12.6 / 14.4 and 11.6 / 14.4, gate/up 49.0 / 47.8 and 45.3 / 39.2, down 28.2 / 25.5 and 23.8 / 22.4.  What bounds it now: bf16
-// -- the stream at the clock that is left beside the products (1.7 GHz: 5.2 TB/s in gate/up); codes -- nothing
-// alone: of 1900 cycles a stage the conversions take 770 of a SIMD, the products as many, the loads 1200 of the
+// -- the stream at the clock that is left beside the products (1.7 GHz: 5.2 TB/s in gate/up; of 1200 cycles a stage the matrix
+// cores work in 380); codes -- nothing alone: of 2200 cycles a stage (counters of a whole launch, its ends taken off) the
+// conversions take 820 of a SIMD, the products 770, the loads 1200 of the
 // CU's way to the L2 (30 bytes a cycle, also with 8 workgroups on the chip: a workgroup reads all of A).  A launch that
 // is short costs 3 us from its start to the first stage and 1 us behind the last one.  Tried: beginning at different
 // stages in different workgroups (no change), A kept in tiles of 64 columns (no
@@ -441,7 +444,8 @@ template <int MB_, bool W4> struct RowsTile {
 };
 
 // 64 lanes x 16 (4) bytes from rsrc + voff + soff to LDS at lds + 16 (4) * lane.  In assembly, because the
-// compiler makes every LDS read wait for all such loads in flight; rows_wait counts them instead.
+// compiler makes every LDS read wait for all such loads in flight; rows_wait counts them instead.  (m0, which the compiler warns of
+// as a reserved register, is written in front of each load and read by nothing else in these kernels.)
 template <bool STREAM>
 __device__ __forceinline__ void load_lds16(unsigned lds, unsigned voff, const u32x4 &rsrc, unsigned soff) {
   if constexpr (STREAM)
@@ -555,7 +559,6 @@ __global__ __launch_bounds__(512, 1) void k_pf_gemm_rows(const _Float16 *__restr
   int at = 0;                                                   // the next stage to load
   // the slice's last stage has 64 columns only
   const bool ragged = W4 && (K & 64) && ks_i == deal.k_split - 1;
-                              // this workgroup is the only reader of its rows of B
   auto issue_as = [&](int buf, auto last) {                     // last: of a ragged row (codes)
     constexpr bool CUT = decltype(last)::value;
     const unsigned dst = lds0 + (unsigned)buf * T::STAGE;
@@ -573,6 +576,7 @@ __global__ __launch_bounds__(512, 1) void k_pf_gemm_rows(const _Float16 *__restr
         else v -= (v - (unsigned)(lane >> 2) * (unsigned)(K >> 1)) & 32u;
       }
       const unsigned along = (unsigned)at * (W4 && j >= MB ? 64u : T::COLS * 2u);          // columns, of codes or 16 bits
+      // (streamed past the caches where all of a round is B's: this workgroup is the only reader of its rows)
       if (8 * j >= T::A_ITEMS) load_lds16<true>(dst + it * 1024u, v, rs[j], along);
       else load_lds16<false>(dst + it * 1024u, v, rs[j], along);
     }
@@ -1165,7 +1169,7 @@ constexpr int attn_lds_bytes(int hd, int ks) { return 2 * ks * (64 * (hd + 8) + 
 // The last prompt position alone (behind the last block's keys and values only it goes on) over positions 0 .. P: one
 // workgroup per (kv head, group of REP of its query heads, split of the positions), 16 lanes per cached
 // position, a running softmax (base 2) per lane group and head, everything but q in fp32.  The splits' results
-// meet in the last workgroup to arrive of a head group, in split order.  Bound by latency: 26 us at 4096 positions of the 8B shape, 11 at
+// meet in the last workgroup to arrive of a head group, in split order.  Bound by latency: 26 us at 4096 positions of the 8B shape, 12 at
 // 512, 8 at 255 of the 1B shape; the tiles above, one row of 32 at work, took 139, 26 and 11.7.  A head per
 // wavefront: with all heads of a kv head in every lane (each row fetched once) it took 46 and 16, the vector
 // instructions of one wavefront per SIMD in a chain.
